@@ -192,9 +192,7 @@ int dint4_weight_sums(const uint8_t *codes, const uint8_t *zero, int64_t N, int6
     if (tsum && (K % TILE_K != 0 || G % TILE_K != 0)) return W4A8_ERR_SHAPE;
     if (N == 0) return W4A8_OK;
     if (!codes || !zero || !wsum) return W4A8_ERR_NULL;
-    int rc = launch_weight_sums(codes, zero, N, K, G, G, wsum, (hipStream_t)stream);
-    if (rc != W4A8_OK || !tsum) return rc;
-    return launch_weight_sums(codes, zero, N, K, G, TILE_K, tsum, (hipStream_t)stream);
+    return launch_weight_sums(codes, zero, N, K, G, wsum, tsum, (hipStream_t)stream);
 }
 
 int quantize_weight_dint4(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw,

@@ -180,9 +180,9 @@ __device__ __forceinline__ void decode_word_signed(uint32_t p, const SignedLut &
 // zx == nullptr: symmetric absmax; else asymmetric min-max, token zero-points (minus 128) to zx
 int launch_act_quant(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, const float *s,
                      int8_t *Xq, float *sx, int32_t *zx, hipStream_t st);
-// wsum[N, K/T]: sums of the weights in half steps over blocks of T columns (T divides G)
+// sums of the weights in half steps: wsum [N, K/G] per group, tsum [N, K/128] per 128 columns (or null)
 int launch_weight_sums(const uint8_t *codes, const uint8_t *zero, int64_t N, int64_t K, int64_t G,
-                       int64_t T, int32_t *wsum, hipStream_t st);
+                       int32_t *wsum, int32_t *tsum, hipStream_t st);
 int launch_acc_zero_point(int32_t *acc, const int32_t *zx, const int32_t *wsum, int64_t M,
                           int64_t per_token, hipStream_t st);
 int launch_weight_quant(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw,

@@ -592,7 +592,8 @@ int launch_value_quant(const void *V, int v_dtype, int64_t batch, int64_t T, int
 
 // ---- sums of the quantized weights (needed to take a token zero-point out of the product) ------
 // wsum[n,b] = sum_{k in block b} d[n,k], d in half steps (Eq. 5, second half), over blocks of T
-// consecutive input channels (T divides the group size G): one wave per (row, block).
+// consecutive input channels (T divides the group size G): one wave per (row, block).  Serves the
+// group sizes and alignments that weight_sums_tiles_kernel does not take.
 __global__ __launch_bounds__(256) void weight_block_sums_kernel(const uint8_t *__restrict__ codes,
                                                                 const uint8_t *__restrict__ zero,
                                                                 int64_t N, int64_t K, int64_t G,
@@ -614,12 +615,127 @@ __global__ __launch_bounds__(256) void weight_block_sums_kernel(const uint8_t *_
     if (lane == 0) wsum[seg] = sum;
 }
 
-int launch_weight_sums(const uint8_t *codes, const uint8_t *zero, int64_t N, int64_t K, int64_t G,
-                       int64_t T, int32_t *wsum, hipStream_t st)
+// Sum of d over 16 codes, four per register: with n14, n15 the numbers of special codes,
+//     sum d = 2 sum(code) - 32 z + n14 (2 z - 27) + n15 (2 z - 31)
+// (a special code counted as an integer level gives 2 (14 - z) resp. 2 (15 - z) instead of +-1).
+__device__ __forceinline__ int sum16_half_steps(const uint4 &c, int z)
 {
-    const int64_t segs = N * (K / T);
+    const uint32_t w[4] = {c.x, c.y, c.z, c.w};
+    uint32_t total = 0, special = 0, odd = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t v = w[i] & 0x0f0f0f0fu;
+        total = __builtin_amdgcn_udot4(v, 0x01010101u, total, false);
+        const uint32_t m = (v >> 3) & (v >> 2) & (v >> 1) & 0x01010101u;   // one bit per code >= 14
+        special += m;
+        odd += m & v;                                                      // one bit per code 15
+    }
+    const int n_sp = (int)__builtin_amdgcn_udot4(special, 0x01010101u, 0, false);
+    const int n15 = (int)__builtin_amdgcn_udot4(odd, 0x01010101u, 0, false);
+    return 2 * (int)total - 32 * z + n_sp * (2 * z - 27) - 4 * n15;
+}
+
+// wsum [N, K/G] and tsum [N, K/128] in one pass over the codes, G a multiple of 128 and every
+// 16-code chunk aligned.  Bound by the read of the codes (one byte per weight): the wave-per-block
+// kernel above read them twice, two bytes per lane and instruction, at 0.6 TB/s.  Rows are contiguous, so
+// group gi is codes [gi G, (gi + 1) G) and no index needs a division.  LANES lanes (16 codes each)
+// take a group: 8, 16 or 32 where the group is exactly that long (several groups per wave), else a
+// whole wave that walks it, SUMS_ILP loads in flight.  Eight lanes make one 128-column sum.
+// 13824 x 5120, G = 128: both sums 241 -> 13.1 us (5.4 TB/s); 32768 x 4096 per channel: 313 -> 24 us (5.6 TB/s).
+constexpr int SUMS_ILP = 4;
+
+__device__ __forceinline__ int sum8_lanes(int v)
+{
+    v += dpp_i32<DPP_QUAD_XOR1>(v);
+    v += dpp_i32<DPP_QUAD_XOR2>(v);
+    return v + dpp_i32<DPP_ROW_HALF_MIRROR>(v);
+}
+
+template <int LANES>
+__global__ __launch_bounds__(256) void weight_sums_tiles_kernel(const uint8_t *__restrict__ codes,
+                                                                const uint8_t *__restrict__ zero,
+                                                                int64_t groups, int G,
+                                                                int32_t *__restrict__ wsum,
+                                                                int32_t *__restrict__ tsum)
+{
+    const int lane = threadIdx.x & 63;
+    const int64_t wave = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    const uint4 *src = reinterpret_cast<const uint4 *>(codes);
+    if constexpr (LANES < 64) {
+        constexpr int PER = 64 / LANES;   // groups of one wave load
+        const int64_t g0 = wave * (PER * SUMS_ILP) + lane / LANES;
+        uint4 c[SUMS_ILP];
+        int z[SUMS_ILP];
+#pragma unroll
+        for (int i = 0; i < SUMS_ILP; ++i) {
+            const int64_t g = min(g0 + i * PER, groups - 1);   // (past the end: the last group again, not stored)
+            c[i] = src[g * LANES + (lane & (LANES - 1))];
+            z[i] = zero[g];
+        }
+#pragma unroll
+        for (int i = 0; i < SUMS_ILP; ++i) {
+            const int64_t g = g0 + i * PER;
+            int v = sum8_lanes(sum16_half_steps(c[i], z[i]));
+            if (tsum != nullptr && (lane & 7) == 0 && g < groups)
+                tsum[g * (LANES / 8) + ((lane & (LANES - 1)) >> 3)] = v;
+            if (LANES > 8) v += __shfl_xor(v, 8, WAVE);
+            if (LANES > 16) v += __shfl_xor(v, 16, WAVE);
+            if ((lane & (LANES - 1)) == 0 && g < groups) wsum[g] = v;
+        }
+    } else {
+        if (wave >= groups) return;   // whole wave
+        const int z = zero[wave];
+        const int chunks = G / 16;
+        const uint4 *row = src + wave * chunks;
+        int32_t *trow = tsum != nullptr ? tsum + wave * (chunks / 8) : nullptr;
+        int sum = 0;
+        for (int c0 = 0; c0 < chunks; c0 += 64 * SUMS_ILP) {
+            uint4 c[SUMS_ILP];
+#pragma unroll
+            for (int i = 0; i < SUMS_ILP; ++i) c[i] = row[min(c0 + i * 64 + lane, chunks - 1)];
+#pragma unroll
+            for (int i = 0; i < SUMS_ILP; ++i) {
+                const int at = c0 + i * 64 + lane;   // (chunks % 8 == 0: eight lanes are in range together)
+                const int v = sum8_lanes(sum16_half_steps(c[i], z));
+                if ((lane & 7) == 0 && at < chunks) {
+                    if (trow != nullptr) trow[at >> 3] = v;
+                    sum += v;
+                }
+            }
+        }
+        sum = wave_sum_i32(sum);   // (non-zero in every eighth lane)
+        if (lane == 0) wsum[wave] = sum;
+    }
+}
+
+int launch_weight_sums(const uint8_t *codes, const uint8_t *zero, int64_t N, int64_t K, int64_t G,
+                       int32_t *wsum, int32_t *tsum, hipStream_t st)
+{
+    if (G % TILE_K == 0 && G <= 0x7fffffff && (uintptr_t)codes % 16 == 0) {
+        const int64_t groups = N * (K / G);
+#define W4A8_WS_LAUNCH(LANES_)                                                                       \
+    do {                                                                                             \
+        const int64_t per = LANES_ < 64 ? 4 * (64 / LANES_) * SUMS_ILP : 4;   /* groups per block */ \
+        const int64_t blocks = (groups + per - 1) / per;                                             \
+        if (blocks > 0x7fffffffLL) return W4A8_ERR_SHAPE;                                            \
+        hipLaunchKernelGGL((weight_sums_tiles_kernel<LANES_>), dim3((unsigned)blocks), dim3(256), 0, \
+                           st, codes, zero, groups, (int)G, wsum, tsum);                             \
+    } while (0)
+        if (G == 128) W4A8_WS_LAUNCH(8);
+        else if (G == 256) W4A8_WS_LAUNCH(16);
+        else if (G == 512) W4A8_WS_LAUNCH(32);
+        else W4A8_WS_LAUNCH(64);
+#undef W4A8_WS_LAUNCH
+        return hip_status(hipGetLastError());
+    }
+    const int64_t segs = N * (K / G);
     hipLaunchKernelGGL(weight_block_sums_kernel, dim3((unsigned)((segs + 3) / 4)), dim3(256), 0, st,
-                       codes, zero, N, K, G, T, wsum);
+                       codes, zero, N, K, G, G, wsum);
+    if (tsum != nullptr) {
+        const int64_t tsegs = N * (K / TILE_K);
+        hipLaunchKernelGGL(weight_block_sums_kernel, dim3((unsigned)((tsegs + 3) / 4)), dim3(256), 0, st,
+                           codes, zero, N, K, G, (int64_t)TILE_K, tsum);
+    }
     return hip_status(hipGetLastError());
 }
 
