@@ -1,11 +1,12 @@
 // dINT4 weight quantization of W diag(s)  (Eq. 1 factor Q(W diag(s)); Sec. 4.2, Eq. 5 with b = 4,
 // p = 13; min-max asymmetric ranges per output channel or per group of G input channels, App. A.1).
 //
-// Offline and HBM-bound.  One wavefront owns one (output row, group) segment: a first sweep takes
-// the min / max of w' = W * s with the range extended to contain zero, the lane-0 value of
-// step = (hi - lo) / 13, 1/step and the zero-point z is shared through the wave reduction, and a
-// second sweep (served by the cache) applies Eq. 5 per element.  Every floating-point step is one
-// binary32 operation in the order of the definition (no contraction), divisions are IEEE.
+// Offline; bound by memory and the vector ALU about equally.  Groups of 128 and 256 and segments of 1024 to 16384
+// elements stay in registers between the range and the codes (one sweep over W); other lengths and
+// unaligned rows take one wavefront per (row, group) and two sweeps, the second served by the cache.
+// Range min / max of w' = W * s extended to contain zero, step = (hi - lo) / 13, 1/step and the
+// zero-point z, then Eq. 5 per element.  Every floating-point step is one binary32 operation in the
+// order of the definition (no contraction), divisions are IEEE.
 #include "w4a8_common.hpp"
 
 namespace w4a8 {
@@ -50,28 +51,57 @@ struct CodeFormat {
 };
 __host__ __device__ constexpr CodeFormat dint4_format() { return CodeFormat{DINT4_P, 1}; }
 
-__device__ __forceinline__ uint32_t dint4_code(float w, float istep, int z, CodeFormat f = dint4_format())
+// The code rule with everything that is constant over a (row, group).  The vector ALU is what bounds the
+// quantizer kernels before memory does, so the rule is written for few operations: eight per weight
+// and three quarters of one for packing.
+struct CodeRule {
+    float istep;
+    float lo, hi;        // -z, p - z: clamping u there is clamping rne(u) + z to 0 .. p (the bounds are integers)
+    int z;
+    uint32_t band_lo;    // the special bands (lo_t, hi_t] of |u|, on the bits of |u| shifted left by one:
+    uint32_t band_span;  // a subtraction and one unsigned comparison (span 0: no special levels)
+};
+
+__device__ __forceinline__ CodeRule make_rule(float istep, int z, CodeFormat f = dint4_format())
 {
-    // (the vector ALU, not memory, is what bounds the quantizer kernels: about twenty operations per weight
-    // hold them at 3.6 TB/s, so the rule is written for few operations)
-    // u is clamped first (exactly: values beyond +-64 steps saturate at an end level whatever they are), so
-    // that rne and the conversion are one addition: u + 1.5 * 2^23 holds rne(u) in its low bits for |u| < 2^22
-    float u = w * istep;
-    u = __builtin_amdgcn_fmed3f(u, -64.0f, 64.0f);
-    const int r = (int)__float_as_uint(u + 12582912.0f) - 0x4B400000;
-    int c = min(max(r + z, 0), f.p);   // (one v_med3_i32)
-    if (f.special) {
-        // nearest level: the band of +c runs from the midpoint between 0 and c to the midpoint
-        // between c and one step (0.25 .. 0.75 for c = step/2), ends as in Eq. 5; both bounds exact.
-        // The two bands mirror each other, (lo_t, hi_t] and [-hi_t, -lo_t), i.e. lo_t < |u| <= hi_t,
-        // and the code is 14 + the sign bit (selects, not branches: the lanes of a wave disagree all the time)
-        const float lo_t = f.shift == 1 ? 0.25f : (f.shift == 2 ? 0.125f : 0.0625f);
-        const float hi_t = 0.5f + lo_t;
-        const float au = __builtin_fabsf(u);
-        const int sp = (int)(__float_as_uint(u) >> 31) | 14;
-        c = (au > lo_t && au <= hi_t) ? sp : c;
-    }
-    return (uint32_t)c;
+    // nearest level: the band of +c runs from the midpoint between 0 and c to the midpoint
+    // between c and one step (0.25 .. 0.75 for c = step/2), ends as in Eq. 5; both bounds exact
+    const float lo_t = f.shift == 1 ? 0.25f : (f.shift == 2 ? 0.125f : 0.0625f);
+    const float hi_t = 0.5f + lo_t;
+    CodeRule r;
+    r.istep = istep;
+    r.lo = (float)-z;
+    r.hi = (float)(f.p - z);
+    r.z = z;
+    r.band_lo = (__float_as_uint(lo_t) << 1) + 1u;
+    r.band_span = f.special ? (__float_as_uint(hi_t) - __float_as_uint(lo_t)) << 1 : 0u;
+    return r;
+}
+
+// The code of x in the low byte (the upper bits are whatever the arithmetic left there).
+__device__ __forceinline__ uint32_t code_byte(float x, const CodeRule &r)
+{
+    const float u = x * r.istep;
+    // rne and the conversion are one addition: y + 1.5 * 2^23 holds rne(y) in its low bits (|y| <= 255)
+    const uint32_t c = __float_as_uint(__builtin_amdgcn_fmed3f(u, r.lo, r.hi) + 12582912.0f) + (uint32_t)r.z;
+    const uint32_t bits = __float_as_uint(u);
+    const uint32_t sp = __builtin_amdgcn_alignbit(7u, bits, 31u);   // 14 + the sign bit
+    // (a select, not a branch: the lanes of a wave disagree all the time)
+    return (bits << 1) - r.band_lo < r.band_span ? sp : c;
+}
+
+// Four low bytes into one register, two byte permutes and an OR.
+__device__ __forceinline__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint32_t c, uint32_t d)
+{
+    return __builtin_amdgcn_perm(b, a, 0x0c0c0400u) | __builtin_amdgcn_perm(d, c, 0x04000c0cu);
+}
+
+__device__ __forceinline__ uint2 codes8(const float (&x)[8], const CodeRule &r)
+{
+    uint32_t q[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) q[j] = code_byte(x[j], r);
+    return make_uint2(pack_low_bytes(q[0], q[1], q[2], q[3]), pack_low_bytes(q[4], q[5], q[6], q[7]));
 }
 
 // Min-max asymmetric parameters of a range that contains zero: step = (hi - lo) / p,
@@ -157,32 +187,73 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_kernel(
         }
     }
 
+    const CodeRule rule = make_rule(istep, z, fmt);
     uint8_t *c = codes + n * K + g * G;
     for (int64_t k = (int64_t)lane * V; k < G; k += (int64_t)WAVE * V) {
         float v[V], sv[V];
         loadv<T, V>(w + k, v);
         load_scales<V>(sg, k, s_vec, sv);
-        uint32_t q[V];
+        float x[V];
 #pragma unroll
-        for (int j = 0; j < V; ++j) {
-            const float x = sg ? v[j] * sv[j] : v[j];
-            q[j] = dint4_code(x, istep, z, fmt);
-        }
-        if constexpr (V == 8) {
-            const uint32_t w0 = q[0] | q[1] << 8 | q[2] << 16 | q[3] << 24;
-            const uint32_t w1 = q[4] | q[5] << 8 | q[6] << 16 | q[7] << 24;
-            *reinterpret_cast<uint2 *>(c + k) = make_uint2(w0, w1);
-        } else if constexpr (V == 2) {
-            *reinterpret_cast<uint16_t *>(c + k) = (uint16_t)(q[0] | q[1] << 8);
-        } else {
-            c[k] = (uint8_t)q[0];
-        }
+        for (int j = 0; j < V; ++j) x[j] = sg ? v[j] * sv[j] : v[j];
+        if constexpr (V == 8)
+            *reinterpret_cast<uint2 *>(c + k) = codes8(x, rule);
+        else if constexpr (V == 2)
+            *reinterpret_cast<uint16_t *>(c + k) =
+                (uint16_t)pack_low_bytes(code_byte(x[0], rule), code_byte(x[1], rule), 0u, 0u);
+        else
+            c[k] = (uint8_t)code_byte(x[0], rule);
     }
 }
 
-// Groups of 128 or 256 columns: a wave takes 512 consecutive columns of a row (8 per lane, one
-// 16-byte load), i.e. 4 or 2 whole groups, each reduced over its own LANES = G / 8 lanes; the
+// x[j] = v[j] * sv[j], the eight elements still in their storage type.  fp16: x * s + 0, the same single
+// rounding of the exact product (only the sign of a zero can differ, which neither the range nor the code
+// sees), because the widening folds into a mixed-precision multiply-add.
+template <typename T>
+__device__ __forceinline__ void scaled8(const T *e, const float (&sv)[8], bool has_s, float (&x)[8])
+{
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        if (!has_s) x[j] = to_f32(e[j]);
+        else if constexpr (__is_same(T, __half)) x[j] = __builtin_fmaf(to_f32(e[j]), sv[j], 0.0f);
+        else x[j] = to_f32(e[j]) * sv[j];
+    }
+}
+
+template <typename T>
+struct Raw8 {   // eight elements as they come from memory
+    uint4 w[sizeof(T) / 2];
+    __device__ __forceinline__ void load(const T *p)
+    {
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(T) / 2); ++i) w[i] = reinterpret_cast<const uint4 *>(p)[i];
+    }
+    __device__ __forceinline__ void elements(T (&e)[8]) const { __builtin_memcpy(e, w, sizeof(w)); }
+};
+
+__device__ __forceinline__ void min_max8(const float (&x)[8], float &lo, float &hi)
+{
+#pragma unroll
+    for (int j = 0; j < 8; j += 2) {   // (v_min3 / v_max3)
+        lo = fminf(fminf(lo, x[j]), x[j + 1]);
+        hi = fmaxf(fmaxf(hi, x[j]), x[j + 1]);
+    }
+}
+
+// Groups of 128 or 256 columns: a wave takes 512 consecutive columns (8 per lane, one 16-byte load) of
+// SG_ROWS rows, i.e. 4 or 2 whole groups of each row, each reduced over its own LANES = G / 8 lanes; the
 // elements stay in registers between the range and the codes, so W is read once.
+// Bound by the vector ALU and memory about equally; the rows share the lane's eight AQAS scales (twice the
+// bytes of fp16 weights) and the two IEEE divisions of a group (some 25 operations): lane l computes the
+// parameters of row l % 4 for its group and the four lanes of a quad exchange them.
+// 13824 x 5120, G = 128: 68 -> 47 us (4.5 TB/s).
+constexpr int SG_ROWS = 4;
+
+template <int ROW>
+__device__ __forceinline__ float quad_lane_f32(float v) { return dpp_f32<ROW * 0x55>(v); }
+template <int ROW>
+__device__ __forceinline__ int quad_lane_i32(int v) { return dpp_i32<ROW * 0x55>(v); }
+
 template <typename T, int LANES>
 __global__ __launch_bounds__(WQ_THREADS) void weight_quant_small_groups_kernel(
     const T *__restrict__ W, int64_t N, int64_t K, int64_t ldw, const float *__restrict__ s,
@@ -192,58 +263,155 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_small_groups_kernel(
     constexpr int G = LANES * 8;
     const int lane = threadIdx.x & 63;
     const int64_t chunks = (K + 511) / 512;
-    const int64_t seg = (int64_t)blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);   // (row, chunk)
-    if (seg >= N * chunks) return;
-    const int64_t n = seg / chunks, c = seg - n * chunks;
+    const int64_t seg = (int64_t)blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);   // (four rows, chunk)
+    if (seg >= (N + SG_ROWS - 1) / SG_ROWS * chunks) return;
+    const int64_t n0 = seg / chunks * SG_ROWS, c = seg - n0 / SG_ROWS * chunks;
     const int64_t k = c * 512 + lane * 8;
     if (k >= K) return;   // whole groups of LANES lanes leave together (K % G == 0)
-    float v[8], x[8];
-    loadv<T, 8>(W + n * ldw + k, v);
-    if (s == nullptr) {
+    Raw8<T> raw[SG_ROWS];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = v[j];
-    } else if (s_vec) {
-        // the lane's eight scales with two 16-byte loads (eight dword loads strided by 32 bytes
-        // over the lanes cost the memory pipeline several times as many cycles)
-        const float4 s0 = *reinterpret_cast<const float4 *>(s + k);
-        const float4 s1 = *reinterpret_cast<const float4 *>(s + k + 4);
-        const float sv[8] = {s0.x, s0.y, s0.z, s0.w, s1.x, s1.y, s1.z, s1.w};
+    for (int r = 0; r < SG_ROWS; ++r) raw[r].load(W + min(n0 + r, N - 1) * ldw + k);   // (rows past the end: not stored)
+    float sv[8];
+    load_scales<8>(s, k, s_vec, sv);
+    const int64_t ng = K / G, g = k / G;
+    const int mine = lane & 3;   // the row whose parameters this lane computes
+    float x[SG_ROWS][8];
+    float lo_m = 0.0f, hi_m = 0.0f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = v[j] * sv[j];
-    } else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = v[j] * s[k + j];
+    for (int r = 0; r < SG_ROWS; ++r) {
+        T e[8];
+        raw[r].elements(e);
+        scaled8(e, sv, s != nullptr, x[r]);
+        if (!use_given) {
+            float lo = 0.0f, hi = 0.0f;
+            min_max8(x[r], lo, hi);
+            lo = fminf(lo, dpp_f32<DPP_QUAD_XOR1>(lo));
+            hi = fmaxf(hi, dpp_f32<DPP_QUAD_XOR1>(hi));
+            lo = fminf(lo, dpp_f32<DPP_QUAD_XOR2>(lo));
+            hi = fmaxf(hi, dpp_f32<DPP_QUAD_XOR2>(hi));
+            lo = fminf(lo, dpp_f32<DPP_ROW_HALF_MIRROR>(lo));
+            hi = fmaxf(hi, dpp_f32<DPP_ROW_HALF_MIRROR>(hi));
+            lo = fminf(lo, dpp_f32<DPP_ROW_MIRROR>(lo));
+            hi = fmaxf(hi, dpp_f32<DPP_ROW_MIRROR>(hi));
+            if (LANES == 32) {
+                lo = fminf(lo, __shfl_xor(lo, 16, WAVE));
+                hi = fmaxf(hi, __shfl_xor(hi, 16, WAVE));
+            }
+            lo_m = mine == r ? lo : lo_m;
+            hi_m = mine == r ? hi : hi_m;
+        }
     }
-    const int64_t pidx = n * (K / G) + k / G;
     float st, istep;
     int z;
+    const int64_t pidx = min(n0 + mine, N - 1) * ng + g;
     if (use_given) {
         st = step[pidx];
         z = zero[pidx];
         istep = 1.0f / st;
     } else {
-        float lo = 0.0f, hi = 0.0f;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            lo = fminf(lo, x[j]);
-            hi = fmaxf(hi, x[j]);
-        }
-#pragma unroll
-        for (int off = LANES / 2; off >= 1; off >>= 1) {
-            lo = fminf(lo, __shfl_xor(lo, off, WAVE));
-            hi = fmaxf(hi, __shfl_xor(hi, off, WAVE));
-        }
-        range_params(lo, hi, st, istep, z, fmt);
-        if ((lane & (LANES - 1)) == 0) {
+        range_params(lo_m, hi_m, st, istep, z, fmt);
+        if ((lane & (LANES - 1)) < 4 && n0 + mine < N) {
             step[pidx] = st;
             zero[pidx] = (uint8_t)z;
         }
     }
-    uint32_t q[8];
+    const float is[SG_ROWS] = {quad_lane_f32<0>(istep), quad_lane_f32<1>(istep), quad_lane_f32<2>(istep),
+                               quad_lane_f32<3>(istep)};
+    const int zs[SG_ROWS] = {quad_lane_i32<0>(z), quad_lane_i32<1>(z), quad_lane_i32<2>(z), quad_lane_i32<3>(z)};
 #pragma unroll
-    for (int j = 0; j < 8; ++j) q[j] = dint4_code(x[j], istep, z, fmt);
-    *reinterpret_cast<uint2 *>(codes + n * K + k) =
-        make_uint2(q[0] | q[1] << 8 | q[2] << 16 | q[3] << 24, q[4] | q[5] << 8 | q[6] << 16 | q[7] << 24);
+    for (int r = 0; r < SG_ROWS; ++r) {
+        const uint2 q = codes8(x[r], make_rule(is[r], zs[r], fmt));
+        if (n0 + r < N) *reinterpret_cast<uint2 *>(codes + (n0 + r) * K + k) = q;
+    }
+}
+
+// Segments (a row, or a group of it) of 1024 to 16384 elements: a block takes SEG_ROWS rows' segments of the
+// same columns, CH chunks of eight elements per thread and row, which stay in registers between the range
+// and the codes: W is read once, and the AQAS scales once for both rows.  One barrier.  Bound by
+// memory (3 bytes per fp16 weight) and the vector ALU.  The wave-per-segment kernel above sweeps W
+// twice, and the second time much of it comes from beyond the L2.
+// 36864 x 9216 per channel: 322 -> 217 us (4.7 TB/s).
+constexpr int SEG_ROWS = 2;
+constexpr int SEG_MAX_CHUNKS = 8;
+
+template <typename T, int CH>
+__global__ __launch_bounds__(WQ_THREADS) void weight_quant_segment_kernel(
+    const T *__restrict__ W, int64_t N, int64_t K, int64_t ldw, const float *__restrict__ s, int G,
+    int use_given, uint8_t *__restrict__ codes, float *__restrict__ step, uint8_t *__restrict__ zero,
+    CodeFormat fmt, int s_vec)
+{
+    __shared__ float part[2 * SEG_ROWS][WQ_THREADS / WAVE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t n0 = (int64_t)blockIdx.x * SEG_ROWS, g = blockIdx.y, ng = K / G;
+    const int chunks = G / 8;
+    const int64_t col = g * G;
+    const bool second = n0 + 1 < N;   // (an odd last row is taken twice and stored once)
+    const T *w[SEG_ROWS] = {W + n0 * ldw + col, W + (second ? n0 + 1 : n0) * ldw + col};
+    float x[SEG_ROWS][CH][8];
+    float lo[SEG_ROWS] = {0.0f, 0.0f}, hi[SEG_ROWS] = {0.0f, 0.0f};
+    Raw8<T> raw[SEG_ROWS][CH];
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        // (past the end: the last chunk again, which changes no range and is not stored)
+        const int k = min(c * WQ_THREADS + tid, chunks - 1) * 8;
+#pragma unroll
+        for (int r = 0; r < SEG_ROWS; ++r) raw[r][c].load(w[r] + k);
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const int k = min(c * WQ_THREADS + tid, chunks - 1) * 8;
+        float sv[8];
+        load_scales<8>(s ? s + col : nullptr, k, s_vec, sv);
+#pragma unroll
+        for (int r = 0; r < SEG_ROWS; ++r) {
+            T e[8];
+            raw[r][c].elements(e);
+            scaled8(e, sv, s != nullptr, x[r][c]);
+            if (!use_given) min_max8(x[r][c], lo[r], hi[r]);
+        }
+    }
+    CodeRule rule[SEG_ROWS];
+    if (!use_given) {
+#pragma unroll
+        for (int r = 0; r < SEG_ROWS; ++r) {
+            lo[r] = wave_min(lo[r]);
+            hi[r] = wave_max(hi[r]);
+            if (lane == 0) {
+                part[2 * r][wave] = lo[r];
+                part[2 * r + 1][wave] = hi[r];
+            }
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int r = 0; r < SEG_ROWS; ++r) {
+        const int64_t pidx = (r == 0 || second ? n0 + r : n0) * ng + g;
+        float st, istep;
+        int z;
+        if (use_given) {
+            istep = 1.0f / step[pidx];
+            z = zero[pidx];
+        } else {
+            const float l = fminf(fminf(part[2 * r][0], part[2 * r][1]), fminf(part[2 * r][2], part[2 * r][3]));
+            const float h = fmaxf(fmaxf(part[2 * r + 1][0], part[2 * r + 1][1]),
+                                  fmaxf(part[2 * r + 1][2], part[2 * r + 1][3]));
+            range_params(l, h, st, istep, z, fmt);
+            if (tid == 0 && (r == 0 || second)) {
+                step[pidx] = st;
+                zero[pidx] = (uint8_t)z;
+            }
+        }
+        rule[r] = make_rule(istep, z, fmt);
+    }
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+        const int at = c * WQ_THREADS + tid;
+        if (at >= chunks) break;
+#pragma unroll
+        for (int r = 0; r < SEG_ROWS; ++r)
+            if (r == 0 || second)
+                *reinterpret_cast<uint2 *>(codes + (n0 + r) * K + col + (int64_t)at * 8) = codes8(x[r][c], rule[r]);
+    }
 }
 
 template <typename T>
@@ -264,7 +432,7 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
     hipLaunchKernelGGL((weight_quant_kernel<T, V_>), dim3((unsigned)blocks), dim3(WQ_THREADS), 0, \
                        st, W, N, K, ldw, s, G, use_given, codes, step, zero, fmt, s_vec)
     if ((G == 128 || G == 256) && aligned(8)) {
-        const int64_t wsegs = N * ((K + 511) / 512);
+        const int64_t wsegs = (N + SG_ROWS - 1) / SG_ROWS * ((K + 511) / 512);
         const int64_t wblocks = (wsegs + (WQ_THREADS / WAVE) - 1) / (WQ_THREADS / WAVE);
         if (wblocks > 0x7fffffffLL) return W4A8_ERR_SHAPE;
         if (G == 128)
@@ -275,6 +443,27 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
             hipLaunchKernelGGL((weight_quant_small_groups_kernel<T, 32>), dim3((unsigned)wblocks),
                                dim3(WQ_THREADS), 0, st, W, N, K, ldw, s, use_given, codes, step, zero, fmt,
                                s_vec);
+    } else if (G >= 1024 && G <= SEG_MAX_CHUNKS * 8 * WQ_THREADS && aligned(8) && K / G <= 65535 &&
+               N <= 0x7fffffffLL) {
+        // at least half the threads of a block have a chunk (shorter segments: a wave each, below), and the
+        // elements of two rows fit in registers
+        const dim3 grid((unsigned)((N + SEG_ROWS - 1) / SEG_ROWS), (unsigned)(K / G));
+#define W4A8_WQ_SEGMENT(CH_)                                                                              \
+    case CH_:                                                                                             \
+        hipLaunchKernelGGL((weight_quant_segment_kernel<T, CH_>), grid, dim3(WQ_THREADS), 0, st, W, N, K, \
+                           ldw, s, (int)G, use_given, codes, step, zero, fmt, s_vec);                     \
+        break
+        switch ((int)((G / 8 + WQ_THREADS - 1) / WQ_THREADS)) {
+            W4A8_WQ_SEGMENT(1);
+            W4A8_WQ_SEGMENT(2);
+            W4A8_WQ_SEGMENT(3);
+            W4A8_WQ_SEGMENT(4);
+            W4A8_WQ_SEGMENT(5);
+            W4A8_WQ_SEGMENT(6);
+            W4A8_WQ_SEGMENT(7);
+            W4A8_WQ_SEGMENT(8);
+        }
+#undef W4A8_WQ_SEGMENT
     } else if (G >= 512 && aligned(8)) {
         W4A8_WQ_LAUNCH(8);
     } else if (aligned(2)) {
@@ -420,6 +609,7 @@ __global__ __launch_bounds__(256) void value_quant_kernel(const T *__restrict__ 
         zero[(b * D + d) * ng + g] = (uint8_t)z;
     }
 
+    const CodeRule rule = make_rule(istep, z);
     const int r = threadIdx.x >> 2, q = threadIdx.x & 3;   // write side: channel row, 16-token quarter
     const int64_t dr = (int64_t)blockIdx.x * 64 + r;
     for (int64_t c0 = 0; c0 < G; c0 += 64) {
@@ -435,7 +625,7 @@ __global__ __launch_bounds__(256) void value_quant_kernel(const T *__restrict__ 
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 const int64_t t = c0 + wave * 16 + i4 * 4 + i;
-                if (live && t < G) word |= dint4_code(x[i4 * 4 + i], istep, z) << (8 * i);
+                if (live && t < G) word |= (code_byte(x[i4 * 4 + i], rule) & 0xffu) << (8 * i);
             }
             s_codes[lane][wave * 4 + i4] = word;
         }
@@ -469,8 +659,7 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
 {
     static_assert(sizeof(T) == 2, "16-bit elements");
     __shared__ float s_lo[4][64], s_hi[4][64];
-    __shared__ float s_st[64], s_istep[64];
-    __shared__ int s_z[64];
+    __shared__ float4 s_rule[64];          // 1 / step, -z, p - z, z of each channel
     __shared__ uint32_t s_codes[64][33];   // [channel][32 words of 4 tokens], odd stride
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c8 = tid & 7, t4 = tid >> 3;
@@ -488,11 +677,11 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
 #pragma unroll
         for (int i = 0; i < 4; ++i) loadv<T, 8>(v + (t0 + 4 * t4 + i) * ld_t, x[i]);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4; i += 2)
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
-                lo[j] = fminf(lo[j], x[i][j]);
-                hi[j] = fmaxf(hi[j], x[i][j]);
+                lo[j] = fminf(fminf(lo[j], x[i][j]), x[i + 1][j]);
+                hi[j] = fmaxf(fmaxf(hi[j], x[i][j]), x[i + 1][j]);
             }
     }
     // over the eight lanes of the wave with the same channels (lane bits 3..5), then over the waves
@@ -519,35 +708,35 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
         float st, istep;
         int z;
         range_params(l, h, st, istep, z);
-        s_st[tid] = st;
-        s_istep[tid] = istep;
-        s_z[tid] = z;
+        const CodeRule r = make_rule(istep, z);
+        s_rule[tid] = make_float4(r.istep, r.lo, r.hi, __int_as_float(r.z));
         if (d0 + tid < D) {
             step[(b * D + d0 + tid) * ng + g] = st;
             zero[(b * D + d0 + tid) * ng + g] = (uint8_t)z;
         }
     }
     __syncthreads();
-    float istep[8];
-    int z[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        istep[j] = s_istep[c8 * 8 + j];
-        z[j] = s_z[c8 * 8 + j];
-    }
 
     // ---- codes: 128 tokens per round, transposed through LDS to token-contiguous rows ------------
     const int r = tid >> 2, q = tid & 3;   // write side: channel row, 32-token quarter
     for (int64_t t0 = 0; t0 < G; t0 += 128) {
-        float x[4][8];
+        Raw8<T> raw[4];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) loadv<T, 8>(v + (t0 + 4 * t4 + i) * ld_t, x[i]);
+        for (int i = 0; i < 4; ++i) raw[i].load(v + (t0 + 4 * t4 + i) * ld_t);
+        T e[4][8];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) raw[i].elements(e[i]);
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            uint32_t word = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) word |= dint4_code(x[i][j], istep[j], z[j]) << (8 * i);
-            s_codes[c8 * 8 + j][t4] = word;
+            // (the channel's rule comes from LDS each time: eight of them in registers cost the kernel
+            // a wave per SIMD and 6 % of its time)
+            const float4 f = s_rule[c8 * 8 + j];
+            CodeRule rule = make_rule(f.x, 0);
+            rule.lo = f.y;
+            rule.hi = f.z;
+            rule.z = __float_as_int(f.w);
+            s_codes[c8 * 8 + j][t4] = pack_low_bytes(code_byte(to_f32(e[0][j]), rule), code_byte(to_f32(e[1][j]), rule),
+                                                     code_byte(to_f32(e[2][j]), rule), code_byte(to_f32(e[3][j]), rule));
         }
         __syncthreads();
         if (d0 + r < D) {

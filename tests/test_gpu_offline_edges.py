@@ -74,3 +74,49 @@ def test_pack_tiles_edges(lib, N, K, plain, shift):
                                       zero.data_ptr(), N, K, 0, fmt, y.data_ptr(), 1, N, None, ws.data_ptr(),
                                       ws.numel(), None) == 0
     assert torch.equal(Y[0], Y[1])
+
+
+# rows that do not fill the last set of rows of a block, a last round of columns that is partly empty, the shortest
+# and longest segments of the register-resident kernel and the lengths just outside it, every input type, rows off
+# the vector alignment; ranges made and given
+@pytest.mark.parametrize("N,K,G", [(1, 128, 128), (5, 640, 128), (6, 768, 256), (7, 1792, 256), (3, 1016, 0),
+                                   (3, 1024, 0), (2, 2056, 0), (5, 9216, 0), (1, 16384, 0), (2, 16392, 0),
+                                   (4, 4096, 1024)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_weight_quant_edges(lib, oracle, N, K, G, dtype):
+    rng = np.random.default_rng(31 * N + K)
+    pad = 8 if N % 2 else 3   # an odd stride takes the scalar loads
+    W = torch.from_numpy((rng.standard_normal((N, K + pad)) * 0.02).astype(np.float32))
+    W[:, K // 2] = 0.0
+    W[0, :128] = 0.0                      # an empty range
+    W[-1, :128] = W[-1, :128].abs()       # zero-point 0
+    W = W.to({"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dtype])
+    s = rng.uniform(0.5, 2.0, K).astype(np.float32)
+    Wd = W.cuda()[:, :K]
+    for scale in (s, None):
+        codes, step, zero = lib.quantize_weight_dint4(Wd, None if scale is None else dev(scale), G)
+        rc, rs, rz = oracle.quantize_weight_dint4(W[:, :K].float().numpy(), scale, G)
+        assert np.array_equal(host(step).view(np.uint32), rs.view(np.uint32))
+        assert np.array_equal(host(zero), rz)
+        assert np.array_equal(host(codes), rc)
+    # a third of the range: most groups saturate at both ends
+    st = (rs / 3).astype(np.float32)
+    codes, _, _ = lib.quantize_weight_dint4(Wd, None, G, step=dev(st), zero=dev(rz))
+    rc, _, _ = oracle.quantize_weight_dint4(W[:, :K].float().numpy(), None, G, step=st, zero=rz)
+    assert np.array_equal(host(codes), rc)
+
+
+# every tie and band edge of the rule, one binary32 step to either side of it, and values far beyond the range (within int32, where the oracle rounds): the
+# steps are given, powers of two, so that u is exact
+@pytest.mark.parametrize("G,K", [(128, 1024), (0, 1024), (0, 320)])
+def test_code_rule_edges(lib, oracle, G, K):
+    half = np.arange(-60, 61, dtype=np.float32) / 4
+    u = np.concatenate([half, np.nextafter(half, np.float32(np.inf)), np.nextafter(half, np.float32(-np.inf)),
+                        np.float32([-0.0, 1e9, -1e9, 63.5, -64.5, 300.0, -300.0])]).astype(np.float32)
+    W = np.resize(u, (16, K)).astype(np.float32)
+    ng = K // (G or K)
+    zero = np.resize(np.arange(14, dtype=np.uint8), (16, ng))
+    step = np.full((16, ng), 0.25, np.float32)
+    rc, _, _ = oracle.quantize_weight_dint4(W * 0.25, None, G, step=step, zero=zero)
+    codes, _, _ = lib.quantize_weight_dint4(dev(W * np.float32(0.25)), None, G, step=dev(step), zero=dev(zero))
+    assert np.array_equal(host(codes), rc)
