@@ -520,10 +520,11 @@ int aqas_check(const void *X, const void *W, int dtype, int64_t M, int64_t N, in
 }
 
 // One evaluation of the layer with scale s: err[n] = sum_m (Yq[m,n] - Yref[m,n])^2.
-// clip_uniform >= 0: the weight ranges are shrunk by that clipping index first.
+// clip_uniform >= 0: the weight ranges are shrunk by that clipping index first, and the channels that it
+// serves better than the indices before it are noted (index_out, err_table or null).
 int aqas_evaluate(const void *X, const void *W, int dtype, int64_t M, int64_t N, int64_t K, int64_t ldx,
                   int64_t ldw, int64_t G, const float *s, int clip_uniform, uint8_t *ws, const AqasWs &w,
-                  void *stream)
+                  int32_t *index_out, double *err_table, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
     int8_t *Xq = (int8_t *)(ws + w.Xq);
@@ -542,8 +543,9 @@ int aqas_evaluate(const void *X, const void *W, int dtype, int64_t M, int64_t N,
     rc = w4a8_gemm(Xq, sx, M, Wp, W4A8_LAYOUT_TILED, step, zero, N, K, G, ws + w.Y, W4A8_F16, N, nullptr,
                    w.gemm_bytes ? ws + w.gemm : nullptr, w.gemm_bytes, stream);
     if (rc != W4A8_OK) return rc;
-    return launch_output_sq_error(ws + w.Y, W4A8_F16, N, (const float *)(ws + w.Yref), M, N,
-                                  (double *)(ws + w.err), st);
+    return launch_output_sq_error(ws + w.Y, W4A8_F16, (const float *)(ws + w.Yref), M, N, (double *)(ws + w.err),
+                                  clip_uniform, clip_uniform >= 0 ? (double *)(ws + w.best_err) : nullptr,
+                                  index_out, err_table, st);
 }
 
 }  // namespace
@@ -591,7 +593,7 @@ int aqas_search(const void *X, const void *W, int dtype, int64_t M, int64_t N, i
     if ((rc = launch_ref_gemm(X, W, dtype, M, N, K, ldx, ldw, (float *)(ws + w.Yref), st)) != W4A8_OK) return rc;
     for (int j = 0; j <= AQ_GRID; ++j) {
         if ((rc = launch_aqas_scale(ax, aw, K, j, nullptr, s, st)) != W4A8_OK) return rc;
-        if ((rc = aqas_evaluate(X, W, dtype, M, N, K, ldx, ldw, G, s, -1, ws, w, stream)) != W4A8_OK) return rc;
+        if ((rc = aqas_evaluate(X, W, dtype, M, N, K, ldx, ldw, G, s, -1, ws, w, nullptr, nullptr, stream)) != W4A8_OK) return rc;
         if ((rc = launch_loss_sum((const double *)(ws + w.err), N, losses, j, st)) != W4A8_OK) return rc;
     }
     if ((rc = launch_argmin(losses, AQ_GRID + 1, best_j, st)) != W4A8_OK) return rc;
@@ -626,9 +628,8 @@ int aqas_clip_search(const void *X, const void *W, int dtype, int64_t M, int64_t
     const AqasWs w = plan_aqas(M, N, K, G);
     if ((rc = launch_ref_gemm(X, W, dtype, M, N, K, ldx, ldw, (float *)(ws + w.Yref), st)) != W4A8_OK) return rc;
     for (int i = 0; i < AQ_CLIP_STEPS; ++i) {
-        if ((rc = aqas_evaluate(X, W, dtype, M, N, K, ldx, ldw, G, s, i, ws, w, stream)) != W4A8_OK) return rc;
-        if ((rc = launch_clip_select((const double *)(ws + w.err), N, i, (double *)(ws + w.best_err),
-                                     index_out, err_table, st)) != W4A8_OK)
+        if ((rc = aqas_evaluate(X, W, dtype, M, N, K, ldx, ldw, G, s, i, ws, w, index_out, err_table, stream)) !=
+            W4A8_OK)
             return rc;
     }
     return launch_clip_params(W, dtype, N, K, ldw, s, G, index_out, 0, step_out, zero_out, st);

@@ -178,22 +178,70 @@ int launch_ref_gemm(const void *X, const void *W, int dtype, int64_t M, int64_t 
 }
 
 // ---- error sums ---------------------------------------------------------------------------------
-// err[n] = sum_m (Y[m,n] - Yref[m,n])^2, one lane per output channel, tokens in ascending order
-// (deterministic); the difference in binary32, squares and sums in binary64.
-__global__ __launch_bounds__(256) void output_sq_error_kernel(const uint16_t *__restrict__ Y, int y_dtype,
-                                                              int64_t ldy, const float *__restrict__ Yref,
-                                                              int64_t M, int64_t N, double *__restrict__ err)
+// err[n] = sum_m (Y[m,n] - Yref[m,n])^2; the difference in binary32, squares and sums in binary64, in a
+// fixed order (deterministic).  Bound by the read of Y and Yref (6 bytes per output, mostly from the
+// caches: both were just written).  A block of 1024 threads takes 16 channels of all tokens: a thread four
+// channels of every 256th token (one 8-byte and one 16-byte load), then the 16 lanes of a wave with the
+// same channels and the 16 waves meet.  (One lane per channel over all tokens left all but N / 256 CUs
+// idle and waited for every load in turn: 512 x 4096: 139 us, now 7.2 us.)
+// The clipping search's bookkeeping rides along: candidate i replaces a channel's incumbent only if strictly
+// better (so ties keep the larger range); err_table (may be null) keeps every candidate's errors.
+struct ClipState {
+    int i;
+    double *best_err;      // null: the search of the scale, which wants err itself
+    int32_t *best_idx;
+    double *err_table;
+};
+
+constexpr int SQ_THREADS = 1024;
+constexpr int SQ_CHANNELS = 16;
+
+__global__ __launch_bounds__(SQ_THREADS) void output_sq_error_kernel(const uint16_t *__restrict__ Y, int y_dtype,
+                                                                     const float *__restrict__ Yref, int64_t M,
+                                                                     int64_t N, double *__restrict__ err,
+                                                                     ClipState clip)
 {
-    const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
-    double sum = 0.0;
-    for (int64_t m = 0; m < M; ++m) {
-        const uint16_t b = Y[m * ldy + n];
-        const float y = (y_dtype == W4A8_F16) ? __half2float(__ushort_as_half(b)) : __uint_as_float((uint32_t)b << 16);
-        const float d = y - Yref[m * N + n];
-        sum += (double)d * (double)d;
+    __shared__ double part[SQ_THREADS / WAVE][SQ_CHANNELS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t n = (int64_t)blockIdx.x * SQ_CHANNELS + (tid & 3) * 4;   // N % 16 == 0
+    double sum[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int64_t m = tid >> 2; m < M; m += SQ_THREADS / 4) {
+        const ushort4 b = *reinterpret_cast<const ushort4 *>(Y + m * N + n);
+        const float4 r = *reinterpret_cast<const float4 *>(Yref + m * N + n);
+        const uint16_t bits[4] = {b.x, b.y, b.z, b.w};
+        const float ref[4] = {r.x, r.y, r.z, r.w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float y = (y_dtype == W4A8_F16) ? __half2float(__ushort_as_half(bits[c]))
+                                                  : __uint_as_float((uint32_t)bits[c] << 16);
+            const float d = y - ref[c];
+            sum[c] += (double)d * (double)d;
+        }
     }
-    err[n] = sum;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+        for (int off = 4; off <= 32; off <<= 1) sum[c] += __shfl_xor(sum[c], off, WAVE);
+    if (lane < 4) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) part[wave][lane * 4 + c] = sum[c];
+    }
+    __syncthreads();
+    if (tid < SQ_CHANNELS) {
+        double e = 0.0;
+#pragma unroll
+        for (int w = 0; w < SQ_THREADS / WAVE; ++w) e += part[w][tid];
+        const int64_t ch = (int64_t)blockIdx.x * SQ_CHANNELS + tid;
+        if (clip.best_err == nullptr) {
+            err[ch] = e;
+        } else {
+            if (clip.err_table != nullptr) clip.err_table[(int64_t)clip.i * N + ch] = e;
+            if (clip.i == 0 || e < clip.best_err[ch]) {
+                clip.best_err[ch] = e;
+                clip.best_idx[ch] = clip.i;
+            }
+        }
+    }
 }
 
 // loss[slot] = sum_n err[n]: one workgroup, fixed tree (deterministic)
@@ -222,28 +270,13 @@ __global__ void argmin_kernel(const double *__restrict__ losses, int count, int3
     *best = b;
 }
 
-// per-channel bookkeeping of the clipping search: candidate i replaces the incumbent only if strictly
-// better (so ties keep the larger range); err_table (may be null) keeps every candidate's errors
-__global__ __launch_bounds__(256) void clip_select_kernel(const double *__restrict__ err, int64_t N, int i,
-                                                          double *__restrict__ best_err,
-                                                          int32_t *__restrict__ best_idx,
-                                                          double *__restrict__ err_table)
+// Y and Yref [M, N] dense, N % 16 == 0, both 16-byte aligned.  best_err null: err[n] is written; else the
+// clipping bookkeeping of candidate i.
+int launch_output_sq_error(const void *Y, int y_dtype, const float *Yref, int64_t M, int64_t N, double *err,
+                           int i, double *best_err, int32_t *best_idx, double *err_table, hipStream_t st)
 {
-    const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (n >= N) return;
-    const double e = err[n];
-    if (err_table != nullptr) err_table[(int64_t)i * N + n] = e;
-    if (i == 0 || e < best_err[n]) {
-        best_err[n] = e;
-        best_idx[n] = i;
-    }
-}
-
-int launch_output_sq_error(const void *Y, int y_dtype, int64_t ldy, const float *Yref, int64_t M,
-                           int64_t N, double *err, hipStream_t st)
-{
-    hipLaunchKernelGGL(output_sq_error_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st,
-                       (const uint16_t *)Y, y_dtype, ldy, Yref, M, N, err);
+    hipLaunchKernelGGL(output_sq_error_kernel, dim3((unsigned)(N / SQ_CHANNELS)), dim3(SQ_THREADS), 0, st,
+                       (const uint16_t *)Y, y_dtype, Yref, M, N, err, ClipState{i, best_err, best_idx, err_table});
     return hip_status(hipGetLastError());
 }
 int launch_loss_sum(const double *err, int64_t N, double *losses, int slot, hipStream_t st)
@@ -256,14 +289,6 @@ int launch_argmin(const double *losses, int count, int32_t *best, hipStream_t st
     hipLaunchKernelGGL(argmin_kernel, dim3(1), dim3(64), 0, st, losses, count, best);
     return hip_status(hipGetLastError());
 }
-int launch_clip_select(const double *err, int64_t N, int i, double *best_err, int32_t *best_idx,
-                       double *err_table, hipStream_t st)
-{
-    hipLaunchKernelGGL(clip_select_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, err, N, i,
-                       best_err, best_idx, err_table);
-    return hip_status(hipGetLastError());
-}
-
 // ---- the error split of Sec. 4.1 (Eq. 4) ---------------------------------------------------------
 // delta = Wq - W diag(s) per weight, written to du where the quantized value is zero (underflow) and
 // to dr otherwise (rounding); the other array gets 0.

@@ -199,12 +199,10 @@ int launch_aqas_scale(const float *ax, const float *aw, int64_t K, int j, const 
                       float *s, hipStream_t st);
 int launch_ref_gemm(const void *X, const void *W, int dtype, int64_t M, int64_t N, int64_t K,
                     int64_t ldx, int64_t ldw, float *Y, hipStream_t st);
-int launch_output_sq_error(const void *Y, int y_dtype, int64_t ldy, const float *Yref, int64_t M,
-                           int64_t N, double *err, hipStream_t st);
+int launch_output_sq_error(const void *Y, int y_dtype, const float *Yref, int64_t M, int64_t N, double *err,
+                           int i, double *best_err, int32_t *best_idx, double *err_table, hipStream_t st);
 int launch_loss_sum(const double *err, int64_t N, double *losses, int slot, hipStream_t st);
 int launch_argmin(const double *losses, int count, int32_t *best, hipStream_t st);
-int launch_clip_select(const double *err, int64_t N, int i, double *best_err, int32_t *best_idx,
-                       double *err_table, hipStream_t st);
 // 3-bit storage of dINT3 codes (0..5, 14 -> 6, 15 -> 7): eight codes in three bytes
 int launch_pack3(const uint8_t *codes, int64_t N, int64_t K, uint8_t *packed, hipStream_t st);
 int launch_unpack3(const uint8_t *packed, int64_t N, int64_t K, uint8_t *codes, hipStream_t st);

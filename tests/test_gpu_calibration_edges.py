@@ -1,0 +1,52 @@
+"""Edges of the calibration kernels: token counts around the error sums' 256-token rounds and the tiles of the
+unquantized product, group sizes that take the tiled quantizer and that do not, every input type."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import synthetic_inputs as syn  # noqa: E402
+from gpu_util import host  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+LOSS_TOL = 1e-4   # fp16 outputs against an fp32 matrix-core product: the tolerance of the search's own parity tests
+DTYPES = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2311_05161_amd as w
+    w.load_library()
+    return w
+
+
+@pytest.mark.parametrize("M,K,N,G,dtype,pad", [
+    (1, 128, 16, 128, "f16", 0), (255, 256, 16, 0, "f16", 8), (257, 384, 48, 128, "f16", 0), (520, 256, 144, 256, "f16", 8),
+    (3, 384, 80, 128, "bf16", 0), (129, 256, 272, 0, "bf16", 8), (65, 512, 32, 128, "f32", 4)])
+def test_searches_at_edges(lib, oracle, M, K, N, G, dtype, pad):
+    aq = oracle.aqas_search
+    X, W, _ = syn.random_layer(M + K + N, M, K, N, x_dtype="f32", outlier_frac=0.02, outlier_gain=20.0)
+    Xd, Wd = (torch.zeros((a.shape[0], K + pad), dtype=DTYPES[dtype], device="cuda") for a in (X, W))
+    Xd[:, :K], Wd[:, :K] = (torch.from_numpy(a.astype(np.float32)).cuda() for a in (X, W))
+    Xd, Wd = Xd[:, :K], Wd[:, :K]
+    X, W = (t.float().cpu().numpy() for t in (Xd, Wd))
+    ref = aq.aqas_search(X, W, G)
+    s, best, losses = lib.aqas_search(Xd, Wd, G)
+    losses, j = host(losses), int(host(best)[0])
+    np.testing.assert_allclose(losses, ref["losses"], rtol=LOSS_TOL)
+    assert losses[j] == losses.min() and np.all(losses[:j] > losses[j])
+    np.testing.assert_array_equal(host(s), aq.aqas_scale(ref["ax"], ref["aw"], j))
+    rc = aq.clip_search(X, W, host(s), G)
+    idx, step, zero, table = lib.aqas_clip_search(Xd, Wd, s, G, want_table=True)
+    idx, table = host(idx), host(table)
+    # An fp16 output whose exact value lies within fp32 rounding (1e-6 relative) of a midpoint may round either way: one
+    # output in some 250, i.e. at most a handful of a channel's M.  Each moves its squared difference d^2 by
+    # ulp (2 |d| + ulp) at most, ulp = 2^-10 of the channel's largest output, |d| within three times its rms.
+    ulp = 2.0 ** -10 * np.abs(X.astype(np.float64) @ W.astype(np.float64).T).max(axis=0) * 1.1
+    bound = 6 * ulp * (6 * np.sqrt(rc["err"] / M) + ulp)
+    assert np.all(np.abs(table - rc["err"]) <= 1e-5 * rc["err"] + bound)
+    for n in range(N):
+        assert table[idx[n], n] == table[:, n].min() and np.all(table[:idx[n], n] > table[idx[n], n])
+    st, z = aq.clipped_params(W, host(s), G, np.array([aq.clip_factor(int(i)) for i in idx], np.float32))
+    np.testing.assert_array_equal(host(step), st)
+    np.testing.assert_array_equal(host(zero), z)
