@@ -519,33 +519,34 @@ int aqas_check(const void *X, const void *W, int dtype, int64_t M, int64_t N, in
     return W4A8_OK;
 }
 
-// One evaluation of the layer with scale s: err[n] = sum_m (Yq[m,n] - Yref[m,n])^2.
+// One evaluation of the layer with scale s: err[n] = sum_m (Yq[m,n] - Yref[m,n])^2.  The quantized
+// activations (Xq, sx in the workspace) are there already.
 // clip_uniform >= 0: the weight ranges are shrunk by that clipping index first, and the channels that it
 // serves better than the indices before it are noted (index_out, err_table or null).
-int aqas_evaluate(const void *X, const void *W, int dtype, int64_t M, int64_t N, int64_t K, int64_t ldx,
-                  int64_t ldw, int64_t G, const float *s, int clip_uniform, uint8_t *ws, const AqasWs &w,
-                  int32_t *index_out, double *err_table, void *stream)
+int aqas_evaluate(const void *W, int dtype, int64_t M, int64_t N, int64_t K, int64_t ldw, int64_t G,
+                  const float *s, int clip_uniform, uint8_t *ws, const AqasWs &w, int32_t *index_out,
+                  double *err_table, void *stream)
 {
     hipStream_t st = (hipStream_t)stream;
-    int8_t *Xq = (int8_t *)(ws + w.Xq);
-    float *sx = (float *)(ws + w.sx), *step = (float *)(ws + w.step);
+    float *step = (float *)(ws + w.step);
     uint8_t *codes = ws + w.codes, *zero = ws + w.zero, *Wp = ws + w.Wp;
-    int rc = quantize_act_int8(X, dtype, M, K, ldx, s, Xq, sx, stream);
-    if (rc != W4A8_OK) return rc;
-    if (clip_uniform >= 0) {
-        rc = launch_clip_params(W, dtype, N, K, ldw, s, G, nullptr, clip_uniform, step, zero, st);
+    const bool clipping = clip_uniform >= 0;
+    const Clipping clip = {nullptr, clipping ? clip_uniform : 0};
+    int rc;
+    if (weight_quant_packs(W, dtype, N, K, ldw, G)) {
+        rc = launch_weight_quant_packed(W, dtype, N, K, ldw, s, G, Wp, step, zero, clip, st);
+    } else {
+        rc = launch_weight_quant(W, dtype, N, K, ldw, s, G, 0, codes, step, zero, W4A8_FMT_DINT4, st, clip);
         if (rc != W4A8_OK) return rc;
+        rc = pack_dint4(codes, N, K, Wp, W4A8_LAYOUT_TILED, stream);
     }
-    rc = quantize_weight_dint4(W, dtype, N, K, ldw, s, G, clip_uniform >= 0 ? 1 : 0, codes, step, zero, stream);
     if (rc != W4A8_OK) return rc;
-    rc = pack_dint4(codes, N, K, Wp, W4A8_LAYOUT_TILED, stream);
-    if (rc != W4A8_OK) return rc;
-    rc = w4a8_gemm(Xq, sx, M, Wp, W4A8_LAYOUT_TILED, step, zero, N, K, G, ws + w.Y, W4A8_F16, N, nullptr,
-                   w.gemm_bytes ? ws + w.gemm : nullptr, w.gemm_bytes, stream);
+    rc = w4a8_gemm((const int8_t *)(ws + w.Xq), (const float *)(ws + w.sx), M, Wp, W4A8_LAYOUT_TILED, step, zero, N,
+                   K, G, ws + w.Y, W4A8_F16, N, nullptr, w.gemm_bytes ? ws + w.gemm : nullptr, w.gemm_bytes, stream);
     if (rc != W4A8_OK) return rc;
     return launch_output_sq_error(ws + w.Y, W4A8_F16, (const float *)(ws + w.Yref), M, N, (double *)(ws + w.err),
-                                  clip_uniform, clip_uniform >= 0 ? (double *)(ws + w.best_err) : nullptr,
-                                  index_out, err_table, st);
+                                  clip_uniform, clipping ? (double *)(ws + w.best_err) : nullptr, index_out,
+                                  err_table, st);
 }
 
 }  // namespace
@@ -573,7 +574,7 @@ int aqas_scale(const float *ax, const float *aw, int64_t K, int j, float *s, voi
 {
     if (K < 1 || j < 0 || j > AQ_GRID) return W4A8_ERR_SHAPE;
     if (!ax || !aw || !s) return W4A8_ERR_NULL;
-    return launch_aqas_scale(ax, aw, K, j, nullptr, s, (hipStream_t)stream);
+    return launch_aqas_scale(ax, aw, K, j, s, (hipStream_t)stream);
 }
 
 int aqas_search(const void *X, const void *W, int dtype, int64_t M, int64_t N, int64_t K, int64_t ldx,
@@ -591,13 +592,15 @@ int aqas_search(const void *X, const void *W, int dtype, int64_t M, int64_t N, i
     if ((rc = launch_channel_absmax(X, dtype, M, K, ldx, ax, st)) != W4A8_OK) return rc;
     if ((rc = launch_channel_absmax(W, dtype, N, K, ldw, aw, st)) != W4A8_OK) return rc;
     if ((rc = launch_ref_gemm(X, W, dtype, M, N, K, ldx, ldw, (float *)(ws + w.Yref), st)) != W4A8_OK) return rc;
+    const double *err = (const double *)(ws + w.err);
     for (int j = 0; j <= AQ_GRID; ++j) {
-        if ((rc = launch_aqas_scale(ax, aw, K, j, nullptr, s, st)) != W4A8_OK) return rc;
-        if ((rc = aqas_evaluate(X, W, dtype, M, N, K, ldx, ldw, G, s, -1, ws, w, nullptr, nullptr, stream)) != W4A8_OK) return rc;
-        if ((rc = launch_loss_sum((const double *)(ws + w.err), N, losses, j, st)) != W4A8_OK) return rc;
+        if ((rc = launch_aqas_next_point(ax, aw, K, j, s, err, N, losses, st)) != W4A8_OK) return rc;
+        rc = quantize_act_int8(X, dtype, M, K, ldx, s, (int8_t *)(ws + w.Xq), (float *)(ws + w.sx), stream);
+        if (rc != W4A8_OK) return rc;
+        if ((rc = aqas_evaluate(W, dtype, M, N, K, ldw, G, s, -1, ws, w, nullptr, nullptr, stream)) != W4A8_OK)
+            return rc;
     }
-    if ((rc = launch_argmin(losses, AQ_GRID + 1, best_j, st)) != W4A8_OK) return rc;
-    return launch_aqas_scale(ax, aw, K, 0, best_j, s_out, st);
+    return launch_aqas_finish(ax, aw, K, s_out, err, N, losses, best_j, st);
 }
 
 int dint4_clipped_params(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s,
@@ -610,8 +613,8 @@ int dint4_clipped_params(const void *W, int w_dtype, int64_t N, int64_t K, int64
     if (!index && (uniform_index < 0 || uniform_index >= AQ_CLIP_STEPS)) return W4A8_ERR_SHAPE;
     if (N == 0) return W4A8_OK;
     if (!W || !step || !zero) return W4A8_ERR_NULL;
-    return launch_clip_params(W, w_dtype, N, K, ldw, s, G, index, uniform_index, step, zero,
-                              (hipStream_t)stream);
+    return launch_weight_quant(W, w_dtype, N, K, ldw, s, G, 0, nullptr, step, zero, W4A8_FMT_DINT4,
+                               (hipStream_t)stream, Clipping{index, uniform_index});
 }
 
 int aqas_clip_search(const void *X, const void *W, int dtype, int64_t M, int64_t N, int64_t K,
@@ -627,12 +630,15 @@ int aqas_clip_search(const void *X, const void *W, int dtype, int64_t M, int64_t
     uint8_t *ws = (uint8_t *)workspace;
     const AqasWs w = plan_aqas(M, N, K, G);
     if ((rc = launch_ref_gemm(X, W, dtype, M, N, K, ldx, ldw, (float *)(ws + w.Yref), st)) != W4A8_OK) return rc;
+    // (the activations do not depend on the clipping: quantized once for all factors)
+    rc = quantize_act_int8(X, dtype, M, K, ldx, s, (int8_t *)(ws + w.Xq), (float *)(ws + w.sx), stream);
+    if (rc != W4A8_OK) return rc;
     for (int i = 0; i < AQ_CLIP_STEPS; ++i) {
-        if ((rc = aqas_evaluate(X, W, dtype, M, N, K, ldx, ldw, G, s, i, ws, w, index_out, err_table, stream)) !=
-            W4A8_OK)
+        if ((rc = aqas_evaluate(W, dtype, M, N, K, ldw, G, s, i, ws, w, index_out, err_table, stream)) != W4A8_OK)
             return rc;
     }
-    return launch_clip_params(W, dtype, N, K, ldw, s, G, index_out, 0, step_out, zero_out, st);
+    return launch_weight_quant(W, dtype, N, K, ldw, s, G, 0, nullptr, step_out, zero_out, W4A8_FMT_DINT4, st,
+                               Clipping{index_out, 0});
 }
 
 }  // extern "C"

@@ -1,8 +1,8 @@
 // AQAS scale search (Sec. 3.2, Eq. 1: the scale vector s minimizes the squared error of the quantized
 // layer's output against the unquantized product on calibration activations; App. A.4: maximum
 // magnitude per input channel as the representative of activations and weights, a grid search, then
-// weight clipping).  Offline work whose inner loop is the layer itself: every candidate runs
-// quantize_act_int8, quantize_weight_dint4, pack_dint4 and w4a8_gemm, the kernels below supply the
+// weight clipping).  Offline work whose inner loop is the layer itself: every candidate runs the layer's
+// activation and weight quantizers, packing and w4a8_gemm, the kernels below supply the
 // representatives, the scale family, the unquantized product and the error sums.  Everything stays on
 // the stream: the best grid point is picked on the device and the final scale is computed from it there.
 //
@@ -84,29 +84,24 @@ __device__ __forceinline__ float pow_sixteenths(float x, int j)
     return out;
 }
 
-// j_dev != null: the grid point is read from device memory (the search's own result)
+__device__ __forceinline__ float scale_at(float x, float w, int j)
+{
+    if (x == 0.0f || w == 0.0f) return 1.0f;
+    const float v = pow_sixteenths(x, j) / pow_sixteenths(w, AQ_GRID - j);
+    return fminf(fmaxf(v, 1e-4f), 1e4f);
+}
+
 __global__ __launch_bounds__(256) void aqas_scale_kernel(const float *__restrict__ ax,
                                                          const float *__restrict__ aw, int64_t K, int j,
-                                                         const int32_t *__restrict__ j_dev,
                                                          float *__restrict__ s)
 {
     const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (k >= K) return;
-    if (j_dev != nullptr) j = *j_dev;
-    const float x = ax[k], w = aw[k];
-    float v = 1.0f;
-    if (x != 0.0f && w != 0.0f) {
-        v = pow_sixteenths(x, j) / pow_sixteenths(w, AQ_GRID - j);
-        v = fminf(fmaxf(v, 1e-4f), 1e4f);
-    }
-    s[k] = v;
+    if (k < K) s[k] = scale_at(ax[k], aw[k], j);
 }
 
-int launch_aqas_scale(const float *ax, const float *aw, int64_t K, int j, const int32_t *j_dev,
-                      float *s, hipStream_t st)
+int launch_aqas_scale(const float *ax, const float *aw, int64_t K, int j, float *s, hipStream_t st)
 {
-    hipLaunchKernelGGL(aqas_scale_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, ax, aw, K,
-                       j, j_dev, s);
+    hipLaunchKernelGGL(aqas_scale_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, ax, aw, K, j, s);
     return hip_status(hipGetLastError());
 }
 
@@ -244,30 +239,68 @@ __global__ __launch_bounds__(SQ_THREADS) void output_sq_error_kernel(const uint1
     }
 }
 
-// loss[slot] = sum_n err[n]: one workgroup, fixed tree (deterministic)
-__global__ __launch_bounds__(256) void loss_sum_kernel(const double *__restrict__ err, int64_t N,
-                                                       double *__restrict__ losses, int slot)
+// sum_n err[n] in thread 0's return value: one workgroup of THREADS, fixed tree (deterministic)
+template <int THREADS>
+__device__ __forceinline__ double block_sum(const double *__restrict__ err, int64_t N, double *part)
 {
-    __shared__ double part[256];
     double s = 0.0;
-    for (int64_t n = threadIdx.x; n < N; n += 256) s += err[n];
+    for (int64_t n = threadIdx.x; n < N; n += THREADS) s += err[n];
     part[threadIdx.x] = s;
     __syncthreads();
-    for (int w = 128; w >= 1; w >>= 1) {
+    for (int w = THREADS / 2; w >= 1; w >>= 1) {
         if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) losses[slot] = part[0];
+    return part[0];
 }
 
-// first minimum of losses[0..count)
-__global__ void argmin_kernel(const double *__restrict__ losses, int count, int32_t *__restrict__ best)
+// Between two grid points: losses[j - 1] from the errors of the point just evaluated (the last block;
+// j = 0: nothing to sum) and the scale of point j.  Neither depends on the other; two launches cost twice
+// the launch time, which is all either takes.
+__global__ __launch_bounds__(256) void aqas_next_point_kernel(const float *__restrict__ ax,
+                                                              const float *__restrict__ aw, int64_t K, int j,
+                                                              float *__restrict__ s,
+                                                              const double *__restrict__ err, int64_t N,
+                                                              double *__restrict__ losses)
 {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    int b = 0;
-    for (int i = 1; i < count; ++i)
-        if (losses[i] < losses[b]) b = i;
-    *best = b;
+    __shared__ double part[256];
+    if (blockIdx.x + 1 == gridDim.x) {
+        if (j == 0) return;
+        const double sum = block_sum<256>(err, N, part);
+        if (threadIdx.x == 0) losses[j - 1] = sum;
+        return;
+    }
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k < K) s[k] = scale_at(ax[k], aw[k], j);
+}
+
+// After the last grid point: its loss, the first minimum of all of them, the scale there.
+__global__ __launch_bounds__(1024) void aqas_finish_kernel(const float *__restrict__ ax,
+                                                           const float *__restrict__ aw, int64_t K,
+                                                           float *__restrict__ s,
+                                                           const double *__restrict__ err, int64_t N,
+                                                           double *__restrict__ losses, int32_t *__restrict__ best)
+{
+    __shared__ double part[1024];
+    __shared__ int s_best;
+    const double last = block_sum<1024>(err, N, part);
+    if (threadIdx.x == 0) {
+        losses[AQ_GRID] = last;
+        int b = 0;
+        double at_b = losses[0];
+        for (int i = 1; i <= AQ_GRID; ++i) {
+            const double l = i == AQ_GRID ? last : losses[i];
+            if (l < at_b) {
+                b = i;
+                at_b = l;
+            }
+        }
+        *best = b;
+        s_best = b;
+    }
+    __syncthreads();
+    const int j = s_best;
+    for (int64_t k = threadIdx.x; k < K; k += 1024) s[k] = scale_at(ax[k], aw[k], j);
 }
 
 // Y and Yref [M, N] dense, N % 16 == 0, both 16-byte aligned.  best_err null: err[n] is written; else the
@@ -279,16 +312,20 @@ int launch_output_sq_error(const void *Y, int y_dtype, const float *Yref, int64_
                        (const uint16_t *)Y, y_dtype, Yref, M, N, err, ClipState{i, best_err, best_idx, err_table});
     return hip_status(hipGetLastError());
 }
-int launch_loss_sum(const double *err, int64_t N, double *losses, int slot, hipStream_t st)
+int launch_aqas_next_point(const float *ax, const float *aw, int64_t K, int j, float *s, const double *err,
+                           int64_t N, double *losses, hipStream_t st)
 {
-    hipLaunchKernelGGL(loss_sum_kernel, dim3(1), dim3(256), 0, st, err, N, losses, slot);
+    hipLaunchKernelGGL(aqas_next_point_kernel, dim3((unsigned)((K + 255) / 256 + 1)), dim3(256), 0, st, ax, aw, K,
+                       j, s, err, N, losses);
     return hip_status(hipGetLastError());
 }
-int launch_argmin(const double *losses, int count, int32_t *best, hipStream_t st)
+int launch_aqas_finish(const float *ax, const float *aw, int64_t K, float *s, const double *err, int64_t N,
+                       double *losses, int32_t *best, hipStream_t st)
 {
-    hipLaunchKernelGGL(argmin_kernel, dim3(1), dim3(64), 0, st, losses, count, best);
+    hipLaunchKernelGGL(aqas_finish_kernel, dim3(1), dim3(1024), 0, st, ax, aw, K, s, err, N, losses, best);
     return hip_status(hipGetLastError());
 }
+
 // ---- the error split of Sec. 4.1 (Eq. 4) ---------------------------------------------------------
 // delta = Wq - W diag(s) per weight, written to du where the quantized value is zero (underflow) and
 // to dr otherwise (rounding); the other array gets 0.

@@ -91,15 +91,6 @@ __global__ __launch_bounds__(PK_THREADS) void pack_tiled_kernel(
     }
 }
 
-// Four codes (one per byte, upper bits ignored) -> their nibbles of the tiled layout, one per byte:
-// (c >> 1) | (c & 1) << 3, with bit 3 flipped for the special codes 14 / 15 (`special` = 0x01010101;
-// 0 for ordinary INT4, whose codes 14 and 15 are an integer pair like the others).
-__device__ __forceinline__ uint32_t recode4(uint32_t c, uint32_t special)
-{
-    const uint32_t m = (c >> 3) & (c >> 2) & (c >> 1) & special;
-    return ((c >> 1) & 0x07070707u) | (((c & 0x01010101u) ^ m) << 3);
-}
-
 // pack_tiled_kernel for 16-byte aligned buffers.  Bound by memory: 1.5 bytes per code (0.5 + 0.5 from
 // canonical bytes) come and go once.  A wave takes one 1 KB tile per round, a lane its 32 consecutive
 // codes (two 16-byte loads) and its 16 bytes of the tile (one store), four codes per register; the

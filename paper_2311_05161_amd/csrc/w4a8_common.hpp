@@ -94,6 +94,16 @@ __device__ __forceinline__ int wave_sum_i32(int v)
            __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
 }
 
+// ---- nibbles of the tiled layout -------------------------------------------------------------
+// Four codes (one per byte, upper bits ignored) -> their nibbles of the tiled layout, one per byte:
+// (c >> 1) | (c & 1) << 3, with bit 3 flipped for the special codes 14 / 15 (`special` = 0x01010101;
+// 0 for ordinary INT4, whose codes 14 and 15 are an integer pair like the others).
+__device__ __forceinline__ uint32_t recode4(uint32_t c, uint32_t special)
+{
+    const uint32_t m = (c >> 3) & (c >> 2) & (c >> 1) & special;
+    return ((c >> 1) & 0x07070707u) | (((c & 0x01010101u) ^ m) << 3);
+}
+
 // ---- dINT4 nibble decode for the int8 matrix cores -----------------------------------------
 //
 // A stored nibble is e = l | h << 3 (see the tiled layout in w4a8.h): l in 0..6 names the pair
@@ -185,24 +195,36 @@ int launch_weight_sums(const uint8_t *codes, const uint8_t *zero, int64_t N, int
                        int32_t *wsum, int32_t *tsum, hipStream_t st);
 int launch_acc_zero_point(int32_t *acc, const int32_t *zx, const int32_t *wsum, int64_t M,
                           int64_t per_token, hipStream_t st);
+// The clipping of the ranges: each is shrunk by rho = 1 - 0.05 i, i = idx[n] (or `uniform` when idx is
+// null); i = 0 leaves it as it is.
+struct Clipping {
+    const int32_t *idx;
+    int uniform;
+};
+// codes null: only step and zero are made
 int launch_weight_quant(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw,
                         const float *s, int64_t G, int use_given, uint8_t *codes, float *step,
-                        uint8_t *zero, int format, hipStream_t st);
-// step / zero of the ranges shrunk by rho = 1 - 0.05 i, i = idx[n] (or `uniform` when idx is null)
-int launch_clip_params(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s,
-                       int64_t G, const int32_t *idx, int uniform, float *step, uint8_t *zero,
-                       hipStream_t st);
+                        uint8_t *zero, int format, hipStream_t st, Clipping clip = Clipping{nullptr, 0});
+// dINT4 straight to the tiled packed form (step and zero as launch_weight_quant makes them), where
+// weight_quant_packs() says that the group size and alignment allow it
+bool weight_quant_packs(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, int64_t G);
+int launch_weight_quant_packed(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s,
+                               int64_t G, uint8_t *packed, float *step, uint8_t *zero, Clipping clip,
+                               hipStream_t st);
 // AQAS scale search helpers (aqas_search.hip)
 int launch_channel_absmax(const void *A, int dtype, int64_t R, int64_t K, int64_t lda, float *out,
                           hipStream_t st);
-int launch_aqas_scale(const float *ax, const float *aw, int64_t K, int j, const int32_t *j_dev,
-                      float *s, hipStream_t st);
+int launch_aqas_scale(const float *ax, const float *aw, int64_t K, int j, float *s, hipStream_t st);
+// losses[j - 1] = sum of err (j > 0) and the scale s of grid point j; then the last loss, the first minimum
+// of all losses and the scale there
+int launch_aqas_next_point(const float *ax, const float *aw, int64_t K, int j, float *s, const double *err,
+                           int64_t N, double *losses, hipStream_t st);
+int launch_aqas_finish(const float *ax, const float *aw, int64_t K, float *s, const double *err, int64_t N,
+                       double *losses, int32_t *best, hipStream_t st);
 int launch_ref_gemm(const void *X, const void *W, int dtype, int64_t M, int64_t N, int64_t K,
                     int64_t ldx, int64_t ldw, float *Y, hipStream_t st);
 int launch_output_sq_error(const void *Y, int y_dtype, const float *Yref, int64_t M, int64_t N, double *err,
                            int i, double *best_err, int32_t *best_idx, double *err_table, hipStream_t st);
-int launch_loss_sum(const double *err, int64_t N, double *losses, int slot, hipStream_t st);
-int launch_argmin(const double *losses, int count, int32_t *best, hipStream_t st);
 // 3-bit storage of dINT3 codes (0..5, 14 -> 6, 15 -> 7): eight codes in three bytes
 int launch_pack3(const uint8_t *codes, int64_t N, int64_t K, uint8_t *packed, hipStream_t st);
 int launch_unpack3(const uint8_t *packed, int64_t N, int64_t K, uint8_t *codes, hipStream_t st);

@@ -125,6 +125,13 @@ __device__ __forceinline__ void range_params(float lo, float hi, float &st, floa
     }
 }
 
+// Factor of a row's ranges (App. A.4: after the scale search the weights are additionally clipped): the
+// (zero-containing) ends are multiplied by it, one binary32 multiply each; values beyond saturate.
+__device__ __forceinline__ float clip_factor(const Clipping &clip, int64_t n)
+{
+    return 1.0f - 0.05f * (float)(clip.idx ? clip.idx[n] : clip.uniform);
+}
+
 // The V scales of a lane's V consecutive columns (1 where there is no scale vector).  Eight of
 // them with two 16-byte loads where the vector is aligned: eight dword loads strided by 32 bytes
 // over the lanes cost the memory pipeline several times as many cycles.
@@ -149,7 +156,7 @@ template <typename T, int V>
 __global__ __launch_bounds__(WQ_THREADS) void weight_quant_kernel(
     const T *__restrict__ W, int64_t N, int64_t K, int64_t ldw, const float *__restrict__ s,
     int64_t G, int use_given, uint8_t *__restrict__ codes, float *__restrict__ step,
-    uint8_t *__restrict__ zero, CodeFormat fmt, int s_vec)
+    uint8_t *__restrict__ zero, CodeFormat fmt, int s_vec, Clipping clip)
 {
     const int lane = threadIdx.x & 63;
     const int64_t ng = K / G;
@@ -178,14 +185,16 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_kernel(
                 hi = fmaxf(hi, x);
             }
         }
-        lo = wave_min(lo);
-        hi = wave_max(hi);
+        const float rho = clip_factor(clip, n);
+        lo = wave_min(lo) * rho;
+        hi = wave_max(hi) * rho;
         range_params(lo, hi, st, istep, z, fmt);
         if (lane == 0) {
             step[seg] = st;
             zero[seg] = (uint8_t)z;
         }
     }
+    if (codes == nullptr) return;
 
     const CodeRule rule = make_rule(istep, z, fmt);
     uint8_t *c = codes + n * K + g * G;
@@ -258,7 +267,7 @@ template <typename T, int LANES>
 __global__ __launch_bounds__(WQ_THREADS) void weight_quant_small_groups_kernel(
     const T *__restrict__ W, int64_t N, int64_t K, int64_t ldw, const float *__restrict__ s,
     int use_given, uint8_t *__restrict__ codes, float *__restrict__ step, uint8_t *__restrict__ zero,
-    CodeFormat fmt, int s_vec)
+    CodeFormat fmt, int s_vec, Clipping clip)
 {
     constexpr int G = LANES * 8;
     const int lane = threadIdx.x & 63;
@@ -309,12 +318,14 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_small_groups_kernel(
         z = zero[pidx];
         istep = 1.0f / st;
     } else {
-        range_params(lo_m, hi_m, st, istep, z, fmt);
+        const float rho = clip_factor(clip, min(n0 + mine, N - 1));
+        range_params(lo_m * rho, hi_m * rho, st, istep, z, fmt);
         if ((lane & (LANES - 1)) < 4 && n0 + mine < N) {
             step[pidx] = st;
             zero[pidx] = (uint8_t)z;
         }
     }
+    if (codes == nullptr) return;
     const float is[SG_ROWS] = {quad_lane_f32<0>(istep), quad_lane_f32<1>(istep), quad_lane_f32<2>(istep),
                                quad_lane_f32<3>(istep)};
     const int zs[SG_ROWS] = {quad_lane_i32<0>(z), quad_lane_i32<1>(z), quad_lane_i32<2>(z), quad_lane_i32<3>(z)};
@@ -338,7 +349,7 @@ template <typename T, int CH>
 __global__ __launch_bounds__(WQ_THREADS) void weight_quant_segment_kernel(
     const T *__restrict__ W, int64_t N, int64_t K, int64_t ldw, const float *__restrict__ s, int G,
     int use_given, uint8_t *__restrict__ codes, float *__restrict__ step, uint8_t *__restrict__ zero,
-    CodeFormat fmt, int s_vec)
+    CodeFormat fmt, int s_vec, Clipping clip)
 {
     __shared__ float part[2 * SEG_ROWS][WQ_THREADS / WAVE];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -385,7 +396,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_segment_kernel(
     }
 #pragma unroll
     for (int r = 0; r < SEG_ROWS; ++r) {
-        const int64_t pidx = (r == 0 || second ? n0 + r : n0) * ng + g;
+        const int64_t n = r == 0 || second ? n0 + r : n0, pidx = n * ng + g;
         float st, istep;
         int z;
         if (use_given) {
@@ -395,7 +406,8 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_segment_kernel(
             const float l = fminf(fminf(part[2 * r][0], part[2 * r][1]), fminf(part[2 * r][2], part[2 * r][3]));
             const float h = fmaxf(fmaxf(part[2 * r + 1][0], part[2 * r + 1][1]),
                                   fmaxf(part[2 * r + 1][2], part[2 * r + 1][3]));
-            range_params(l, h, st, istep, z, fmt);
+            const float rho = clip_factor(clip, n);
+            range_params(l * rho, h * rho, st, istep, z, fmt);
             if (tid == 0 && (r == 0 || second)) {
                 step[pidx] = st;
                 zero[pidx] = (uint8_t)z;
@@ -403,6 +415,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_segment_kernel(
         }
         rule[r] = make_rule(istep, z, fmt);
     }
+    if (codes == nullptr) return;
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
         const int at = c * WQ_THREADS + tid;
@@ -417,7 +430,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_segment_kernel(
 template <typename T>
 static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, const float *s,
                                  int64_t G, int use_given, uint8_t *codes, float *step,
-                                 uint8_t *zero, CodeFormat fmt, hipStream_t st)
+                                 uint8_t *zero, CodeFormat fmt, hipStream_t st, Clipping clip)
 {
     const int64_t segs = N * (K / G);
     if (segs == 0) return W4A8_OK;
@@ -430,7 +443,7 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
     };
 #define W4A8_WQ_LAUNCH(V_)                                                                        \
     hipLaunchKernelGGL((weight_quant_kernel<T, V_>), dim3((unsigned)blocks), dim3(WQ_THREADS), 0, \
-                       st, W, N, K, ldw, s, G, use_given, codes, step, zero, fmt, s_vec)
+                       st, W, N, K, ldw, s, G, use_given, codes, step, zero, fmt, s_vec, clip)
     if ((G == 128 || G == 256) && aligned(8)) {
         const int64_t wsegs = (N + SG_ROWS - 1) / SG_ROWS * ((K + 511) / 512);
         const int64_t wblocks = (wsegs + (WQ_THREADS / WAVE) - 1) / (WQ_THREADS / WAVE);
@@ -438,11 +451,11 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
         if (G == 128)
             hipLaunchKernelGGL((weight_quant_small_groups_kernel<T, 16>), dim3((unsigned)wblocks),
                                dim3(WQ_THREADS), 0, st, W, N, K, ldw, s, use_given, codes, step, zero, fmt,
-                               s_vec);
+                               s_vec, clip);
         else
             hipLaunchKernelGGL((weight_quant_small_groups_kernel<T, 32>), dim3((unsigned)wblocks),
                                dim3(WQ_THREADS), 0, st, W, N, K, ldw, s, use_given, codes, step, zero, fmt,
-                               s_vec);
+                               s_vec, clip);
     } else if (G >= 1024 && G <= SEG_MAX_CHUNKS * 8 * WQ_THREADS && aligned(8) && K / G <= 65535 &&
                N <= 0x7fffffffLL) {
         // at least half the threads of a block have a chunk (shorter segments: a wave each, below), and the
@@ -451,7 +464,7 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
 #define W4A8_WQ_SEGMENT(CH_)                                                                              \
     case CH_:                                                                                             \
         hipLaunchKernelGGL((weight_quant_segment_kernel<T, CH_>), grid, dim3(WQ_THREADS), 0, st, W, N, K, \
-                           ldw, s, (int)G, use_given, codes, step, zero, fmt, s_vec);                     \
+                           ldw, s, (int)G, use_given, codes, step, zero, fmt, s_vec, clip);                     \
         break
         switch ((int)((G / 8 + WQ_THREADS - 1) / WQ_THREADS)) {
             W4A8_WQ_SEGMENT(1);
@@ -477,7 +490,7 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
 
 int launch_weight_quant(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw,
                         const float *s, int64_t G, int use_given, uint8_t *codes, float *step,
-                        uint8_t *zero, int format, hipStream_t st)
+                        uint8_t *zero, int format, hipStream_t st, Clipping clip)
 {
     CodeFormat fmt;
     switch (format) {
@@ -491,72 +504,115 @@ int launch_weight_quant(const void *W, int w_dtype, int64_t N, int64_t K, int64_
     switch (w_dtype) {
         case W4A8_F32:
             return launch_weight_quant_t((const float *)W, N, K, ldw, s, G, use_given, codes, step,
-                                         zero, fmt, st);
+                                         zero, fmt, st, clip);
         case W4A8_F16:
             return launch_weight_quant_t((const __half *)W, N, K, ldw, s, G, use_given, codes, step,
-                                         zero, fmt, st);
+                                         zero, fmt, st, clip);
         case W4A8_BF16:
             return launch_weight_quant_t((const bf16_t *)W, N, K, ldw, s, G, use_given, codes, step,
-                                         zero, fmt, st);
+                                         zero, fmt, st, clip);
         default: return W4A8_ERR_DTYPE;
     }
 }
 
-// ---- clipped ranges (App. A.4: after the scale search the weights are additionally clipped) ------
-// step / zero of the (zero-containing) min-max range of each (row, group) of W diag(s), shrunk by
-// rho = 1 - 0.05 i: i = idx[n] per output row, or the same `uniform` index for all rows.  The codes
-// then come from quantize_weight_dint4 with these parameters given (values beyond the shrunk range
-// saturate at its end levels).  One wave per (row, group).
+// ---- quantized straight to the tiled packed form --------------------------------------------------
+// dINT4 with groups of 128: a 16 x 128 tile of the packed form is 16 whole groups.  A wave takes two tiles of
+// the same columns (they share the AQAS scales): lane l holds row l % 16, columns 32 c + 8 (l / 16) .. + 7,
+// c = 0..3, so that a load instruction reads 64 contiguous bytes of each row (32 consecutive columns per
+// lane, which would make one 16-byte store, read 16-byte pieces and measured the same), the four
+// lanes of a group meet in two shuffles, and codes 8 c' .. of quarter c are one word of the tile.
+// Bound by the read of W (2.5 bytes per fp16 weight move instead of the 4 of quantizing and packing
+// one after the other).  4096 x 4096 fp16: 14.7 + 5.5 -> 13.4 us.
+constexpr int WQT_TILES = 2;
+
 template <typename T>
-__global__ __launch_bounds__(WQ_THREADS) void clip_params_kernel(
-    const T *__restrict__ W, int64_t N, int64_t K, int64_t ldw, const float *__restrict__ s, int64_t G,
-    const int32_t *__restrict__ idx, int uniform, float *__restrict__ step, uint8_t *__restrict__ zero)
+__global__ __launch_bounds__(WQ_THREADS) void weight_quant_packed_kernel(
+    const T *__restrict__ W, uint32_t NT, uint32_t KT, int64_t ldw, const float *__restrict__ s,
+    uint32_t *__restrict__ packed, float *__restrict__ step, uint8_t *__restrict__ zero, int s_vec, Clipping clip)
 {
     const int lane = threadIdx.x & 63;
-    const int64_t ng = K / G;
-    const int64_t seg = (int64_t)blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);
-    if (seg >= N * ng) return;
-    const int64_t n = seg / ng, g = seg % ng;
-    const T *w = W + n * ldw + g * G;
-    const float *sg = s ? s + g * G : nullptr;
-    float lo = 0.0f, hi = 0.0f;
-    for (int64_t k = lane; k < G; k += WAVE) {
-        const float v = to_f32(w[k]);
-        const float x = sg ? v * sg[k] : v;
-        lo = fminf(lo, x);
-        hi = fmaxf(hi, x);
+    const uint32_t wave = blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);
+    const uint32_t ntp = wave / KT, kt = wave - ntp * KT;   // (pair of row tiles, k-tile)
+    if (ntp * WQT_TILES >= NT) return;                      // whole wave
+    const int row = lane & 15;
+    const int kb = lane >> 4;
+    const int64_t k = (int64_t)kt * TILE_K + kb * 8;
+    uint32_t nt[WQT_TILES];
+    Raw8<T> raw[WQT_TILES][4];
+#pragma unroll
+    for (int i = 0; i < WQT_TILES; ++i) {
+        nt[i] = min(ntp * WQT_TILES + i, NT - 1);   // (past the end: the last tile again, the same results)
+        const T *w = W + ((int64_t)nt[i] * TILE_N + row) * ldw + k;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) raw[i][c].load(w + 32 * c);
     }
-    lo = wave_min(lo);
-    hi = wave_max(hi);
-    const float rho = 1.0f - 0.05f * (float)(idx ? idx[n] : uniform);
-    lo = lo * rho;
-    hi = hi * rho;
-    float st, istep;
-    int z;
-    range_params(lo, hi, st, istep, z);
-    if (lane == 0) {
-        step[seg] = st;
-        zero[seg] = (uint8_t)z;
+    float x[WQT_TILES][4][8];
+    float lo[WQT_TILES], hi[WQT_TILES];
+#pragma unroll
+    for (int i = 0; i < WQT_TILES; ++i) lo[i] = hi[i] = 0.0f;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        float sv[8];
+        load_scales<8>(s, k + 32 * c, s_vec, sv);
+#pragma unroll
+        for (int i = 0; i < WQT_TILES; ++i) {
+            T e[8];
+            raw[i][c].elements(e);
+            scaled8(e, sv, s != nullptr, x[i][c]);
+            min_max8(x[i][c], lo[i], hi[i]);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < WQT_TILES; ++i) {
+        lo[i] = fminf(lo[i], __shfl_xor(lo[i], 16, WAVE));
+        hi[i] = fmaxf(hi[i], __shfl_xor(hi[i], 16, WAVE));
+        lo[i] = fminf(lo[i], __shfl_xor(lo[i], 32, WAVE));
+        hi[i] = fmaxf(hi[i], __shfl_xor(hi[i], 32, WAVE));
+        const int64_t n = (int64_t)nt[i] * TILE_N + row;
+        const float rho = clip_factor(clip, n);
+        float st, istep;
+        int z;
+        range_params(lo[i] * rho, hi[i] * rho, st, istep, z);
+        if (lane < 16) {
+            step[n * KT + kt] = st;
+            zero[n * KT + kt] = (uint8_t)z;
+        }
+        const CodeRule rule = make_rule(istep, z);
+        uint32_t *tile = packed + ((int64_t)nt[i] * KT + kt) * (TILE_BYTES / 4) + row * 4 + kb;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {   // word kb of lane (row, quarter c): 256 contiguous bytes per store
+            const uint2 q = codes8(x[i][c], rule);
+            tile[c * 64] = recode4(q.x, 0x01010101u) | (recode4(q.y, 0x01010101u) << 4);
+        }
     }
 }
 
-int launch_clip_params(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s,
-                       int64_t G, const int32_t *idx, int uniform, float *step, uint8_t *zero,
-                       hipStream_t st)
+bool weight_quant_packs(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, int64_t G)
 {
-    const int64_t segs = N * (K / G);
-    if (segs == 0) return W4A8_OK;
-    const dim3 grid((unsigned)((segs + (WQ_THREADS / WAVE) - 1) / (WQ_THREADS / WAVE)));
-#define W4A8_CP_LAUNCH(T_)                                                                        \
-    hipLaunchKernelGGL((clip_params_kernel<T_>), grid, dim3(WQ_THREADS), 0, st, (const T_ *)W, N, K, \
-                       ldw, s, G, idx, uniform, step, zero)
+    const int64_t es = w_dtype == W4A8_F32 ? 4 : 2;
+    return G == TILE_K && N % TILE_N == 0 && K % TILE_K == 0 && (uintptr_t)W % 16 == 0 && ldw * es % 16 == 0 &&
+           (N / TILE_N) * (K / TILE_K) <= 0x7fffffffLL;
+}
+
+int launch_weight_quant_packed(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s,
+                               int64_t G, uint8_t *packed, float *step, uint8_t *zero, Clipping clip,
+                               hipStream_t st)
+{
+    if (!weight_quant_packs(W, w_dtype, N, K, ldw, G) || (uintptr_t)packed % 16 != 0) return W4A8_ERR_SHAPE;
+    const uint32_t NT = (uint32_t)(N / TILE_N), KT = (uint32_t)(K / TILE_K);
+    const int64_t waves = (int64_t)((NT + WQT_TILES - 1) / WQT_TILES) * KT;
+    const dim3 grid((unsigned)((waves + WQ_THREADS / WAVE - 1) / (WQ_THREADS / WAVE)));
+    const int s_vec = (uintptr_t)s % 16 == 0;
+#define W4A8_WQT_LAUNCH(T_)                                                                                    \
+    hipLaunchKernelGGL((weight_quant_packed_kernel<T_>), grid, dim3(WQ_THREADS), 0, st, (const T_ *)W, NT, KT, \
+                       ldw, s, (uint32_t *)packed, step, zero, s_vec, clip)
     switch (w_dtype) {
-        case W4A8_F32: W4A8_CP_LAUNCH(float); break;
-        case W4A8_F16: W4A8_CP_LAUNCH(__half); break;
-        case W4A8_BF16: W4A8_CP_LAUNCH(bf16_t); break;
+        case W4A8_F32: W4A8_WQT_LAUNCH(float); break;
+        case W4A8_F16: W4A8_WQT_LAUNCH(__half); break;
+        case W4A8_BF16: W4A8_WQT_LAUNCH(bf16_t); break;
         default: return W4A8_ERR_DTYPE;
     }
-#undef W4A8_CP_LAUNCH
+#undef W4A8_WQT_LAUNCH
     return hip_status(hipGetLastError());
 }
 
