@@ -17,6 +17,7 @@ constexpr float AQ_FLT_MAX = 3.402823466e+38f;   // a token whose 127 / max|t| i
 
 constexpr int AQ_THREADS = 256;
 constexpr int AQ_VEC = 8;
+constexpr int AQ_FEW_ROWS = 256;   // up to here (one per CU) a row gets a workgroup of 1024 lanes
 
 template <typename T>
 __device__ __forceinline__ void load8(const T *p, float (&v)[8]);
@@ -52,6 +53,8 @@ __device__ __forceinline__ void load8<bf16_t>(const bf16_t *p, float (&v)[8])
     }
 }
 
+// maximum over a workgroup of WAVES waves; red: WAVES floats
+template <int WAVES>
 __device__ __forceinline__ float block_max(float v, float *red)
 {
     v = wave_max(v);
@@ -59,10 +62,14 @@ __device__ __forceinline__ float block_max(float v, float *red)
     __syncthreads();  // `red` may still be read by the previous row
     if ((threadIdx.x & 63) == 0) red[wave] = v;
     __syncthreads();
-    return fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    v = red[0];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) v = fmaxf(v, red[w]);
+    return v;
 }
 
-// both at once: returns max over the workgroup of (a, b)
+// both at once: the maxima of a and of b; red: 2 * WAVES floats
+template <int WAVES>
 __device__ __forceinline__ void block_max2(float &a, float &b, float *red)
 {
     a = wave_max(a);
@@ -71,11 +78,36 @@ __device__ __forceinline__ void block_max2(float &a, float &b, float *red)
     __syncthreads();
     if ((threadIdx.x & 63) == 0) {
         red[wave] = a;
-        red[4 + wave] = b;
+        red[WAVES + wave] = b;
     }
     __syncthreads();
-    a = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
-    b = fmaxf(fmaxf(red[4], red[5]), fmaxf(red[6], red[7]));
+    a = red[0];
+    b = red[WAVES];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) {
+        a = fmaxf(a, red[w]);
+        b = fmaxf(b, red[WAVES + w]);
+    }
+}
+
+// rs[m] = sum of a row's codes over the workgroup; red: WAVES ints, its own
+template <int WAVES>
+__device__ __forceinline__ void block_row_sum(int v, int *red, int32_t *out)
+{
+    v = wave_sum_i32(v);
+    __syncthreads();   // `red` may still be read for the previous row
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        v = red[0];
+#pragma unroll
+        for (int w = 1; w < WAVES; ++w) v += red[w];
+        *out = v;
+    }
+}
+__device__ __forceinline__ int sum4_codes(uint32_t w, int sum)
+{
+    return __builtin_amdgcn_sdot4((int)w, 0x01010101, sum, false);
 }
 
 // asymmetric: code = clamp(rne(t * isx) + zx, 0, 255), stored as code - 128
@@ -183,12 +215,19 @@ __device__ __forceinline__ uint32_t quant1_bits(float t, float inv)
 // of a workgroup's next row are issued before anything is done with the current one (the first row's
 // before the reciprocal scales are computed; a second row of look-ahead measured the same), and the
 // launch keeps about three workgroups on every CU.
-template <typename T, int NCH, bool ASYM>
-__global__ __launch_bounds__(AQ_THREADS) void act_quant_rows_kernel(
+// THREADS = 1024: few rows (decode and short prompts), one row per workgroup; all there is then is the chain
+// load - divide - reduce - round - store, and a thread's share of the divisions is its longest link
+// (16 x 13824: 56 per thread of 256, 16 per thread of 1024).
+// rs (or null): the sums of each row's codes, which the per-channel product needs to remove its decode bias.
+template <typename T, int NCH, bool ASYM, int THREADS>
+__global__ __launch_bounds__(THREADS) void act_quant_rows_kernel(
     const T *__restrict__ X, int64_t M, int K, int64_t ldx, const float *__restrict__ s,
-    int8_t *__restrict__ Xq, float *__restrict__ sx, int32_t *__restrict__ zx, int rows_per_block)
+    int8_t *__restrict__ Xq, float *__restrict__ sx, int32_t *__restrict__ zx, int32_t *__restrict__ rs,
+    int rows_per_block)
 {
-    __shared__ float red[8];
+    constexpr int WAVES = THREADS / WAVE;
+    __shared__ float red[2 * WAVES];
+    __shared__ int red_sum[WAVES];
     const int tid = threadIdx.x;
     const int nchunks = K / AQ_VEC;
     const int64_t row0 = (int64_t)blockIdx.x * rows_per_block;
@@ -199,7 +238,7 @@ __global__ __launch_bounds__(AQ_THREADS) void act_quant_rows_kernel(
         const T *x = X + m * ldx;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            const int ch = tid + c * AQ_THREADS;
+            const int ch = tid + c * THREADS;
             if (ch < nchunks) dst[c] = load_raw8<T>(x + (int64_t)ch * AQ_VEC);
         }
     };
@@ -208,7 +247,7 @@ __global__ __launch_bounds__(AQ_THREADS) void act_quant_rows_kernel(
     float r[NCH][AQ_VEC];
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-        const int ch = tid + c * AQ_THREADS;
+        const int ch = tid + c * THREADS;
 #pragma unroll
         for (int j = 0; j < AQ_VEC; ++j) r[c][j] = 1.0f;
         if (s != nullptr && ch < nchunks) {
@@ -226,7 +265,7 @@ __global__ __launch_bounds__(AQ_THREADS) void act_quant_rows_kernel(
         float a = 0.0f, b = 0.0f;   // symmetric: a = max |t|;  asymmetric: a = max(0, t), b = max(0, -t)
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            const int ch = tid + c * AQ_THREADS;
+            const int ch = tid + c * THREADS;
             if (ch < nchunks) {
                 float xv[8];
                 widen8(cur[c], xv);
@@ -248,23 +287,24 @@ __global__ __launch_bounds__(AQ_THREADS) void act_quant_rows_kernel(
         float inv = 0.0f;
         AsymParams ap = {1.0f, 0.0f, 0.0f};
         if (ASYM) {
-            block_max2(a, b, red);
+            block_max2<WAVES>(a, b, red);
             ap = asym_params(-b, a);   // lo = -max(0, -t) = min(0, t)
             if (tid == 0) {
                 sx[m] = ap.sx;
                 zx[m] = (int)ap.zf - 128;
             }
         } else {
-            a = block_max(a, red);
+            a = block_max<WAVES>(a, red);
             const float inv0 = 127.0f / a;
             const bool zero_row = !(inv0 <= AQ_FLT_MAX);   // a == 0, or so small that 127 / a overflows
             inv = zero_row ? 0.0f : inv0;
             if (tid == 0) sx[m] = zero_row ? 1.0f : a / 127.0f;
         }
         int8_t *q = Xq + m * (int64_t)K;
+        int sum = 0;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) {
-            const int ch = tid + c * AQ_THREADS;
+            const int ch = tid + c * THREADS;
             if (ch < nchunks) {
                 uint32_t w0 = 0, w1 = 0;
                 if (ASYM) {
@@ -283,8 +323,10 @@ __global__ __launch_bounds__(AQ_THREADS) void act_quant_rows_kernel(
                     w1 = pack4_low_bytes(b[4], b[5], b[6], b[7]);
                 }
                 *reinterpret_cast<uint2 *>(q + (int64_t)ch * AQ_VEC) = make_uint2(w0, w1);
+                if (!ASYM) sum = sum4_codes(w1, sum4_codes(w0, sum));
             }
         }
+        if (!ASYM && rs != nullptr) block_row_sum<WAVES>(sum, red_sum, rs + m);
 #pragma unroll
         for (int c = 0; c < NCH; ++c) cur[c] = nxt[c];
     }
@@ -302,7 +344,8 @@ constexpr int AQW_WAVES = 4;
 template <typename T, int NCW, bool ASYM>
 __global__ __launch_bounds__(AQW_WAVES *WAVE, 2) void act_quant_wave_kernel(
     const T *__restrict__ X, int64_t M, int K, int64_t ldx, const float *__restrict__ s,
-    int8_t *__restrict__ Xq, float *__restrict__ sx, int32_t *__restrict__ zx, int rows_per_wave)
+    int8_t *__restrict__ Xq, float *__restrict__ sx, int32_t *__restrict__ zx, int32_t *__restrict__ rs,
+    int rows_per_wave)
 {
     // [2][NCW * 64] float4: elements 0..3 and 4..7 of every chunk's reciprocals, each half contiguous
     // over the chunks so that a wave's 16-byte reads are conflict free; zero beyond the row's end
@@ -399,6 +442,7 @@ __global__ __launch_bounds__(AQW_WAVES *WAVE, 2) void act_quant_wave_kernel(
             if (lane == 0) sx[m] = zero_row ? 1.0f : a / 127.0f;
         }
         __amdgpu_buffer_rsrc_t rq = __builtin_amdgcn_make_buffer_rsrc((void *)(Xq + m * (int64_t)K), 0, K, 0x00020000);
+        int sum = 0;
 #pragma unroll
         for (int c = 0; c < NCW; ++c) {
             uint32_t b8[8];
@@ -407,6 +451,11 @@ __global__ __launch_bounds__(AQW_WAVES *WAVE, 2) void act_quant_wave_kernel(
                 b8[j] = ASYM ? (uint32_t)quant1_asym(t[c][j], ap.isx, ap.zf) : quant1_bits(t[c][j], inv);
             const v2u out = {pack4_low_bytes(b8[0], b8[1], b8[2], b8[3]), pack4_low_bytes(b8[4], b8[5], b8[6], b8[7])};
             __builtin_amdgcn_raw_buffer_store_b64(out, rq, (lane + c * WAVE) * AQ_VEC, 0, 0);
+            if (!ASYM) sum = sum4_codes(out.y, sum4_codes(out.x, sum));
+        }
+        if (!ASYM && rs != nullptr) {
+            sum = wave_sum_i32(sum);
+            if (lane == 0) rs[m] = sum;
         }
     }
 }
@@ -417,7 +466,8 @@ __global__ __launch_bounds__(AQ_THREADS) void act_quant_generic_kernel(
     const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx, const float *__restrict__ s,
     int8_t *__restrict__ Xq, float *__restrict__ sx, int32_t *__restrict__ zx)
 {
-    __shared__ float red[8];
+    constexpr int WAVES = AQ_THREADS / WAVE;
+    __shared__ float red[2 * WAVES];
     const int64_t m = blockIdx.x;
     const T *x = X + m * ldx;
     float a = 0.0f, b = 0.0f;
@@ -434,14 +484,14 @@ __global__ __launch_bounds__(AQ_THREADS) void act_quant_generic_kernel(
     float inv = 0.0f;
     AsymParams ap = {1.0f, 0.0f, 0.0f};
     if (ASYM) {
-        block_max2(a, b, red);
+        block_max2<WAVES>(a, b, red);
         ap = asym_params(-b, a);
         if (threadIdx.x == 0) {
             sx[m] = ap.sx;
             zx[m] = (int)ap.zf - 128;
         }
     } else {
-        a = block_max(a, red);
+        a = block_max<WAVES>(a, red);
         const float inv0 = 127.0f / a;
         const bool zero_row = !(inv0 <= AQ_FLT_MAX);   // a == 0, or so small that 127 / a overflows
         inv = zero_row ? 0.0f : inv0;
@@ -455,18 +505,37 @@ __global__ __launch_bounds__(AQ_THREADS) void act_quant_generic_kernel(
     }
 }
 
+// What the vector kernels assume of their operands (everything else: act_quant_generic_kernel).
+static bool act_quant_vectors(const void *X, int64_t elem, int64_t K, int64_t ldx, const float *s, const int8_t *Xq)
+{
+    return K % AQ_VEC == 0 && (ldx * elem) % 16 == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)Xq % 8 == 0 &&
+           (s == nullptr || (uintptr_t)s % 16 == 0) && K <= (int64_t)AQ_THREADS * AQ_VEC * 8;
+}
+
 template <typename T, bool ASYM>
 static int launch_act_quant_t(const T *X, int64_t M, int64_t K, int64_t ldx, const float *s,
-                              int8_t *Xq, float *sx, int32_t *zx, hipStream_t st)
+                              int8_t *Xq, float *sx, int32_t *zx, int32_t *rs, hipStream_t st)
 {
-    const bool aligned = (K % AQ_VEC == 0) && ((ldx * sizeof(T)) % 16 == 0) &&
-                         ((uintptr_t)X % 16 == 0) && ((uintptr_t)Xq % 8 == 0) &&
-                         (s == nullptr || (uintptr_t)s % 16 == 0) &&
-                         K <= (int64_t)AQ_THREADS * AQ_VEC * 8;
-    if (!aligned) {
+    if (!act_quant_vectors(X, sizeof(T), K, ldx, s, Xq)) {
+        if (rs != nullptr) return W4A8_ERR_SHAPE;   // (callers ask act_quant_sums_rows first)
         hipLaunchKernelGGL((act_quant_generic_kernel<T, ASYM>), dim3((unsigned)M), dim3(AQ_THREADS),
                            0, st, X, M, K, ldx, s, Xq, sx, zx);
         return hip_status(hipGetLastError());
+    }
+    // Few rows: one of them per workgroup of 1024 lanes, at most one workgroup per CU.  Measured (cached rows, us,
+    // this / the kernels below): 16 x 4096 2.8 / 3.7, 16 x 5120 3.0 / 4.1, 16 x 13824 3.9 / 5.1, 256 x 5120 3.4 / 4.3,
+    // 256 x 13824 4.6 / 5.7; 512 rows are even and 1024 rows lose (5120: 7.0 / 4.9).
+    if (M <= AQ_FEW_ROWS && K >= 2048) {
+#define W4A8_AQ_FEW(N_)                                                                                     \
+    case N_:                                                                                                \
+        hipLaunchKernelGGL((act_quant_rows_kernel<T, N_, ASYM, 1024>), dim3((unsigned)M), dim3(1024), 0, st, \
+                           X, M, (int)K, ldx, s, Xq, sx, zx, rs, 1);                                        \
+        return hip_status(hipGetLastError())
+        switch ((int)((K / AQ_VEC + 1023) / 1024)) {
+            W4A8_AQ_FEW(1);
+            W4A8_AQ_FEW(2);   // K <= 16384 (act_quant_vectors)
+        }
+#undef W4A8_AQ_FEW
     }
     // Rows of up to 5120 16-bit (3072 binary32) elements: one wave per row, the scaled row and the next
     // row's raw chunks in its registers.
@@ -482,7 +551,7 @@ static int launch_act_quant_t(const T *X, int64_t M, int64_t K, int64_t ldx, con
     if (ncw <= N_) {                                                                               \
         lds = (size_t)N_ * WAVE * AQ_VEC * sizeof(float);                                          \
         hipLaunchKernelGGL((act_quant_wave_kernel<T, N_, ASYM>), dim3(grid), dim3(AQW_WAVES *WAVE), \
-                           lds, st, X, M, (int)K, ldx, s, Xq, sx, zx, rows);                       \
+                           lds, st, X, M, (int)K, ldx, s, Xq, sx, zx, rs, rows);                   \
         return hip_status(hipGetLastError());                                                      \
     }
         W4A8_AQW_CASE(2) W4A8_AQW_CASE(4) W4A8_AQW_CASE(6)
@@ -497,10 +566,10 @@ static int launch_act_quant_t(const T *X, int64_t M, int64_t K, int64_t ldx, con
     if (rows > 16) rows = 16;
     const unsigned grid = (unsigned)((M + rows - 1) / rows);
     const int nch = (int)((K / AQ_VEC + AQ_THREADS - 1) / AQ_THREADS);
-#define W4A8_AQ_CASE(N_)                                                                       \
-    case N_:                                                                                   \
-        hipLaunchKernelGGL((act_quant_rows_kernel<T, N_, ASYM>), dim3(grid), dim3(AQ_THREADS), \
-                           0, st, X, M, (int)K, ldx, s, Xq, sx, zx, rows);                     \
+#define W4A8_AQ_CASE(N_)                                                                                   \
+    case N_:                                                                                               \
+        hipLaunchKernelGGL((act_quant_rows_kernel<T, N_, ASYM, AQ_THREADS>), dim3(grid), dim3(AQ_THREADS), \
+                           0, st, X, M, (int)K, ldx, s, Xq, sx, zx, rs, rows);                             \
         break;
     switch (nch) {
         W4A8_AQ_CASE(1) W4A8_AQ_CASE(2) W4A8_AQ_CASE(3) W4A8_AQ_CASE(4)
@@ -511,13 +580,18 @@ static int launch_act_quant_t(const T *X, int64_t M, int64_t K, int64_t ldx, con
     return hip_status(hipGetLastError());
 }
 
+bool act_quant_sums_rows(const void *X, int x_dtype, int64_t K, int64_t ldx, const float *s, const int8_t *Xq)
+{
+    return act_quant_vectors(X, x_dtype == W4A8_F32 ? 4 : 2, K, ldx, s, Xq);
+}
+
 // zx == nullptr: symmetric absmax; else asymmetric min-max with the token zero-points in zx
 int launch_act_quant(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, const float *s,
-                     int8_t *Xq, float *sx, int32_t *zx, hipStream_t st)
+                     int8_t *Xq, float *sx, int32_t *zx, hipStream_t st, int32_t *rs)
 {
 #define W4A8_AQ_T(T_)                                                                       \
-    (zx ? launch_act_quant_t<T_, true>((const T_ *)X, M, K, ldx, s, Xq, sx, zx, st)         \
-        : launch_act_quant_t<T_, false>((const T_ *)X, M, K, ldx, s, Xq, sx, nullptr, st))
+    (zx ? launch_act_quant_t<T_, true>((const T_ *)X, M, K, ldx, s, Xq, sx, zx, nullptr, st) \
+        : launch_act_quant_t<T_, false>((const T_ *)X, M, K, ldx, s, Xq, sx, nullptr, rs, st))
     switch (x_dtype) {
         case W4A8_F32: return W4A8_AQ_T(float);
         case W4A8_F16: return W4A8_AQ_T(__half);

@@ -69,13 +69,14 @@ WsPlan plan_workspace(int64_t M, int64_t N, int64_t K, int64_t G, int layout)
     return w;
 }
 
-// w4a8_gemm and w4a8_gemm_asym (zx, wsum, tsum null for the former)
+// w4a8_gemm and w4a8_gemm_asym (zx, wsum, tsum null for the former); rs_ready: the tokens' row-sums are in
+// the workspace already (see gemm_reads_row_sums)
 int gemm_common(const int8_t *Xq, const float *sx, const int32_t *zx, int64_t M,
                 const uint8_t *Wp, int layout, const float *step, const uint8_t *zero,
                 const int32_t *wsum, const int32_t *tsum, int64_t N, int64_t K, int64_t group_size,
                 void *Y, int y_dtype, int64_t ldy,
                 int32_t *acc_out, void *workspace, size_t workspace_bytes, void *stream,
-                int format = W4A8_FMT_DINT4, bool validate_only = false)
+                int format = W4A8_FMT_DINT4, bool validate_only = false, bool rs_ready = false)
 {
     if (!valid_layout(layout)) return W4A8_ERR_DTYPE;
     if (format != W4A8_FMT_DINT4 && format != W4A8_FMT_INT4 && format != W4A8_FMT_DINT3) return W4A8_ERR_DTYPE;
@@ -122,7 +123,7 @@ int gemm_common(const int8_t *Xq, const float *sx, const int32_t *zx, int64_t M,
         if (rc != W4A8_OK) return rc;
     }
     const int rc = launch_gemm(Xq, sx, zp, (int32_t *)(wsb + ws.rs_off), M, Wt, step, zero, N,
-                               K, G, Y, y_dtype, ldy, acc_out, (float *)(wsb + ws.part_off), st, plain);
+                               K, G, Y, y_dtype, ldy, acc_out, (float *)(wsb + ws.part_off), st, plain, rs_ready);
     if (rc != W4A8_OK || !zx || !acc_out) return rc;
     return launch_acc_zero_point(acc_out, zx, wsum, M, N * (K / G), st);
 }
@@ -387,10 +388,15 @@ int w4a8_linear(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, c
                          y_dtype, ldy, acc_out, w.gemm_bytes ? wsb + w.gemm : nullptr, w.gemm_bytes, stream,
                          W4A8_FMT_DINT4, true);
     if (rc != W4A8_OK) return rc;
-    rc = launch_act_quant(X, x_dtype, M, K, ldx, s, Xq, sx, nullptr, st);
+    // the quantizer also leaves the row-sums that a per-channel product of many tokens would make in a pre-pass
+    const bool sums = M > 16 && gemv_token_blocks(M, N, K, G) == 0 && gemm_reads_row_sums(M, N, K, G) &&
+                      act_quant_sums_rows(X, x_dtype, K, ldx, s, Xq);
+    int32_t *rs = sums ? (int32_t *)(wsb + w.gemm + plan_workspace(M, N, K, G, layout).rs_off) : nullptr;
+    rc = launch_act_quant(X, x_dtype, M, K, ldx, s, Xq, sx, nullptr, st, rs);
     if (rc != W4A8_OK) return rc;
     return gemm_common(Xq, sx, nullptr, M, Wp, layout, step, zero, nullptr, nullptr, N, K, group_size, Y,
-                       y_dtype, ldy, acc_out, w.gemm_bytes ? wsb + w.gemm : nullptr, w.gemm_bytes, stream);
+                       y_dtype, ldy, acc_out, w.gemm_bytes ? wsb + w.gemm : nullptr, w.gemm_bytes, stream,
+                       W4A8_FMT_DINT4, false, sums);
 }
 
 // ---- w4a8_gemm for callers that cannot allocate: the workspace is a static device array ----------

@@ -1321,11 +1321,13 @@ bool gemm_mid_pc_applies(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
 
 static int launch_gemm_mid_pc(const int8_t *Xq, const float *sx, int32_t *rs, int64_t M, const uint8_t *Wt,
                               const float *step, const uint8_t *zero, int64_t N, int64_t K, void *Y, int y_dtype,
-                              int64_t ldy, int32_t *acc_out, hipStream_t st, int plain)
+                              int64_t ldy, int32_t *acc_out, hipStream_t st, int plain, bool rs_ready)
 {
     // the tokens' row-sums over all of K (bias removal in the epilogue)
-    hipLaunchKernelGGL(rowsum_kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, Xq, M, (int)K, 1, (int)K, rs);
-    if (hipGetLastError() != hipSuccess) return W4A8_ERR_HIP;
+    if (!rs_ready) {
+        hipLaunchKernelGGL(rowsum_kernel, dim3((unsigned)((M + 3) / 4)), dim3(256), 0, st, Xq, M, (int)K, 1, (int)K, rs);
+        if (hipGetLastError() != hipSuccess) return W4A8_ERR_HIP;
+    }
     const int grid_m = (int)((M + MP_BM - 1) / MP_BM);
     const int grid_n = (int)((N + MD_BN - 1) / MD_BN);
     const int vec_store = (((uintptr_t)Y % 8 == 0) && (ldy % 4 == 0)) ? 1 : 0;
@@ -1417,10 +1419,15 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t G)
     return pl;
 }
 
+bool gemm_reads_row_sums(int64_t M, int64_t N, int64_t K, int64_t G)
+{
+    return G == K && (gemm_mid_pc_applies(M, N, K, G, false) || plan_gemm(M, N, K, G).splits == 1);
+}
+
 int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, int64_t M,
                 const uint8_t *Wt, const float *step, const uint8_t *zero, int64_t N, int64_t K,
                 int64_t G, void *Y, int y_dtype, int64_t ldy, int32_t *acc_out, float *partial,
-                hipStream_t st, int plain)
+                hipStream_t st, int plain, bool rs_ready)
 {
     const bool grouped = G != K;
     if ((M + 63) / 64 * ((N + 255) / 256) * 64 > 0x7fffffLL || M * K > 0x7fffffffLL)
@@ -1428,9 +1435,10 @@ int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, in
     if (gemm_mid_applies(M, N, K, G, zp.zx != nullptr))
         return launch_gemm_mid(Xq, sx, M, Wt, step, zero, N, K, Y, y_dtype, ldy, acc_out, st, plain);
     if (gemm_mid_pc_applies(M, N, K, G, zp.zx != nullptr))
-        return launch_gemm_mid_pc(Xq, sx, rs, M, Wt, step, zero, N, K, Y, y_dtype, ldy, acc_out, st, plain);
+        return launch_gemm_mid_pc(Xq, sx, rs, M, Wt, step, zero, N, K, Y, y_dtype, ldy, acc_out, st, plain,
+                                  rs_ready);
     const GemmPlan pl = plan_gemm(M, N, K, G);
-    if (!grouped) {
+    if (!grouped && !(rs_ready && pl.splits == 1)) {
         const int64_t segs = M * pl.splits;
         hipLaunchKernelGGL(rowsum_kernel, dim3((unsigned)((segs + 3) / 4)), dim3(256), 0, st, Xq, M,
                            (int)K, pl.splits, pl.kt_per_split * TILE_K, rs);

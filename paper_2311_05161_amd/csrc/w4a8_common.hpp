@@ -188,8 +188,10 @@ __device__ __forceinline__ void decode_word_signed(uint32_t p, const SignedLut &
 
 // Host-side launchers (defined in the .hip files, called from the C ABI in api.hip).
 // zx == nullptr: symmetric absmax; else asymmetric min-max, token zero-points (minus 128) to zx
+// rs != nullptr (symmetric form, where act_quant_sums_rows allows it): the int32 sum of each row's codes
 int launch_act_quant(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, const float *s,
-                     int8_t *Xq, float *sx, int32_t *zx, hipStream_t st);
+                     int8_t *Xq, float *sx, int32_t *zx, hipStream_t st, int32_t *rs = nullptr);
+bool act_quant_sums_rows(const void *X, int x_dtype, int64_t K, int64_t ldx, const float *s, const int8_t *Xq);
 // sums of the weights in half steps: wsum [N, K/G] per group, tsum [N, K/128] per 128 columns (or null)
 int launch_weight_sums(const uint8_t *codes, const uint8_t *zero, int64_t N, int64_t K, int64_t G,
                        int32_t *wsum, int32_t *tsum, hipStream_t st);
@@ -322,7 +324,10 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t G);
 int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, int64_t M,
                 const uint8_t *Wt, const float *step, const uint8_t *zero, int64_t N, int64_t K,
                 int64_t G, void *Y, int y_dtype, int64_t ldy, int32_t *acc_out, float *partial,
-                hipStream_t st, int plain = 0);
+                hipStream_t st, int plain = 0, bool rs_ready = false);
+// Whether launch_gemm reads the tokens' row-sums over all of K from rs (per-channel weights, K in one range):
+// a caller that has them already passes rs_ready and saves the pre-pass.
+bool gemm_reads_row_sums(int64_t M, int64_t N, int64_t K, int64_t G);
 
 inline int hip_status(hipError_t e) { return e == hipSuccess ? W4A8_OK : W4A8_ERR_HIP; }
 
