@@ -45,6 +45,7 @@ constexpr int GV_RED_BYTES = 2 * GV_CW * 256 * 4; // partial sums of the compute
 constexpr int GV_MAX_LDS = GV_RED_BYTES + GV_LDS_BUDGET;
 constexpr int GV_LDS_LIMIT = 160 * 1024;          // LDS of a CU: what a kernel may opt into
 constexpr int GV_FUSED_STAGE = 8;                 // decode records such an instance's thread prepares at most
+constexpr int GV_FEW = 4;                         // tokens up to which those instances spread their lanes over four rows
 constexpr int GV_FUSED_MAX_AT = 7;                // k-tiles per wave of the instances that quantize the activations themselves
 
 __device__ __forceinline__ void lds_barrier()
@@ -122,7 +123,11 @@ struct GemvArgs {
 // LDS) and round t * (127 / a) into the very registers the int8 fragments would have been loaded
 // into.  Every floating-point step is the single binary32 operation of the definition, so Xq and sx
 // have the bits quantize_act_int8 gives.  One K range only (every workgroup sees whole rows).
-template <bool GROUPED, int AT, int D, bool ACC_OUT, bool ASYM, bool FUSED = false>
+// FUSED = 2 (M <= GV_FEW): the same with the lanes spread over four rows instead of sixteen -- a k-tile's row of
+// 128 elements over 16 lanes, 8 each.  The quantizer's work is what the fused launch adds (two passes
+// of some five vector operations per element and lane, 3.4 us for 16 rows of 4096 whether they exist or not),
+// and it falls to a quarter; rows 4 .. 15 of the operand are zeros.  1 x 4096 x 4096: 9.4 -> 7.1 us.
+template <bool GROUPED, int AT, int D, bool ACC_OUT, bool ASYM, int FUSED = 0>
 __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(const GemvArgs args)
 {
     // blockIdx.z: independent problems of one shape, densely stacked (batched launch), or the
@@ -233,10 +238,13 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(const GemvArgs args)
     // Raw rows: lane (row = lane / 4, q = lane % 4) holds columns 16 q .. + 15 and 64 + 16 q .. + 15 of
     // each of its k-tiles as four 16-byte pieces -- the columns its int8 fragments a0 / a1 cover.
     constexpr int NS = GV_FUSED_MAX_AT * 2;   // scales per thread: K <= 8 * 128 * GV_FUSED_MAX_AT, 512 threads
-    v4u xr[FUSED ? AT : 1][4];
+    constexpr bool FEW = FUSED == 2;
+    constexpr int XP = FEW ? 1 : 4;           // 16-byte pieces per lane and k-tile
+    v4u xr[FUSED ? AT : 1][XP];
     float sv[FUSED ? NS : 1];
     float *r_lds = reinterpret_cast<float *>(smem + (FUSED ? a.fused_lds_off : 0));   // [K], then maxima [8][16]
-    const int xcol = (lane & 3) * 16;   // first column of the lane's first half within a k-tile
+    const int xrow = FEW ? lane >> 4 : lane >> 2;
+    const int xcol = FEW ? (lane & 15) * 8 : (lane & 3) * 16;   // first column of the lane's (first) piece within a k-tile
     if (FUSED && wave < GV_CW) {
         const int tpw_x = (KTs - wave + GV_CW - 1) / GV_CW;
 #pragma unroll
@@ -246,14 +254,16 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(const GemvArgs args)
         }
         __amdgpu_buffer_rsrc_t rxx = __builtin_amdgcn_make_buffer_rsrc(
             (void *)a.X, 0, (int)((((int64_t)M - 1) * a.ldx + K) * 2), 0x00020000);
-        const int voff_raw = ((lane >> 2) * (int)a.ldx + xcol) * 2;
+        const int voff_raw = (xrow * (int)a.ldx + xcol) * 2;
 #pragma unroll
         for (int u = 0; u < AT; ++u) {
             const int vo = u < tpw_x ? voff_raw + (wave + u * GV_CW) * (TILE_K * 2) : GV_OOB;
             xr[u][0] = __builtin_amdgcn_raw_buffer_load_b128(rxx, vo, 0, 0);
-            xr[u][1] = __builtin_amdgcn_raw_buffer_load_b128(rxx, vo + 16, 0, 0);
-            xr[u][2] = __builtin_amdgcn_raw_buffer_load_b128(rxx, vo + 128, 0, 0);
-            xr[u][3] = __builtin_amdgcn_raw_buffer_load_b128(rxx, vo + 144, 0, 0);
+            if constexpr (!FEW) {
+                xr[u][1] = __builtin_amdgcn_raw_buffer_load_b128(rxx, vo + 16, 0, 0);
+                xr[u][2] = __builtin_amdgcn_raw_buffer_load_b128(rxx, vo + 128, 0, 0);
+                xr[u][3] = __builtin_amdgcn_raw_buffer_load_b128(rxx, vo + 144, 0, 0);
+            }
         }
         order_fence();
     }
@@ -447,9 +457,9 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(const GemvArgs args)
     auto quantize_slot = [&](int u) __attribute__((always_inline)) {
 #pragma clang fp contract(off)
         const float *rk = r_lds + (wave + u * GV_CW) * TILE_K + xcol;
-        uint32_t o[8];
+        uint32_t o[2 * XP];
 #pragma unroll
-        for (int pc = 0; pc < 4; ++pc) {
+        for (int pc = 0; pc < XP; ++pc) {
             float t[8];
             // (slots without a k-tile hold zeros; their reciprocals are read from the last k-tile's place)
             scaled8(xr[u][pc], (u < tpw ? rk : r_lds) + (pc >> 1) * 64 + (pc & 1) * 8, t);
@@ -464,12 +474,18 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(const GemvArgs args)
             o[2 * pc + 1] = __builtin_amdgcn_perm(b[5], b[4], 0x0c0c0400u) | __builtin_amdgcn_perm(b[7], b[6], 0x04000c0cu);
             __builtin_amdgcn_sched_barrier(0);   // (piece by piece, as above)
         }
-        a0[u] = v4u{o[0], o[1], o[2], o[3]};
-        a1[u] = v4u{o[4], o[5], o[6], o[7]};
-        if (a.Xq_out != nullptr && blk == 0 && u < tpw && (lane >> 2) < M) {   // test hook
-            int8_t *qo = a.Xq_out + (int64_t)(lane >> 2) * K + (wave + u * GV_CW) * TILE_K + xcol;
-            *reinterpret_cast<v4u *>(qo) = a0[u];
-            *reinterpret_cast<v4u *>(qo + 64) = a1[u];
+        const bool show = a.Xq_out != nullptr && blk == 0 && u < tpw && xrow < M;   // test hook
+        int8_t *qo = a.Xq_out + (int64_t)xrow * K + (wave + u * GV_CW) * TILE_K + xcol;
+        if constexpr (FEW) {
+            a0[u] = v4u{o[0], o[1], 0u, 0u};
+            if (show) *reinterpret_cast<v2u *>(qo) = v2u{o[0], o[1]};
+        } else {
+            a0[u] = v4u{o[0], o[1], o[2], o[3]};
+            a1[u] = v4u{o[4 % (2 * XP)], o[5 % (2 * XP)], o[6 % (2 * XP)], o[7 % (2 * XP)]};
+            if (show) {
+                *reinterpret_cast<v4u *>(qo) = a0[u];
+                *reinterpret_cast<v4u *>(qo + 64) = a1[u];
+            }
         }
     };
     if (FUSED) {
@@ -478,7 +494,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(const GemvArgs args)
         for (int u = 0; u < AT; ++u) {
             const float *rk = r_lds + (wave + u * GV_CW) * TILE_K + xcol;
 #pragma unroll
-            for (int pc = 0; pc < 4; ++pc) {
+            for (int pc = 0; pc < XP; ++pc) {
                 float t[8];
                 scaled8(xr[u][pc], (u < tpw ? rk : r_lds) + (pc >> 1) * 64 + (pc & 1) * 8, t);
 #pragma unroll
@@ -492,16 +508,21 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(const GemvArgs args)
         // registers per slot)
 #pragma unroll
         for (int u = 0; u < AT; ++u)
-            asm volatile("" : "+v"(xr[u][0]), "+v"(xr[u][1]), "+v"(xr[u][2]), "+v"(xr[u][3]));
-        // the row's four lanes, then the eight waves through LDS
+#pragma unroll
+            for (int pc = 0; pc < XP; ++pc) asm volatile("" : "+v"(xr[u][pc]));
+        // the row's four (sixteen) lanes, then the eight waves through LDS
         am = fmaxf(am, dpp_f32<DPP_QUAD_XOR1>(am));
         am = fmaxf(am, dpp_f32<DPP_QUAD_XOR2>(am));
+        if (FEW) {
+            am = fmaxf(am, dpp_f32<DPP_ROW_HALF_MIRROR>(am));
+            am = fmaxf(am, dpp_f32<DPP_ROW_MIRROR>(am));
+        }
         float *mx = r_lds + K;
-        if ((lane & 3) == 0) mx[wave * 16 + (lane >> 2)] = am;
+        if ((lane & (FEW ? 15 : 3)) == 0) mx[wave * 16 + xrow] = am;   // (FEW: rows 4 .. 15 are read by nobody)
         lds_barrier();   // the row maxima are complete
         float arow = 0.f;
 #pragma unroll
-        for (int w = 0; w < GV_CW; ++w) arow = fmaxf(arow, mx[w * 16 + (lane >> 2)]);
+        for (int w = 0; w < GV_CW; ++w) arow = fmaxf(arow, mx[w * 16 + xrow]);
         q_inv = 127.0f / arow;
         if (!(q_inv <= 3.402823466e+38f)) q_inv = 0.f;   // all-zero token, or one so small that 127 / a overflows
     }
@@ -517,13 +538,19 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(const GemvArgs args)
     uint8_t *stg1 = reinterpret_cast<uint8_t *>(red + (GV_CW + wave) * 256);
     const uint8_t *stg_src = ((kb & 2) ? stg1 : stg0) + (4 * ln + 2 * (kb & 1)) * 16;
     auto to_operand_layout = [&](int u) __attribute__((always_inline)) {
-        *reinterpret_cast<v4u *>(stg0 + lane * 16) = a0[u];
-        *reinterpret_cast<v4u *>(stg1 + lane * 16) = a1[u];
+        if constexpr (FEW) {   // lane (row, q): bytes 8 q .. + 7 of the row, first half-row q < 8
+            uint8_t *dst = ((lane & 8) ? stg1 : stg0) + xrow * 64 + (lane & 7) * 8;
+            *reinterpret_cast<v2u *>(dst) = v2u{a0[u].x, a0[u].y};
+        } else {
+            *reinterpret_cast<v4u *>(stg0 + lane * 16) = a0[u];
+            *reinterpret_cast<v4u *>(stg1 + lane * 16) = a1[u];
+        }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
         a0[u] = *reinterpret_cast<const v4u *>(stg_src);
         a1[u] = *reinterpret_cast<const v4u *>(stg_src + 16);
+        if (FEW && ln >= GV_FEW) a0[u] = a1[u] = v4u{0u, 0u, 0u, 0u};
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
@@ -768,7 +795,7 @@ GemvPlan plan_gemv(int64_t M, int64_t N, int64_t K, int64_t G, int64_t batch)
     return pl;
 }
 
-template <bool GROUPED, bool ACC_OUT, bool ASYM, bool FUSED = false>
+template <bool GROUPED, bool ACC_OUT, bool ASYM, int FUSED = 0>
 static int launch_gemv_at(const GemvPlan &pl, const GemvArgs &ga, int batch, hipStream_t st)
 {
     const dim3 grid((unsigned)pl.blocks_per_split, (unsigned)pl.splits, (unsigned)batch);
@@ -805,7 +832,7 @@ static int launch_gemv_at(const GemvPlan &pl, const GemvArgs &ga, int batch, hip
                     W4A8_GV_CASE(6, 1);
                     W4A8_GV_CASE(7, 1);
                     default:
-                        if constexpr (!FUSED) {
+                        if constexpr (FUSED == 0) {
                             switch (pl.at) {
                                 W4A8_GV_CASE(8, 1);
                                 W4A8_GV_CASE(9, 1);
@@ -887,13 +914,13 @@ int launch_gemv(const int8_t *Xq, const float *sx, ZeroPoint zp, int64_t M, cons
     if (fused != nullptr) {
         ga.X = fused->X; ga.s = fused->s; ga.ldx = fused->ldx;
         ga.Xq_out = fused->Xq_out; ga.sx_out = fused->sx_out;
-        if (grouped) {
-            if (acc_out) rc = launch_gemv_at<true, true, false, true>(pl, ga, 1, st);
-            else rc = launch_gemv_at<true, false, false, true>(pl, ga, 1, st);
-        } else {
-            if (acc_out) rc = launch_gemv_at<false, true, false, true>(pl, ga, 1, st);
-            else rc = launch_gemv_at<false, false, false, true>(pl, ga, 1, st);
-        }
+#define W4A8_GV_FUSED(F_)                                                     \
+    (grouped ? (acc_out ? launch_gemv_at<true, true, false, F_>(pl, ga, 1, st)   \
+                        : launch_gemv_at<true, false, false, F_>(pl, ga, 1, st)) \
+             : (acc_out ? launch_gemv_at<false, true, false, F_>(pl, ga, 1, st)  \
+                        : launch_gemv_at<false, false, false, F_>(pl, ga, 1, st)))
+        rc = M <= GV_FEW ? W4A8_GV_FUSED(2) : W4A8_GV_FUSED(1);
+#undef W4A8_GV_FUSED
         return rc;
     }
     if (grouped) {
