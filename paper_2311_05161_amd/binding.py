@@ -3,6 +3,10 @@
 Argument marshalling only: every step of the layer runs in the HIP kernels.  PyTorch supplies
 device memory (``tensor.data_ptr()``) and the current HIP stream, nothing else.  There is no CPU
 fallback: if the shared library is missing, loading raises.
+
+The online calls (the layer, its two steps, and both for activations with a token zero-point) are
+marshalled in native code (``csrc/native_calls.cpp``) when they are asked for nothing but fresh outputs; the Python
+form beside it takes preallocated outputs, check outputs, workspaces and tensor subclasses.
 """
 from __future__ import annotations
 
@@ -37,6 +41,8 @@ EXPORTS = (
 FMT_DINT4, FMT_INT4, FMT_DINT3, FMT_DINT4_C4, FMT_DINT4_C8 = 0, 1, 2, 3, 4
 
 _lib = None
+_native = None   # the native marshalling, and the addresses of the entry points that it calls
+_addr = {}
 
 
 class W4A8Error(RuntimeError):
@@ -133,6 +139,16 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
     lib.dint_error_terms.restype = ci
     lib.w4a8_status_string.argtypes = [ci]
     lib.w4a8_status_string.restype = ctypes.c_char_p
+    try:
+        from . import _native as native
+    except ImportError as e:
+        raise FileNotFoundError("the native marshalling (_native.so) is not built or does not match this torch: "
+                                "run `python -m paper_2311_05161_amd.build`") from e
+    global _native
+    for name in ("quantize_act_int8", "quantize_act_int8_asym", "w4a8_gemm", "w4a8_gemm_asym", "w4a8_linear",
+                 "w4a8_gemm_workspace_bytes", "w4a8_linear_workspace_bytes"):
+        _addr[name] = ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+    _native = native
     _lib = lib
     return lib
 
@@ -149,6 +165,29 @@ def _stream():
     return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
 
 
+def _address(name: str) -> int:
+    if not _addr:
+        load_library()
+    return _addr[name]
+
+
+def _raw_stream() -> int:
+    """The current stream's handle (without building a Stream object)."""
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+
+
+def _native_call(name: str, where: str, *args):
+    """A native form's outputs; NotImplemented where the Python form has to take the call."""
+    if _native is None:
+        load_library()
+    if not torch.cuda.is_initialized():
+        return NotImplemented
+    out = getattr(_native, name)(*args, _raw_stream())
+    if type(out) is int:
+        _check(out, where)
+    return out
+
+
 def _check(status: int, where: str):
     if status != OK:
         raise W4A8Error(status, where)
@@ -162,6 +201,10 @@ def _rows(t: torch.Tensor, what: str):
 
 def quantize_act_int8(X: torch.Tensor, s: torch.Tensor | None = None, Xq=None, sx=None):
     """Xq int8 [M,K], sx float32 [M] = per-token absmax INT8 of X diag(s)^-1."""
+    if Xq is None and sx is None:
+        out = _native_call("act_quant", "quantize_act_int8", _address("quantize_act_int8"), X, s)
+        if out is not NotImplemented:
+            return out
     M, K, ldx = _rows(X, "X")
     if Xq is None:
         Xq = torch.empty((M, K), dtype=torch.int8, device=X.device)
@@ -218,6 +261,11 @@ def w4a8_gemm(Xq: torch.Tensor, sx: torch.Tensor, Wp: torch.Tensor, step: torch.
               zero: torch.Tensor, N: int, K: int, group_size: int = 0, layout: int = LAYOUT_TILED,
               out_dtype=torch.float16, Y=None, acc_out=None, workspace=None, want_acc=False):
     """Y [M,N] = dequant(Xq . dINT4(Wp)^T); optionally also the exact int32 accumulators."""
+    if Y is None and acc_out is None and workspace is None and not want_acc:
+        out = _native_call("gemm", "w4a8_gemm", _address("w4a8_gemm"), _address("w4a8_gemm_workspace_bytes"), Xq, sx,
+                           Wp, step, zero, N, K, group_size or 0, layout, _DTYPES[out_dtype])
+        if out is not NotImplemented:
+            return out
     M = Xq.shape[0]
     if Y is None:
         Y = torch.empty((M, N), dtype=out_dtype, device=Xq.device)
@@ -241,6 +289,11 @@ def w4a8_linear(X: torch.Tensor, s, Wp: torch.Tensor, step: torch.Tensor, zero: 
                 want_quantized=False, want_acc=False, workspace=None):
     """The whole layer in one call (one launch for up to 16 tokens of fp16 activations).
     Returns Y, or (Y, Xq, sx[, acc]) with want_quantized / want_acc."""
+    if Y is None and workspace is None and not want_quantized and not want_acc:
+        out = _native_call("linear", "w4a8_linear", _address("w4a8_linear"), _address("w4a8_linear_workspace_bytes"),
+                           X, s, Wp, step, zero, N, group_size or 0, layout, _DTYPES[out_dtype])
+        if out is not NotImplemented:
+            return out
     M, K, ldx = _rows(X, "X")
     if Y is None:
         Y = torch.empty((M, N), dtype=out_dtype, device=X.device)
@@ -283,6 +336,10 @@ def quantize_act_int8_asym(X: torch.Tensor, s: torch.Tensor | None = None, Xq=No
                            zx=None):
     """Token-wise min-max asymmetric 8-bit quantization of X diag(s)^-1.
     Returns (Xq int8 = code - 128, sx float32 [M], zx int32 [M] = zero-point - 128)."""
+    if Xq is None and sx is None and zx is None:
+        out = _native_call("act_quant_asym", "quantize_act_int8_asym", _address("quantize_act_int8_asym"), X, s)
+        if out is not NotImplemented:
+            return out
     M, K, ldx = _rows(X, "X")
     if Xq is None:
         Xq = torch.empty((M, K), dtype=torch.int8, device=X.device)
@@ -314,6 +371,12 @@ def w4a8_gemm_asym(Xq: torch.Tensor, sx: torch.Tensor, zx: torch.Tensor, Wp: tor
                    N: int, K: int, group_size: int = 0, layout: int = LAYOUT_TILED,
                    out_dtype=torch.float16, Y=None, acc_out=None, workspace=None, want_acc=False):
     """w4a8_gemm for activations with a token zero-point (quantize_act_int8_asym)."""
+    if Y is None and acc_out is None and workspace is None and not want_acc:
+        out = _native_call("gemm_asym", "w4a8_gemm_asym", _address("w4a8_gemm_asym"),
+                           _address("w4a8_gemm_workspace_bytes"), Xq, sx, zx, Wp, step, zero, wsum, tsum, N, K,
+                           group_size or 0, layout, _DTYPES[out_dtype])
+        if out is not NotImplemented:
+            return out
     M = Xq.shape[0]
     if Y is None:
         Y = torch.empty((M, N), dtype=out_dtype, device=Xq.device)

@@ -1,4 +1,4 @@
-"""Builds libw4a8.so (gfx950 code object + host C ABI) with hipcc, in-tree.
+"""Builds libw4a8.so (gfx950 code object + host C ABI) with hipcc and the binding's native marshalling, in-tree.
 
     python -m paper_2311_05161_amd.build          # compile everything, link
 """
@@ -13,6 +13,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ_DIR = os.path.join(HERE, "_build")
 LIB_PATH = os.path.join(HERE, "libw4a8.so")
+NATIVE_PATH = os.path.join(HERE, "_native.so")
 
 # The quantizers must evaluate the definition one binary32 operation at a time (bit-exact
 # contract with a CPU evaluation), so no mul+add contraction there.  The GEMM epilogue is free
@@ -63,12 +64,30 @@ def _compile(name: str, extra, verbose: bool) -> str:
     return obj
 
 
+def build_native(verbose: bool = False) -> str:
+    """Compile the argument marshalling (host code against torch's headers; it holds no GPU code)."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", os.path.join(CSRC, "native_calls.cpp"), "-o", NATIVE_PATH,
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           f"-I{root}/include", f"-I{root}/include/torch/csrc/api/include", f"-I{sysconfig.get_paths()['include']}",
+           f"-L{root}/lib", "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    _run(cmd)
+    return NATIVE_PATH
+
+
 def build(verbose: bool = False, extra_flags=()) -> str:
     """Compile every HIP source for gfx950 and link the shared library.  Always recompiles."""
     os.makedirs(OBJ_DIR, exist_ok=True)
-    with ThreadPoolExecutor(max_workers=7) as pool:
+    with ThreadPoolExecutor(max_workers=8) as pool:
+        native = pool.submit(build_native, verbose)
         objs = list(pool.map(lambda kv: _compile(kv[0], [*kv[1], *extra_flags], verbose),
                              SOURCES.items()))
+        native.result()
     cmd = [_hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_PATH, *objs]
     if verbose:
         print(" ".join(cmd), flush=True)

@@ -1,0 +1,260 @@
+// Argument marshalling of the layer's online calls in native code.  A decode step of a small layer runs for
+// 5 to 7 us on the GPU; marshalling it in Python (attribute look-ups, two torch.empty, twenty ctypes conversions)
+// took the host about 11 us per call, so that a loop of eager calls was bound by it: 1 x 4096 x 4096 13.9 us a
+// call with it, 5.9 us with this.
+//
+// Every function takes the address of the C entry point (the library is loaded by Python) and returns
+//   a tensor or a tuple of tensors   on success,
+//   an int                           the entry point's status when it is not W4A8_OK,
+//   NotImplemented                   for operands that are not plain torch tensors of the expected kind: the
+//                                    caller's Python form decides what to do with them.
+// Nothing is cached between calls.  The GIL is released around the entry points, as ctypes does.
+#include <torch/extension.h>
+
+#include "../../include/w4a8.h"
+
+namespace {
+
+constexpr int LAYOUT_TILED = W4A8_LAYOUT_TILED;
+
+bool to_i64(PyObject *o, int64_t &v)
+{
+    v = PyLong_AsLongLong(o);
+    return !(v == -1 && PyErr_Occurred());
+}
+template <typename F>
+bool to_fn(PyObject *o, F &f)
+{
+    f = reinterpret_cast<F>(PyLong_AsVoidPtr(o));
+    return !PyErr_Occurred();
+}
+
+// plain tensors only (no subclass may observe or replace these calls)
+bool plain(PyObject *o) { return THPVariable_CheckExact(o); }
+bool plain_or_none(PyObject *o) { return o == Py_None || THPVariable_CheckExact(o); }
+void *ptr(PyObject *o) { return o == Py_None ? nullptr : THPVariable_Unpack(o).data_ptr(); }
+
+// element type of activations / outputs: its id, or -1
+int dtype_id(at::ScalarType t)
+{
+    switch (t) {
+        case at::kFloat: return W4A8_F32;
+        case at::kHalf: return W4A8_F16;
+        case at::kBFloat16: return W4A8_BF16;
+        default: return -1;
+    }
+}
+at::ScalarType y_type(int64_t id)
+{
+    return id == W4A8_F16 ? at::kHalf : id == W4A8_BF16 ? at::kBFloat16 : at::kFloat;
+}
+
+struct Rows {   // a 2-D activation tensor with contiguous rows
+    int64_t M, K, ld;
+    int dtype;
+    bool ok;
+};
+Rows rows_of(const at::Tensor &X)
+{
+    Rows r{0, 0, 0, -1, false};
+    if (X.dim() != 2 || X.stride(1) != 1) return r;
+    r.M = X.size(0);
+    r.K = X.size(1);
+    r.ld = r.M > 1 ? X.stride(0) : std::max(X.stride(0), r.K);
+    r.dtype = dtype_id(X.scalar_type());
+    r.ok = r.dtype >= 0;
+    return r;
+}
+
+at::Tensor make(const at::Tensor &like, at::IntArrayRef size, at::ScalarType t)
+{
+    return at::empty(size, like.options().dtype(t));
+}
+
+PyObject *not_implemented() { Py_RETURN_NOTIMPLEMENTED; }
+PyObject *status(int rc) { return PyLong_FromLong(rc); }
+
+#define NATIVE_TRY try {
+#define NATIVE_CATCH                                      \
+    }                                                     \
+    catch (const python_error &) { return nullptr; }      \
+    catch (const std::exception &e)                       \
+    {                                                     \
+        PyErr_SetString(PyExc_RuntimeError, e.what());    \
+        return nullptr;                                   \
+    }
+
+// act_quant(entry, X, s, stream) -> (Xq, sx)
+PyObject *act_quant(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    NATIVE_TRY
+    if (n != 4 || !plain(a[1]) || !plain_or_none(a[2])) return not_implemented();
+    decltype(&quantize_act_int8) entry;
+    int64_t stream;
+    if (!to_fn(a[0], entry) || !to_i64(a[3], stream)) return nullptr;
+    const at::Tensor &X = THPVariable_Unpack(a[1]);
+    const Rows r = rows_of(X);
+    if (!r.ok) return not_implemented();
+    at::Tensor Xq = make(X, {r.M, r.K}, at::kChar), sx = make(X, {r.M}, at::kFloat);
+    const void *x = X.data_ptr();
+    const float *s = (const float *)ptr(a[2]);
+    int8_t *q = (int8_t *)Xq.data_ptr();
+    float *sxp = (float *)sx.data_ptr();
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = entry(x, r.dtype, r.M, r.K, r.ld, s, q, sxp, (void *)stream);
+    Py_END_ALLOW_THREADS
+    if (rc != W4A8_OK) return status(rc);
+    return PyTuple_Pack(2, py::reinterpret_steal<py::object>(THPVariable_Wrap(Xq)).ptr(),
+                        py::reinterpret_steal<py::object>(THPVariable_Wrap(sx)).ptr());
+    NATIVE_CATCH
+}
+
+// act_quant_asym(entry, X, s, stream) -> (Xq, sx, zx)
+PyObject *act_quant_asym(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    NATIVE_TRY
+    if (n != 4 || !plain(a[1]) || !plain_or_none(a[2])) return not_implemented();
+    decltype(&quantize_act_int8_asym) entry;
+    int64_t stream;
+    if (!to_fn(a[0], entry) || !to_i64(a[3], stream)) return nullptr;
+    const at::Tensor &X = THPVariable_Unpack(a[1]);
+    const Rows r = rows_of(X);
+    if (!r.ok) return not_implemented();
+    at::Tensor Xq = make(X, {r.M, r.K}, at::kChar), sx = make(X, {r.M}, at::kFloat), zx = make(X, {r.M}, at::kInt);
+    const void *x = X.data_ptr();
+    const float *s = (const float *)ptr(a[2]);
+    int8_t *q = (int8_t *)Xq.data_ptr();
+    float *sxp = (float *)sx.data_ptr();
+    int32_t *zxp = (int32_t *)zx.data_ptr();
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = entry(x, r.dtype, r.M, r.K, r.ld, s, q, sxp, zxp, (void *)stream);
+    Py_END_ALLOW_THREADS
+    if (rc != W4A8_OK) return status(rc);
+    return PyTuple_Pack(3, py::reinterpret_steal<py::object>(THPVariable_Wrap(Xq)).ptr(),
+                        py::reinterpret_steal<py::object>(THPVariable_Wrap(sx)).ptr(),
+                        py::reinterpret_steal<py::object>(THPVariable_Wrap(zx)).ptr());
+    NATIVE_CATCH
+}
+
+// gemm(entry, workspace_entry, Xq, sx, Wp, step, zero, N, K, group_size, layout, y_dtype, stream) -> Y
+PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    NATIVE_TRY
+    if (n != 13) return not_implemented();
+    for (int i = 2; i < 7; ++i)
+        if (!plain(a[i])) return not_implemented();
+    decltype(&w4a8_gemm) entry;
+    decltype(&w4a8_gemm_workspace_bytes) need;
+    int64_t N, K, G, layout, yd, stream;
+    if (!to_fn(a[0], entry) || !to_fn(a[1], need) || !to_i64(a[7], N) || !to_i64(a[8], K) || !to_i64(a[9], G) ||
+        !to_i64(a[10], layout) || !to_i64(a[11], yd) || !to_i64(a[12], stream))
+        return nullptr;
+    const at::Tensor &Xq = THPVariable_Unpack(a[2]);
+    if (Xq.dim() < 1 || N < 0) return not_implemented();
+    const int64_t M = Xq.size(0);
+    at::Tensor Y = make(Xq, {M, N}, y_type(yd));
+    const size_t bytes = need(M, N, K, G, (int)layout);
+    at::Tensor ws;
+    if (bytes > 0) ws = make(Xq, {(int64_t)bytes}, at::kByte);
+    const int8_t *q = (const int8_t *)ptr(a[2]);
+    const float *sx = (const float *)ptr(a[3]), *step = (const float *)ptr(a[5]);
+    const uint8_t *Wp = (const uint8_t *)ptr(a[4]), *zero = (const uint8_t *)ptr(a[6]);
+    void *y = Y.data_ptr(), *w = bytes > 0 ? ws.data_ptr() : nullptr;
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = entry(q, sx, M, Wp, (int)layout, step, zero, N, K, G, y, (int)yd, N, nullptr, w, bytes, (void *)stream);
+    Py_END_ALLOW_THREADS
+    return rc != W4A8_OK ? status(rc) : THPVariable_Wrap(Y);
+    NATIVE_CATCH
+}
+
+// gemm_asym(entry, workspace_entry, Xq, sx, zx, Wp, step, zero, wsum, tsum, N, K, group_size, layout, y_dtype,
+//           stream) -> Y
+PyObject *gemm_asym(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    NATIVE_TRY
+    if (n != 16) return not_implemented();
+    for (int i = 2; i < 10; ++i)
+        if (!plain(a[i])) return not_implemented();
+    decltype(&w4a8_gemm_asym) entry;
+    decltype(&w4a8_gemm_workspace_bytes) need;
+    int64_t N, K, G, layout, yd, stream;
+    if (!to_fn(a[0], entry) || !to_fn(a[1], need) || !to_i64(a[10], N) || !to_i64(a[11], K) || !to_i64(a[12], G) ||
+        !to_i64(a[13], layout) || !to_i64(a[14], yd) || !to_i64(a[15], stream))
+        return nullptr;
+    const at::Tensor &Xq = THPVariable_Unpack(a[2]);
+    if (Xq.dim() < 1 || N < 0) return not_implemented();
+    const int64_t M = Xq.size(0);
+    at::Tensor Y = make(Xq, {M, N}, y_type(yd));
+    const size_t bytes = need(M, N, K, G, (int)layout);
+    at::Tensor ws;
+    if (bytes > 0) ws = make(Xq, {(int64_t)bytes}, at::kByte);
+    const int8_t *q = (const int8_t *)ptr(a[2]);
+    const float *sx = (const float *)ptr(a[3]), *step = (const float *)ptr(a[6]);
+    const int32_t *zx = (const int32_t *)ptr(a[4]), *wsum = (const int32_t *)ptr(a[8]), *tsum = (const int32_t *)ptr(a[9]);
+    const uint8_t *Wp = (const uint8_t *)ptr(a[5]), *zero = (const uint8_t *)ptr(a[7]);
+    void *y = Y.data_ptr(), *w = bytes > 0 ? ws.data_ptr() : nullptr;
+    int rc;
+    Py_BEGIN_ALLOW_THREADS
+    rc = entry(q, sx, zx, M, Wp, (int)layout, step, zero, wsum, tsum, N, K, G, y, (int)yd, N, nullptr, w, bytes,
+               (void *)stream);
+    Py_END_ALLOW_THREADS
+    return rc != W4A8_OK ? status(rc) : THPVariable_Wrap(Y);
+    NATIVE_CATCH
+}
+
+// linear(entry, workspace_entry, X, s, Wp, step, zero, N, group_size, layout, y_dtype, stream) -> Y
+PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
+{
+    NATIVE_TRY
+    if (n != 12 || !plain(a[2]) || !plain_or_none(a[3]) || !plain(a[4]) || !plain(a[5]) || !plain(a[6]))
+        return not_implemented();
+    decltype(&w4a8_linear) entry;
+    decltype(&w4a8_linear_workspace_bytes) need;
+    int64_t N, G, layout, yd, stream;
+    if (!to_fn(a[0], entry) || !to_fn(a[1], need) || !to_i64(a[7], N) || !to_i64(a[8], G) ||
+        !to_i64(a[9], layout) || !to_i64(a[10], yd) || !to_i64(a[11], stream))
+        return nullptr;
+    const at::Tensor &X = THPVariable_Unpack(a[2]);
+    const Rows r = rows_of(X);
+    if (!r.ok || N < 0) return not_implemented();
+    at::Tensor Y = make(X, {r.M, N}, y_type(yd));
+    const void *x = X.data_ptr();
+    const float *s = (const float *)ptr(a[3]), *step = (const float *)ptr(a[5]);
+    const uint8_t *Wp = (const uint8_t *)ptr(a[4]), *zero = (const uint8_t *)ptr(a[6]);
+    void *y = Y.data_ptr();
+    int rc = W4A8_ERR_WORKSPACE;
+    auto call = [&](void *w, size_t bytes) {
+        Py_BEGIN_ALLOW_THREADS
+        rc = entry(x, r.dtype, r.M, r.K, r.ld, s, Wp, (int)layout, step, zero, N, G, y, (int)yd, N, nullptr, nullptr,
+                   nullptr, w, bytes, (void *)stream);
+        Py_END_ALLOW_THREADS
+    };
+    // The one-launch decode step needs no workspace: try without (a call that needs one is turned down
+    // before anything is launched).
+    if (r.M <= 16 && r.dtype == W4A8_F16 && layout == LAYOUT_TILED) call(nullptr, 0);
+    if (rc == W4A8_ERR_WORKSPACE) {
+        const size_t bytes = need(r.M, N, r.K, G, (int)layout);
+        at::Tensor ws;
+        if (bytes > 0) ws = make(X, {(int64_t)bytes}, at::kByte);
+        call(bytes > 0 ? ws.data_ptr() : nullptr, bytes);
+    }
+    return rc != W4A8_OK ? status(rc) : THPVariable_Wrap(Y);
+    NATIVE_CATCH
+}
+
+PyMethodDef methods[] = {
+    {"act_quant", (PyCFunction)(void (*)(void))act_quant, METH_FASTCALL, nullptr},
+    {"act_quant_asym", (PyCFunction)(void (*)(void))act_quant_asym, METH_FASTCALL, nullptr},
+    {"gemm", (PyCFunction)(void (*)(void))gemm, METH_FASTCALL, nullptr},
+    {"gemm_asym", (PyCFunction)(void (*)(void))gemm_asym, METH_FASTCALL, nullptr},
+    {"linear", (PyCFunction)(void (*)(void))linear, METH_FASTCALL, nullptr},
+    {nullptr, nullptr, 0, nullptr}};
+
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_native", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__native() { return PyModule_Create(&module); }
