@@ -718,46 +718,51 @@ static int launch_gemm_t(const GemmPlan &pl, const int8_t *Xq, const float *sx, 
 #undef W4A8_GM2
 }
 
-// ---- group-128 weights at a few hundred tokens ---------------------------------------------------
+// ---- group-128 weights whose tiles do not fill the chip twice --------------------------------------
 // Between the streaming kernel (<= 16 tokens per pass over the weights) and the tile kernel at full
-// occupancy lies the ridge of the roofline (M ~ 156): a 128-token tile kernel has only N / 256 tiles for
-// 256 CUs there, and cutting K into ranges over more workgroups moves more fp32 partial sums through
+// occupancy (512 resident 128 x 128 tiles) lie a few hundred tokens, or more on narrow layers: the tile kernel has
+// too few tiles there, and cutting K into ranges over more workgroups moves more fp32 partial sums through
 // memory than the layer has weights.  This kernel cuts K inside the workgroup instead.  A workgroup
-// owns 128 tokens x 64 channels; its 8 waves are 2 (channel halves of 32) x 4 (K phases): phase q takes
-// the k-tiles kt = 4 i + q -- with 128-wide groups each k-tile is one whole group, so a wave decodes,
+// owns 128 tokens x 256 / KQ channels; its 8 waves are 8 / KQ channel parts of 32 x KQ K phases: phase q takes
+// the k-tiles kt = KQ i + q -- with 128-wide groups each k-tile is one whole group, so a wave decodes,
 // multiplies and rescales complete groups exactly like the tile kernel does, and no group is shared.
-// The four k-tiles of a super-step are consumed concurrently from four LDS slots while the next four
-// land in the other four (global -> LDS copies, issued right behind the barrier that frees the slots):
-// one barrier per FOUR k-tiles.  At the end the phases' fp32 sums meet through LDS in a fixed order
-// ((q0 + q1) + (q2 + q3)), and the two phase-0 waves apply the token scale and store.  N / 64 workgroups
-// per 128 tokens, no workspace, no second launch.
+// The KQ k-tiles of a super-step are consumed concurrently from KQ LDS slots while the next KQ
+// land in the other KQ (global -> LDS copies, issued under the first MFMAs behind the barrier that frees the slots):
+// one barrier per KQ k-tiles.  At the end the phases' fp32 sums meet through LDS in a fixed order
+// (q0 + q1, or (q0 + q1) + (q2 + q3)), and the phase-0 waves apply the token scale and store.  No workspace, no second
+// launch.  KQ = 4: 64 channels per workgroup; KQ = 2: 128, for twice the tiles on the same CUs.
+// ASYM: token zero-points, one 24-bit multiply-add per accumulator and group as in gemm_kernel.
 constexpr int MD_BM = 128, MD_BN = 64, MD_KQ = 4, MD_THREADS = 512;
 constexpr int MD_TILE = MD_BM * TILE_K;   // bytes of one activation k-tile in LDS
 
-template <bool ACC_OUT>
+template <bool ACC_OUT, int KQ, bool ASYM>
 __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
-    const int8_t *__restrict__ Xq, const float *__restrict__ sx, int M, const uint8_t *__restrict__ Wt,
+    const int8_t *__restrict__ Xq, const float *__restrict__ sx, const int32_t *__restrict__ zx,
+    const int32_t *__restrict__ wsum, int M, const uint8_t *__restrict__ Wt,
     const float *__restrict__ step, const uint8_t *__restrict__ zero, int N, int K,
     uint16_t *__restrict__ Y, int y_dtype, int64_t ldy, int vec_store, int32_t *__restrict__ acc_out,
     int grid_m, int plain)
 {
     constexpr int MS = MD_BM / 32;
-    extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];   // [2 * MD_KQ][MD_TILE]
-    __shared__ __attribute__((aligned(16))) float s_ges[4 * MD_KQ][MD_BN];   // step / 8 per k-tile (= group) of four super-steps, and channel
-    __shared__ int s_gz[4 * MD_KQ][MD_BN];
+    constexpr int WN = 8 / KQ;       // channel parts
+    constexpr int BN = 32 * WN;      // channels of the workgroup (KQ * BN = 256)
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];   // [2 * KQ][MD_TILE]
+    __shared__ __attribute__((aligned(16))) float s_ges[4 * KQ][BN];   // step / 8 per k-tile (= group) of four super-steps, and channel
+    __shared__ int s_gz[4 * KQ][BN];
+    __shared__ __attribute__((aligned(16))) int s_gw[ASYM ? 4 * KQ : 1][ASYM ? BN : 4];   // 4 * (sum of the group's weights)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wn = wave & 1;      // channel half
-    const int kq = wave >> 1;     // K phase
+    const int wn = wave % WN;     // channel part
+    const int kq = wave / WN;     // K phase
     const int r32 = lane & 31;
     const int kh = lane >> 5;
     const int KT = K / TILE_K;    // = number of groups
-    const int SS = (KT + MD_KQ - 1) / MD_KQ;
+    const int SS = (KT + KQ - 1) / KQ;
     const int bm = blockIdx.x % grid_m, bn = blockIdx.x / grid_m;
     const int m0 = bm * MD_BM;
-    const int nb0 = bn * MD_BN;
+    const int nb0 = bn * BN;
     const int n0 = nb0 + wn * 32;
 
     __amdgpu_buffer_rsrc_t rw =
@@ -783,33 +788,35 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         avoff[i] = (m0 + row) * K + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
     }
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds_raw;
-    // this wave's share of the four k-tiles of super-step ss (into the slots of its parity): eight copies
+    // this wave's share of the KQ k-tiles of super-step ss (into the slots of its parity): 2 KQ copies
     // of 1 KB, c = 2 j + i for block i of k-tile j
     auto dma_one = [&](int ss, int c) {
         const int j = c >> 1, i = c & 1;
-        const int kt = min(ss * MD_KQ + j, KT - 1);
-        const int slot = (ss & 1) * MD_KQ + j;
+        const int kt = min(ss * KQ + j, KT - 1);
+        const int slot = (ss & 1) * KQ + j;
         dma_b128(rx, avoff[i], kt * TILE_K, lds_base + (uint32_t)(slot * MD_TILE + (i * 8 + wave) * 1024));
     };
     auto dma_super_step = [&](int ss) {
 #pragma unroll
-        for (int c = 0; c < 2 * MD_KQ; ++c) dma_one(ss, c);
+        for (int c = 0; c < 2 * KQ; ++c) dma_one(ss, c);
     };
-    // group parameters of a super-step: thread (j = tid / 64, ch = tid % 64), tid < 256
+    // group parameters of a super-step: thread (j = tid / BN, ch = tid % BN), tid < 256
     float gp_es = 0.f;
-    int gp_z = 0;
+    int gp_z = 0, gp_w = 0;
     auto fetch_params = [&](int ss) {
-        if (tid < MD_KQ * MD_BN) {
-            const int kt = min(ss * MD_KQ + (tid >> 6), KT - 1);
-            const int nn = nb0 + (tid & 63) < N ? nb0 + (tid & 63) : 0;
+        if (tid < KQ * BN) {
+            const int kt = min(ss * KQ + tid / BN, KT - 1);
+            const int nn = nb0 + tid % BN < N ? nb0 + tid % BN : 0;
             gp_es = step[(int64_t)nn * KT + kt];   // (used only in publish_params: nothing here waits for the load)
             gp_z = zero[(int64_t)nn * KT + kt];
+            if (ASYM) gp_w = wsum[(int64_t)nn * KT + kt];
         }
     };
     auto publish_params = [&](int ss) {
-        if (tid < MD_KQ * MD_BN) {
-            s_ges[(ss & 3) * MD_KQ + (tid >> 6)][tid & 63] = gp_es * 0.125f;
-            s_gz[(ss & 3) * MD_KQ + (tid >> 6)][tid & 63] = gp_z;
+        if (tid < KQ * BN) {
+            s_ges[(ss & 3) * KQ + tid / BN][tid % BN] = gp_es * 0.125f;
+            s_gz[(ss & 3) * KQ + tid / BN][tid % BN] = gp_z;
+            if (ASYM) s_gw[(ss & 3) * KQ + tid / BN][tid % BN] = 4 * gp_w;
         }
     };
 
@@ -841,12 +848,17 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     };
     // y += (step / 8) * acc for accumulator registers 4 b .. 4 b + 3 of token block ms (group kt)
     v4f es4[4];   // step / 8 of this lane's 16 channels for the group in the accumulators
+    v4i gw4[ASYM ? 4 : 1];   // and 4 * (sum of the group's weights)
+    int nzx[MS];  // minus the zero-point of this lane's token of each block
+#pragma unroll
+    for (int ms = 0; ms < MS; ++ms) nzx[ms] = (ASYM && m0 + ms * 32 + r32 < M) ? -zx[m0 + ms * 32 + r32] : 0;
     auto flush_quarter = [&](int ms, int b, int kt) {
         const int m = m0 + ms * 32 + r32;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int v = acc[ms][4 * b + r];
-            y[ms][4 * b + r] = __builtin_fmaf(es4[b][r], (float)v, y[ms][4 * b + r]);
+            const int vz = ASYM ? v + __mul24(nzx[ms], gw4[ASYM ? b : 0][r]) : v;   // (|4 wsum| < 2^23)
+            y[ms][4 * b + r] = __builtin_fmaf(es4[b][r], (float)vz, y[ms][4 * b + r]);
             if (ACC_OUT && m < M) {
                 const int nn = nb0 + wn * 32 + 8 * b + 4 * kh + r;
                 if (nn < N) acc_out[((int64_t)m * N + nn) * KT + kt] = v >> 2;
@@ -859,7 +871,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     v4u pw[4][2];   // packed weights of this wave's next four k-tiles (the weights come from HBM, read once)
     dma_super_step(0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_b(i * MD_KQ + kq, pw[i]);
+    for (int i = 0; i < 4; ++i) load_b(i * KQ + kq, pw[i]);
     fetch_params(0);
     publish_params(0);
     fetch_params(min(1, SS - 1));
@@ -885,18 +897,18 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     // P: packed weights of this k-tile, refilled for the wave's k-tile four super-steps on; PN: those of
     // the next super-step (decoded here); PNN: those of the one after (completed here, see below).
     // Order of the memory accesses of a wave (vmcnt retires in this order):
-    //   behind barrier(ss - 1): [2 parameter loads of ss + 2]
-    //   in super-step ss:       8 copies of super-step ss + 1 (their slots were freed by barrier(ss - 1))
+    //   behind barrier(ss - 1): [2 (ASYM: 3) parameter loads of ss + 2]
+    //   in super-step ss:       2 KQ copies of super-step ss + 1 (their slots were freed by barrier(ss - 1))
     //   at the end of ss:       2 weight loads for ss + 4
     // so "at most 2 outstanding" at the end of super-step ss means the copies of ss + 1 have landed and
     // every older weight load is complete; the barrier then publishes the copies and frees the slots
     // of ss for ss + 2.  Group parameters: ring of four super-steps, published two ahead (the decode of
     // the next k-tile needs its zero-points before the next barrier).
     auto super_step = [&](v4u(&P)[2], v4u(&PN)[2], v4u(&PNN)[2], int ss) __attribute__((always_inline)) {
-        const int kt = ss * MD_KQ + kq;
-        const int slot = (ss & 1) * MD_KQ + kq;
-        const int pslot = (ss & 3) * MD_KQ + kq;
-        const int pslot_next = ((ss + 1) & 3) * MD_KQ + kq;
+        const int kt = ss * KQ + kq;
+        const int slot = (ss & 1) * KQ + kq;
+        const int pslot = (ss & 3) * KQ + kq;
+        const int pslot_next = ((ss + 1) & 3) * KQ + kq;
         const bool live = kt < KT;   // (uniform over the wave; live k-tiles come first)
         if (live) {
 #pragma unroll
@@ -904,13 +916,18 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         }
         if (pending) {
 #pragma unroll
-            for (int b = 0; b < 4; ++b) flush_quarter(3, b, kt - MD_KQ);
+            for (int b = 0; b < 4; ++b) flush_quarter(3, b, kt - KQ);
             pending = false;
         }
         if (live) {
 #pragma unroll
             for (int b = 0; b < 4; ++b)
                 es4[b] = *reinterpret_cast<const v4f *>(&s_ges[pslot][wn * 32 + 8 * b + 4 * kh]);
+            if constexpr (ASYM) {
+#pragma unroll
+                for (int b = 0; b < 4; ++b)
+                    gw4[b] = *reinterpret_cast<const v4i *>(&s_gw[pslot][wn * 32 + 8 * b + 4 * kh]);
+            }
             int z_next = s_gz[pslot_next][wn * 32 + r32];
             const v16i z16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
@@ -919,6 +936,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
                     // the scales and the next zero-point are in registers from here on (their reads were
                     // issued before the first block's MFMAs; without this the reads sink to their uses)
                     asm volatile("" : "+v"(es4[0]), "+v"(es4[1]), "+v"(es4[2]), "+v"(es4[3]), "+v"(z_next));
+                    if constexpr (ASYM) asm volatile("" : "+v"(gw4[0]), "+v"(gw4[1]), "+v"(gw4[2]), "+v"(gw4[3]));
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
@@ -926,11 +944,11 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
                     if (k == 0) acc[ms] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[0], af[0], z16, 0, 0, 0);
                     else acc[ms] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[k], af[k], acc[ms], 0, 0, 0);
                     if (ms + 1 < MS) af[k] = read_a(slot, ms + 1, k);
-                    // the copies of the next super-step, two per MFMA of the first block: issued in one burst
+                    // the copies of the next super-step, spread over the MFMAs of the first block: issued in one burst
                     // by all eight waves they fill the address queue of the CU and hold every wave up
                     if (ms == 0) {
-                        dma_one(ss + 1, 2 * k);
-                        dma_one(ss + 1, 2 * k + 1);
+#pragma unroll
+                        for (int c = 0; c < KQ / 2; ++c) dma_one(ss + 1, k * (KQ / 2) + c);
                     }
                     if (ms > 0) flush_quarter(ms - 1, k, kt);
                     if (ms + 1 == MS) {
@@ -948,12 +966,12 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
             dma_super_step(ss + 1);
         }
         gm_order_fence();
-        load_b((ss + 4) * MD_KQ + kq, P);
+        load_b((ss + 4) * KQ + kq, P);
         gm_order_fence();
         wait_copies<2>();
         // (a use in every lane, outside any branch: all waits for the parameter loads and for PNN happen
         // here, none behind the copies issued below)
-        asm volatile("" : "+v"(PNN[0]), "+v"(PNN[1]), "+v"(gp_es), "+v"(gp_z));
+        asm volatile("" : "+v"(PNN[0]), "+v"(PNN[1]), "+v"(gp_es), "+v"(gp_z), "+v"(gp_w));
         publish_params(ss + 2);   // (fetched behind the last barrier)
         __syncthreads();
         fetch_params(min(ss + 3, SS - 1));
@@ -971,16 +989,16 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         if (ss < SS) super_step(pw[0], pw[1], pw[2], ss);
         if (ss + 1 < SS) super_step(pw[1], pw[2], pw[3], ss + 1);
         if (ss + 2 < SS) super_step(pw[2], pw[3], pw[0], ss + 2);
-        if (pending) {   // the last live k-tile of this wave: 4 (SS - 1) + q, or the one before
-            const int kt_last = (SS - 1) * MD_KQ + kq;
+        if (pending) {   // the last live k-tile of this wave: KQ (SS - 1) + q, or the one before
+            const int kt_last = (SS - 1) * KQ + kq;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) flush_quarter(3, b, kt_last < KT ? kt_last : kt_last - MD_KQ);
+            for (int b = 0; b < 4; ++b) flush_quarter(3, b, kt_last < KT ? kt_last : kt_last - KQ);
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
-    // ---- the four phases' sums meet in LDS: (q0 + q1) + (q2 + q3)
+    // ---- the phases' sums meet in LDS: q0 + q1, or (q0 + q1) + (q2 + q3)
     float *red = reinterpret_cast<float *>(lds_raw);   // [..][64 lanes][64 floats], 16 KB per wave
     auto red_ptr = [&](int slot) { return red + ((size_t)slot * 64 + lane) * 64; };
     auto put = [&](int slot) {
@@ -1000,14 +1018,16 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
                 y[ms][r] += t.x; y[ms][r + 1] += t.y; y[ms][r + 2] += t.z; y[ms][r + 3] += t.w;
             }
     };
-    if (kq & 1) put((kq >> 1) * 2 + wn);          // q1 -> slots 0, 1; q3 -> slots 2, 3
+    if (kq & 1) put((kq >> 1) * WN + wn);         // q1 -> the first WN slots, q3 -> the next
     __syncthreads();
-    if (!(kq & 1)) add((kq >> 1) * 2 + wn);       // q0 += q1, q2 += q3
-    __syncthreads();
-    if (kq == 2) put(wn);
-    __syncthreads();
+    if (!(kq & 1)) add((kq >> 1) * WN + wn);      // q0 += q1, q2 += q3
+    if constexpr (KQ == 4) {
+        __syncthreads();
+        if (kq == 2) put(wn);
+        __syncthreads();
+        if (kq == 0) add(wn);
+    }
     if (kq != 0) return;
-    add(wn);
 
     // ---- epilogue (phase-0 waves): Y[m, n .. n+3] = cast(sx[m] * y)
 #pragma unroll
@@ -1273,36 +1293,47 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_pc_kernel(
     }
 }
 
-// Whether a shape takes gemm_mid_kernel: 128-wide groups, symmetric activations, 65 .. 256 tokens, and a
-// grid of at most one workgroup per CU.  Measured against the tile kernel with K cut into ranges (which
-// is what these shapes would otherwise run): ahead wherever the grid covers at least half the CUs
-// (LLaMA-13B up-projection at 128 tokens: 39 -> 26 us; 4096 x 4096 at 256: 29 -> 22 us), behind on long K
-// with few workgroups (13824 -> 5120 at 128 tokens: 80 workgroups, 27 super-steps, 45 against 37 us) and
-// with more than one workgroup per CU.
-bool gemm_mid_applies(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
+// K phases with which a shape takes gemm_mid_kernel (0: it does not): 128-wide groups, more than 64 tokens, and a
+// grid of at most one workgroup per CU -- with four phases (64 channels per workgroup) if that fits, else with two.
+// The line between it and the tile kernel with K in ranges: a workgroup here takes a time proportional to
+// its share of K whatever the grid (0.4 us per k-tile with four phases, 0.73 with two, some 5 us besides), the tile
+// kernel one proportional to tiles x K (3.4 ns per 128 x 128 k-tile of the chip) with some 16 us for partial
+// sums, their combine launch and two prologues.  Equating them gives K-tiles x (W - workgroups) <= C; the constants are
+// where the measured times cross, and below 64 workgroups (four phases) or 12 k-tiles (two) the tile kernel won
+// throughout.  A token zero-point costs relatively more here (one vector operation per accumulator and group).
+// Measured, tile kernel / this, us -- four phases: 512 x 4096 x 4096 32.4 / 23.3, 384 x 5120 x 5120 35.1 / 26.0,
+// 512 x 1152 x 4096 25.3 / 13.8, 512 x 11008 x 4096 58.2 / 46.6; 512 x 6144 x 1024 (64 workgroups) 25.0 / 25.4, 300 x 4096 x 1024
+// (48) 18.2 / 20.3.  Two phases: 256 x 5120 x 13824 51.8 / 39.6, 1024 x 4096 x 4096 47.6 / 33.2, 2048 x 4096 x 2048 47.8 / 31.8,
+// 607 x 11008 x 4096 (160 workgroups) 64.8 / 64.5, 512 x 13824 x 5120 (160) 78.0 / 82.8, 1024 x 1024 x 4096 (8 k-tiles) 14.0 / 16.5.
+// With zero-points: 512 x 4096 x 4096 37.4 / 29.3, 900 x 4096 x 4096 56.2 / 38.8, 607 x 8192 x 4096 58.0 / 57.6, 512 x 8192 x 2048 35.6 / 38.5.
+int gemm_mid_phases(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
 {
-    if (asym || G != TILE_K || G == K || M <= 64 || M > 256) return false;
-    const int64_t wgs = (M + MD_BM - 1) / MD_BM * ((N + MD_BN - 1) / MD_BN);
-    const int64_t KT = K / TILE_K;
-    return KT >= 8 && wgs <= 256 && (wgs >= 128 || KT <= 48);
+    const int64_t KT = K / TILE_K, gm = (M + MD_BM - 1) / MD_BM;
+    if (G != TILE_K || G == K || M <= 64 || KT < 8) return 0;
+    const int64_t w4 = gm * ((N + MD_BN - 1) / MD_BN);
+    if (w4 <= 256) return w4 >= 64 && KT * (244 - w4) <= (asym ? 5200 : 7200) ? 4 : 0;
+    const int64_t w2 = gm * ((N + 2 * MD_BN - 1) / (2 * MD_BN));
+    return w2 <= 256 && KT >= 12 && KT * (216 - w2) <= (asym ? 3400 : 4800) ? 2 : 0;
 }
 
-static int launch_gemm_mid(const int8_t *Xq, const float *sx, int64_t M, const uint8_t *Wt, const float *step,
-                           const uint8_t *zero, int64_t N, int64_t K, void *Y, int y_dtype, int64_t ldy,
-                           int32_t *acc_out, hipStream_t st, int plain)
+template <int KQ, bool ASYM>
+static int launch_gemm_mid_t(const int8_t *Xq, const float *sx, ZeroPoint zp, int64_t M, const uint8_t *Wt,
+                             const float *step, const uint8_t *zero, int64_t N, int64_t K, void *Y, int y_dtype,
+                             int64_t ldy, int32_t *acc_out, hipStream_t st, int plain)
 {
+    constexpr int BN = 256 / KQ;
     const int grid_m = (int)((M + MD_BM - 1) / MD_BM);
-    const int grid_n = (int)((N + MD_BN - 1) / MD_BN);
+    const int grid_n = (int)((N + BN - 1) / BN);
     const int vec_store = (((uintptr_t)Y % 8 == 0) && (ldy % 4 == 0)) ? 1 : 0;
-    constexpr int lds_bytes = 2 * MD_KQ * MD_TILE;   // 128 KB
-#define W4A8_MD(AO_)                                                                                      \
-    do {                                                                                                  \
-        static std::atomic<uint64_t> lds_opted{0};                                                        \
-        if (opt_in_dynamic_lds((const void *)gemm_mid_kernel<AO_>, lds_bytes, lds_opted) != W4A8_OK)      \
-            return W4A8_ERR_HIP;                                                                          \
-        hipLaunchKernelGGL((gemm_mid_kernel<AO_>), dim3((unsigned)(grid_m * grid_n)), dim3(MD_THREADS),   \
-                           lds_bytes, st, Xq, sx, (int)M, Wt, step, zero, (int)N, (int)K, (uint16_t *)Y,  \
-                           y_dtype, ldy, vec_store, acc_out, grid_m, plain);                              \
+    constexpr int lds_bytes = 2 * KQ * MD_TILE;   // 128 or 64 KB
+#define W4A8_MD(AO_)                                                                                           \
+    do {                                                                                                       \
+        static std::atomic<uint64_t> lds_opted{0};                                                             \
+        if (opt_in_dynamic_lds((const void *)gemm_mid_kernel<AO_, KQ, ASYM>, lds_bytes, lds_opted) != W4A8_OK) \
+            return W4A8_ERR_HIP;                                                                               \
+        hipLaunchKernelGGL((gemm_mid_kernel<AO_, KQ, ASYM>), dim3((unsigned)(grid_m * grid_n)),                \
+                           dim3(MD_THREADS), lds_bytes, st, Xq, sx, zp.zx, zp.wsum, (int)M, Wt, step, zero,    \
+                           (int)N, (int)K, (uint16_t *)Y, y_dtype, ldy, vec_store, acc_out, grid_m, plain);    \
     } while (0)
     if (acc_out) W4A8_MD(true);
     else W4A8_MD(false);
@@ -1310,13 +1341,15 @@ static int launch_gemm_mid(const int8_t *Xq, const float *sx, int64_t M, const u
     return hip_status(hipGetLastError());
 }
 
-// The per-channel variant (gemm_mid_pc_kernel), same token range and grid condition.
+// The per-channel variant (gemm_mid_pc_kernel): the same grid condition; beyond 256 tokens only up to K = 9216
+// (tile kernel / this, us: 1000 x 2048 x 512 19.0 / 12.3, 512 x 4096 x 2048 27.3 / 17.6, 1000 x 8192 x 1024 35.3 / 23.6, but
+// 400 x 13824 x 2048 31.6 / 33.6 and 600 x 13824 x 512 26.1 / 29.0).
 bool gemm_mid_pc_applies(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
 {
-    if (asym || G != K || M <= 64 || M > 256) return false;
+    if (asym || G != K || M <= 64) return false;
     const int64_t wgs = (M + MP_BM - 1) / MP_BM * ((N + MD_BN - 1) / MD_BN);
     const int64_t KT = K / TILE_K;
-    return KT >= 8 && wgs <= 256;
+    return KT >= 8 && wgs <= 256 && (M <= 256 || KT <= 72);
 }
 
 static int launch_gemm_mid_pc(const int8_t *Xq, const float *sx, int32_t *rs, int64_t M, const uint8_t *Wt,
@@ -1432,8 +1465,13 @@ int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, in
     const bool grouped = G != K;
     if ((M + 63) / 64 * ((N + 255) / 256) * 64 > 0x7fffffLL || M * K > 0x7fffffffLL)
         return W4A8_ERR_SHAPE;
-    if (gemm_mid_applies(M, N, K, G, zp.zx != nullptr))
-        return launch_gemm_mid(Xq, sx, M, Wt, step, zero, N, K, Y, y_dtype, ldy, acc_out, st, plain);
+    if (const int phases = gemm_mid_phases(M, N, K, G, zp.zx != nullptr)) {
+#define W4A8_MD_T(KQ_, AS_) \
+    launch_gemm_mid_t<KQ_, AS_>(Xq, sx, zp, M, Wt, step, zero, N, K, Y, y_dtype, ldy, acc_out, st, plain)
+        if (zp.zx != nullptr) return phases == 4 ? W4A8_MD_T(4, true) : W4A8_MD_T(2, true);
+        return phases == 4 ? W4A8_MD_T(4, false) : W4A8_MD_T(2, false);
+#undef W4A8_MD_T
+    }
     if (gemm_mid_pc_applies(M, N, K, G, zp.zx != nullptr))
         return launch_gemm_mid_pc(Xq, sx, rs, M, Wt, step, zero, N, K, Y, y_dtype, ldy, acc_out, st, plain,
                                   rs_ready);
