@@ -760,7 +760,14 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     const int kh = lane >> 5;
     const int KT = K / TILE_K;    // = number of groups
     const int SS = (KT + KQ - 1) / KQ;
-    const int bm = blockIdx.x % grid_m, bn = blockIdx.x / grid_m;
+    // (workgroups are handed to the 8 XCDs round-robin: renumbered so that the token tiles that share weights
+    // share an L2)
+    int bid = blockIdx.x;
+    {
+        const int per = (int)gridDim.x / 8;
+        if (bid < per * 8) bid = (bid & 7) * per + (bid >> 3);
+    }
+    const int bm = bid % grid_m, bn = bid / grid_m;
     const int m0 = bm * MD_BM;
     const int nb0 = bn * BN;
     const int n0 = nb0 + wn * 32;
