@@ -13,8 +13,8 @@
 
 namespace w4a8 {
 
-typedef _Float16 v4h __attribute__((ext_vector_type(4)));
 typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 typedef float v16f __attribute__((ext_vector_type(16)));
 
 constexpr int AQ_GRID = 16;
@@ -106,10 +106,92 @@ int launch_aqas_scale(const float *ax, const float *aw, int64_t K, int j, float 
 }
 
 // ---- the unquantized product Yref[m,n] = sum_k X[m,k] W[n,k] in fp32 on the matrix cores ----------
-// One wave per 32 x 32 output tile, operands straight from global memory (offline work, small M).
-// fp16 inputs: v_mfma_f32_32x32x8_f16, a lane fetches 8 consecutive k per 16-column step and feeds
-// them as two MFMAs (any split of k over lanes and instructions is fine as long as both operands use
-// the same one); other input types are widened exactly and go through v_mfma_f32_32x32x2_f32.
+// 16-bit inputs, rows 16-byte aligned and K % 64 == 0: products of 16-bit numbers are exact in fp32, so the 16-bit matrix
+// instructions (32 x 32 x 16) lose nothing against widened operands.  A block of four waves makes a 64 x 128 tile,
+// wave w the columns 32 w .. + 31 of all 64 rows; 64 columns of K at a time go through LDS (rows of 128 bytes in
+// 16-byte chunks, chunk index XORed with half the row so that the reads of 16 rows at one chunk cover all
+// banks), the next four steps are on their way to registers meanwhile.  Bound by the L2 reads of the tiles (24 KB
+// per step and block): at 512 x 4096 x 4096 the grid is one block per CU.  One wave per 32 x 32 tile straight from global memory, 16
+// bytes of 32 rows per load, took 127 us there, this 41 us.
+constexpr int RG_BM = 64, RG_BN = 128, RG_BK = 64, RG_AHEAD = 4;
+
+template <typename T>
+__global__ __launch_bounds__(256) void ref_gemm16_kernel(const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx,
+                                                         const T *__restrict__ W, int64_t N, int64_t ldw,
+                                                         float *__restrict__ Y)
+{
+    constexpr int ROWS = RG_BM + RG_BN;          // rows of X, then rows of W
+    constexpr int LOADS = ROWS * 8 / 256;        // 16-byte chunks per thread and step (6)
+    __shared__ __attribute__((aligned(16))) v4u tile[2][ROWS * 8];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t m0 = (int64_t)blockIdx.y * RG_BM, n0 = (int64_t)blockIdx.x * RG_BN;
+    const int r32 = lane & 31, kh = lane >> 5;
+    // thread: rows tid / 8 + 32 i, chunk tid % 8 (eight lanes read 128 contiguous bytes of a row)
+    const v4u *src[LOADS];
+    int dst[LOADS];
+#pragma unroll
+    for (int i = 0; i < LOADS; ++i) {
+        const int row = tid / 8 + 32 * i, c = tid & 7;
+        // (rows past the end repeat the last one; they are not stored)
+        const T *p = row < RG_BM ? X + min(m0 + row, M - 1) * ldx : W + min(n0 + row - RG_BM, N - 1) * ldw;
+        src[i] = reinterpret_cast<const v4u *>(p) + c;
+        dst[i] = row * 8 + (c ^ ((row >> 1) & 7));
+    }
+    v16f acc[2];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.0f;
+    // RG_AHEAD steps of loads are in flight against the memory latency (vector-typed registers: an array of the
+    // HIP struct type went to scratch memory, and the kernel took 128 to 168 us)
+    v4u ring[RG_AHEAD][LOADS];
+    const int64_t steps = K / RG_BK;
+#pragma unroll
+    for (int p = 0; p < RG_AHEAD; ++p)
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) ring[p][i] = src[i][min((int64_t)p, steps - 1) * 8];
+    for (int64_t s0 = 0; s0 < steps; s0 += RG_AHEAD) {
+#pragma unroll
+        for (int p = 0; p < RG_AHEAD; ++p) {   // (RG_AHEAD is even: step s0 + p uses buffer p & 1)
+            if (s0 + p >= steps) break;        // uniform
+            v4u *t = tile[p & 1];
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) t[dst[i]] = ring[p][i];
+            const int64_t ahead = min(s0 + p + RG_AHEAD, steps - 1);   // (past the end: the last step again, unused)
+#pragma unroll
+            for (int i = 0; i < LOADS; ++i) ring[p][i] = src[i][ahead * 8];
+            // (one barrier per step: a wave that is a step ahead writes the other buffer; the loads above stay in flight)
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+#pragma unroll
+            for (int q = 0; q < RG_BK / 16; ++q) {   // lane (r32, kh) holds 8 consecutive k of its row, as both operands agree on
+                const int c = (2 * q + kh) ^ ((r32 >> 1) & 7);
+                const v4u wv = t[(RG_BM + wave * 32 + r32) * 8 + c];
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const v4u xv = t[(h * 32 + r32) * 8 + c];
+                    if constexpr (__is_same(T, bf16_t))
+                        acc[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, xv),
+                                                                         __builtin_bit_cast(v8bf, wv), acc[h], 0, 0, 0);
+                    else
+                        acc[h] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, xv),
+                                                                        __builtin_bit_cast(v8h, wv), acc[h], 0, 0, 0);
+                }
+            }
+        }
+    }
+    // D[i][j], A = tokens, B = channels: lane holds channel n0 + 32 wave + r32, tokens 8 (r / 4) + 4 kh + r % 4
+    const int64_t n = n0 + wave * 32 + r32;
+    if (n < N) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int64_t m = m0 + 32 * h + 8 * (r >> 2) + 4 * kh + (r & 3);
+                if (m < M) Y[m * N + n] = acc[h][r];
+            }
+    }
+}
+
+// Every other input (binary32, odd lengths and alignments): one wave per 32 x 32 output tile, operands straight from
+// global memory, widened exactly, v_mfma_f32_32x32x2_f32.
 template <typename T>
 __global__ __launch_bounds__(256) void ref_gemm_kernel(const T *__restrict__ X, int64_t M, int64_t K,
                                                        int64_t ldx, const T *__restrict__ W, int64_t N,
@@ -125,19 +207,8 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(const T *__restrict__ X, 
     v16f acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
-    if constexpr (sizeof(T) == 2 && !__is_same(T, bf16_t)) {
-        for (int64_t k = 0; k < K; k += 16) {
-            const v8h a = *reinterpret_cast<const v8h *>(xr + k + 8 * kh);
-            const v8h b = *reinterpret_cast<const v8h *>(wr + k + 8 * kh);
-            acc = __builtin_amdgcn_mfma_f32_32x32x8f16(__builtin_shufflevector(a, a, 0, 1, 2, 3),
-                                                       __builtin_shufflevector(b, b, 0, 1, 2, 3), acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x8f16(__builtin_shufflevector(a, a, 4, 5, 6, 7),
-                                                       __builtin_shufflevector(b, b, 4, 5, 6, 7), acc, 0, 0, 0);
-        }
-    } else {
-        for (int64_t k = 0; k < K; k += 2)
-            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(to_f32(xr[k + kh]), to_f32(wr[k + kh]), acc, 0, 0, 0);
-    }
+    for (int64_t k = 0; k < K; k += 2)
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(to_f32(xr[k + kh]), to_f32(wr[k + kh]), acc, 0, 0, 0);
     // D[i][j] = sum_k A[i][k] B[k][j], A = tokens, B = channels: lane holds channel n0 + r32 and the
     // tokens m0 + 8 (r / 4) + 4 kh + r % 4
     const int64_t n = n0 + r32;
@@ -153,6 +224,17 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(const T *__restrict__ X, 
 int launch_ref_gemm(const void *X, const void *W, int dtype, int64_t M, int64_t N, int64_t K,
                     int64_t ldx, int64_t ldw, float *Y, hipStream_t st)
 {
+    if (dtype != W4A8_F32 && K % RG_BK == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)W % 16 == 0 && ldx % 8 == 0 &&
+        ldw % 8 == 0 && (M + RG_BM - 1) / RG_BM <= 65535) {
+        const dim3 grid16((unsigned)((N + RG_BN - 1) / RG_BN), (unsigned)((M + RG_BM - 1) / RG_BM));
+        if (dtype == W4A8_F16)
+            hipLaunchKernelGGL((ref_gemm16_kernel<__half>), grid16, dim3(256), 0, st, (const __half *)X, M, K, ldx,
+                               (const __half *)W, N, ldw, Y);
+        else
+            hipLaunchKernelGGL((ref_gemm16_kernel<bf16_t>), grid16, dim3(256), 0, st, (const bf16_t *)X, M, K, ldx,
+                               (const bf16_t *)W, N, ldw, Y);
+        return hip_status(hipGetLastError());
+    }
     const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
     switch (dtype) {
         case W4A8_F16:
