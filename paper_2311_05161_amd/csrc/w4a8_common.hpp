@@ -53,6 +53,8 @@ constexpr int DPP_QUAD_XOR1 = 0xB1;        // quad_perm [1, 0, 3, 2]
 constexpr int DPP_QUAD_XOR2 = 0x4E;        // quad_perm [2, 3, 0, 1]
 constexpr int DPP_ROW_HALF_MIRROR = 0x141; // lane i <-> 7 - i within 8 lanes
 constexpr int DPP_ROW_MIRROR = 0x140;      // lane i <-> 15 - i within 16 lanes
+constexpr int DPP_ROW_ROR4 = 0x124;        // rotations within 16 lanes
+constexpr int DPP_ROW_ROR8 = 0x128;
 
 template <int CTRL>
 __device__ __forceinline__ int dpp_i32(int v)

@@ -805,6 +805,133 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
     }
 }
 
+// Longer groups, 16-bit elements under the same conditions: the group's values of 32 channels stay in registers
+// between the range and the codes (1024 threads, 16 R registers each), so V is read once -- the kernel above sweeps
+// it twice, and beyond the last-level cache's reach the second sweep comes from memory again.
+// Bound by memory: 3 bytes per value.  Thread (c4, t4) = (tid % 4, tid / 4) owns channels 8 c4 .. + 7 and the tokens
+// 1024 r + 4 t4 .. + 3, r < R: one word of codes per channel and r, which goes through LDS (two buffers, one barrier
+// per r) to the thread that stores 32 tokens of the channel's row.  A row of 32 channels is 64 bytes, half a cache line:
+// the channel parts of a head run on one XCD, so that its L2 serves the other half.
+// 256 heads x 4096 tokens x 128 channels: 126 -> 112 us (3.6 TB/s; 64 heads 60 -> 27).
+constexpr int VR_THREADS = 1024, VR_CHANNELS = 32, VR_TOKENS = 1024;
+constexpr int VR_STRIDE = VR_TOKENS / 4 + 4;   // words per channel row in LDS (16-byte aligned)
+
+template <typename T, int R>
+__global__ __launch_bounds__(VR_THREADS) void value_quant_resident_kernel(const T *__restrict__ V, uint32_t groups,
+                                                                          uint32_t parts, uint32_t ng, int64_t Tn,
+                                                                          int64_t D, int64_t ld_t, int64_t ld_b,
+                                                                          int G, uint8_t *__restrict__ codes,
+                                                                          float *__restrict__ step,
+                                                                          uint8_t *__restrict__ zero)
+{
+    static_assert(sizeof(T) == 2, "16-bit elements");
+    constexpr int WAVES = VR_THREADS / WAVE;
+    __shared__ float s_lo[WAVES][VR_CHANNELS], s_hi[WAVES][VR_CHANNELS];
+    __shared__ float4 s_rule[VR_CHANNELS];          // 1 / step, -z, p - z, z of each channel
+    __shared__ __attribute__((aligned(16))) uint32_t s_codes[R > 1 ? 2 : 1][VR_CHANNELS * VR_STRIDE];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // block -> (head and group, channel part): the parts of one follow each other on one XCD (blocks go round-robin
+    // over eight)
+    const uint32_t xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
+    const uint32_t hg = seq / parts * 8 + xcd, part = seq % parts;
+    if (hg >= groups) return;   // whole block
+    const int64_t b = hg / ng, g = hg % ng;
+    const int64_t d0 = (int64_t)part * VR_CHANNELS;
+    const int c4 = tid & 3, t4 = tid >> 2;
+    const bool live = d0 + c4 * 8 < D;   // D % 8 == 0: the eight channels are valid together
+    const T *v = V + b * ld_b + g * G * ld_t + (live ? d0 + c4 * 8 : 0);
+
+    v4u raw[R][4];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int t = r * VR_TOKENS + 4 * t4;
+        const T *p = v + (int64_t)(t < G ? t : 0) * ld_t;   // (past the end, G % 4 == 0: the first four tokens again)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) raw[r][i] = *reinterpret_cast<const v4u *>(p + i * ld_t);
+    }
+    auto element = [](const v4u &w, int j) {
+        const uint32_t h = (j & 1) ? w[j >> 1] >> 16 : w[j >> 1] & 0xffffu;
+        if constexpr (__is_same(T, bf16_t)) return __uint_as_float(h << 16);
+        else return __half2float(__ushort_as_half((uint16_t)h));
+    };
+    // ---- ranges: the thread's tokens, the 16 lanes of the wave with the same channels, the waves
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        float lo = 0.0f, hi = 0.0f;
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int i = 0; i < 4; i += 2) {
+                const float x0 = element(raw[r][i], j), x1 = element(raw[r][i + 1], j);
+                lo = fminf(fminf(lo, x0), x1);
+                hi = fmaxf(fmaxf(hi, x0), x1);
+            }
+        lo = fminf(lo, dpp_f32<DPP_ROW_ROR4>(lo));
+        hi = fmaxf(hi, dpp_f32<DPP_ROW_ROR4>(hi));
+        lo = fminf(lo, dpp_f32<DPP_ROW_ROR8>(lo));
+        hi = fmaxf(hi, dpp_f32<DPP_ROW_ROR8>(hi));
+#pragma unroll
+        for (int off = 16; off <= 32; off <<= 1) {
+            lo = fminf(lo, __shfl_xor(lo, off, WAVE));
+            hi = fmaxf(hi, __shfl_xor(hi, off, WAVE));
+        }
+        if (lane < 4) {
+            s_lo[wave][lane * 8 + j] = lo;
+            s_hi[wave][lane * 8 + j] = hi;
+        }
+        __builtin_amdgcn_sched_barrier(0);   // (channel by channel: interleaved, all of them are widened at once)
+    }
+    __syncthreads();
+    if (tid < VR_CHANNELS) {   // one thread per channel: step, zero-point
+        float l = 0.0f, h = 0.0f;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            l = fminf(l, s_lo[w][tid]);
+            h = fmaxf(h, s_hi[w][tid]);
+        }
+        float st, istep;
+        int z;
+        range_params(l, h, st, istep, z);
+        const CodeRule rule = make_rule(istep, z);
+        s_rule[tid] = make_float4(rule.istep, rule.lo, rule.hi, __int_as_float(rule.z));
+        if (d0 + tid < D) {
+            step[(b * D + d0 + tid) * ng + g] = st;
+            zero[(b * D + d0 + tid) * ng + g] = (uint8_t)z;
+        }
+    }
+    __syncthreads();
+
+    // (the values are widened again below: kept widened from the ranges they would be twice the registers)
+#pragma unroll
+    for (int r = 0; r < R; ++r) asm volatile("" : "+v"(raw[r][0]), "+v"(raw[r][1]), "+v"(raw[r][2]), "+v"(raw[r][3]));
+    // ---- codes, transposed through LDS to token-contiguous rows
+    const int row = tid >> 5, q = tid & 31;   // write side: channel row, 32-token piece
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        uint32_t *buf = s_codes[R > 1 ? r & 1 : 0];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const float4 f = s_rule[c4 * 8 + j];
+            CodeRule rule = make_rule(f.x, 0);
+            rule.lo = f.y;
+            rule.hi = f.z;
+            rule.z = __float_as_int(f.w);
+            buf[(c4 * 8 + j) * VR_STRIDE + t4] =
+                pack_low_bytes(code_byte(element(raw[r][0], j), rule), code_byte(element(raw[r][1], j), rule),
+                               code_byte(element(raw[r][2], j), rule), code_byte(element(raw[r][3], j), rule));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        __syncthreads();   // (a wave that is a round ahead writes the other buffer)
+        const int t = r * VR_TOKENS + q * 32;
+        if (d0 + row < D && t < G) {   // G % 32 == 0
+            v4u *dst = reinterpret_cast<v4u *>(codes + (b * D + d0 + row) * Tn + g * G + t);
+            const v4u *w = reinterpret_cast<const v4u *>(buf + row * VR_STRIDE + q * 8);
+            dst[0] = w[0];
+            dst[1] = w[1];
+        }
+    }
+}
+
 int launch_value_quant(const void *V, int v_dtype, int64_t batch, int64_t T, int64_t D, int64_t ld_t,
                        int64_t ld_b, int64_t G, uint8_t *codes, float *step, uint8_t *zero,
                        hipStream_t st)
@@ -814,6 +941,33 @@ int launch_value_quant(const void *V, int v_dtype, int64_t batch, int64_t T, int
     // 16-bit elements, every row and every store 16-byte aligned: eight channels per load
     if (v_dtype != W4A8_F32 && vec_ok && G % 128 == 0 && D % 8 == 0 && ld_t % 8 == 0 && ld_b % 8 == 0 &&
         (uintptr_t)V % 16 == 0) {
+        const int64_t parts = (D + VR_CHANNELS - 1) / VR_CHANNELS, groups = batch * (T / G);
+        const int64_t blocks = (groups + 7) / 8 * 8 * parts;
+        const int64_t rounds = (G + VR_TOKENS - 1) / VR_TOKENS;
+        // Groups that fill at least three quarters of their rounds.  Measured, the two-sweep kernel / this, us (256 heads of
+        // 128 channels): 1024 tokens 30.8 / 27.1, 2048 62.8 / 45.7, 4096 146 / 122 (64 heads 60 / 27, 8 heads 47 / 18); but 512
+        // tokens 19.2 / 23.7, 640 21.9 / 25.0 and 1152 33.4 / 36.4.
+        if (G >= VR_TOKENS && rounds <= 5 && 4 * G >= 3 * rounds * VR_TOKENS && blocks <= 0x7fffffffLL) {
+#define W4A8_VR_LAUNCH(T_, R_)                                                                                     \
+    hipLaunchKernelGGL((value_quant_resident_kernel<T_, R_>), dim3((unsigned)blocks), dim3(VR_THREADS), 0, st,     \
+                       (const T_ *)V, (uint32_t)groups, (uint32_t)parts, (uint32_t)(T / G), T, D, ld_t, ld_b, (int)G, \
+                       codes, step, zero)
+#define W4A8_VR_CASE(R_)                                     \
+    case R_:                                                 \
+        if (v_dtype == W4A8_F16) W4A8_VR_LAUNCH(__half, R_); \
+        else W4A8_VR_LAUNCH(bf16_t, R_);                     \
+        break
+            switch ((int)rounds) {
+                W4A8_VR_CASE(1);
+                W4A8_VR_CASE(2);
+                W4A8_VR_CASE(3);
+                W4A8_VR_CASE(4);
+                W4A8_VR_CASE(5);
+            }
+#undef W4A8_VR_CASE
+#undef W4A8_VR_LAUNCH
+            return hip_status(hipGetLastError());
+        }
         if (v_dtype == W4A8_F16)
             hipLaunchKernelGGL((value_quant_vec_kernel<__half>), grid, dim3(256), 0, st, (const __half *)V, T,
                                D, ld_t, ld_b, G, codes, step, zero);

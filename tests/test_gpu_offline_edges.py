@@ -120,3 +120,29 @@ def test_code_rule_edges(lib, oracle, G, K):
     rc, _, _ = oracle.quantize_weight_dint4(W * 0.25, None, G, step=step, zero=zero)
     codes, _, _ = lib.quantize_weight_dint4(dev(W * np.float32(0.25)), None, G, step=dev(step), zero=dev(zero))
     assert np.array_equal(host(codes), rc)
+
+
+# Value caches around the kernel that keeps a group in registers: the shortest and longest groups it takes and their
+# neighbours, a last round of tokens that is partly empty, channels that end inside a block, heads that do not fill the
+# eight XCDs, interleaved heads, rows off the alignment (general kernel)
+@pytest.mark.parametrize("B,T,D,G", [(1, 896, 32, 0), (3, 384, 40, 0), (9, 1024, 64, 0), (2, 1024, 128, 0), (1, 1152, 80, 0),
+                                     (5, 2048, 64, 1024), (2, 3072, 128, 1536), (1, 3072, 32, 0), (1, 4096, 128, 0), (2, 5120, 72, 0),
+                                     (1, 5248, 40, 0), (2, 1040, 64, 0)])
+@pytest.mark.parametrize("dtype,interleaved", [("f16", False), ("bf16", True), ("f16", True)])
+def test_value_quant_edges(lib, oracle, B, T, D, G, dtype, interleaved):
+    _, V = syn.attention_value(B + T + D, B, 1, T, D, v_dtype="f32")
+    V[0, :, 0] = 0.0                      # an empty range
+    V[-1, :, D - 1] = np.abs(V[-1, :, D - 1])
+    td = torch.float16 if dtype == "f16" else torch.bfloat16
+    if interleaved:                       # a [T, heads, D] cache
+        Vd = dev(V.transpose(1, 0, 2)).to(td).transpose(0, 1)
+    else:
+        Vd = dev(V).to(td)
+    codes, step, zero = lib.quantize_value_dint4(Vd, G)
+    Vh = Vd.float().cpu().numpy()
+    for b in range(B):
+        rc, rs, rz = oracle.quantize_weight_dint4(np.ascontiguousarray(Vh[b].T), None, G)
+        rows = slice(b * D, (b + 1) * D)
+        assert np.array_equal(host(step)[rows].view(np.uint32), rs.view(np.uint32))
+        assert np.array_equal(host(zero)[rows], rz)
+        assert np.array_equal(host(codes)[rows], rc)
