@@ -1407,6 +1407,17 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t G)
         const int64_t rem = t128 % 512;
         const double rounds128 = (double)(t128 / 512) + (rem == 0 ? 0.0 : rem <= 256 ? 0.6 : 1.0);
         pl.bm = rounds128 < 0.95 * rounds256 ? 128 : 256;
+        // A few tiles beyond whole rounds cost 0.6 of a round like that, a whole one with 256-row tiles.  Where the
+        // K-phase kernel takes the channels of that round in one go (at most one of its workgroups per CU), it does
+        // so in about a third of a round, from the same row-sums and without a workspace.  us, before / after:
+        // 1531 x 4096 x 11008 (4 tiles) 89.8 / 84.1, 2560 x 4096 x 6656 (8) 87.4 / 81.8, 1300 x 9216 x 12288 (16) 172 / 157,
+        // 700 x 4096 x 22016 (4) 82.4 / 78.7, 2048 x 4096 x 8448 (16) 83.0 / 79.5; 1537 x 1024 x 11008 even.
+        const int64_t gm = (M + 127) / 128, full = t128 / 512, gn_main = full * 512 / gm;
+        const int64_t rem_n = N - gn_main * GM_BN, KTs = K / TILE_K;
+        if (gn_main > 0 && rem_n > 0 && KTs >= 8 && KTs <= 72 &&
+            (M + MP_BM - 1) / MP_BM * ((rem_n + MD_BN - 1) / MD_BN) <= 256 &&
+            (double)full + 0.35 < 0.95 * std::min(rounds128, rounds256))
+            pl.pc_rem_n = (int)rem_n;
     }
     // too few output tiles for 256 CUs: split K as well (whole groups, at least 4 k-tiles each)
     const bool half = grouped && pl.bm == 128;   // 128-channel tiles, two workgroups per CU
@@ -1530,6 +1541,15 @@ int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, in
             return launch_gemv_combine(partial, sx, nullptr, ZeroPoint{nullptr, nullptr, nullptr}, M, pl.rem_n,
                                        pl.rem_splits, y2, y_dtype, ldy, st);
         }
+    } else if (pl.pc_rem_n > 0 && zp.zx == nullptr && acc_out == nullptr) {
+        const int64_t n1 = N - pl.pc_rem_n;   // whole 256-channel tiles; the rest is a problem of its own
+        GemmPlan p1 = pl;
+        p1.bm = 128;
+        rc = launch_gemm_t<128, 1, 8, false, true>(p1, Xq, sx, zp, rs, M, Wt, step, zero, n1, K, K, Y, y_dtype, ldy,
+                                                   nullptr, partial, st, plain, N);
+        if (rc != W4A8_OK) return rc;
+        return launch_gemm_mid_pc(Xq, sx, rs, M, Wt + n1 / TILE_N * (K / TILE_K) * TILE_BYTES, step + n1, zero + n1,
+                                  pl.pc_rem_n, K, (uint16_t *)Y + n1, y_dtype, ldy, nullptr, st, plain, true);
     } else {
         if (pl.bm == 128 && wgs > 256) W4A8_GM(128, 1, 8, false, true);
         else if (pl.bm == 128) W4A8_GM(128, 1, 8, false, false);

@@ -321,6 +321,9 @@ struct GemmPlan {
     int rem_n;             // output channels of the remainder launch (the last ones)
     int rem_splits;
     int rem_kt_per_split;
+    // Per-channel weights, a last round of a few 128-token tiles: the channels of that round run on the K-phase
+    // kernel behind whole rounds of two-per-CU 128-token tiles (0: no such remainder).
+    int pc_rem_n;
 };
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t G);
 int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, int64_t M,

@@ -68,3 +68,21 @@ def test_per_channel(M, K, N):
     _check(M, K, N, 0, False)
     if M < 400:
         _check(M, K, N, 0, False, hook=True)
+
+
+# per channel, a few tiles beyond a whole round of 512: the last channels (one ragged 64-channel part and more) go to the
+# K-phase kernel; with zero-points or the accumulator hook the whole layer stays on the tile kernel and gives the same outputs
+@pytest.mark.parametrize("M,K,N", [(1100, 1024, 14480), (1100, 1152, 14592), (4140, 1024, 4112)])
+def test_per_channel_remainder(M, K, N):
+    import paper_2311_05161_amd as lib
+    _check(M, K, N, 0, False, ypad=3)
+    if K == 1024 and N > 10000:
+        _check(M, K, N, 0, True)
+    rng = np.random.default_rng(5)
+    Xq = dev(rng.integers(-127, 128, (M, K), dtype=np.int8))
+    sx = dev(rng.uniform(0.01, 0.02, M).astype(np.float32))
+    codes = dev(rng.integers(0, 16, (N, K), dtype=np.uint8))
+    step, zero = torch.rand((N, 1), device="cuda") * 0.01, torch.full((N, 1), 5, dtype=torch.uint8, device="cuda")
+    Wp = lib.pack_dint4(codes)
+    Y, _ = lib.w4a8_gemm(Xq, sx, Wp, step, zero, N, K, 0, want_acc=True)
+    assert torch.equal(Y, lib.w4a8_gemm(Xq, sx, Wp, step, zero, N, K, 0))
