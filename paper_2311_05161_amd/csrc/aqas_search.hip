@@ -321,16 +321,21 @@ __global__ __launch_bounds__(SQ_THREADS) void output_sq_error_kernel(const uint1
     }
 }
 
-// sum_n err[n] in thread 0's return value: one workgroup of THREADS, fixed tree (deterministic)
-template <int THREADS>
-__device__ __forceinline__ double block_sum(const double *__restrict__ err, int64_t N, double *part)
+// sum_n err[n] in every thread's return value: 256 partial sums and one fixed tree, whatever the size of the
+// workgroup (256 or more threads, part: 256 doubles).  All losses are compared with each other, so all go
+// through this one order: equal errors give equal losses, and the first grid point wins a tie.
+constexpr int LOSS_LANES = 256;
+__device__ __forceinline__ double loss_sum(const double *__restrict__ err, int64_t N, double *part)
 {
-    double s = 0.0;
-    for (int64_t n = threadIdx.x; n < N; n += THREADS) s += err[n];
-    part[threadIdx.x] = s;
+    const int tid = (int)threadIdx.x;
+    if (tid < LOSS_LANES) {
+        double s = 0.0;
+        for (int64_t n = tid; n < N; n += LOSS_LANES) s += err[n];
+        part[tid] = s;
+    }
     __syncthreads();
-    for (int w = THREADS / 2; w >= 1; w >>= 1) {
-        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+    for (int w = LOSS_LANES / 2; w >= 1; w >>= 1) {
+        if (tid < w) part[tid] += part[tid + w];
         __syncthreads();
     }
     return part[0];
@@ -345,10 +350,10 @@ __global__ __launch_bounds__(256) void aqas_next_point_kernel(const float *__res
                                                               const double *__restrict__ err, int64_t N,
                                                               double *__restrict__ losses)
 {
-    __shared__ double part[256];
+    __shared__ double part[LOSS_LANES];
     if (blockIdx.x + 1 == gridDim.x) {
         if (j == 0) return;
-        const double sum = block_sum<256>(err, N, part);
+        const double sum = loss_sum(err, N, part);
         if (threadIdx.x == 0) losses[j - 1] = sum;
         return;
     }
@@ -363,9 +368,9 @@ __global__ __launch_bounds__(1024) void aqas_finish_kernel(const float *__restri
                                                            const double *__restrict__ err, int64_t N,
                                                            double *__restrict__ losses, int32_t *__restrict__ best)
 {
-    __shared__ double part[1024];
+    __shared__ double part[LOSS_LANES];
     __shared__ int s_best;
-    const double last = block_sum<1024>(err, N, part);
+    const double last = loss_sum(err, N, part);
     if (threadIdx.x == 0) {
         losses[AQ_GRID] = last;
         int b = 0;

@@ -50,3 +50,19 @@ def test_searches_at_edges(lib, oracle, M, K, N, G, dtype, pad):
     st, z = aq.clipped_params(W, host(s), G, np.array([aq.clip_factor(int(i)) for i in idx], np.float32))
     np.testing.assert_array_equal(host(step), st)
     np.testing.assert_array_equal(host(zero), z)
+
+
+# Every channel maximum of X and W is exactly 1, so every grid point's scale is 1 and all error vectors are the same: the
+# losses have to be the same bits, and the first grid point wins (the header's rule for ties).
+@pytest.mark.parametrize("N", [2064, 4096, 11008])
+def test_equal_scales_give_equal_losses(lib, N):
+    M, K = 16, 128
+    for seed in range(16):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        X = (torch.rand((M, K), generator=g, device="cuda") * 2 - 1).half()
+        W = (torch.rand((N, K), generator=g, device="cuda") * 2 - 1).half()
+        X[0], W[0] = 1.0, -1.0
+        s, best, losses = lib.aqas_search(X, W, 128)
+        assert (host(s) == 1.0).all()
+        assert (host(losses) == host(losses)[0]).all(), (N, seed)
+        assert int(host(best)[0]) == 0
