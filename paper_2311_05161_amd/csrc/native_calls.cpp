@@ -6,8 +6,8 @@
 // Every function takes the address of the C entry point (the library is loaded by Python) and returns
 //   a tensor or a tuple of tensors   on success,
 //   an int                           the entry point's status when it is not W4A8_OK,
-//   NotImplemented                   for operands that are not plain torch tensors of the expected kind: the
-//                                    caller's Python form decides what to do with them.
+//   NotImplemented                   for operands that are not plain torch tensors of the expected kind, and sizes
+//                                    that are not 64-bit ints: the caller's Python form decides what to do with them.
 // Nothing is cached between calls.  The GIL is released around the entry points, as ctypes does.
 #include <torch/extension.h>
 
@@ -17,10 +17,13 @@ namespace {
 
 constexpr int LAYOUT_TILED = W4A8_LAYOUT_TILED;
 
+// an int that fits 64 bits; anything else (floats, strings, array scalars) is the Python form's to convert or refuse
 bool to_i64(PyObject *o, int64_t &v)
 {
-    v = PyLong_AsLongLong(o);
-    return !(v == -1 && PyErr_Occurred());
+    if (!PyLong_Check(o)) return false;
+    int overflow = 0;
+    v = PyLong_AsLongLongAndOverflow(o, &overflow);
+    return overflow == 0;
 }
 template <typename F>
 bool to_fn(PyObject *o, F &f)
@@ -91,7 +94,8 @@ PyObject *act_quant(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (n != 4 || !plain(a[1]) || !plain_or_none(a[2])) return not_implemented();
     decltype(&quantize_act_int8) entry;
     int64_t stream;
-    if (!to_fn(a[0], entry) || !to_i64(a[3], stream)) return nullptr;
+    if (!to_fn(a[0], entry)) return nullptr;
+    if (!to_i64(a[3], stream)) return not_implemented();
     const at::Tensor &X = THPVariable_Unpack(a[1]);
     const Rows r = rows_of(X);
     if (!r.ok) return not_implemented();
@@ -117,7 +121,8 @@ PyObject *act_quant_asym(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (n != 4 || !plain(a[1]) || !plain_or_none(a[2])) return not_implemented();
     decltype(&quantize_act_int8_asym) entry;
     int64_t stream;
-    if (!to_fn(a[0], entry) || !to_i64(a[3], stream)) return nullptr;
+    if (!to_fn(a[0], entry)) return nullptr;
+    if (!to_i64(a[3], stream)) return not_implemented();
     const at::Tensor &X = THPVariable_Unpack(a[1]);
     const Rows r = rows_of(X);
     if (!r.ok) return not_implemented();
@@ -148,9 +153,10 @@ PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n)
     decltype(&w4a8_gemm) entry;
     decltype(&w4a8_gemm_workspace_bytes) need;
     int64_t N, K, G, layout, yd, stream;
-    if (!to_fn(a[0], entry) || !to_fn(a[1], need) || !to_i64(a[7], N) || !to_i64(a[8], K) || !to_i64(a[9], G) ||
+    if (!to_fn(a[0], entry) || !to_fn(a[1], need)) return nullptr;
+    if (!to_i64(a[7], N) || !to_i64(a[8], K) || !to_i64(a[9], G) ||
         !to_i64(a[10], layout) || !to_i64(a[11], yd) || !to_i64(a[12], stream))
-        return nullptr;
+        return not_implemented();
     const at::Tensor &Xq = THPVariable_Unpack(a[2]);
     if (Xq.dim() < 1 || N < 0) return not_implemented();
     const int64_t M = Xq.size(0);
@@ -181,9 +187,10 @@ PyObject *gemm_asym(PyObject *, PyObject *const *a, Py_ssize_t n)
     decltype(&w4a8_gemm_asym) entry;
     decltype(&w4a8_gemm_workspace_bytes) need;
     int64_t N, K, G, layout, yd, stream;
-    if (!to_fn(a[0], entry) || !to_fn(a[1], need) || !to_i64(a[10], N) || !to_i64(a[11], K) || !to_i64(a[12], G) ||
+    if (!to_fn(a[0], entry) || !to_fn(a[1], need)) return nullptr;
+    if (!to_i64(a[10], N) || !to_i64(a[11], K) || !to_i64(a[12], G) ||
         !to_i64(a[13], layout) || !to_i64(a[14], yd) || !to_i64(a[15], stream))
-        return nullptr;
+        return not_implemented();
     const at::Tensor &Xq = THPVariable_Unpack(a[2]);
     if (Xq.dim() < 1 || N < 0) return not_implemented();
     const int64_t M = Xq.size(0);
@@ -214,9 +221,10 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
     decltype(&w4a8_linear) entry;
     decltype(&w4a8_linear_workspace_bytes) need;
     int64_t N, G, layout, yd, stream;
-    if (!to_fn(a[0], entry) || !to_fn(a[1], need) || !to_i64(a[7], N) || !to_i64(a[8], G) ||
+    if (!to_fn(a[0], entry) || !to_fn(a[1], need)) return nullptr;
+    if (!to_i64(a[7], N) || !to_i64(a[8], G) ||
         !to_i64(a[9], layout) || !to_i64(a[10], yd) || !to_i64(a[11], stream))
-        return nullptr;
+        return not_implemented();
     const at::Tensor &X = THPVariable_Unpack(a[2]);
     const Rows r = rows_of(X);
     if (!r.ok || N < 0) return not_implemented();

@@ -1,6 +1,8 @@
 """The natively marshalled calls against the binding's Python forms: same outputs, same refusals."""
+import ctypes
 import threading
 
+import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
@@ -93,3 +95,28 @@ def test_current_stream_and_threads():
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(Y, ref) and torch.equal(Z, ref)
+
+
+# what the Python forms convert stays accepted, what they refuse stays refused, with and without a given output
+def test_sizes_that_are_not_ints():
+    M, K, N = 4, 512, 64
+    X, s, Wp, step, zero, (wsum, tsum) = _layer(M, K, N, 128)
+    Xq, sx = w.quantize_act_int8(X, s)
+    Aq, ax, az = w.quantize_act_int8_asym(X, s)
+
+    def calls(n=N, **kw):
+        for Y in (None, torch.empty((M, N), dtype=torch.float16, device="cuda")):
+            yield lambda: w.w4a8_linear(X, s, Wp, step, zero, n, Y=Y, **kw)
+            yield lambda: w.w4a8_gemm(Xq, sx, Wp, step, zero, n, K, Y=Y, **kw)
+            yield lambda: w.w4a8_gemm_asym(Aq, ax, az, Wp, step, zero, wsum, tsum, n, K, Y=Y, **kw)
+
+    ref = [f().clone() for f in calls(group_size=128)]
+    for kw in (dict(group_size=128.0), dict(group_size="128"), dict(group_size=np.int64(128)),
+               dict(group_size=128, layout=float(w.LAYOUT_TILED)), dict(group_size=128, layout=str(w.LAYOUT_TILED))):
+        for f, r in zip(calls(**kw), ref):
+            assert torch.equal(f(), r)
+    for f, r in zip(calls(n=np.int64(N), group_size=128), ref):
+        assert torch.equal(f(), r)
+    for f in calls(n=float(N), group_size=128):
+        with pytest.raises((ctypes.ArgumentError, TypeError)):
+            f()
