@@ -77,20 +77,10 @@ at::Tensor make(const at::Tensor &like, at::IntArrayRef size, at::ScalarType t)
 PyObject *not_implemented() { Py_RETURN_NOTIMPLEMENTED; }
 PyObject *status(int rc) { return PyLong_FromLong(rc); }
 
-#define NATIVE_TRY try {
-#define NATIVE_CATCH                                      \
-    }                                                     \
-    catch (const python_error &) { return nullptr; }      \
-    catch (const std::exception &e)                       \
-    {                                                     \
-        PyErr_SetString(PyExc_RuntimeError, e.what());    \
-        return nullptr;                                   \
-    }
-
 // act_quant(entry, X, s, stream) -> (Xq, sx)
 PyObject *act_quant(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    NATIVE_TRY
+    HANDLE_TH_ERRORS   // (torch's own translation: an allocation that fails stays torch.OutOfMemoryError)
     if (n != 4 || !plain(a[1]) || !plain_or_none(a[2])) return not_implemented();
     decltype(&quantize_act_int8) entry;
     int64_t stream;
@@ -111,13 +101,13 @@ PyObject *act_quant(PyObject *, PyObject *const *a, Py_ssize_t n)
     if (rc != W4A8_OK) return status(rc);
     return PyTuple_Pack(2, py::reinterpret_steal<py::object>(THPVariable_Wrap(Xq)).ptr(),
                         py::reinterpret_steal<py::object>(THPVariable_Wrap(sx)).ptr());
-    NATIVE_CATCH
+    END_HANDLE_TH_ERRORS
 }
 
 // act_quant_asym(entry, X, s, stream) -> (Xq, sx, zx)
 PyObject *act_quant_asym(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    NATIVE_TRY
+    HANDLE_TH_ERRORS
     if (n != 4 || !plain(a[1]) || !plain_or_none(a[2])) return not_implemented();
     decltype(&quantize_act_int8_asym) entry;
     int64_t stream;
@@ -140,13 +130,13 @@ PyObject *act_quant_asym(PyObject *, PyObject *const *a, Py_ssize_t n)
     return PyTuple_Pack(3, py::reinterpret_steal<py::object>(THPVariable_Wrap(Xq)).ptr(),
                         py::reinterpret_steal<py::object>(THPVariable_Wrap(sx)).ptr(),
                         py::reinterpret_steal<py::object>(THPVariable_Wrap(zx)).ptr());
-    NATIVE_CATCH
+    END_HANDLE_TH_ERRORS
 }
 
 // gemm(entry, workspace_entry, Xq, sx, Wp, step, zero, N, K, group_size, layout, y_dtype, stream) -> Y
 PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    NATIVE_TRY
+    HANDLE_TH_ERRORS
     if (n != 13) return not_implemented();
     for (int i = 2; i < 7; ++i)
         if (!plain(a[i])) return not_implemented();
@@ -173,14 +163,14 @@ PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n)
     rc = entry(q, sx, M, Wp, (int)layout, step, zero, N, K, G, y, (int)yd, N, nullptr, w, bytes, (void *)stream);
     Py_END_ALLOW_THREADS
     return rc != W4A8_OK ? status(rc) : THPVariable_Wrap(Y);
-    NATIVE_CATCH
+    END_HANDLE_TH_ERRORS
 }
 
 // gemm_asym(entry, workspace_entry, Xq, sx, zx, Wp, step, zero, wsum, tsum, N, K, group_size, layout, y_dtype,
 //           stream) -> Y
 PyObject *gemm_asym(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    NATIVE_TRY
+    HANDLE_TH_ERRORS
     if (n != 16) return not_implemented();
     for (int i = 2; i < 10; ++i)
         if (!plain(a[i])) return not_implemented();
@@ -209,13 +199,13 @@ PyObject *gemm_asym(PyObject *, PyObject *const *a, Py_ssize_t n)
                (void *)stream);
     Py_END_ALLOW_THREADS
     return rc != W4A8_OK ? status(rc) : THPVariable_Wrap(Y);
-    NATIVE_CATCH
+    END_HANDLE_TH_ERRORS
 }
 
 // linear(entry, workspace_entry, X, s, Wp, step, zero, N, group_size, layout, y_dtype, stream) -> Y
 PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
-    NATIVE_TRY
+    HANDLE_TH_ERRORS
     if (n != 12 || !plain(a[2]) || !plain_or_none(a[3]) || !plain(a[4]) || !plain(a[5]) || !plain(a[6]))
         return not_implemented();
     decltype(&w4a8_linear) entry;
@@ -250,7 +240,7 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         call(bytes > 0 ? ws.data_ptr() : nullptr, bytes);
     }
     return rc != W4A8_OK ? status(rc) : THPVariable_Wrap(Y);
-    NATIVE_CATCH
+    END_HANDLE_TH_ERRORS
 }
 
 PyMethodDef methods[] = {

@@ -120,3 +120,24 @@ def test_sizes_that_are_not_ints():
     for f in calls(n=float(N), group_size=128):
         with pytest.raises((ctypes.ArgumentError, TypeError)):
             f()
+
+
+# an output or workspace that does not fit raises what torch.empty raises (callers catch it to shrink a batch)
+def test_out_of_memory_is_torch_s_own():
+    X, s, Wp, step, zero, (wsum, tsum) = _layer(4096, 512, 64, 128)
+    Xq, sx = w.quantize_act_int8(X, s)
+    Aq, ax, az = w.quantize_act_int8_asym(X, s)
+    # 8 GiB of outputs where the allocator may hold 1 % of the card; a call that got past it would be refused
+    # for its group size before any launch
+    N, G = 1 << 20, 100
+    torch.cuda.empty_cache()
+    torch.cuda.set_per_process_memory_fraction(0.01)
+    try:
+        for f in (lambda: w.w4a8_linear(X, s, Wp, step, zero, N, G),
+                  lambda: w.w4a8_gemm(Xq, sx, Wp, step, zero, N, 512, G),
+                  lambda: w.w4a8_gemm_asym(Aq, ax, az, Wp, step, zero, wsum, tsum, N, 512, G)):
+            with pytest.raises(torch.OutOfMemoryError):
+                f()
+    finally:
+        torch.cuda.set_per_process_memory_fraction(1.0)
+    assert w.w4a8_linear(X, s, Wp, step, zero, 64, 128).shape == (4096, 64)
