@@ -41,8 +41,8 @@ EXPORTS = (
 FMT_DINT4, FMT_INT4, FMT_DINT3, FMT_DINT4_C4, FMT_DINT4_C8 = 0, 1, 2, 3, 4
 
 _lib = None
-_native = None   # the native marshalling, and the addresses of the entry points that it calls
-_addr = {}
+_native = None   # the native marshalling
+_addr = {}       # the addresses of the entry points that it calls (replaced as a whole, never filled in place)
 
 
 class W4A8Error(RuntimeError):
@@ -144,10 +144,11 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
     except ImportError as e:
         raise FileNotFoundError("the native marshalling (_native.so) is not built or does not match this torch: "
                                 "run `python -m paper_2311_05161_amd.build`") from e
-    global _native
-    for name in ("quantize_act_int8", "quantize_act_int8_asym", "w4a8_gemm", "w4a8_gemm_asym", "w4a8_linear",
-                 "w4a8_gemm_workspace_bytes", "w4a8_linear_workspace_bytes"):
-        _addr[name] = ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+    global _native, _addr
+    # (several threads may be here at once: each global is published complete)
+    _addr = {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+             for name in ("quantize_act_int8", "quantize_act_int8_asym", "w4a8_gemm", "w4a8_gemm_asym", "w4a8_linear",
+                          "w4a8_gemm_workspace_bytes", "w4a8_linear_workspace_bytes")}
     _native = native
     _lib = lib
     return lib
