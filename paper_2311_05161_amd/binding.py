@@ -6,12 +6,15 @@ fallback: if the shared library is missing, loading raises.
 
 The online calls (the layer, its two steps, and both for activations with a token zero-point) are
 marshalled in native code (``csrc/native_calls.cpp``) when they are asked for nothing but fresh outputs; the Python
-form beside it takes preallocated outputs, check outputs, workspaces and tensor subclasses.
+form beside it takes preallocated outputs, check outputs, workspaces and tensor subclasses, and every call where the
+extension is not there (it is built for one Python and one torch; ``libw4a8.so`` alone does all the work).
 """
 from __future__ import annotations
 
 import ctypes
+import importlib
 import os
+import warnings
 
 import torch
 
@@ -41,7 +44,7 @@ EXPORTS = (
 FMT_DINT4, FMT_INT4, FMT_DINT3, FMT_DINT4_C4, FMT_DINT4_C8 = 0, 1, 2, 3, 4
 
 _lib = None
-_native = None   # the native marshalling
+_native = None   # the native marshalling; False where it cannot be imported
 _addr = {}       # the addresses of the entry points that it calls (replaced as a whole, never filled in place)
 
 
@@ -139,12 +142,8 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
     lib.dint_error_terms.restype = ci
     lib.w4a8_status_string.argtypes = [ci]
     lib.w4a8_status_string.restype = ctypes.c_char_p
-    try:
-        from . import _native as native
-    except ImportError as e:
-        raise FileNotFoundError("the native marshalling (_native.so) is not built or does not match this torch: "
-                                "run `python -m paper_2311_05161_amd.build`") from e
     global _native, _addr
+    native = _import_native() if _native is None else _native
     # (several threads may be here at once: each global is published complete)
     _addr = {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
              for name in ("quantize_act_int8", "quantize_act_int8_asym", "w4a8_gemm", "w4a8_gemm_asym", "w4a8_linear",
@@ -152,6 +151,16 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
     _native = native
     _lib = lib
     return lib
+
+
+def _import_native():
+    try:
+        return importlib.import_module("._native", __package__)
+    except ImportError as e:
+        warnings.warn(f"the native marshalling is not built or does not match this Python and torch ({e}): calls are "
+                      "marshalled in Python, about 8 us of host time each; run `python -m paper_2311_05161_amd.build`",
+                      RuntimeWarning, stacklevel=3)
+        return False
 
 
 def status_string(status: int) -> str:
@@ -181,7 +190,7 @@ def _native_call(name: str, where: str, *args):
     """A native form's outputs; NotImplemented where the Python form has to take the call."""
     if _native is None:
         load_library()
-    if not torch.cuda.is_initialized():
+    if _native is False or not torch.cuda.is_initialized():
         return NotImplemented
     out = getattr(_native, name)(*args, _raw_stream())
     if type(out) is int:

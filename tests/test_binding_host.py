@@ -1,10 +1,12 @@
 """The binding's loading, on the CPU: no call here gets as far as a launch."""
+import sys
 import threading
 
 import pytest
 
 torch = pytest.importorskip("torch")
 
+import paper_2311_05161_amd as w  # noqa: E402
 from paper_2311_05161_amd import binding  # noqa: E402
 
 
@@ -51,4 +53,14 @@ def test_first_use_while_another_thread_is_loading(unloaded, monkeypatch):
         go_on.set()
         loader.join()
     assert not errors
+    _refused_call()
+
+
+def test_library_loads_without_the_native_marshalling(unloaded, monkeypatch):
+    monkeypatch.setitem(sys.modules, w.__name__ + "._native", None)   # import raises ImportError
+    monkeypatch.delattr(w, "_native", raising=False)
+    with pytest.warns(RuntimeWarning, match="marshalled in Python"):
+        lib = binding.load_library()
+    assert lib.w4a8_gemm_workspace_bytes(200, 4096, 4096, 128, binding.LAYOUT_TILED) > 0
+    assert binding.status_string(binding.ERR_SHAPE)
     _refused_call()

@@ -141,3 +141,19 @@ def test_out_of_memory_is_torch_s_own():
     finally:
         torch.cuda.set_per_process_memory_fraction(1.0)
     assert w.w4a8_linear(X, s, Wp, step, zero, 64, 128).shape == (4096, 64)
+
+
+# without the extension every call takes its Python form
+def test_calls_without_the_extension(monkeypatch):
+    X, s, Wp, step, zero, (wsum, tsum) = _layer(5, 1024, 64, 128)
+
+    def calls():
+        Xq, sx = w.quantize_act_int8(X, s)
+        Aq, ax, az = w.quantize_act_int8_asym(X, s)
+        return (Xq, sx, Aq, ax, az, w.w4a8_linear(X, s, Wp, step, zero, 64, 128),
+                w.w4a8_gemm(Xq, sx, Wp, step, zero, 64, 1024, 128),
+                w.w4a8_gemm_asym(Aq, ax, az, Wp, step, zero, wsum, tsum, 64, 1024, 128))
+
+    ref = calls()
+    monkeypatch.setattr(binding, "_native", False)
+    assert all(torch.equal(a, b) for a, b in zip(calls(), ref))
