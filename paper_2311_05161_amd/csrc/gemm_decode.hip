@@ -750,7 +750,7 @@ __global__ __launch_bounds__(256) void gemv_combine_kernel(const float *__restri
     }
 }
 
-GemvPlan plan_gemv(int64_t M, int64_t N, int64_t K, int64_t G, int64_t batch)
+GemvPlan plan_gemv(int64_t M, int64_t N, int64_t K, int64_t G, int64_t batch, bool token_blocks)
 {
     GemvPlan pl{};
     const int KT = (int)(K / TILE_K), NT = (int)(N / TILE_N);
@@ -790,7 +790,8 @@ GemvPlan plan_gemv(int64_t M, int64_t N, int64_t K, int64_t G, int64_t batch)
     // blocks' workgroups on one set of n-tiles share an XCD (workgroups go round-robin over eight), and its L2
     // serves all but the first of them.  Only where no workgroup gets more n-tiles for it.  us, before / after:
     // 33 x 5120 x 13824 26.4 / 21.8, 48 x 4096 x 11008 15.6 / 12.8, 33 x 5120 x 5120 12.9 / 11.1, 33 x 4096 x 4096 10.0 / 9.2.
-    if (batch > 1) {
+    // (Problems with weights of their own share nothing and only lose workgroups: 7 x 1 x 4096 x 4096 13.8 rounded, 13.4 not.)
+    if (token_blocks && batch > 1) {
         int b8 = bps;
         while (b8 > 1 && b8 * pl.splits % 8 != 0) --b8;
         if (b8 * pl.splits % 8 == 0 && (NT + b8 - 1) / b8 == q) bps = b8;
@@ -875,7 +876,7 @@ int gemv_token_blocks(int64_t M, int64_t N, int64_t K, int64_t G)
     const int nb = (int)((M + 15) / 16);
     // the decode records cap the n-tiles per workgroup: not more than two generations of workgroups
     // (one for more than four blocks)
-    const GemvPlan pl = plan_gemv(16, N, K, G, nb);
+    const GemvPlan pl = plan_gemv(16, N, K, G, nb, true);
     if ((int64_t)pl.blocks_per_split * pl.splits * nb > (nb > 4 ? 256 : 512)) return 0;
     return nb;
 }
@@ -900,7 +901,7 @@ int launch_gemv(const int8_t *Xq, const float *sx, ZeroPoint zp, int64_t M, cons
     const int token_blocks = M > 16 ? gemv_token_blocks(M, N, K, G) : 0;
     if (M > 16 && (token_blocks == 0 || batch != 1)) return W4A8_ERR_SHAPE;
     if (token_blocks) batch = token_blocks;
-    const GemvPlan pl = plan_gemv(token_blocks ? 16 : M, N, K, G, batch);
+    const GemvPlan pl = plan_gemv(token_blocks ? 16 : M, N, K, G, batch, token_blocks > 0);
     if (batch > 1 && !token_blocks && (pl.splits > 1 || acc_out != nullptr)) return W4A8_ERR_SHAPE;
     const bool grouped = G != K;
     float *part = pl.splits > 1 ? partial : nullptr;

@@ -274,7 +274,8 @@ struct GemvPlan {
     int lds_bytes;
     size_t partial_bytes;  // fp32 partial sums [splits][M][N] when splits > 1, else 0
 };
-GemvPlan plan_gemv(int64_t M, int64_t N, int64_t K, int64_t G, int64_t batch = 1);
+// batch: problems in the launch; token_blocks: they are 16-token blocks of one problem, on the same weights
+GemvPlan plan_gemv(int64_t M, int64_t N, int64_t K, int64_t G, int64_t batch = 1, bool token_blocks = false);
 // Asymmetric activations: zx = token zero-points, wsum = weight sums per group [N, K/G],
 // tsum = weight sums per 128 columns [N, K/128]; all three null for the symmetric form.
 struct ZeroPoint {
