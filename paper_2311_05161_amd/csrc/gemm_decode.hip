@@ -683,8 +683,10 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(const GemvArgs args)
 // the partials are the int32 accumulators (times 4) of a per-channel launch; their exact sum,
 // minus the zero-point term when zx is given, is scaled by int_step[n] / 8.
 // Bound by the read of the partial sums (the ranges' rows of a layer: tens of megabytes, just written).  A
-// thread takes four channels (16-byte loads, four ranges in flight) of the tokens blockIdx.y, + gridDim.y, ...; one output per
-// thread with 4-byte loads and a 64-bit division took 9.6 us on 4 x 512 x 4096 and on 3 x 607 x 4096, this 7.3 us.
+// thread takes CH = 4 channels (16-byte loads, four ranges in flight) of the tokens blockIdx.y, + gridDim.y, ...; one output per
+// thread with 4-byte loads and a 64-bit division took 9.6 us on 4 x 512 x 4096 and on 3 x 607 x 4096, this 6.8 and 5.9 us.
+// CH = 1: the few outputs of a decode step, where the launch is as long as one thread's chain of operations.
+template <int CH>
 __global__ __launch_bounds__(256) void gemv_combine_kernel(const float *__restrict__ partial,
                                                            const float *__restrict__ sx,
                                                            const float *__restrict__ int_step,
@@ -693,59 +695,62 @@ __global__ __launch_bounds__(256) void gemv_combine_kernel(const float *__restri
                                                            int N, int splits, uint16_t *__restrict__ Y,
                                                            int y_dtype, int64_t ldy, int vec_store)
 {
-    const int n = (int)(blockIdx.x * blockDim.x + threadIdx.x) * 4;   // N % 16 == 0
+    struct __attribute__((aligned(4 * CH))) Sums { float v[CH]; };   // CH partial sums, one load
+    const int n = (int)(blockIdx.x * blockDim.x + threadIdx.x) * CH;   // N % 16 == 0
     if (n >= N) return;
     const int64_t slab = (int64_t)M * N;
     for (int m = blockIdx.y; m < M; m += gridDim.y) {
         const float *p = partial + (int64_t)m * N + n;
-        float v[4];
+        float v[CH];
         if (int_step != nullptr) {
-            int sum[4] = {0, 0, 0, 0};
+            int sum[CH] = {};
             for (int s0 = 0; s0 < splits; s0 += 4) {
-                int4 q[4];
+                Sums q[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) q[i] = *reinterpret_cast<const int4 *>(p + min(s0 + i, splits - 1) * slab);
+                for (int i = 0; i < 4; ++i) q[i] = *reinterpret_cast<const Sums *>(p + min(s0 + i, splits - 1) * slab);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     if (s0 + i >= splits) break;
-                    sum[0] += q[i].x; sum[1] += q[i].y; sum[2] += q[i].z; sum[3] += q[i].w;
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) sum[c] += __float_as_int(q[i].v[c]);
                 }
             }
             const int z = zx != nullptr ? 4 * zx[m] : 0;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {
+            for (int c = 0; c < CH; ++c) {
                 if (zx != nullptr) sum[c] -= z * wsum[n + c];
                 v[c] = (int_step[n + c] * 0.125f) * (float)sum[c];
             }
         } else {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) v[c] = 0.f;
+            for (int c = 0; c < CH; ++c) v[c] = 0.f;
             for (int s0 = 0; s0 < splits; s0 += 4) {
-                float4 q[4];
+                Sums q[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) q[i] = *reinterpret_cast<const float4 *>(p + min(s0 + i, splits - 1) * slab);
+                for (int i = 0; i < 4; ++i) q[i] = *reinterpret_cast<const Sums *>(p + min(s0 + i, splits - 1) * slab);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     if (s0 + i >= splits) break;
-                    v[0] += q[i].x; v[1] += q[i].y; v[2] += q[i].z; v[3] += q[i].w;
+#pragma unroll
+                    for (int c = 0; c < CH; ++c) v[c] += q[i].v[c];
                 }
             }
         }
         const float sxm = sx[m];
-        uint16_t h[4];
+        uint16_t h[CH];
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
+        for (int c = 0; c < CH; ++c) {
             float out = sxm * v[c];   // binary32 product, then the cast (see gemv_kernel)
             asm volatile("" : "+v"(out));
             h[c] = (y_dtype == W4A8_F16) ? f32_to_f16_bits(out) : f32_to_bf16_bits(out);
         }
         uint16_t *y = Y + (int64_t)m * ldy + n;
-        if (vec_store) {
-            *reinterpret_cast<uint2 *>(y) =
-                uint2{(uint32_t)h[0] | ((uint32_t)h[1] << 16), (uint32_t)h[2] | ((uint32_t)h[3] << 16)};
+        if (CH == 4 && vec_store) {
+            *reinterpret_cast<uint2 *>(y) = uint2{(uint32_t)h[0] | ((uint32_t)h[1 % CH] << 16),
+                                                  (uint32_t)h[2 % CH] | ((uint32_t)h[3 % CH] << 16)};
         } else {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) y[c] = h[c];
+            for (int c = 0; c < CH; ++c) y[c] = h[c];
         }
     }
 }
@@ -962,11 +967,15 @@ int launch_gemv_combine(const float *partial, const float *sx, const float *int_
 {
     const int vec_store = (uintptr_t)Y % 8 == 0 && ldy % 4 == 0;
     const unsigned rows = (unsigned)(M < 65535 ? M : 65535);
-    // (decode: one wave per block, so that 16 x 5120 outputs are 320 blocks and not 80)
-    const int threads = M * N <= (1 << 18) ? 64 : 256;
-    hipLaunchKernelGGL(gemv_combine_kernel, dim3((unsigned)((N / 4 + threads - 1) / threads), rows), dim3(threads), 0, st,
-                       partial, sx, int_step, int_step ? zp.zx : nullptr, zp.wsum, (int)M, (int)N,
-                       splits, (uint16_t *)Y, y_dtype, ldy, vec_store);
+    // One output per thread up to 2^18 of them.  The whole product with four / one, us: 1 x 4096 x 11008 9.70 / 9.37,
+    // 16 x 4096 x 11008 11.19 / 10.97, 33 x 4096 x 11008 16.5 / 16.0, 64 x 4096 x 11008 18.75 / 18.06 (all per channel).
+#define W4A8_COMBINE(CH_)                                                                                            \
+    hipLaunchKernelGGL(gemv_combine_kernel<CH_>, dim3((unsigned)((N / CH_ + 255) / 256), rows), dim3(256), 0, st, partial, \
+                       sx, int_step, int_step ? zp.zx : nullptr, zp.wsum, (int)M, (int)N, splits, (uint16_t *)Y, \
+                       y_dtype, ldy, vec_store)
+    if (M * N <= (1 << 18)) W4A8_COMBINE(1);
+    else W4A8_COMBINE(4);
+#undef W4A8_COMBINE
     return hip_status(hipGetLastError());
 }
 
