@@ -683,9 +683,12 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(const GemvArgs args)
 // the partials are the int32 accumulators (times 4) of a per-channel launch; their exact sum,
 // minus the zero-point term when zx is given, is scaled by int_step[n] / 8.
 // Bound by the read of the partial sums (the ranges' rows of a layer: tens of megabytes, just written).  A
-// thread takes CH = 4 channels (16-byte loads, four ranges in flight) of the tokens blockIdx.y, + gridDim.y, ...; one output per
+// thread takes CH = 4 channels (16-byte loads, four ranges in flight); one output per
 // thread with 4-byte loads and a 64-bit division took 9.6 us on 4 x 512 x 4096 and on 3 x 607 x 4096, this 6.8 and 5.9 us.
 // CH = 1: the few outputs of a decode step, where the launch is as long as one thread's chain of operations.
+// A block takes 256 channels (of CH tokens at a time) and the blocks of a token follow each other: where N / 256 is a multiple of
+// eight, a channel's sums are read by the XCD that wrote them in its L2.  1024 channels per block (256 threads) lost that at
+// N = 2048: 192 x 5120 x 2048 in groups of 256 17.2 -> 23.7 us, with 256 per block 17.5.
 template <int CH>
 __global__ __launch_bounds__(256) void gemv_combine_kernel(const float *__restrict__ partial,
                                                            const float *__restrict__ sx,
@@ -699,7 +702,7 @@ __global__ __launch_bounds__(256) void gemv_combine_kernel(const float *__restri
     const int n = (int)(blockIdx.x * blockDim.x + threadIdx.x) * CH;   // N % 16 == 0
     if (n >= N) return;
     const int64_t slab = (int64_t)M * N;
-    for (int m = blockIdx.y; m < M; m += gridDim.y) {
+    for (int m = blockIdx.y * blockDim.y + threadIdx.y; m < M; m += gridDim.y * blockDim.y) {
         const float *p = partial + (int64_t)m * N + n;
         float v[CH];
         if (int_step != nullptr) {
@@ -966,15 +969,17 @@ int launch_gemv_combine(const float *partial, const float *sx, const float *int_
                         hipStream_t st)
 {
     const int vec_store = (uintptr_t)Y % 8 == 0 && ldy % 4 == 0;
-    const unsigned rows = (unsigned)(M < 65535 ? M : 65535);
     // One output per thread up to 2^18 of them.  The whole product with four / one, us: 1 x 4096 x 11008 9.70 / 9.37,
     // 16 x 4096 x 11008 11.19 / 10.97, 33 x 4096 x 11008 16.5 / 16.0, 64 x 4096 x 11008 18.75 / 18.06 (all per channel).
-#define W4A8_COMBINE(CH_)                                                                                            \
-    hipLaunchKernelGGL(gemv_combine_kernel<CH_>, dim3((unsigned)((N / CH_ + 255) / 256), rows), dim3(256), 0, st, partial, \
-                       sx, int_step, int_step ? zp.zx : nullptr, zp.wsum, (int)M, (int)N, splits, (uint16_t *)Y, \
-                       y_dtype, ldy, vec_store)
-    if (M * N <= (1 << 18)) W4A8_COMBINE(1);
-    else W4A8_COMBINE(4);
+#define W4A8_COMBINE(CH_, ROWS_)                                                                                    \
+    do {                                                                                                            \
+        const int64_t gy = (M + ROWS_ - 1) / ROWS_;                                                                 \
+        hipLaunchKernelGGL(gemv_combine_kernel<CH_>, dim3((unsigned)((N + 255) / 256), (unsigned)(gy < 65535 ? gy : 65535)), \
+                           dim3(256 / CH_, ROWS_), 0, st, partial, sx, int_step, int_step ? zp.zx : nullptr, zp.wsum, \
+                           (int)M, (int)N, splits, (uint16_t *)Y, y_dtype, ldy, vec_store);                         \
+    } while (0)
+    if (M * N <= (1 << 18)) W4A8_COMBINE(1, 1);
+    else W4A8_COMBINE(4, 4);
 #undef W4A8_COMBINE
     return hip_status(hipGetLastError());
 }
