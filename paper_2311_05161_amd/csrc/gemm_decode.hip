@@ -969,8 +969,11 @@ int launch_gemv_combine(const float *partial, const float *sx, const float *int_
                         hipStream_t st)
 {
     const int vec_store = (uintptr_t)Y % 8 == 0 && ldy % 4 == 0;
-    // One output per thread up to 2^18 of them.  The whole product with four / one, us: 1 x 4096 x 11008 9.70 / 9.37,
-    // 16 x 4096 x 11008 11.19 / 10.97, 33 x 4096 x 11008 16.5 / 16.0, 64 x 4096 x 11008 18.75 / 18.06 (all per channel).
+    // One output per thread while that makes at most 1024 blocks, and with more than four ranges (rounds of loads that wait for
+    // each other) at most 2048, eight on every CU.  The whole product with four / one, us: 1 x 4096 x 11008 9.70 / 9.37, 16 x 4096 x 11008 11.19 / 10.97,
+    // 33 x 4096 x 11008 16.5 / 16.0, 64 x 4096 x 11008 18.75 / 18.06 (per channel); in groups 515 x 11008 x 512 27.7 / 27.0,
+    // 160 x 8192 x 1792 26.1 / 25.4, 384 x 10752 x 1024 28.4 / 27.8; but 1290 x 13568 x 352
+    // (2580 blocks) 30.7 / 33.2, 130 x 10752 x 4096 29.8 / 31.4, 700 x 2048 x 1024 17.0 / 18.1.
 #define W4A8_COMBINE(CH_, ROWS_)                                                                                    \
     do {                                                                                                            \
         const int64_t gy = (M + ROWS_ - 1) / ROWS_;                                                                 \
@@ -978,7 +981,7 @@ int launch_gemv_combine(const float *partial, const float *sx, const float *int_
                            dim3(256 / CH_, ROWS_), 0, st, partial, sx, int_step, int_step ? zp.zx : nullptr, zp.wsum, \
                            (int)M, (int)N, splits, (uint16_t *)Y, y_dtype, ldy, vec_store);                         \
     } while (0)
-    if (M * N <= (1 << 18)) W4A8_COMBINE(1, 1);
+    if (M * ((N + 255) / 256) <= (splits > 4 ? 2048 : 1024)) W4A8_COMBINE(1, 1);
     else W4A8_COMBINE(4, 4);
 #undef W4A8_COMBINE
     return hip_status(hipGetLastError());
