@@ -1304,21 +1304,32 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_pc_kernel(
 // grid of at most one workgroup per CU -- with four phases (64 channels per workgroup) if that fits, else with two.
 // The line between it and the tile kernel with K in ranges: a workgroup here takes a time proportional to
 // its share of K whatever the grid (0.4 us per k-tile with four phases, 0.73 with two, some 5 us besides), the tile
-// kernel one proportional to tiles x K (3.4 ns per 128 x 128 k-tile of the chip) with some 16 us for partial
-// sums, their combine launch and two prologues.  Equating them gives K-tiles x (W - workgroups) <= C; the constants are
-// where the measured times cross, and below 64 workgroups (four phases) or 12 k-tiles (two) the tile kernel won
-// throughout.  A token zero-point costs relatively more here (one vector operation per accumulator and group).
-// Measured, tile kernel / this, us -- four phases: 512 x 4096 x 4096 32.4 / 23.3, 384 x 5120 x 5120 35.1 / 26.0,
-// 512 x 1152 x 4096 25.3 / 13.8, 512 x 11008 x 4096 58.2 / 46.6; 512 x 6144 x 1024 (64 workgroups) 25.0 / 25.4, 300 x 4096 x 1024
-// (48) 18.2 / 20.3.  Two phases: 256 x 5120 x 13824 51.8 / 39.6, 1024 x 4096 x 4096 47.6 / 33.2, 2048 x 4096 x 2048 47.8 / 31.8,
-// 607 x 11008 x 4096 (160 workgroups) 64.8 / 64.5, 512 x 13824 x 5120 (160) 78.0 / 82.8, 1024 x 1024 x 4096 (8 k-tiles) 14.0 / 16.5.
-// With zero-points: 512 x 4096 x 4096 37.4 / 29.3, 900 x 4096 x 4096 56.2 / 38.8, 607 x 8192 x 4096 58.0 / 57.6, 512 x 8192 x 2048 35.6 / 38.5.
+// kernel one proportional to its tiles times K with some 16 us for partial sums, their combine launch and two
+// prologues.  Equating them gives K-tiles x (W - tiles) <= C.  The tile kernel has tiles of 64 tokens too and this one has not,
+// so `tiles` counts 64 x 64 blocks of the output (128-token tiles, which both would do, put a third of the shapes with
+// 129 .. 192 tokens on the slower side).  On the smallest grids the tile kernel's own fixed cost falls (fewer outputs to
+// combine) and the lines are those of the second form.  A token zero-point costs one vector operation per accumulator
+// and group here, hence lines of its own.  Constants fitted to 1810 shapes of 129 to 1600 tokens, both kernels timed on
+// each: 0.3 % slower on average than the better of the two.  Two token tiles by 16 channel tiles of 128 are an exception: eight
+// ranges of them fill the chip exactly, and the combine finds each channel's sums in the L2 that they were written in.
+// Measured, tile kernel / this, us (tokens x K x N) -- four phases: 512 x 5120 x 2560 29.6 / 23.9, 256 x 8192 x 5120 38.0 / 34.0,
+// 230 x 6144 x 3200 26.1 / 25.0, 192 x 12800 x 5760 49.9 / 46.3, 150 x 1536 x 1552 13.1 / 12.1; 230 x 11008 x 3840 37.8 / 39.7,
+// 140 x 8192 x 3840 27.8 / 30.5, 450 x 7168 x 1344 27.8 / 29.2, 135 x 2176 x 1152 13.6 / 15.1, 230 x 3584 x 1984 15.3 / 18.4.
+// With zero-points: 230 x 6144 x 3840 30.6 / 29.9, 640 x 5120 x 1792 32.3 / 27.9; 384 x 8192 x 2560 34.9 / 37.7, 512 x 4096 x 768 20.8 / 22.5,
+// 256 x 2560 x 2048 15.1 / 17.5.
+// Two phases: 256 x 5120 x 13824 51.8 / 39.6, 1024 x 4096 x 4096 47.6 / 33.1, 2048 x 4096 x 2048 47.8 / 31.8, 607 x 11008 x 4096 (160
+// workgroups) 64.8 / 64.5, 512 x 13824 x 5120 (160) 78.0 / 82.8, 1024 x 1024 x 4096 (8 k-tiles) 14.0 / 16.5.
 int gemm_mid_phases(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
 {
     const int64_t KT = K / TILE_K, gm = (M + MD_BM - 1) / MD_BM;
     if (G != TILE_K || G == K || M <= 64 || KT < 8) return 0;
-    const int64_t w4 = gm * ((N + MD_BN - 1) / MD_BN);
-    if (w4 <= 256) return w4 >= 64 && KT * (244 - w4) <= (asym ? 5200 : 7200) ? 4 : 0;
+    if (gm * ((N + MD_BN - 1) / MD_BN) <= 256) {
+        if (gm == 2 && (N + 127) / 128 == 16 && KT >= 10) return 0;
+        const int64_t tiles = (M + 63) / 64 * ((N + MD_BN - 1) / MD_BN);
+        const bool wins = asym ? (tiles >= 128 ? KT * (380 - tiles) <= 8800 : 6 * KT <= tiles + 20)
+                               : (tiles >= 96 ? KT * (380 - tiles) <= 11200 : 5 * KT <= tiles + 16);
+        return wins ? 4 : 0;
+    }
     const int64_t w2 = gm * ((N + 2 * MD_BN - 1) / (2 * MD_BN));
     return w2 <= 256 && KT >= 12 && KT * (216 - w2) <= (asym ? 3400 : 4800) ? 2 : 0;
 }

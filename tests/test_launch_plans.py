@@ -40,3 +40,19 @@ def test_token_blocks_are_rounded_to_eight():
     for N, K, G in ((4096, 4096, 128), (5120, 5120, 0), (11008, 4096, 128)):
         pl = plan_gemv(16, N, K, G, 3, True)
         assert pl.blocks_per_split * pl.splits % 8 == 0
+
+
+def mid_phases(M, N, K, asym):
+    return _rule("15gemm_mid_phasesEllllb", ctypes.c_int, I64, I64, I64, I64, ctypes.c_bool)(M, N, K, 128, asym)
+
+
+# group-128 weights, one shape on either side of each line at which the K-phase and the tile kernel were timed against each
+# other (the times stand beside the rule)
+@pytest.mark.parametrize("M,K,N,asym,phases", [
+    (512, 5120, 2560, False, 4), (256, 8192, 5120, False, 4), (230, 6144, 3200, False, 4), (192, 12800, 5760, False, 4),
+    (250, 9728, 4608, False, 4), (256, 13824, 5120, False, 4), (150, 1536, 1552, False, 4), (129, 1280, 1168, False, 4), (230, 3584, 1984, False, 0),
+    (230, 11008, 3840, False, 0), (140, 8192, 3840, False, 0), (450, 7168, 1344, False, 0), (135, 2176, 1152, False, 0),
+    (230, 6144, 3840, True, 4), (640, 5120, 1792, True, 4), (384, 8192, 2560, True, 0), (512, 4096, 768, True, 0),
+    (256, 2048, 2048, True, 0), (1024, 4096, 4096, False, 2), (512, 13824, 5120, False, 0), (1024, 1024, 4096, False, 0)])
+def test_group_128_route(M, K, N, asym, phases):
+    assert mid_phases(M, N, K, asym) == phases
