@@ -1422,10 +1422,12 @@ GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t G)
         // K-phase kernel takes the channels of that round in one go (at most one of its workgroups per CU), it does
         // so in about a third of a round, from the same row-sums and without a workspace.  us, before / after:
         // 1531 x 4096 x 11008 (4 tiles) 89.8 / 84.1, 2560 x 4096 x 6656 (8) 87.4 / 81.8, 1300 x 9216 x 12288 (16) 172 / 157,
-        // 700 x 4096 x 22016 (4) 82.4 / 78.7, 2048 x 4096 x 8448 (16) 83.0 / 79.5; 1537 x 1024 x 11008 even.
+        // 700 x 4096 x 22016 (4) 82.4 / 78.7, 2048 x 4096 x 8448 (16) 83.0 / 79.5.  From K = 3072: the second launch costs 4 us
+        // whatever K is, and a round is short against that below (75 shapes: K = 3072 gains 2 %, 2560 is even, 2048 loses up to 9 %
+        // (1934 x 2048 x 8672 50.6 / 55.2), 1024 up to 17 % (1100 x 1024 x 14480 31.4 / 36.6)).
         const int64_t gm = (M + 127) / 128, full = t128 / 512, gn_main = full * 512 / gm;
         const int64_t rem_n = N - gn_main * GM_BN, KTs = K / TILE_K;
-        if (gn_main > 0 && rem_n > 0 && KTs >= 8 && KTs <= 72 &&
+        if (gn_main > 0 && rem_n > 0 && KTs >= 24 && KTs <= 72 &&
             (M + MP_BM - 1) / MP_BM * ((rem_n + MD_BN - 1) / MD_BN) <= 256 &&
             (double)full + 0.35 < 0.95 * std::min(rounds128, rounds256))
             pl.pc_rem_n = (int)rem_n;

@@ -36,10 +36,12 @@ def test_act_quant_row_edges(lib, oracle, M, K, dtype):
         assert np.array_equal(host(ax).view(np.uint32), r.view(np.uint32)) and np.array_equal(host(az) + 128, z)
 
 
-# per-channel layers that read row-sums: the K-phase kernel, both tile kernels, K in ranges (which makes its own) and rows
-# that the vector quantizer does not take (pre-pass)
+# per-channel layers that read row-sums: the K-phase kernel, both tile kernels, a tile kernel with its last channels on the
+# K-phase kernel (both read the same sums), K in ranges (which makes its own) and rows that the vector quantizer does not take
+# (pre-pass)
 @pytest.mark.parametrize("M,K,N,pad", [(130, 2048, 272, 0), (300, 2560, 528, 0), (700, 1024, 4112, 8), (270, 5248, 16, 0),
-                                       (2100, 256, 8208, 0), (140, 2048, 256, 3)])
+                                       (2100, 256, 8208, 0), (140, 2048, 256, 3), (1100, 3072, 14480, 0),
+                                       (3495, 3072, 4656, 8)])
 def test_row_sums_from_the_quantizer(lib, oracle, M, K, N, pad):
     X, W, s = syn.random_layer(M + N, M, K, N)
     buf = torch.zeros((M, K + pad), dtype=torch.float16, device="cuda")

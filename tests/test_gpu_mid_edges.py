@@ -70,13 +70,15 @@ def test_per_channel(M, K, N):
         _check(M, K, N, 0, False, hook=True)
 
 
-# per channel, a few tiles beyond a whole round of 512: the last channels (one ragged 64-channel part and more) go to the
-# K-phase kernel; with zero-points or the accumulator hook the whole layer stays on the tile kernel and gives the same outputs
-@pytest.mark.parametrize("M,K,N", [(1100, 1024, 14480), (1100, 1152, 14592), (4140, 1024, 4112)])
+# per channel, a few tiles beyond a whole round of 512: from K = 3072 the last channels (one ragged 64-channel part and more,
+# few and many token tiles) go to the K-phase kernel; with zero-points or the accumulator hook the whole layer stays on the tile
+# kernel and gives the same outputs.  (4140, 3072, 4112) has too many such channels, the short K stay whole.
+@pytest.mark.parametrize("M,K,N", [(1100, 3072, 14480), (1100, 3200, 14592), (3495, 3072, 4656), (4140, 3072, 4112),
+                                   (1100, 1024, 14480), (1100, 1152, 14592), (4140, 1024, 4112)])
 def test_per_channel_remainder(M, K, N):
     import paper_2311_05161_amd as lib
     _check(M, K, N, 0, False, ypad=3)
-    if K == 1024 and N > 10000:
+    if K in (1024, 3072) and N > 10000:
         _check(M, K, N, 0, True)
     rng = np.random.default_rng(5)
     Xq = dev(rng.integers(-127, 128, (M, K), dtype=np.int8))

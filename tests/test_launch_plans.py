@@ -13,6 +13,12 @@ class GemvPlan(ctypes.Structure):   # csrc/w4a8_common.hpp
                                             "lds_bytes")] + [("partial_bytes", ctypes.c_size_t)]
 
 
+class GemmPlan(ctypes.Structure):
+    _fields_ = [(n, ctypes.c_int) for n in ("bm", "splits", "kt_per_split")] + [
+        (n, ctypes.c_size_t) for n in ("rs_bytes", "partial_bytes")] + [
+        (n, ctypes.c_int) for n in ("rem_n", "rem_splits", "rem_kt_per_split", "pc_rem_n")]
+
+
 def _rule(symbol, restype, *argtypes):
     f = w.load_library()["_ZN4w4a8" + symbol]
     f.restype, f.argtypes = restype, argtypes
@@ -56,3 +62,13 @@ def mid_phases(M, N, K, asym):
     (256, 2048, 2048, True, 0), (1024, 4096, 4096, False, 2), (512, 13824, 5120, False, 0), (1024, 1024, 4096, False, 0)])
 def test_group_128_route(M, K, N, asym, phases):
     assert mid_phases(M, N, K, asym) == phases
+
+
+# per-channel layers a few tiles beyond whole rounds: the channels that go to the K-phase kernel, none below K = 3072
+@pytest.mark.parametrize("M,K,N,rem_n", [
+    (1531, 4096, 11008, 256), (1100, 3072, 14480, 144), (1100, 3200, 14592, 256), (3495, 3072, 4656, 48), (700, 9216, 22016, 256),
+    (1100, 1024, 14480, 0), (1934, 2048, 8672, 0), (2394, 2560, 6832, 0), (1100, 9344, 14480, 0), (4140, 3072, 4112, 0),
+    (2048, 4096, 8192, 0)])
+def test_per_channel_remainder(M, K, N, rem_n):
+    pl = _rule("9plan_gemmEllll", GemmPlan, I64, I64, I64, I64)(M, N, K, K)
+    assert pl.pc_rem_n == rem_n and pl.splits == 1
