@@ -250,12 +250,14 @@ __device__ __forceinline__ void min_max8(const float (&x)[8], float &lo, float &
 }
 
 // Groups of 128 or 256 columns: a wave takes 512 consecutive columns (8 per lane, one 16-byte load) of
-// SG_ROWS rows, i.e. 4 or 2 whole groups of each row, each reduced over its own LANES = G / 8 lanes; the
+// ROWS rows, i.e. 4 or 2 whole groups of each row, each reduced over its own LANES = G / 8 lanes; the
 // elements stay in registers between the range and the codes, so W is read once.
 // Bound by the vector ALU and memory about equally; the rows share the lane's eight AQAS scales (twice the
 // bytes of fp16 weights) and the two IEEE divisions of a group (some 25 operations): lane l computes the
 // parameters of row l % 4 for its group and the four lanes of a quad exchange them.
 // 13824 x 5120, G = 128: 68 -> 47 us (4.5 TB/s).
+// ROWS = 1: small matrices, for which four rows per wave leave most CUs idle (one / four rows, us: 768 x 768 3.5 / 4.3,
+// 1024 x 1024 3.6 / 4.3, 512 x 4096 4.5 / 4.5, 1024 x 4096 6.2 / 5.8).
 constexpr int SG_ROWS = 4;
 
 template <int ROW>
@@ -263,31 +265,32 @@ __device__ __forceinline__ float quad_lane_f32(float v) { return dpp_f32<ROW * 0
 template <int ROW>
 __device__ __forceinline__ int quad_lane_i32(int v) { return dpp_i32<ROW * 0x55>(v); }
 
-template <typename T, int LANES>
+template <typename T, int LANES, int ROWS>
 __global__ __launch_bounds__(WQ_THREADS) void weight_quant_small_groups_kernel(
     const T *__restrict__ W, int64_t N, int64_t K, int64_t ldw, const float *__restrict__ s,
     int use_given, uint8_t *__restrict__ codes, float *__restrict__ step, uint8_t *__restrict__ zero,
     CodeFormat fmt, int s_vec, Clipping clip)
 {
+    static_assert(ROWS == 1 || ROWS == 4, "the lanes of a quad share the work on four rows");
     constexpr int G = LANES * 8;
     const int lane = threadIdx.x & 63;
     const int64_t chunks = (K + 511) / 512;
-    const int64_t seg = (int64_t)blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);   // (four rows, chunk)
-    if (seg >= (N + SG_ROWS - 1) / SG_ROWS * chunks) return;
-    const int64_t n0 = seg / chunks * SG_ROWS, c = seg - n0 / SG_ROWS * chunks;
+    const int64_t seg = (int64_t)blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);   // (ROWS rows, chunk)
+    if (seg >= (N + ROWS - 1) / ROWS * chunks) return;
+    const int64_t n0 = seg / chunks * ROWS, c = seg - n0 / ROWS * chunks;
     const int64_t k = c * 512 + lane * 8;
     if (k >= K) return;   // whole groups of LANES lanes leave together (K % G == 0)
-    Raw8<T> raw[SG_ROWS];
+    Raw8<T> raw[ROWS];
 #pragma unroll
-    for (int r = 0; r < SG_ROWS; ++r) raw[r].load(W + min(n0 + r, N - 1) * ldw + k);   // (rows past the end: not stored)
+    for (int r = 0; r < ROWS; ++r) raw[r].load(W + min(n0 + r, N - 1) * ldw + k);   // (rows past the end: not stored)
     float sv[8];
     load_scales<8>(s, k, s_vec, sv);
     const int64_t ng = K / G, g = k / G;
-    const int mine = lane & 3;   // the row whose parameters this lane computes
-    float x[SG_ROWS][8];
+    const int mine = ROWS == 4 ? lane & 3 : 0;   // the row whose parameters this lane computes
+    float x[ROWS][8];
     float lo_m = 0.0f, hi_m = 0.0f;
 #pragma unroll
-    for (int r = 0; r < SG_ROWS; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
         T e[8];
         raw[r].elements(e);
         scaled8(e, sv, s != nullptr, x[r]);
@@ -320,17 +323,18 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_small_groups_kernel(
     } else {
         const float rho = clip_factor(clip, min(n0 + mine, N - 1));
         range_params(lo_m * rho, hi_m * rho, st, istep, z, fmt);
-        if ((lane & (LANES - 1)) < 4 && n0 + mine < N) {
+        if ((lane & (LANES - 1)) < ROWS && n0 + mine < N) {
             step[pidx] = st;
             zero[pidx] = (uint8_t)z;
         }
     }
     if (codes == nullptr) return;
-    const float is[SG_ROWS] = {quad_lane_f32<0>(istep), quad_lane_f32<1>(istep), quad_lane_f32<2>(istep),
-                               quad_lane_f32<3>(istep)};
-    const int zs[SG_ROWS] = {quad_lane_i32<0>(z), quad_lane_i32<1>(z), quad_lane_i32<2>(z), quad_lane_i32<3>(z)};
+    // (one row: every lane has its parameters)
+    const float is[4] = {ROWS == 4 ? quad_lane_f32<0>(istep) : istep, quad_lane_f32<1>(istep), quad_lane_f32<2>(istep),
+                         quad_lane_f32<3>(istep)};
+    const int zs[4] = {ROWS == 4 ? quad_lane_i32<0>(z) : z, quad_lane_i32<1>(z), quad_lane_i32<2>(z), quad_lane_i32<3>(z)};
 #pragma unroll
-    for (int r = 0; r < SG_ROWS; ++r) {
+    for (int r = 0; r < ROWS; ++r) {
         const uint2 q = codes8(x[r], make_rule(is[r], zs[r], fmt));
         if (n0 + r < N) *reinterpret_cast<uint2 *>(codes + (n0 + r) * K + k) = q;
     }
@@ -445,17 +449,21 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
     hipLaunchKernelGGL((weight_quant_kernel<T, V_>), dim3((unsigned)blocks), dim3(WQ_THREADS), 0, \
                        st, W, N, K, ldw, s, G, use_given, codes, step, zero, fmt, s_vec, clip)
     if ((G == 128 || G == 256) && aligned(8)) {
-        const int64_t wsegs = (N + SG_ROWS - 1) / SG_ROWS * ((K + 511) / 512);
+        const int rows = N * K <= (1 << 21) ? 1 : SG_ROWS;
+        const int64_t wsegs = (N + rows - 1) / rows * ((K + 511) / 512);
         const int64_t wblocks = (wsegs + (WQ_THREADS / WAVE) - 1) / (WQ_THREADS / WAVE);
         if (wblocks > 0x7fffffffLL) return W4A8_ERR_SHAPE;
-        if (G == 128)
-            hipLaunchKernelGGL((weight_quant_small_groups_kernel<T, 16>), dim3((unsigned)wblocks),
-                               dim3(WQ_THREADS), 0, st, W, N, K, ldw, s, use_given, codes, step, zero, fmt,
-                               s_vec, clip);
-        else
-            hipLaunchKernelGGL((weight_quant_small_groups_kernel<T, 32>), dim3((unsigned)wblocks),
-                               dim3(WQ_THREADS), 0, st, W, N, K, ldw, s, use_given, codes, step, zero, fmt,
-                               s_vec, clip);
+#define W4A8_WQ_SMALL(LANES_, ROWS_)                                                                              \
+    hipLaunchKernelGGL((weight_quant_small_groups_kernel<T, LANES_, ROWS_>), dim3((unsigned)wblocks), dim3(WQ_THREADS), \
+                       0, st, W, N, K, ldw, s, use_given, codes, step, zero, fmt, s_vec, clip)
+        if (G == 128) {
+            if (rows == 1) W4A8_WQ_SMALL(16, 1);
+            else W4A8_WQ_SMALL(16, SG_ROWS);
+        } else {
+            if (rows == 1) W4A8_WQ_SMALL(32, 1);
+            else W4A8_WQ_SMALL(32, SG_ROWS);
+        }
+#undef W4A8_WQ_SMALL
     } else if (G >= 1024 && G <= SEG_MAX_CHUNKS * 8 * WQ_THREADS && aligned(8) && K / G <= 65535 &&
                N <= 0x7fffffffLL) {
         // at least half the threads of a block have a chunk (shorter segments: a wave each, below), and the
