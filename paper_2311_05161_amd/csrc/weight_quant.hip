@@ -1,7 +1,7 @@
 // dINT4 weight quantization of W diag(s)  (Eq. 1 factor Q(W diag(s)); Sec. 4.2, Eq. 5 with b = 4,
 // p = 13; min-max asymmetric ranges per output channel or per group of G input channels, App. A.1).
 //
-// Offline; bound by memory and the vector ALU about equally.  Groups of 128 and 256 and segments of 1024 to 16384
+// Offline; bound by memory and the vector ALU about equally.  Groups of 128 and 256 and most segments of 1024 to 16384
 // elements stay in registers between the range and the codes (one sweep over W); other lengths and
 // unaligned rows take one wavefront per (row, group) and two sweeps, the second served by the cache.
 // Range min / max of w' = W * s extended to contain zero, step = (hi - lo) / 13, 1/step and the
@@ -445,6 +445,18 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
         return G % v == 0 && K % v == 0 && (ldw * sizeof(T)) % (v * sizeof(T)) == 0 &&
                (uintptr_t)W % (v * sizeof(T)) == 0 && (uintptr_t)codes % v == 0 && ldw % v == 0;
     };
+    // Segments of 1024 to 16384 elements (the elements of two rows fit in registers): the segment kernel, except where too many of
+    // its threads have no chunk.  It works in rounds of 2048 elements, a wave of the wave-per-segment kernel in rounds of 512:
+    // with three or fewer of the latter, or five, more than a quarter of a block idles.  Up to 1024 segments (latency) it wins at every
+    // length, and in binary32 with five rounds, or three and more than 70 MiB of weights (the second sweep comes from memory).
+    // Wave / segment kernel, us, fp16: 16384 x 1024 17.5 / 23.4, 4096 x 1536 8.1 / 9.0, 4096 x 1792 9.8 / 9.5, 4096 x 2304 11.8 / 12.3,
+    // 16384 x 2816 37.9 / 35.2, 16384 x 4096 51.6 / 42.5, 1024 x 1280 4.9 / 4.6; binary32: 4096 x 1024 6.4 / 8.1, 4096 x 2304 12.9 / 12.6,
+    // 16384 x 1280 26.5 / 23.3, 4096 x 8192 in groups of 1024 33.3 / 37.7.
+    const auto segment_pays = [&] {
+        const int64_t rounds = (G + WAVE * 8 - 1) / (WAVE * 8);
+        return segs <= 1024 || rounds == 4 || rounds >= 6 ||
+               (sizeof(T) == 4 && (rounds == 5 || (rounds == 3 && N * K * 4 > (70 << 20))));
+    };
 #define W4A8_WQ_LAUNCH(V_)                                                                        \
     hipLaunchKernelGGL((weight_quant_kernel<T, V_>), dim3((unsigned)blocks), dim3(WQ_THREADS), 0, \
                        st, W, N, K, ldw, s, G, use_given, codes, step, zero, fmt, s_vec, clip)
@@ -465,9 +477,7 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
         }
 #undef W4A8_WQ_SMALL
     } else if (G >= 1024 && G <= SEG_MAX_CHUNKS * 8 * WQ_THREADS && aligned(8) && K / G <= 65535 &&
-               N <= 0x7fffffffLL) {
-        // at least half the threads of a block have a chunk (shorter segments: a wave each, below), and the
-        // elements of two rows fit in registers
+               N <= 0x7fffffffLL && segment_pays()) {
         const dim3 grid((unsigned)((N + SEG_ROWS - 1) / SEG_ROWS), (unsigned)(K / G));
 #define W4A8_WQ_SEGMENT(CH_)                                                                              \
     case CH_:                                                                                             \
