@@ -218,8 +218,9 @@ __device__ __forceinline__ uint32_t quant1_bits(float t, float inv)
 // THREADS = 1024: few rows (decode and short prompts), one row per workgroup; all there is then is the chain
 // load - divide - reduce - round - store, and a thread's share of the divisions is its longest link
 // (16 x 13824: 56 per thread of 256, 16 per thread of 1024).
-// rs (or null): the sums of each row's codes, which the per-channel product needs to remove its decode bias.
-template <typename T, int NCH, bool ASYM, int THREADS>
+// SUMS: rs gets the sums of each row's codes, which the per-channel product needs to remove its decode bias (an
+// instance of its own: 1024 x 5120 5.05 us without the sums in the code, 5.35 with them switched off at run time).
+template <typename T, int NCH, bool ASYM, int THREADS, bool SUMS>
 __global__ __launch_bounds__(THREADS) void act_quant_rows_kernel(
     const T *__restrict__ X, int64_t M, int K, int64_t ldx, const float *__restrict__ s,
     int8_t *__restrict__ Xq, float *__restrict__ sx, int32_t *__restrict__ zx, int32_t *__restrict__ rs,
@@ -323,10 +324,10 @@ __global__ __launch_bounds__(THREADS) void act_quant_rows_kernel(
                     w1 = pack4_low_bytes(b[4], b[5], b[6], b[7]);
                 }
                 *reinterpret_cast<uint2 *>(q + (int64_t)ch * AQ_VEC) = make_uint2(w0, w1);
-                if (!ASYM) sum = sum4_codes(w1, sum4_codes(w0, sum));
+                if (SUMS) sum = sum4_codes(w1, sum4_codes(w0, sum));
             }
         }
-        if (!ASYM && rs != nullptr) block_row_sum<WAVES>(sum, red_sum, rs + m);
+        if (SUMS) block_row_sum<WAVES>(sum, red_sum, rs + m);
 #pragma unroll
         for (int c = 0; c < NCH; ++c) cur[c] = nxt[c];
     }
@@ -341,7 +342,7 @@ __global__ __launch_bounds__(THREADS) void act_quant_rows_kernel(
 // ragged row's end load zeros and their stores are dropped by the bounds check (the whole offset
 // is a vector offset: a scalar offset would not be checked), so the chunk code has no branches.
 constexpr int AQW_WAVES = 4;
-template <typename T, int NCW, bool ASYM>
+template <typename T, int NCW, bool ASYM, bool SUMS>
 __global__ __launch_bounds__(AQW_WAVES *WAVE, 2) void act_quant_wave_kernel(
     const T *__restrict__ X, int64_t M, int K, int64_t ldx, const float *__restrict__ s,
     int8_t *__restrict__ Xq, float *__restrict__ sx, int32_t *__restrict__ zx, int32_t *__restrict__ rs,
@@ -451,9 +452,9 @@ __global__ __launch_bounds__(AQW_WAVES *WAVE, 2) void act_quant_wave_kernel(
                 b8[j] = ASYM ? (uint32_t)quant1_asym(t[c][j], ap.isx, ap.zf) : quant1_bits(t[c][j], inv);
             const v2u out = {pack4_low_bytes(b8[0], b8[1], b8[2], b8[3]), pack4_low_bytes(b8[4], b8[5], b8[6], b8[7])};
             __builtin_amdgcn_raw_buffer_store_b64(out, rq, (lane + c * WAVE) * AQ_VEC, 0, 0);
-            if (!ASYM) sum = sum4_codes(out.y, sum4_codes(out.x, sum));
+            if (SUMS) sum = sum4_codes(out.y, sum4_codes(out.x, sum));
         }
-        if (!ASYM && rs != nullptr) {
+        if (SUMS) {
             sum = wave_sum_i32(sum);
             if (lane == 0) rs[m] = sum;
         }
@@ -512,23 +513,24 @@ static bool act_quant_vectors(const void *X, int64_t elem, int64_t K, int64_t ld
            (s == nullptr || (uintptr_t)s % 16 == 0) && K <= (int64_t)AQ_THREADS * AQ_VEC * 8;
 }
 
-template <typename T, bool ASYM>
+template <typename T, bool ASYM, bool SUMS>
 static int launch_act_quant_t(const T *X, int64_t M, int64_t K, int64_t ldx, const float *s,
                               int8_t *Xq, float *sx, int32_t *zx, int32_t *rs, hipStream_t st)
 {
     if (!act_quant_vectors(X, sizeof(T), K, ldx, s, Xq)) {
-        if (rs != nullptr) return W4A8_ERR_SHAPE;   // (callers ask act_quant_sums_rows first)
+        if (SUMS) return W4A8_ERR_SHAPE;   // (callers ask act_quant_sums_rows first)
         hipLaunchKernelGGL((act_quant_generic_kernel<T, ASYM>), dim3((unsigned)M), dim3(AQ_THREADS),
                            0, st, X, M, K, ldx, s, Xq, sx, zx);
         return hip_status(hipGetLastError());
     }
     // Few rows: one of them per workgroup of 1024 lanes, at most one workgroup per CU.  Measured (cached rows, us,
     // this / the kernels below): 16 x 4096 2.8 / 3.7, 16 x 5120 3.0 / 4.1, 16 x 13824 3.9 / 5.1, 256 x 5120 3.4 / 4.3,
-    // 256 x 13824 4.6 / 5.7; 512 rows are even and 1024 rows lose (5120: 7.0 / 4.9).
-    if (M <= AQ_FEW_ROWS && K >= 2048) {
+    // 256 x 13824 4.6 / 5.7; 512 rows are even and 1024 rows lose (5120: 7.0 / 4.9).  16-bit rows of 2048 (a quarter of the lanes
+    // have a chunk) only up to 128 of them: 1 x 2048 2.2 / 2.4, 128 x 2048 2.7 / 2.7, 256 x 2048 2.85 / 2.75 (asymmetric 3.2 / 3.1).
+    if (M <= AQ_FEW_ROWS && (K > 2048 || (K == 2048 && (M <= 128 || sizeof(T) == 4)))) {
 #define W4A8_AQ_FEW(N_)                                                                                     \
     case N_:                                                                                                \
-        hipLaunchKernelGGL((act_quant_rows_kernel<T, N_, ASYM, 1024>), dim3((unsigned)M), dim3(1024), 0, st, \
+        hipLaunchKernelGGL((act_quant_rows_kernel<T, N_, ASYM, 1024, SUMS>), dim3((unsigned)M), dim3(1024), 0, st, \
                            X, M, (int)K, ldx, s, Xq, sx, zx, rs, 1);                                        \
         return hip_status(hipGetLastError())
         switch ((int)((K / AQ_VEC + 1023) / 1024)) {
@@ -550,7 +552,7 @@ static int launch_act_quant_t(const T *X, int64_t M, int64_t K, int64_t ldx, con
 #define W4A8_AQW_CASE(N_)                                                                          \
     if (ncw <= N_) {                                                                               \
         lds = (size_t)N_ * WAVE * AQ_VEC * sizeof(float);                                          \
-        hipLaunchKernelGGL((act_quant_wave_kernel<T, N_, ASYM>), dim3(grid), dim3(AQW_WAVES *WAVE), \
+        hipLaunchKernelGGL((act_quant_wave_kernel<T, N_, ASYM, SUMS>), dim3(grid), dim3(AQW_WAVES *WAVE), \
                            lds, st, X, M, (int)K, ldx, s, Xq, sx, zx, rs, rows);                   \
         return hip_status(hipGetLastError());                                                      \
     }
@@ -568,7 +570,7 @@ static int launch_act_quant_t(const T *X, int64_t M, int64_t K, int64_t ldx, con
     const int nch = (int)((K / AQ_VEC + AQ_THREADS - 1) / AQ_THREADS);
 #define W4A8_AQ_CASE(N_)                                                                                   \
     case N_:                                                                                               \
-        hipLaunchKernelGGL((act_quant_rows_kernel<T, N_, ASYM, AQ_THREADS>), dim3(grid), dim3(AQ_THREADS), \
+        hipLaunchKernelGGL((act_quant_rows_kernel<T, N_, ASYM, AQ_THREADS, SUMS>), dim3(grid), dim3(AQ_THREADS), \
                            0, st, X, M, (int)K, ldx, s, Xq, sx, zx, rs, rows);                             \
         break;
     switch (nch) {
@@ -590,8 +592,9 @@ int launch_act_quant(const void *X, int x_dtype, int64_t M, int64_t K, int64_t l
                      int8_t *Xq, float *sx, int32_t *zx, hipStream_t st, int32_t *rs)
 {
 #define W4A8_AQ_T(T_)                                                                       \
-    (zx ? launch_act_quant_t<T_, true>((const T_ *)X, M, K, ldx, s, Xq, sx, zx, nullptr, st) \
-        : launch_act_quant_t<T_, false>((const T_ *)X, M, K, ldx, s, Xq, sx, nullptr, rs, st))
+    (zx   ? launch_act_quant_t<T_, true, false>((const T_ *)X, M, K, ldx, s, Xq, sx, zx, nullptr, st)    \
+     : rs ? launch_act_quant_t<T_, false, true>((const T_ *)X, M, K, ldx, s, Xq, sx, nullptr, rs, st)    \
+          : launch_act_quant_t<T_, false, false>((const T_ *)X, M, K, ldx, s, Xq, sx, nullptr, nullptr, st))
     switch (x_dtype) {
         case W4A8_F32: return W4A8_AQ_T(float);
         case W4A8_F16: return W4A8_AQ_T(__half);

@@ -18,9 +18,9 @@ def lib():
     return w
 
 
-# 256 / 257 rows and 2040 / 2048 columns are the edges of the workgroup-per-row form, 8192 / 8200 those of its two
-# instances, 16384 the longest row of the vector kernels
-@pytest.mark.parametrize("M,K", [(1, 2040), (1, 2048), (256, 2056), (257, 2056), (7, 8192), (7, 8200), (3, 16384), (2, 16392)])
+# 256 / 257 rows and 2040 / 2048 columns (with 128 / 129 rows) are the edges of the workgroup-per-row form, 8192 / 8200 those of
+# its two instances, 16384 the longest row of the vector kernels
+@pytest.mark.parametrize("M,K", [(1, 2040), (1, 2048), (128, 2048), (129, 2048), (256, 2056), (257, 2056), (7, 8192), (7, 8200), (3, 16384), (2, 16392)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
 def test_act_quant_row_edges(lib, oracle, M, K, dtype):
     X, _, s = syn.random_layer(M + K, M, K, 16, x_dtype="f32")
