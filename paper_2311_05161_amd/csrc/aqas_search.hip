@@ -118,13 +118,14 @@ constexpr int RG_BM = 64, RG_BN = 128, RG_BK = 64, RG_AHEAD = 4;
 template <typename T>
 __global__ __launch_bounds__(256) void ref_gemm16_kernel(const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx,
                                                          const T *__restrict__ W, int64_t N, int64_t ldw,
-                                                         float *__restrict__ Y)
+                                                         float *__restrict__ Y, uint32_t grid_n)
 {
     constexpr int ROWS = RG_BM + RG_BN;          // rows of X, then rows of W
     constexpr int LOADS = ROWS * 8 / 256;        // 16-byte chunks per thread and step (6)
     __shared__ __attribute__((aligned(16))) v4u tile[2][ROWS * 8];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int64_t m0 = (int64_t)blockIdx.y * RG_BM, n0 = (int64_t)blockIdx.x * RG_BN;
+    const uint32_t bm = blockIdx.x / grid_n, bn = blockIdx.x - bm * grid_n;
+    const int64_t m0 = (int64_t)bm * RG_BM, n0 = (int64_t)bn * RG_BN;
     const int r32 = lane & 31, kh = lane >> 5;
     // thread: rows tid / 8 + 32 i, chunk tid % 8 (eight lanes read 128 contiguous bytes of a row)
     const v4u *src[LOADS];
@@ -190,8 +191,8 @@ __global__ __launch_bounds__(256) void ref_gemm16_kernel(const T *__restrict__ X
     }
 }
 
-// Every other input (binary32, odd lengths and alignments): one wave per 32 x 32 output tile, operands straight from
-// global memory, widened exactly, v_mfma_f32_32x32x2_f32.
+// Binary32, and bfloat16 off the 16-byte alignment (fp16 rows have to have it): one wave per 32 x 32 output tile, operands
+// straight from global memory, widened exactly, v_mfma_f32_32x32x2_f32.
 template <typename T>
 __global__ __launch_bounds__(256) void ref_gemm_kernel(const T *__restrict__ X, int64_t M, int64_t K,
                                                        int64_t ldx, const T *__restrict__ W, int64_t N,
@@ -224,23 +225,21 @@ __global__ __launch_bounds__(256) void ref_gemm_kernel(const T *__restrict__ X, 
 int launch_ref_gemm(const void *X, const void *W, int dtype, int64_t M, int64_t N, int64_t K,
                     int64_t ldx, int64_t ldw, float *Y, hipStream_t st)
 {
+    const int64_t gn16 = (N + RG_BN - 1) / RG_BN, blocks16 = (M + RG_BM - 1) / RG_BM * gn16;
     if (dtype != W4A8_F32 && K % RG_BK == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)W % 16 == 0 && ldx % 8 == 0 &&
-        ldw % 8 == 0 && (M + RG_BM - 1) / RG_BM <= 65535) {
-        const dim3 grid16((unsigned)((N + RG_BN - 1) / RG_BN), (unsigned)((M + RG_BM - 1) / RG_BM));
+        ldw % 8 == 0 && blocks16 <= 0x7fffffffLL) {
+        const dim3 grid16((unsigned)blocks16);
         if (dtype == W4A8_F16)
             hipLaunchKernelGGL((ref_gemm16_kernel<__half>), grid16, dim3(256), 0, st, (const __half *)X, M, K, ldx,
-                               (const __half *)W, N, ldw, Y);
+                               (const __half *)W, N, ldw, Y, (uint32_t)gn16);
         else
             hipLaunchKernelGGL((ref_gemm16_kernel<bf16_t>), grid16, dim3(256), 0, st, (const bf16_t *)X, M, K, ldx,
-                               (const bf16_t *)W, N, ldw, Y);
+                               (const bf16_t *)W, N, ldw, Y, (uint32_t)gn16);
         return hip_status(hipGetLastError());
     }
     const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
     switch (dtype) {
-        case W4A8_F16:
-            hipLaunchKernelGGL((ref_gemm_kernel<__half>), grid, dim3(256), 0, st, (const __half *)X, M, K, ldx,
-                               (const __half *)W, N, ldw, Y);
-            break;
+        case W4A8_F16: return W4A8_ERR_SHAPE;   // (all that the callers accept went above)
         case W4A8_BF16:
             hipLaunchKernelGGL((ref_gemm_kernel<bf16_t>), grid, dim3(256), 0, st, (const bf16_t *)X, M, K, ldx,
                                (const bf16_t *)W, N, ldw, Y);

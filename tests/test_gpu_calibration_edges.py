@@ -22,7 +22,7 @@ def lib():
 
 @pytest.mark.parametrize("M,K,N,G,dtype,pad", [
     (1, 128, 16, 128, "f16", 0), (255, 256, 16, 0, "f16", 8), (257, 384, 48, 128, "f16", 0), (520, 256, 144, 256, "f16", 8),
-    (3, 384, 80, 128, "bf16", 0), (129, 256, 272, 0, "bf16", 8), (65, 512, 32, 128, "f32", 4)])
+    (3, 384, 80, 128, "bf16", 0), (129, 256, 272, 0, "bf16", 8), (70, 384, 48, 128, "bf16", 3), (65, 512, 32, 128, "f32", 4)])
 def test_searches_at_edges(lib, oracle, M, K, N, G, dtype, pad):
     aq = oracle.aqas_search
     X, W, _ = syn.random_layer(M + K + N, M, K, N, x_dtype="f32", outlier_frac=0.02, outlier_gain=20.0)
