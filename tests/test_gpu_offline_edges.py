@@ -123,6 +123,47 @@ def test_code_rule_edges(lib, oracle, G, K):
     assert np.array_equal(host(codes), rc)
 
 
+# Infinities and NaN: with given parameters an infinity takes the end level and NaN code 0; with ranges from the weights every
+# kernel gives what the element-per-lane kernel gives on the same weights (rows off the alignment).  One and four rows per
+# wave, the segment kernel, the wave-per-segment kernel.
+@pytest.mark.parametrize("N,K,G", [(6, 1024, 128), (5, 420608, 256), (6, 2048, 0), (6, 1000, 0), (5, 512, 512)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
+def test_weight_quant_nonfinite(lib, N, K, G, dtype):
+    td = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dtype]
+    g = torch.Generator(device="cuda").manual_seed(N + K)
+    W = (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(td)
+    ng = K // (G or K)
+    where = torch.randint(0, K, (3, N, 8), generator=g, device="cuda")
+    for i, v in enumerate((float("nan"), float("inf"), -float("inf"))):
+        rows = torch.arange(N, device="cuda")[i:, None] if i else torch.arange(N, device="cuda")[:, None]
+        W[rows, where[i][i:] if i else where[0]] = v      # row 0: NaN only, row 1: and inf, the others: all three
+    off = torch.zeros((N, K + 1), dtype=td, device="cuda")
+    off[:, :K] = W
+    s = torch.rand((K,), generator=g, device="cuda") + 0.5
+    for scale in (s, None):
+        a = lib.quantize_weight_dint4(W, scale, G)
+        b = lib.quantize_weight_dint4(off[:, :K], scale, G)
+        assert torch.equal(a[0], b[0]) and torch.equal(a[1].view(torch.int32), b[1].view(torch.int32)) and torch.equal(a[2], b[2])
+    step = torch.full((N, ng), 0.01, device="cuda")
+    zero = torch.full((N, ng), 6, dtype=torch.uint8, device="cuda")
+    codes, _, _ = lib.quantize_weight_dint4(W, s, G, step=step, zero=zero)
+    assert (codes[W.isnan()] == 0).all() and (codes[W == float("inf")] == 13).all() and (codes[W == -float("inf")] == 0).all()
+
+
+# the same for the Value cache: the register-resident kernel, the two-sweep kernel, and rows off the alignment
+@pytest.mark.parametrize("T", [1024, 512])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_value_quant_nonfinite(lib, T, dtype):
+    B, D = 3, 64
+    g = torch.Generator(device="cuda").manual_seed(T)
+    V = torch.randn((B, T, D), generator=g, device="cuda").to(dtype)
+    V[0, 5, 0], V[0, 6, 1], V[1, 7, 2], V[1, 8, 3], V[1, 9, 3] = float("nan"), float("inf"), -float("inf"), float("nan"), float("inf")
+    off = torch.zeros((B, T, D + 1), dtype=dtype, device="cuda")
+    off[:, :, :D] = V
+    a, b = lib.quantize_value_dint4(V), lib.quantize_value_dint4(off[:, :, :D])
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1].view(torch.int32), b[1].view(torch.int32)) and torch.equal(a[2], b[2])
+
+
 # Value caches around the kernel that keeps a group in registers: the shortest and longest groups it takes and their
 # neighbours, a last round of tokens that is partly empty, channels that end inside a block, heads that do not fill the
 # eight XCDs, interleaved heads, rows off the alignment (general kernel)

@@ -72,3 +72,12 @@ def test_group_128_route(M, K, N, asym, phases):
 def test_per_channel_remainder(M, K, N, rem_n):
     pl = _rule("9plan_gemmEllll", GemmPlan, I64, I64, I64, I64)(M, N, K, K)
     assert pl.pc_rem_n == rem_n and pl.splits == 1
+
+
+# the shapes of the kernels' own tests are on the kernels that they are meant for
+def test_edge_shapes_take_their_kernels():
+    from test_gpu_mid_edges import FOUR, TILE, TWO
+    for asym in (False, True):
+        assert [mid_phases(s[0], s[2], s[1], asym) for s in FOUR[1:]] == [4] * (len(FOUR) - 1)
+        assert [mid_phases(s[0], s[2], s[1], asym) for s in TWO] == [2] * len(TWO)
+        assert [mid_phases(s[0], s[2], s[1], asym) for s in TILE] == [0, 0, 4, 0, 0, 0]
