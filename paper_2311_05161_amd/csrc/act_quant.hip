@@ -3,11 +3,12 @@
 // asymmetric form with a token zero-point (ASYM = true; codes 0..255 are stored minus 128 so that
 // the signed int8 matrix cores can take them, and so is the zero-point).
 //
-// HBM-bound: one read of X, one write of Xq.  A workgroup of 256 lanes owns a set of token rows.
-// Each lane keeps the reciprocal scales r[k] = 1/s[k] of its own columns in registers (true IEEE
-// division, done once per workgroup and reused for every row), loads 8 consecutive elements per
-// 16-byte access, keeps the scaled row t = x * r in registers between the absmax reduction and the
-// rounding pass, and stores 8 int8 per lane.  Every floating-point step is a single binary32
+// HBM-bound with many rows (one read of X, one write of Xq), a chain of latencies with few.  Three kernels: a wave
+// per row (rows up to 5120 16-bit elements), a workgroup of 256 lanes per set of rows (longer rows), and for few rows a
+// workgroup of 1024 lanes per row; a fourth takes rows off the alignment one element at a time.  Each lane has the
+// reciprocal scales r[k] = 1/s[k] of its own columns (true IEEE division, done once per workgroup and reused for every
+// row), loads 8 consecutive elements per 16-byte access, keeps the scaled row t = x * r in registers between the absmax
+// reduction and the rounding pass, and stores 8 int8 per lane.  Every floating-point step is a single binary32
 // operation in the order of the definition, so the result is bit-identical to a CPU evaluation.
 #include "w4a8_common.hpp"
 

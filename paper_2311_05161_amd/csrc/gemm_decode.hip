@@ -518,7 +518,7 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(const GemvArgs args)
             am = fmaxf(am, dpp_f32<DPP_ROW_MIRROR>(am));
         }
         float *mx = r_lds + K;
-        if ((lane & (FEW ? 15 : 3)) == 0) mx[wave * 16 + xrow] = am;   // (FEW: rows 4 .. 15 are read by nobody)
+        if ((lane & (FEW ? 15 : 3)) == 0) mx[wave * 16 + xrow] = am;   // (FEW: rows 4 .. 15 stay unwritten; the helper wave reads them, and uses none of rows >= M)
         lds_barrier();   // the row maxima are complete
         float arow = 0.f;
 #pragma unroll
