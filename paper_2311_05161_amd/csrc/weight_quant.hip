@@ -447,14 +447,14 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
     };
     // Segments of 1024 to 16384 elements (the elements of two rows fit in registers): the segment kernel, except where too many of
     // its threads have no chunk.  It works in rounds of 2048 elements, a wave of the wave-per-segment kernel in rounds of 512:
-    // with three or fewer of the latter, or five, more than a quarter of a block idles.  Up to 1024 segments (latency) it wins at every
+    // with three or fewer of the latter, or five, more than a quarter of a block idles.  Up to 1536 segments, 1024 of the shortest (latency), it wins at every
     // length, and in binary32 with five rounds, or three and more than 70 MiB of weights (the second sweep comes from memory).
     // Wave / segment kernel, us, fp16: 16384 x 1024 17.5 / 23.4, 4096 x 1536 8.1 / 9.0, 4096 x 1792 9.8 / 9.5, 4096 x 2304 11.8 / 12.3,
     // 16384 x 2816 37.9 / 35.2, 16384 x 4096 51.6 / 42.5, 1024 x 1280 4.9 / 4.6; binary32: 4096 x 1024 6.4 / 8.1, 4096 x 2304 12.9 / 12.6,
     // 16384 x 1280 26.5 / 23.3, 4096 x 8192 in groups of 1024 33.3 / 37.7.
     const auto segment_pays = [&] {
         const int64_t rounds = (G + WAVE * 8 - 1) / (WAVE * 8);
-        return segs <= 1024 || rounds == 4 || rounds >= 6 ||
+        return segs <= (rounds >= 3 ? 1536 : 1024) || rounds == 4 || rounds >= 6 ||
                (sizeof(T) == 4 && (rounds == 5 || (rounds == 3 && N * K * 4 > (70 << 20))));
     };
 #define W4A8_WQ_LAUNCH(V_)                                                                        \
