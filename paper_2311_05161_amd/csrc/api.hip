@@ -364,6 +364,9 @@ int w4a8_linear(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, c
 
     // At most 16 tokens of fp16 activations on tiled weights whose K the streaming kernel takes in one
     // range: ONE launch, the activations are quantized inside it.
+    // One launch / two, both under a graph, us: 4 x 4096 x 4096 6.3 / 7.9, 4 x 7168 x 2048 8.1 / 9.1, 16 x 768 x 768 4.6 / 5.2, 16 x 2048 x 1024
+    // 5.9 / 5.85; but beyond four tokens, where each workgroup quantizes sixteen rows, 5 x 4096 x 4096 8.9 / 7.9, 16 x 5120 x 13824 16.2 / 15.7,
+    // 16 x 7168 x 2048 12.4 / 9.7: there the line is from before the separate quantizer took 1024 lanes per row, and has not been moved.
     const bool one_launch = M <= 16 && x_dtype == W4A8_F16 && layout == W4A8_LAYOUT_TILED &&
                             (uintptr_t)X % 16 == 0 && ldx % 8 == 0 && ldx <= (1LL << 24) &&
                             gemv_can_fuse(M, N, K, G);

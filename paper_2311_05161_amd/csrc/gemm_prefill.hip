@@ -1305,9 +1305,10 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_pc_kernel(
 // The line between it and the tile kernel with K in ranges: a workgroup here takes a time proportional to
 // its share of K whatever the grid (0.4 us per k-tile with four phases, 0.73 with two, some 5 us besides), the tile
 // kernel one proportional to its tiles times K with some 16 us for partial sums, their combine launch and two
-// prologues.  Equating them gives K-tiles x (W - tiles) <= C.  The tile kernel has tiles of 64 tokens too and this one has not,
-// so `tiles` counts 64 x 64 blocks of the output (128-token tiles, which both would do, put a third of the shapes with
-// 129 .. 192 tokens on the slower side).  On the smallest grids the tile kernel's own fixed cost falls (fewer outputs to
+// prologues.  Equating them gives K-tiles x (W - tiles) <= C, where `tiles` counts 64 x 64 blocks
+// of the output: the partial sums that the tile kernel writes, reads and combines go with the live tokens, not with whole
+// 128-token tiles (which, counted on both sides, put a third of the shapes with 129 .. 192 tokens on the slower side).
+// On the smallest grids the tile kernel's own fixed cost falls (fewer outputs to
 // combine) and the lines are those of the second form.  A token zero-point costs one vector operation per accumulator
 // and group here, hence lines of its own.  Constants fitted to 1810 shapes of 129 to 1600 tokens, both kernels timed on
 // each: 0.3 % slower on average than the better of the two.  Two token tiles by 16 channel tiles of 128 are an exception: eight
