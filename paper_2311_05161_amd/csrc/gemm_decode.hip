@@ -686,9 +686,10 @@ __global__ __launch_bounds__(GV_THREADS) void gemv_kernel(const GemvArgs args)
 // thread takes CH = 4 channels (16-byte loads, four ranges in flight); one output per
 // thread with 4-byte loads and a 64-bit division took 9.6 us on 4 x 512 x 4096 and on 3 x 607 x 4096, this 6.8 and 5.9 us.
 // CH = 1: the few outputs of a decode step, where the launch is as long as one thread's chain of operations.
-// A block takes 256 channels (of CH tokens at a time) and the blocks of a token follow each other: where N / 256 is a multiple of
-// eight, a channel's sums are read by the XCD that wrote them in its L2.  1024 channels per block (256 threads) lost that at
-// N = 2048: 192 x 5120 x 2048 in groups of 256 17.2 -> 23.7 us, with 256 per block 17.5.
+// The tile kernel gives each XCD a contiguous eighth of the channels; the blocks here follow it (blocks go round-robin over
+// the XCDs), so that sums are read from the L2 they were written in.  Blocks in row-major order match that only by chance:
+// 192 x 5120 x 2048 in groups of 256 17.5 us with 256 channels per block, 23.7 with 1024; 173 x 1280 x 8128 26.3 with 256,
+// 16.7 with 1024, and 16.9 by eighths.
 template <int CH>
 __global__ __launch_bounds__(256) void gemv_combine_kernel(const float *__restrict__ partial,
                                                            const float *__restrict__ sx,
@@ -696,13 +697,18 @@ __global__ __launch_bounds__(256) void gemv_combine_kernel(const float *__restri
                                                            const int32_t *__restrict__ zx,
                                                            const int32_t *__restrict__ wsum, int M,
                                                            int N, int splits, uint16_t *__restrict__ Y,
-                                                           int y_dtype, int64_t ldy, int vec_store)
+                                                           int y_dtype, int64_t ldy, int vec_store,
+                                                           int xcd_shift, int xcd_channels, uint32_t chunks)
 {
     struct __attribute__((aligned(4 * CH))) Sums { float v[CH]; };   // CH partial sums, one load
-    const int n = (int)(blockIdx.x * blockDim.x + threadIdx.x) * CH;   // N % 16 == 0
-    if (n >= N) return;
+    // block -> (token rows, chunk of the XCD's channels); xcd_shift 0: chunks of all channels, in row-major order
+    const uint32_t seq = blockIdx.x >> xcd_shift, row = seq / chunks;
+    const int c = (int)((seq - row * chunks) * blockDim.x + threadIdx.x) * CH;
+    const int n = (int)(blockIdx.x - (seq << xcd_shift)) * xcd_channels + c;   // N % 16 == 0, xcd_channels % 16 == 0
+    if (c >= xcd_channels || n >= N) return;
     const int64_t slab = (int64_t)M * N;
-    for (int m = blockIdx.y * blockDim.y + threadIdx.y; m < M; m += gridDim.y * blockDim.y) {
+    const int m = (int)(row * blockDim.y + threadIdx.y);
+    if (m < M) {
         const float *p = partial + (int64_t)m * N + n;
         float v[CH];
         if (int_step != nullptr) {
@@ -970,19 +976,29 @@ int launch_gemv_combine(const float *partial, const float *sx, const float *int_
 {
     const int vec_store = (uintptr_t)Y % 8 == 0 && ldy % 4 == 0;
     // One output per thread while that makes at most 1024 blocks, and with more than four ranges (rounds of loads that wait for
-    // each other) at most 2048, eight on every CU.  The whole product with four / one, us: 1 x 4096 x 11008 9.70 / 9.37, 16 x 4096 x 11008 11.19 / 10.97,
-    // 33 x 4096 x 11008 16.5 / 16.0, 64 x 4096 x 11008 18.75 / 18.06 (per channel); in groups 515 x 11008 x 512 27.7 / 27.0,
-    // 160 x 8192 x 1792 26.1 / 25.4, 384 x 10752 x 1024 28.4 / 27.8; but 1290 x 13568 x 352
-    // (2580 blocks) 30.7 / 33.2, 130 x 10752 x 4096 29.8 / 31.4, 700 x 2048 x 1024 17.0 / 18.1.
-#define W4A8_COMBINE(CH_, ROWS_)                                                                                    \
-    do {                                                                                                            \
-        const int64_t gy = (M + ROWS_ - 1) / ROWS_;                                                                 \
-        hipLaunchKernelGGL(gemv_combine_kernel<CH_>, dim3((unsigned)((N + 255) / 256), (unsigned)(gy < 65535 ? gy : 65535)), \
-                           dim3(256 / CH_, ROWS_), 0, st, partial, sx, int_step, int_step ? zp.zx : nullptr, zp.wsum, \
-                           (int)M, (int)N, splits, (uint16_t *)Y, y_dtype, ldy, vec_store);                         \
-    } while (0)
-    if (M * ((N + 255) / 256) <= (splits > 4 ? 2048 : 1024)) W4A8_COMBINE(1, 1);
-    else W4A8_COMBINE(4, 4);
+    // each other) up to 5 * 2^16 outputs, or 2048 blocks where the eighths (below) are ragged.  The whole product with four / one,
+    // us: 1 x 11008 x 4096 9.70 / 9.37, 16 x 11008 x 4096 11.19 / 10.97, 33 x 11008 x 4096 16.5 / 16.0 (per channel); in groups
+    // 515 x 11008 x 512 27.7 / 27.0, 160 x 8192 x 1792 26.2 / 25.4; but 384 x 5120 x 1024 17.1 / 22.6, 1290 x 13568 x 352 (2580
+    // blocks) 30.7 / 33.2, 130 x 10752 x 4096 29.8 / 31.4, 700 x 2048 x 1024 17.0 / 18.1 (tokens x K x N).
+    // The XCDs' eighths of the channels where they fill four fifths of their blocks' threads or more; few outputs and ragged
+    // eighths lose more to idle threads (640 x 9728 x 640 27.1 us in row-major order, 32.0 in eighths).
+    const int eighth = (int)((N + 127) / 128 * 16), lanes = eighth / 4;   // (whole n-tiles)
+    unsigned bx = 64;
+    while (bx > 4 && (int)bx / 2 >= lanes) bx /= 2;
+    const bool whole = lanes * 5 >= (lanes + (int)bx - 1) / (int)bx * (int)bx * 4;
+    const int64_t ones = M * ((N + 255) / 256);   // blocks with one output per thread
+    const bool one = ones <= 1024 || (splits > 4 && (M * N <= 5 << 16 || (!whole && ones <= 2048))), eighths = whole && !one;
+    if (!eighths) bx = one ? 256 : 64;
+    const int xcd_channels = eighths ? eighth : (int)N, per_block = (int)bx * (one ? 1 : 4);
+    const unsigned by = 256 / bx, chunks = (unsigned)((xcd_channels + per_block - 1) / per_block);
+    const int64_t blocks = (eighths ? 8 : 1) * (int64_t)chunks * ((M + by - 1) / by);
+    if (blocks > 0x7fffffffLL) return W4A8_ERR_SHAPE;
+#define W4A8_COMBINE(CH_)                                                                                           \
+    hipLaunchKernelGGL(gemv_combine_kernel<CH_>, dim3((unsigned)blocks), dim3(bx, by), 0, st, partial, sx, int_step, \
+                       int_step ? zp.zx : nullptr, zp.wsum, (int)M, (int)N, splits, (uint16_t *)Y, y_dtype, ldy,    \
+                       vec_store, eighths ? 3 : 0, xcd_channels, chunks)
+    if (one) W4A8_COMBINE(1);
+    else W4A8_COMBINE(4);
 #undef W4A8_COMBINE
     return hip_status(hipGetLastError());
 }

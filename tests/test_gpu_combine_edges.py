@@ -1,6 +1,6 @@
 """Products whose K is cut into ranges: the kernel that adds the ranges' partial sums, at its edges (more than four
 ranges, channels that do not fill a block, rows of Y off the vector alignment, both output types, both forms, and both
-sides of the 1024 blocks, 2048 with more than four ranges, up to which a thread makes one)."""
+sides of the 1024 blocks, 2048 with more than four ranges, up to which a thread makes one, channels in eighths for the XCDs (whole and ragged) and in row-major order)."""
 import numpy as np
 import pytest
 
@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("M,K,N,G", [(16, 13824, 1040, 128), (3, 11008, 48, 0), (130, 16384, 48, 128),
                                      (130, 16384, 48, 0), (260, 8192, 272, 512), (1, 27648, 16, 0),
                                      (64, 11008, 4096, 0), (70, 13824, 4112, 512),
-                                     (1290, 5120, 48, 128), (1030, 16384, 304, 128)])
+                                     (1290, 5120, 48, 128), (1030, 16384, 304, 128),
+                                     (390, 5120, 1024, 256), (173, 1280, 8128, 256), (150, 2048, 2064, 512),
+                                     (130, 5120, 4112, 0)])
 @pytest.mark.parametrize("ypad,ydtype", [(0, "f16"), (1, "bf16"), (6, "f16")])
 def test_combine_edges(M, K, N, G, ypad, ydtype):
     import paper_2311_05161_amd as lib
