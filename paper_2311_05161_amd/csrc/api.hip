@@ -1,5 +1,7 @@
 // The C ABI of w4a8.h: host-side argument validation and dispatch.  No allocation, no state,
 // no synchronization; every error is reported before anything is launched.
+#include <algorithm>
+
 #include "w4a8_common.hpp"
 
 using namespace w4a8;
@@ -479,10 +481,22 @@ namespace {
 constexpr int AQ_GRID = 16, AQ_CLIP_STEPS = 11;
 
 struct AqasWs {
-    size_t ax, aw, s, Xq, sx, codes, step, zero, Wp, Y, Yref, err, best_err, gemm, gemm_bytes, total;
+    int cand;   // candidates of a search that run side by side (1: one after the other)
+    size_t ax, aw, s, r, Xq, sx, codes, step, zero, Wp, Y, Yref, err, best_err, rs, gemm, gemm_bytes, total;
 };
 
-AqasWs plan_aqas(int64_t M, int64_t N, int64_t K, int64_t G)
+// How many candidates run side by side: as many as keep their operands and outputs within 320 MiB (a good half of the
+// last-level cache, through which the launches hand them on).  Fewer than four gain nothing (the layer fills the chip by
+// itself then).
+int aqas_candidates(int64_t M, int64_t N, int64_t K, int64_t G)
+{
+    if (M <= 16 || !aqas_act_quant_applies(K) || !gemm_shape_ok(M, N, K, G)) return 1;
+    const double each = (double)M * K + (double)N * K * (G == TILE_K ? 0.5 : 1.5) + (double)N * (K / G) * 5 + (double)M * N * 2 + (double)M * 8;
+    const double fit = 320.0 * (1 << 20) / each;
+    return fit >= AQ_GRID + 1 ? AQ_GRID + 1 : fit >= 4.0 ? (int)fit : 1;
+}
+
+AqasWs plan_aqas(int64_t M, int64_t N, int64_t K, int64_t G, int cand)
 {
     AqasWs w{};
     size_t off = 0;
@@ -491,24 +505,41 @@ AqasWs plan_aqas(int64_t M, int64_t N, int64_t K, int64_t G)
         off = align_up(off + bytes);
         return at;
     };
-    const size_t ng = (size_t)(K / G);
+    const size_t ng = (size_t)(K / G), c = (size_t)cand, points = cand > 1 ? AQ_GRID + 1 : 1;
+    w.cand = cand;
     w.ax = take((size_t)K * 4);
     w.aw = take((size_t)K * 4);
-    w.s = take((size_t)K * 4);
-    w.Xq = take((size_t)M * K);
-    w.sx = take((size_t)M * 4);
-    w.codes = take((size_t)N * K);
-    w.step = take((size_t)N * ng * 4);
-    w.zero = take((size_t)N * ng);
-    w.Wp = take((size_t)N * K / 2);
-    w.Y = take((size_t)M * N * 2);
+    w.s = take(points * K * 4);
+    w.Xq = take(c * M * K);
+    w.sx = take(c * M * 4);
+    w.codes = take((G == TILE_K ? 1 : c) * N * K);   // (groups of 128 go straight to the packed form)
+    w.step = take(c * N * ng * 4);
+    w.zero = take(c * N * ng);
+    w.Wp = take(c * N * K / 2);
+    w.Y = take(c * M * N * 2);
     w.Yref = take((size_t)M * N * 4);
-    w.err = take((size_t)N * 8);
+    w.err = take(points * N * 8);
     w.best_err = take((size_t)N * 8);
-    w.gemm_bytes = plan_workspace(M, N, K, G, W4A8_LAYOUT_TILED).total;
-    w.gemm = take(w.gemm_bytes);
+    if (cand > 1) {
+        w.r = take(points * K * 4);
+        w.rs = take(c * M * 4);
+    } else {
+        w.gemm_bytes = plan_workspace(M, N, K, G, W4A8_LAYOUT_TILED).total;
+        w.gemm = take(w.gemm_bytes);
+    }
     w.total = off;
     return w;
+}
+
+// the side-by-side plan where the workspace holds it (a caller may have kept a size from when there was none)
+AqasWs plan_aqas_for(int64_t M, int64_t N, int64_t K, int64_t G, size_t workspace_bytes)
+{
+    const int cand = aqas_candidates(M, N, K, G);
+    if (cand > 1) {
+        const AqasWs w = plan_aqas(M, N, K, G, cand);
+        if (workspace_bytes >= w.total) return w;
+    }
+    return plan_aqas(M, N, K, G, 1);
 }
 
 int aqas_check(const void *X, const void *W, int dtype, int64_t M, int64_t N, int64_t K, int64_t ldx,
@@ -523,7 +554,7 @@ int aqas_check(const void *X, const void *W, int dtype, int64_t M, int64_t N, in
     // (part of the interface: the fp16 product has only the form with 16-byte loads; bfloat16 has another one besides)
     if (dtype == W4A8_F16 && ((uintptr_t)X % 16 != 0 || (uintptr_t)W % 16 != 0 || ldx % 8 != 0 || ldw % 8 != 0))
         return W4A8_ERR_SHAPE;
-    if (!workspace || (uintptr_t)workspace % WS_ALIGN != 0 || workspace_bytes < plan_aqas(M, N, K, G).total)
+    if (!workspace || (uintptr_t)workspace % WS_ALIGN != 0 || workspace_bytes < plan_aqas(M, N, K, G, 1).total)
         return W4A8_ERR_WORKSPACE;
     return W4A8_OK;
 }
@@ -558,6 +589,36 @@ int aqas_evaluate(const void *W, int dtype, int64_t M, int64_t N, int64_t K, int
                                   err_table, st);
 }
 
+// `count` candidates side by side, errors to err [count][N]: candidate v has the scales s + v s_stride, the clipping
+// index clip0 + v clip_stride and, where `tokens` is M, activations of its own (0: the same for all).
+int aqas_evaluate_batch(const void *W, int dtype, int64_t M, int64_t N, int64_t K, int64_t ldw, int64_t G, const float *s,
+                        int64_t s_stride, int clip0, int clip_stride, int64_t tokens, int count, uint8_t *ws,
+                        const AqasWs &w, double *err, hipStream_t st)
+{
+    float *step = (float *)(ws + w.step);
+    uint8_t *zero = ws + w.zero, *Wp = ws + w.Wp;
+    int rc;
+    const Clipping clip = {nullptr, clip0, count, clip_stride, s_stride};
+    if (weight_quant_packs(W, dtype, N, K, ldw, G)) {
+        rc = launch_weight_quant_packed(W, dtype, N, K, ldw, s, G, Wp, step, zero, clip, st);
+    } else if (G != TILE_K) {
+        rc = launch_weight_quant(W, dtype, N, K, ldw, s, G, 0, ws + w.codes, step, zero, W4A8_FMT_DINT4, st, clip);
+        if (rc == W4A8_OK) rc = launch_pack(ws + w.codes, count * N, K, Wp, W4A8_LAYOUT_TILED, st);
+    } else {   // (unaligned weights: room for the codes of one candidate)
+        rc = W4A8_OK;
+        for (int v = 0; v < count && rc == W4A8_OK; ++v) {
+            rc = launch_weight_quant(W, dtype, N, K, ldw, s ? s + v * s_stride : nullptr, G, 0, ws + w.codes, step + v * N * (K / G),
+                                     zero + v * N * (K / G), W4A8_FMT_DINT4, st, Clipping{nullptr, clip0 + v * clip_stride});
+            if (rc == W4A8_OK) rc = launch_pack(ws + w.codes, N, K, Wp + v * (N * K / 2), W4A8_LAYOUT_TILED, st);
+        }
+    }
+    if (rc != W4A8_OK) return rc;
+    rc = launch_gemm_batch((const int8_t *)(ws + w.Xq), (const float *)(ws + w.sx), (int32_t *)(ws + w.rs), M, Wp, step,
+                           zero, N, K, G, ws + w.Y, W4A8_F16, GemmBatch{count, tokens}, st);
+    if (rc != W4A8_OK) return rc;
+    return launch_sq_error_many(ws + w.Y, (const float *)(ws + w.Yref), M, N, err, count, st);
+}
+
 }  // namespace
 
 extern "C" {
@@ -567,7 +628,7 @@ size_t aqas_search_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t grou
     int64_t G = group_size;
     if (M < 1 || N < 1 || !resolve_group(K, G) || K % TILE_K != 0 || G % TILE_K != 0 || N % TILE_N != 0)
         return 0;
-    return plan_aqas(M, N, K, G).total;
+    return std::max(plan_aqas(M, N, K, G, 1).total, plan_aqas(M, N, K, G, aqas_candidates(M, N, K, G)).total);
 }
 
 int aqas_channel_absmax(const void *A, int dtype, int64_t R, int64_t K, int64_t lda, float *out,
@@ -596,12 +657,27 @@ int aqas_search(const void *X, const void *W, int dtype, int64_t M, int64_t N, i
     if (!s_out || !best_j || !losses) return W4A8_ERR_NULL;
     hipStream_t st = (hipStream_t)stream;
     uint8_t *ws = (uint8_t *)workspace;
-    const AqasWs w = plan_aqas(M, N, K, G);
+    const AqasWs w = plan_aqas_for(M, N, K, G, workspace_bytes);
     float *ax = (float *)(ws + w.ax), *aw = (float *)(ws + w.aw), *s = (float *)(ws + w.s);
     if ((rc = launch_channel_absmax(X, dtype, M, K, ldx, ax, st)) != W4A8_OK) return rc;
     if ((rc = launch_channel_absmax(W, dtype, N, K, ldw, aw, st)) != W4A8_OK) return rc;
     if ((rc = launch_ref_gemm(X, W, dtype, M, N, K, ldx, ldw, (float *)(ws + w.Yref), st)) != W4A8_OK) return rc;
     const double *err = (const double *)(ws + w.err);
+    if (w.cand > 1) {
+        constexpr int points = AQ_GRID + 1;
+        const int rounds = (points + w.cand - 1) / w.cand, per = (points + rounds - 1) / rounds;
+        float *r = (float *)(ws + w.r);
+        if ((rc = launch_aqas_all_scales(ax, aw, K, s, r, st)) != W4A8_OK) return rc;
+        for (int j = 0; j < points; j += per) {
+            const int count = std::min(per, points - j);
+            rc = launch_aqas_act_quant(X, dtype, M, K, ldx, r + j * K, (int8_t *)(ws + w.Xq), (float *)(ws + w.sx), count, st);
+            if (rc != W4A8_OK) return rc;
+            rc = aqas_evaluate_batch(W, dtype, M, N, K, ldw, G, s + j * K, K, 0, 0, M, count, ws, w,
+                                     (double *)(ws + w.err) + j * N, st);
+            if (rc != W4A8_OK) return rc;
+        }
+        return launch_aqas_finish_all(ax, aw, K, s_out, err, N, losses, best_j, st);
+    }
     for (int j = 0; j <= AQ_GRID; ++j) {
         if ((rc = launch_aqas_next_point(ax, aw, K, j, s, err, N, losses, st)) != W4A8_OK) return rc;
         rc = quantize_act_int8(X, dtype, M, K, ldx, s, (int8_t *)(ws + w.Xq), (float *)(ws + w.sx), stream);
@@ -637,11 +713,24 @@ int aqas_clip_search(const void *X, const void *W, int dtype, int64_t M, int64_t
     if (!index_out || !step_out || !zero_out) return W4A8_ERR_NULL;
     hipStream_t st = (hipStream_t)stream;
     uint8_t *ws = (uint8_t *)workspace;
-    const AqasWs w = plan_aqas(M, N, K, G);
+    const AqasWs w = plan_aqas_for(M, N, K, G, workspace_bytes);
     if ((rc = launch_ref_gemm(X, W, dtype, M, N, K, ldx, ldw, (float *)(ws + w.Yref), st)) != W4A8_OK) return rc;
     // (the activations do not depend on the clipping: quantized once for all factors)
     rc = quantize_act_int8(X, dtype, M, K, ldx, s, (int8_t *)(ws + w.Xq), (float *)(ws + w.sx), stream);
     if (rc != W4A8_OK) return rc;
+    if (w.cand > 1) {
+        const int rounds = (AQ_CLIP_STEPS + w.cand - 1) / w.cand, per = (AQ_CLIP_STEPS + rounds - 1) / rounds;
+        for (int i = 0; i < AQ_CLIP_STEPS; i += per) {
+            const int count = std::min(per, AQ_CLIP_STEPS - i);
+            double *err = (double *)(ws + w.err);
+            rc = aqas_evaluate_batch(W, dtype, M, N, K, ldw, G, s, 0, i, 1, 0, count, ws, w, err, st);
+            if (rc != W4A8_OK) return rc;
+            rc = launch_clip_pick(err, N, i, count, (double *)(ws + w.best_err), index_out, err_table, st);
+            if (rc != W4A8_OK) return rc;
+        }
+        return launch_weight_quant(W, dtype, N, K, ldw, s, G, 0, nullptr, step_out, zero_out, W4A8_FMT_DINT4, st,
+                                   Clipping{index_out, 0});
+    }
     for (int i = 0; i < AQ_CLIP_STEPS; ++i) {
         if ((rc = aqas_evaluate(W, dtype, M, N, K, ldw, G, s, i, ws, w, index_out, err_table, stream)) != W4A8_OK)
             return rc;

@@ -33,8 +33,16 @@ __global__ __launch_bounds__(256) void channel_absmax_kernel(const T *__restrict
     const int64_t r0 = (int64_t)blockIdx.y * rows_per_block;
     const int64_t r1 = min(R, r0 + rows_per_block);
     float m = 0.0f;
-    if (k < K)
-        for (int64_t r = r0 + wave; r < r1; r += 4) m = fmaxf(m, fabsf(to_f32(A[r * lda + k])));
+    if (k < K) {
+        // eight loads in flight (rows past the end repeat the last one)
+        for (int64_t r = r0 + wave; r < r1; r += 32) {
+            T a[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) a[i] = A[min(r + 4 * i, r1 - 1) * lda + k];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) m = fmaxf(m, fabsf(to_f32(a[i])));
+        }
+    }
     part[wave][lane] = m;
     __syncthreads();
     if (wave == 0 && k < K) {
@@ -54,7 +62,10 @@ int launch_channel_absmax(const void *A, int dtype, int64_t R, int64_t K, int64_
 {
     hipLaunchKernelGGL(fill_f32_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, out, K, 0.0f);
     if (R == 0) return hip_status(hipGetLastError());
-    const int rpb = 256;
+    // Rows per block: few enough to fill the chip, many enough that a channel's atomics do not queue up (one row at a
+    // time and always 256 of them: 512 x 4096 28 us, 4096 x 4096 21 us).
+    const int64_t blocks128 = (K + 63) / 64 * ((R + 127) / 128);
+    const int rpb = blocks128 < 512 ? 32 : R > 65535 * 128LL ? 256 : 128;
     const dim3 grid((unsigned)((K + 63) / 64), (unsigned)((R + rpb - 1) / rpb));
     switch (dtype) {
         case W4A8_F32:
@@ -280,6 +291,8 @@ __global__ __launch_bounds__(SQ_THREADS) void output_sq_error_kernel(const uint1
     __shared__ double part[SQ_THREADS / WAVE][SQ_CHANNELS];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t n = (int64_t)blockIdx.x * SQ_CHANNELS + (tid & 3) * 4;   // N % 16 == 0
+    Y += blockIdx.y * M * N;   // (several candidates' outputs against one reference)
+    err += blockIdx.y * N;
     double sum[4] = {0.0, 0.0, 0.0, 0.0};
     for (int64_t m = tid >> 2; m < M; m += SQ_THREADS / 4) {
         const ushort4 b = *reinterpret_cast<const ushort4 *>(Y + m * N + n);
@@ -369,7 +382,8 @@ __global__ __launch_bounds__(1024) void aqas_finish_kernel(const float *__restri
 {
     __shared__ double part[LOSS_LANES];
     __shared__ int s_best;
-    const double last = loss_sum(err, N, part);
+    // (err null: all losses are there)
+    const double last = err != nullptr ? loss_sum(err, N, part) : losses[AQ_GRID];
     if (threadIdx.x == 0) {
         losses[AQ_GRID] = last;
         int b = 0;
@@ -409,6 +423,245 @@ int launch_aqas_finish(const float *ax, const float *aw, int64_t K, float *s, co
                        double *losses, int32_t *best, hipStream_t st)
 {
     hipLaunchKernelGGL(aqas_finish_kernel, dim3(1), dim3(1024), 0, st, ax, aw, K, s, err, N, losses, best);
+    return hip_status(hipGetLastError());
+}
+
+// ---- several candidates per launch ----------------------------------------------------------------
+// One candidate at a time, a layer of 4096 x 4096 on 512 tokens is five launches of 4 to 22 us per grid point: the product
+// has one workgroup per CU, the others wait for one memory round trip after the other.  With the candidates of a
+// search side by side every launch fills the chip several times over.
+
+// s[j][k] and 1 / s[j][k] of all grid points
+__global__ __launch_bounds__(256) void aqas_all_scales_kernel(const float *__restrict__ ax, const float *__restrict__ aw,
+                                                              int64_t K, float *__restrict__ s, float *__restrict__ r)
+{
+    const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (k >= K) return;
+    const float v = scale_at(ax[k], aw[k], blockIdx.y);
+    s[blockIdx.y * K + k] = v;
+    r[blockIdx.y * K + k] = 1.0f / v;
+}
+
+// Symmetric activation quantizer (the definition's operations, one binary32 rounding each, as in the layer's own kernels)
+// for `count` candidates: a workgroup loads a token row once and keeps it in registers, four consecutive elements
+// per thread and chunk, then takes the candidates one by one, each with its reciprocal scales from the cache.
+template <typename T, int NC>
+__global__ __launch_bounds__(256) void aqas_act_quant_kernel(const T *__restrict__ X, int64_t M, int K, int64_t ldx,
+                                                             const float *__restrict__ r, int8_t *__restrict__ Xq,
+                                                             float *__restrict__ sx, int count, int per_block)
+{
+    __shared__ float red[2][4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t m = blockIdx.x;
+    const T *x = X + m * ldx;
+    float v[NC][4];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        const int k = (tid + 256 * c) * 4;   // K % 4 == 0
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[c][i] = k < K ? to_f32(x[k + i]) : 0.0f;
+    }
+    const int first = blockIdx.y * per_block, last = min(count, first + per_block);
+    for (int j = first; j < last; ++j) {
+        const float *rj = r + (int64_t)j * K;
+        float t[NC][4], a = 0.0f;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int k = (tid + 256 * c) * 4;
+            float4 q = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            if (k < K) q = *reinterpret_cast<const float4 *>(rj + k);
+            t[c][0] = v[c][0] * q.x; t[c][1] = v[c][1] * q.y; t[c][2] = v[c][2] * q.z; t[c][3] = v[c][3] * q.w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a = fmaxf(a, fabsf(t[c][i]));
+        }
+        a = wave_max(a);
+        float *part = red[j & 1];   // (two sets: a wave a candidate ahead writes the other one)
+        if (lane == 0) part[wave] = a;
+        __syncthreads();
+        a = fmaxf(fmaxf(part[0], part[1]), fmaxf(part[2], part[3]));
+        float inv = 127.0f / a;
+        const bool zero_row = !(inv <= 3.402823466e+38f);   // a == 0, or so small that 127 / a overflows
+        if (zero_row) inv = 0.0f;
+        if (tid == 0) sx[(int64_t)j * M + m] = zero_row ? 1.0f : a / 127.0f;
+        uint32_t *out = reinterpret_cast<uint32_t *>(Xq + ((int64_t)j * M + m) * K);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            const int k = (tid + 256 * c) * 4;
+            uint32_t b[4];
+            // rne and the conversion in one addition (|t inv| <= 127 (1 + 2^-23): the low byte is the code)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) b[i] = __float_as_uint(t[c][i] * inv + 12582912.0f);
+            if (k < K)
+                out[k / 4] = __builtin_amdgcn_perm(b[1], b[0], 0x0c0c0400u) | __builtin_amdgcn_perm(b[3], b[2], 0x04000c0cu);
+        }
+    }
+}
+
+bool aqas_act_quant_applies(int64_t K) { return K % 4 == 0 && K <= 8 * 1024; }
+
+__global__ __launch_bounds__(256) void aqas_losses_kernel(const double *__restrict__ err, int64_t N,
+                                                          double *__restrict__ losses)
+{
+    __shared__ double part[LOSS_LANES];
+    const double sum = loss_sum(err + blockIdx.x * N, N, part);
+    if (threadIdx.x == 0) losses[blockIdx.x] = sum;
+}
+
+// a candidate replaces a channel's incumbent only if strictly better (ties keep the larger range)
+__global__ __launch_bounds__(256) void clip_pick_kernel(const double *__restrict__ err, int64_t N, int i0, int count,
+                                                        double *__restrict__ best_err, int32_t *__restrict__ best_idx,
+                                                        double *__restrict__ err_table)
+{
+    const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (n >= N) return;
+    double best = 0.0;
+    int32_t idx = 0;
+    if (i0 > 0) {
+        best = best_err[n];
+        idx = best_idx[n];
+    }
+    for (int c = 0; c < count; ++c) {
+        const double e = err[c * N + n];
+        if (err_table != nullptr) err_table[(i0 + c) * N + n] = e;
+        if (i0 + c == 0 || e < best) {
+            best = e;
+            idx = i0 + c;
+        }
+    }
+    best_err[n] = best;
+    best_idx[n] = idx;
+}
+
+int launch_aqas_all_scales(const float *ax, const float *aw, int64_t K, float *s, float *r, hipStream_t st)
+{
+    hipLaunchKernelGGL(aqas_all_scales_kernel, dim3((unsigned)((K + 255) / 256), AQ_GRID + 1), dim3(256), 0, st, ax, aw,
+                       K, s, r);
+    return hip_status(hipGetLastError());
+}
+
+template <typename T>
+static int launch_aqas_act_quant_t(const T *X, int64_t M, int64_t K, int64_t ldx, const float *r, int8_t *Xq, float *sx,
+                                   int count, hipStream_t st)
+{
+    // (all candidates in the workgroup that has the row, unless that leaves CUs without work)
+    int per_block = (int)(M * count / 1024);
+    if (per_block < 1) per_block = 1;
+    if (per_block > count) per_block = count;
+    const dim3 grid((unsigned)M, (unsigned)((count + per_block - 1) / per_block));
+#define W4A8_AAQ(NC_)                                                                                                  \
+    if (K <= NC_ * 1024) {                                                                                             \
+        hipLaunchKernelGGL((aqas_act_quant_kernel<T, NC_>), grid, dim3(256), 0, st, X, M, (int)K, ldx, r, Xq, sx, count, \
+                           per_block);                                                                                 \
+        return hip_status(hipGetLastError());                                                                          \
+    }
+    W4A8_AAQ(1) W4A8_AAQ(2) W4A8_AAQ(4) W4A8_AAQ(8)
+#undef W4A8_AAQ
+    return W4A8_ERR_SHAPE;
+}
+
+int launch_aqas_act_quant(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, const float *r, int8_t *Xq,
+                          float *sx, int count, hipStream_t st)
+{
+    if (!aqas_act_quant_applies(K)) return W4A8_ERR_SHAPE;
+    switch (dtype) {
+        case W4A8_F32: return launch_aqas_act_quant_t((const float *)X, M, K, ldx, r, Xq, sx, count, st);
+        case W4A8_F16: return launch_aqas_act_quant_t((const __half *)X, M, K, ldx, r, Xq, sx, count, st);
+        case W4A8_BF16: return launch_aqas_act_quant_t((const bf16_t *)X, M, K, ldx, r, Xq, sx, count, st);
+        default: return W4A8_ERR_DTYPE;
+    }
+}
+
+int launch_aqas_finish_all(const float *ax, const float *aw, int64_t K, float *s, const double *err, int64_t N,
+                           double *losses, int32_t *best, hipStream_t st)
+{
+    hipLaunchKernelGGL(aqas_losses_kernel, dim3(AQ_GRID + 1), dim3(256), 0, st, err, N, losses);
+    hipLaunchKernelGGL(aqas_finish_kernel, dim3(1), dim3(1024), 0, st, ax, aw, K, s, (const double *)nullptr, N, losses, best);
+    return hip_status(hipGetLastError());
+}
+
+int launch_clip_pick(const double *err, int64_t N, int i0, int count, double *best_err, int32_t *best_idx,
+                     double *err_table, hipStream_t st)
+{
+    hipLaunchKernelGGL(clip_pick_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, err, N, i0, count, best_err,
+                       best_idx, err_table);
+    return hip_status(hipGetLastError());
+}
+
+// err[v][n] of `count` candidates against one reference (M <= 64 R): as output_sq_error_kernel, but a block takes 64
+// channels (whole 128-byte lines of the outputs: with 16, and as many passes over Yref as candidates, 17 x 512 x 4096
+// took 65 us), keeps its share of Yref in registers and takes its candidates one after the other, the next one's
+// outputs on their way meanwhile.  A wave's four sums per lane meet by halving: two doubles, then one, cross the
+// lanes that hold the other channels.
+constexpr int SQM_CHANNELS = 64;
+
+template <int R>
+__global__ __launch_bounds__(SQ_THREADS) void sq_error_many_kernel(const uint16_t *__restrict__ Y,
+                                                                   const float *__restrict__ Yref, int64_t M, int64_t N,
+                                                                   double *__restrict__ err, int count, int per_block)
+{
+    __shared__ double part[2][SQ_THREADS / WAVE][SQM_CHANNELS];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t nb = (int64_t)blockIdx.x * SQM_CHANNELS;
+    const int64_t n = min(nb + (tid & 15) * 4, N - 4);   // (N % 16 == 0; channels past the end are not stored)
+    const int64_t m0 = tid >> 4;
+    const int first = blockIdx.y * per_block, last = min(count, first + per_block);
+    v2u b[R];
+    auto load = [&](int v) {
+#pragma unroll
+        for (int i = 0; i < R; ++i)   // (rows past the end repeat the last one; they are not added)
+            b[i] = *reinterpret_cast<const v2u *>(Y + (v * M + min(m0 + 64 * i, M - 1)) * N + n);
+    };
+    load(first);
+    v4f ref[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) ref[i] = *reinterpret_cast<const v4f *>(Yref + min(m0 + 64 * i, M - 1) * N + n);
+    for (int v = first; v < last; ++v) {
+        double sum[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const uint16_t bits[4] = {(uint16_t)b[i].x, (uint16_t)(b[i].x >> 16), (uint16_t)b[i].y, (uint16_t)(b[i].y >> 16)};
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const float d = __half2float(__ushort_as_half(bits[c])) - ref[i][c];
+                if (m0 + 64 * i < M) sum[c] += (double)d * (double)d;
+            }
+        }
+        if (v + 1 < last) load(v + 1);
+        const bool up = lane & 32, up2 = lane & 16;   // lanes 16 apart hold the same channels
+        double a0 = up ? sum[2] : sum[0], a1 = up ? sum[3] : sum[1];
+        a0 += __shfl_xor(up ? sum[0] : sum[2], 32, WAVE);
+        a1 += __shfl_xor(up ? sum[1] : sum[3], 32, WAVE);
+        double a = up2 ? a1 : a0;
+        a += __shfl_xor(up2 ? a0 : a1, 16, WAVE);
+        part[v & 1][wave][(lane & 15) * 4 + (up ? 2 : 0) + (up2 ? 1 : 0)] = a;
+        __syncthreads();
+        if (tid < SQM_CHANNELS && nb + tid < N) {   // (the two sets of sums take turns: one barrier per candidate)
+            double e = 0.0;
+#pragma unroll
+            for (int w = 0; w < SQ_THREADS / WAVE; ++w) e += part[v & 1][w][tid];
+            err[v * N + nb + tid] = e;
+        }
+    }
+}
+
+// fp16 outputs Y [count][M][N] against Yref [M][N], N % 16 == 0, both 16-byte aligned
+int launch_sq_error_many(const void *Y, const float *Yref, int64_t M, int64_t N, double *err, int count, hipStream_t st)
+{
+    const int64_t blocks = (N + SQM_CHANNELS - 1) / SQM_CHANNELS;
+    int per_block = (int)(blocks * count / 512);   // all of a block's candidates in turn, unless that leaves CUs idle
+    per_block = per_block < 1 ? 1 : per_block > count ? count : per_block;
+    const dim3 grid((unsigned)blocks, (unsigned)((count + per_block - 1) / per_block));
+#define W4A8_SQM(R_)                                                                                                   \
+    if (M <= 64 * R_) {                                                                                                \
+        hipLaunchKernelGGL((sq_error_many_kernel<R_>), grid, dim3(SQ_THREADS), 0, st, (const uint16_t *)Y, Yref, M, N, err, \
+                           count, per_block);                                                                          \
+        return hip_status(hipGetLastError());                                                                          \
+    }
+    W4A8_SQM(1) W4A8_SQM(2) W4A8_SQM(4) W4A8_SQM(8)
+#undef W4A8_SQM
+    // (longer columns than a block's registers hold)
+    hipLaunchKernelGGL(output_sq_error_kernel, dim3((unsigned)(N / SQ_CHANNELS), (unsigned)count), dim3(SQ_THREADS), 0, st,
+                       (const uint16_t *)Y, (int)W4A8_F16, Yref, M, N, err, ClipState{0, nullptr, nullptr, nullptr});
     return hip_status(hipGetLastError());
 }
 

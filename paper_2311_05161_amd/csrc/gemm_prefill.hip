@@ -125,10 +125,20 @@ __global__ __launch_bounds__(WM * WN * 64, TWO ? 4 : (BN < GM_BN ? 2 : 1)) void 
     const uint8_t *__restrict__ zero, int N, int K, int tiles_per_group, int ng,
     uint16_t *__restrict__ Y, int y_dtype, int64_t ldy, int vec_store,
     int32_t *__restrict__ acc_out, int grid_m, int grid_n, int kt_per_split,
-    float *__restrict__ partial, int plain, int acc_ld)
+    float *__restrict__ partial, int plain, int acc_ld, GemmBatch batch)
 {
     // (acc_ld: channels per token row of acc_out -- N, or the whole layer's when this launch covers a
     // range of its channels)
+    if (gridDim.y > 1) {   // blockIdx.y: independent problems of one shape
+        const int64_t b = blockIdx.y;
+        Xq += b * batch.tokens * K;
+        sx += b * batch.tokens;
+        if (!GROUPED) rs += b * batch.tokens;
+        Wt += b * N * K / 2;
+        step += b * N * ng;
+        zero += b * N * ng;
+        Y += b * M * ldy;
+    }
     constexpr int GM_THREADS = WM * WN * 64;
     constexpr int GM_NS = BN / (WN * 32);       // 32-channel sub-tiles per wave
     constexpr int WROWS = BM / WM;                 // token rows per wave
@@ -675,7 +685,8 @@ template <int BM, int WM, int WN, bool GROUPED, bool ACC_OUT, bool ASYM, bool TW
 static int launch_gemm_t2(const GemmPlan &pl, const int8_t *Xq, const float *sx, ZeroPoint zp,
                           const int32_t *rs, int64_t M, const uint8_t *Wt, const float *step,
                           const uint8_t *zero, int64_t N, int64_t K, int64_t G, void *Y, int y_dtype,
-                          int64_t ldy, int32_t *acc_out, float *partial, hipStream_t st, int plain, int64_t acc_ld)
+                          int64_t ldy, int32_t *acc_out, float *partial, hipStream_t st, int plain, int64_t acc_ld,
+                          GemmBatch batch)
 {
     const int grid_m = (int)((M + BM - 1) / BM);
     const int grid_n = (int)((N + BN - 1) / BN);
@@ -689,11 +700,12 @@ static int launch_gemm_t2(const GemmPlan &pl, const int8_t *Xq, const float *sx,
                            lds_opted) != W4A8_OK)
         return W4A8_ERR_HIP;
     hipLaunchKernelGGL((gemm_kernel<BM, WM, WN, GROUPED, ACC_OUT, ASYM, TWO, BN>),
-                       dim3((unsigned)(grid_m * grid_n * pl.splits)), dim3(WM * WN * 64), lds_bytes, st,
+                       dim3((unsigned)(grid_m * grid_n * pl.splits), (unsigned)batch.count), dim3(WM * WN * 64),
+                       lds_bytes, st,
                        Xq, sx, zp.zx, zp.wsum, zp.tsum, rs, (int)M, Wt, step, zero, (int)N, (int)K,
                        (int)(G / TILE_K), (int)(K / G), (uint16_t *)Y, y_dtype, ldy, vec_store,
                        acc_out, grid_m, grid_n, pl.kt_per_split, pl.splits > 1 ? partial : nullptr, plain,
-                       (int)(acc_ld > 0 ? acc_ld : N));
+                       (int)(acc_ld > 0 ? acc_ld : N), batch);
     return hip_status(hipGetLastError());
 }
 
@@ -702,13 +714,13 @@ static int launch_gemm_t(const GemmPlan &pl, const int8_t *Xq, const float *sx, 
                          const int32_t *rs, int64_t M, const uint8_t *Wt, const float *step,
                          const uint8_t *zero, int64_t N, int64_t K, int64_t G, void *Y, int y_dtype,
                          int64_t ldy, int32_t *acc_out, float *partial, hipStream_t st, int plain,
-                         int64_t acc_ld = 0)
+                         int64_t acc_ld = 0, GemmBatch batch = GemmBatch{1, 0})
 {
     // The accumulator test hook is a separate instance so that the fast path carries none of it;
     // so is the per-group zero-point term of group-wise weights.
 #define W4A8_GM2(AO_, AS_)                                                                       \
     return launch_gemm_t2<BM, WM, WN, GROUPED, AO_, AS_, TWO, BN>(pl, Xq, sx, zp, rs, M, Wt, step, zero, N, K, \
-                                                     G, Y, y_dtype, ldy, acc_out, partial, st, plain, acc_ld)
+                                                     G, Y, y_dtype, ldy, acc_out, partial, st, plain, acc_ld, batch)
     if (GROUPED && zp.zx != nullptr) {
         if (acc_out) W4A8_GM2(true, GROUPED);
         W4A8_GM2(false, GROUPED);
@@ -741,8 +753,17 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     const int32_t *__restrict__ wsum, int M, const uint8_t *__restrict__ Wt,
     const float *__restrict__ step, const uint8_t *__restrict__ zero, int N, int K,
     uint16_t *__restrict__ Y, int y_dtype, int64_t ldy, int vec_store, int32_t *__restrict__ acc_out,
-    int grid_m, int plain)
+    int grid_m, int plain, GemmBatch batch)
 {
+    if (gridDim.y > 1) {   // blockIdx.y: independent problems of one shape
+        const int64_t b = blockIdx.y;
+        Xq += b * batch.tokens * K;
+        sx += b * batch.tokens;
+        Wt += b * N * K / 2;
+        step += b * N * (K / TILE_K);
+        zero += b * N * (K / TILE_K);
+        Y += b * M * ldy;
+    }
     constexpr int MS = MD_BM / 32;
     constexpr int WN = 8 / KQ;       // channel parts
     constexpr int BN = 32 * WN;      // channels of the workgroup (KQ * BN = 256)
@@ -1338,7 +1359,8 @@ int gemm_mid_phases(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
 template <int KQ, bool ASYM>
 static int launch_gemm_mid_t(const int8_t *Xq, const float *sx, ZeroPoint zp, int64_t M, const uint8_t *Wt,
                              const float *step, const uint8_t *zero, int64_t N, int64_t K, void *Y, int y_dtype,
-                             int64_t ldy, int32_t *acc_out, hipStream_t st, int plain)
+                             int64_t ldy, int32_t *acc_out, hipStream_t st, int plain,
+                             GemmBatch batch = GemmBatch{1, 0})
 {
     constexpr int BN = 256 / KQ;
     const int grid_m = (int)((M + MD_BM - 1) / MD_BM);
@@ -1350,9 +1372,9 @@ static int launch_gemm_mid_t(const int8_t *Xq, const float *sx, ZeroPoint zp, in
         static std::atomic<uint64_t> lds_opted{0};                                                             \
         if (opt_in_dynamic_lds((const void *)gemm_mid_kernel<AO_, KQ, ASYM>, lds_bytes, lds_opted) != W4A8_OK) \
             return W4A8_ERR_HIP;                                                                               \
-        hipLaunchKernelGGL((gemm_mid_kernel<AO_, KQ, ASYM>), dim3((unsigned)(grid_m * grid_n)),                \
+        hipLaunchKernelGGL((gemm_mid_kernel<AO_, KQ, ASYM>), dim3((unsigned)(grid_m * grid_n), (unsigned)batch.count), \
                            dim3(MD_THREADS), lds_bytes, st, Xq, sx, zp.zx, zp.wsum, (int)M, Wt, step, zero,    \
-                           (int)N, (int)K, (uint16_t *)Y, y_dtype, ldy, vec_store, acc_out, grid_m, plain);    \
+                           (int)N, (int)K, (uint16_t *)Y, y_dtype, ldy, vec_store, acc_out, grid_m, plain, batch); \
     } while (0)
     if (acc_out) W4A8_MD(true);
     else W4A8_MD(false);
@@ -1573,6 +1595,32 @@ int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, in
     if (rc != W4A8_OK || pl.splits == 1) return rc;
     return launch_gemv_combine(partial, sx, nullptr, ZeroPoint{nullptr, nullptr, nullptr}, M, N,
                                pl.splits, Y, y_dtype, ldy, st);
+}
+
+int launch_gemm_batch(const int8_t *Xq, const float *sx, int32_t *rs, int64_t M, const uint8_t *Wt, const float *step,
+                      const uint8_t *zero, int64_t N, int64_t K, int64_t G, void *Y, int y_dtype, GemmBatch batch,
+                      hipStream_t st)
+{
+    const bool grouped = G != K;
+    if (batch.count < 1 || batch.count > 65535 || M < 1 || M * K > 0x7fffffffLL || N * K / 2 > 0x7fffffffLL ||
+        (M + 63) / 64 * ((N + 127) / 128) > 0x7fffffLL)
+        return W4A8_ERR_SHAPE;
+    const ZeroPoint none = {nullptr, nullptr, nullptr};
+    GemmPlan pl{};
+    pl.splits = 1;
+    pl.kt_per_split = (int)(K / TILE_K);
+#define W4A8_GB(...) \
+    return launch_gemm_t<__VA_ARGS__>(pl, Xq, sx, none, rs, M, Wt, step, zero, N, K, G, Y, y_dtype, N, nullptr, nullptr, st, 0, 0, batch)
+    if (grouped) {
+        if (M <= 64) W4A8_GB(64, 1, 4, true);
+        W4A8_GB(128, 1, 4, true, false, 128);
+    }
+    // the tokens' row-sums, of every problem that has tokens of its own
+    const int64_t rows = batch.tokens ? M * batch.count : M;
+    hipLaunchKernelGGL(rowsum_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, Xq, rows, (int)K, 1, (int)K, rs);
+    if (hipGetLastError() != hipSuccess) return W4A8_ERR_HIP;
+    W4A8_GB(128, 1, 8, false, true);
+#undef W4A8_GB
 }
 
 }  // namespace w4a8

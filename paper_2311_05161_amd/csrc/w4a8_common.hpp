@@ -106,6 +106,14 @@ __device__ __forceinline__ uint32_t recode4(uint32_t c, uint32_t special)
     return ((c >> 1) & 0x07070707u) | (((c & 0x01010101u) ^ m) << 3);
 }
 
+// The same for eight codes (one per byte, 0 .. 15): column i of `lo` in the low nibble of byte i, of `hi` in the high one.
+__device__ __forceinline__ uint32_t recode8(uint32_t lo, uint32_t hi, uint32_t special)
+{
+    const uint32_t p = lo | (hi << 4);
+    const uint32_t m = (p >> 3) & (p >> 2) & (p >> 1) & (special * 0x11u);
+    return ((p >> 1) & 0x77777777u) | (((p & 0x11111111u) ^ m) << 3);
+}
+
 // ---- dINT4 nibble decode for the int8 matrix cores -----------------------------------------
 //
 // A stored nibble is e = l | h << 3 (see the tiled layout in w4a8.h): l in 0..6 names the pair
@@ -201,16 +209,21 @@ int launch_acc_zero_point(int32_t *acc, const int32_t *zx, const int32_t *wsum, 
                           int64_t per_token, hipStream_t st);
 // The clipping of the ranges: each is shrunk by rho = 1 - 0.05 i, i = idx[n] (or `uniform` when idx is
 // null); i = 0 leaves it as it is.
+// `count` candidates in one launch, outputs densely stacked: candidate v takes the scales s + v s_stride and the index
+// uniform + v stride.
 struct Clipping {
     const int32_t *idx;
     int uniform;
+    int count = 1;
+    int stride = 0;
+    int64_t s_stride = 0;
 };
 // codes null: only step and zero are made
 int launch_weight_quant(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw,
                         const float *s, int64_t G, int use_given, uint8_t *codes, float *step,
                         uint8_t *zero, int format, hipStream_t st, Clipping clip = Clipping{nullptr, 0});
 // dINT4 straight to the tiled packed form (step and zero as launch_weight_quant makes them), where
-// weight_quant_packs() says that the group size and alignment allow it
+// weight_quant_packs() says that the group size and alignment allow it; no clipping per row
 bool weight_quant_packs(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, int64_t G);
 int launch_weight_quant_packed(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s,
                                int64_t G, uint8_t *packed, float *step, uint8_t *zero, Clipping clip,
@@ -225,10 +238,24 @@ int launch_aqas_next_point(const float *ax, const float *aw, int64_t K, int j, f
                            int64_t N, double *losses, hipStream_t st);
 int launch_aqas_finish(const float *ax, const float *aw, int64_t K, float *s, const double *err, int64_t N,
                        double *losses, int32_t *best, hipStream_t st);
+// The same for several grid points at a time: the scales s [17][K] of all points and their reciprocals r; the
+// activations quantized with the reciprocals of `count` points (Xq [count][M][K], sx [count][M]; where
+// aqas_act_quant_applies); the losses of all points from err [17][N], the first minimum and the scale there; the clipping
+// bookkeeping of candidates i0 .. i0 + count - 1 (err [count][N]), in their order
+bool aqas_act_quant_applies(int64_t K);
+int launch_aqas_all_scales(const float *ax, const float *aw, int64_t K, float *s, float *r, hipStream_t st);
+int launch_aqas_act_quant(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, const float *r, int8_t *Xq,
+                          float *sx, int count, hipStream_t st);
+int launch_aqas_finish_all(const float *ax, const float *aw, int64_t K, float *s, const double *err, int64_t N,
+                           double *losses, int32_t *best, hipStream_t st);
+int launch_clip_pick(const double *err, int64_t N, int i0, int count, double *best_err, int32_t *best_idx,
+                     double *err_table, hipStream_t st);
 int launch_ref_gemm(const void *X, const void *W, int dtype, int64_t M, int64_t N, int64_t K,
                     int64_t ldx, int64_t ldw, float *Y, hipStream_t st);
 int launch_output_sq_error(const void *Y, int y_dtype, const float *Yref, int64_t M, int64_t N, double *err,
                            int i, double *best_err, int32_t *best_idx, double *err_table, hipStream_t st);
+// err [count][N] of fp16 outputs [count][M][N]
+int launch_sq_error_many(const void *Y, const float *Yref, int64_t M, int64_t N, double *err, int count, hipStream_t st);
 // 3-bit storage of dINT3 codes (0..5, 14 -> 6, 15 -> 7): eight codes in three bytes
 int launch_pack3(const uint8_t *codes, int64_t N, int64_t K, uint8_t *packed, hipStream_t st);
 int launch_unpack3(const uint8_t *packed, int64_t N, int64_t K, uint8_t *codes, hipStream_t st);
@@ -331,6 +358,17 @@ int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, in
                 const uint8_t *Wt, const float *step, const uint8_t *zero, int64_t N, int64_t K,
                 int64_t G, void *Y, int y_dtype, int64_t ldy, int32_t *acc_out, float *partial,
                 hipStream_t st, int plain = 0, bool rs_ready = false);
+// Independent problems of one shape in one launch, densely stacked: weights, step, zero and Y always, the tokens (Xq,
+// sx, their row-sums) `tokens` rows apart (0: the same tokens for all).
+struct GemmBatch {
+    int count;
+    int64_t tokens;
+};
+// Y [count][M][N], whole rows of K per workgroup (no workspace but the row-sums rs of per-channel weights, one per
+// token); dINT4, symmetric activations.
+int launch_gemm_batch(const int8_t *Xq, const float *sx, int32_t *rs, int64_t M, const uint8_t *Wt, const float *step,
+                      const uint8_t *zero, int64_t N, int64_t K, int64_t G, void *Y, int y_dtype, GemmBatch batch,
+                      hipStream_t st);
 // Whether launch_gemm reads the tokens' row-sums over all of K from rs (per-channel weights, K in one range):
 // a caller that has them already passes rs_ready and saves the pre-pass.
 bool gemm_reads_row_sums(int64_t M, int64_t N, int64_t K, int64_t G);

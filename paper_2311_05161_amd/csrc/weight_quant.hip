@@ -7,6 +7,8 @@
 // Range min / max of w' = W * s extended to contain zero, step = (hi - lo) / 13, 1/step and the
 // zero-point z, then Eq. 5 per element.  Every floating-point step is one binary32 operation in the
 // order of the definition (no contraction), divisions are IEEE.
+#include <algorithm>
+
 #include "w4a8_common.hpp"
 
 namespace w4a8 {
@@ -132,6 +134,20 @@ __device__ __forceinline__ float clip_factor(const Clipping &clip, int64_t n)
     return 1.0f - 0.05f * (float)(clip.idx ? clip.idx[n] : clip.uniform);
 }
 
+// blockIdx.z: candidates of a search, their scales and clipping a stride apart, their outputs densely stacked
+__device__ __forceinline__ void take_candidate(Clipping &clip, int64_t N, int64_t K, int64_t ng,
+                                               const float *__restrict__ &s, uint8_t *__restrict__ &codes,
+                                               float *__restrict__ &step, uint8_t *__restrict__ &zero)
+{
+    if (gridDim.z == 1) return;
+    const int64_t v = blockIdx.z;
+    if (s != nullptr) s += v * clip.s_stride;
+    if (codes != nullptr) codes += v * N * K;
+    step += v * N * ng;
+    zero += v * N * ng;
+    clip.uniform += (int)v * clip.stride;
+}
+
 // The V scales of a lane's V consecutive columns (1 where there is no scale vector).  Eight of
 // them with two 16-byte loads where the vector is aligned: eight dword loads strided by 32 bytes
 // over the lanes cost the memory pipeline several times as many cycles.
@@ -160,6 +176,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_kernel(
 {
     const int lane = threadIdx.x & 63;
     const int64_t ng = K / G;
+    take_candidate(clip, N, K, ng, s, codes, step, zero);
     const int64_t seg = (int64_t)blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);
     if (seg >= N * ng) return;  // whole wave leaves together
     const int64_t n = seg / ng, g = seg % ng;
@@ -273,6 +290,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_small_groups_kernel(
 {
     static_assert(ROWS == 1 || ROWS == 4, "the lanes of a quad share the work on four rows");
     constexpr int G = LANES * 8;
+    take_candidate(clip, N, K, K / G, s, codes, step, zero);
     const int lane = threadIdx.x & 63;
     const int64_t chunks = (K + 511) / 512;
     const int64_t seg = (int64_t)blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);   // (ROWS rows, chunk)
@@ -358,6 +376,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_segment_kernel(
     __shared__ float part[2 * SEG_ROWS][WQ_THREADS / WAVE];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int64_t n0 = (int64_t)blockIdx.x * SEG_ROWS, g = blockIdx.y, ng = K / G;
+    take_candidate(clip, N, K, ng, s, codes, step, zero);
     const int chunks = G / 8;
     const int64_t col = g * G;
     const bool second = n0 + 1 < N;   // (an odd last row is taken twice and stored once)
@@ -438,9 +457,11 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
 {
     const int64_t segs = N * (K / G);
     if (segs == 0) return W4A8_OK;
+    if (clip.count < 1 || clip.count > 65535) return W4A8_ERR_SHAPE;
     const int64_t blocks = (segs + (WQ_THREADS / WAVE) - 1) / (WQ_THREADS / WAVE);
     if (blocks > 0x7fffffffLL) return W4A8_ERR_SHAPE;
-    const int s_vec = (uintptr_t)s % 16 == 0;   // (G % 8 == 0 wherever eight scales are loaded at once)
+    const unsigned cands = (unsigned)clip.count;
+    const int s_vec = (uintptr_t)s % 16 == 0 && clip.s_stride % 4 == 0;   // (G % 8 == 0 wherever eight scales are loaded at once)
     const auto aligned = [&](int v) {
         return G % v == 0 && K % v == 0 && (ldw * sizeof(T)) % (v * sizeof(T)) == 0 &&
                (uintptr_t)W % (v * sizeof(T)) == 0 && (uintptr_t)codes % v == 0 && ldw % v == 0;
@@ -454,19 +475,19 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
     // 16384 x 1280 26.5 / 23.3, 4096 x 8192 in groups of 1024 33.3 / 37.7.
     const auto segment_pays = [&] {
         const int64_t rounds = (G + WAVE * 8 - 1) / (WAVE * 8);
-        return segs <= (rounds >= 3 ? 1536 : 1024) || rounds == 4 || rounds >= 6 ||
+        return segs * cands <= (rounds >= 3 ? 1536 : 1024) || rounds == 4 || rounds >= 6 ||
                (sizeof(T) == 4 && (rounds == 5 || (rounds == 3 && N * K * 4 > (70 << 20))));
     };
 #define W4A8_WQ_LAUNCH(V_)                                                                        \
-    hipLaunchKernelGGL((weight_quant_kernel<T, V_>), dim3((unsigned)blocks), dim3(WQ_THREADS), 0, \
+    hipLaunchKernelGGL((weight_quant_kernel<T, V_>), dim3((unsigned)blocks, 1, cands), dim3(WQ_THREADS), 0, \
                        st, W, N, K, ldw, s, G, use_given, codes, step, zero, fmt, s_vec, clip)
     if ((G == 128 || G == 256) && aligned(8)) {
-        const int rows = N * K <= (1 << 21) ? 1 : SG_ROWS;
+        const int rows = N * K * cands <= (1 << 21) ? 1 : SG_ROWS;
         const int64_t wsegs = (N + rows - 1) / rows * ((K + 511) / 512);
         const int64_t wblocks = (wsegs + (WQ_THREADS / WAVE) - 1) / (WQ_THREADS / WAVE);
         if (wblocks > 0x7fffffffLL) return W4A8_ERR_SHAPE;
 #define W4A8_WQ_SMALL(LANES_, ROWS_)                                                                              \
-    hipLaunchKernelGGL((weight_quant_small_groups_kernel<T, LANES_, ROWS_>), dim3((unsigned)wblocks), dim3(WQ_THREADS), \
+    hipLaunchKernelGGL((weight_quant_small_groups_kernel<T, LANES_, ROWS_>), dim3((unsigned)wblocks, 1, cands), dim3(WQ_THREADS), \
                        0, st, W, N, K, ldw, s, use_given, codes, step, zero, fmt, s_vec, clip)
         if (G == 128) {
             if (rows == 1) W4A8_WQ_SMALL(16, 1);
@@ -478,7 +499,7 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
 #undef W4A8_WQ_SMALL
     } else if (G >= 1024 && G <= SEG_MAX_CHUNKS * 8 * WQ_THREADS && aligned(8) && K / G <= 65535 &&
                N <= 0x7fffffffLL && segment_pays()) {
-        const dim3 grid((unsigned)((N + SEG_ROWS - 1) / SEG_ROWS), (unsigned)(K / G));
+        const dim3 grid((unsigned)((N + SEG_ROWS - 1) / SEG_ROWS), (unsigned)(K / G), cands);
 #define W4A8_WQ_SEGMENT(CH_)                                                                              \
     case CH_:                                                                                             \
         hipLaunchKernelGGL((weight_quant_segment_kernel<T, CH_>), grid, dim3(WQ_THREADS), 0, st, W, N, K, \
@@ -546,7 +567,8 @@ constexpr int WQT_TILES = 2;
 template <typename T>
 __global__ __launch_bounds__(WQ_THREADS) void weight_quant_packed_kernel(
     const T *__restrict__ W, uint32_t NT, uint32_t KT, int64_t ldw, const float *__restrict__ s,
-    uint32_t *__restrict__ packed, float *__restrict__ step, uint8_t *__restrict__ zero, int s_vec, Clipping clip)
+    uint32_t *__restrict__ packed, float *__restrict__ step, uint8_t *__restrict__ zero, int s_vec, Clipping clip,
+    int per_block)
 {
     const int lane = threadIdx.x & 63;
     const uint32_t wave = blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);
@@ -566,41 +588,51 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_packed_kernel(
     }
     float x[WQT_TILES][4][8];
     float lo[WQT_TILES], hi[WQT_TILES];
+    const int first = blockIdx.y * per_block, last = min(clip.count, first + per_block);
+    for (int v = first; v < last; ++v) {   // (uniform)
+        if (v == first || clip.s_stride != 0) {   // candidates with one scale differ in the clipping of the range only
+            const float *sc = s != nullptr ? s + v * clip.s_stride : nullptr;
 #pragma unroll
-    for (int i = 0; i < WQT_TILES; ++i) lo[i] = hi[i] = 0.0f;
+            for (int i = 0; i < WQT_TILES; ++i) lo[i] = hi[i] = 0.0f;
 #pragma unroll
-    for (int c = 0; c < 4; ++c) {
-        float sv[8];
-        load_scales<8>(s, k + 32 * c, s_vec, sv);
+            for (int c = 0; c < 4; ++c) {
+                float sv[8];
+                load_scales<8>(sc, k + 32 * c, s_vec, sv);
+#pragma unroll
+                for (int i = 0; i < WQT_TILES; ++i) {
+                    T e[8];
+                    raw[i][c].elements(e);
+                    scaled8(e, sv, s != nullptr, x[i][c]);
+                    min_max8(x[i][c], lo[i], hi[i]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < WQT_TILES; ++i) {
+                lo[i] = fminf(lo[i], __shfl_xor(lo[i], 16, WAVE));
+                hi[i] = fmaxf(hi[i], __shfl_xor(hi[i], 16, WAVE));
+                lo[i] = fminf(lo[i], __shfl_xor(lo[i], 32, WAVE));
+                hi[i] = fmaxf(hi[i], __shfl_xor(hi[i], 32, WAVE));
+            }
+        }
+        const float rho = clip_factor(Clipping{nullptr, clip.uniform + v * clip.stride}, 0);
+        const int64_t tiles = (int64_t)v * NT * KT;   // of the candidates before this one
 #pragma unroll
         for (int i = 0; i < WQT_TILES; ++i) {
-            T e[8];
-            raw[i][c].elements(e);
-            scaled8(e, sv, s != nullptr, x[i][c]);
-            min_max8(x[i][c], lo[i], hi[i]);
-        }
-    }
+            const int64_t n = (int64_t)nt[i] * TILE_N + row;
+            float st, istep;
+            int z;
+            range_params(lo[i] * rho, hi[i] * rho, st, istep, z);
+            if (lane < 16) {
+                step[tiles * TILE_N + n * KT + kt] = st;
+                zero[tiles * TILE_N + n * KT + kt] = (uint8_t)z;
+            }
+            const CodeRule rule = make_rule(istep, z);
+            uint32_t *tile = packed + (tiles + (int64_t)nt[i] * KT + kt) * (TILE_BYTES / 4) + row * 4 + kb;
 #pragma unroll
-    for (int i = 0; i < WQT_TILES; ++i) {
-        lo[i] = fminf(lo[i], __shfl_xor(lo[i], 16, WAVE));
-        hi[i] = fmaxf(hi[i], __shfl_xor(hi[i], 16, WAVE));
-        lo[i] = fminf(lo[i], __shfl_xor(lo[i], 32, WAVE));
-        hi[i] = fmaxf(hi[i], __shfl_xor(hi[i], 32, WAVE));
-        const int64_t n = (int64_t)nt[i] * TILE_N + row;
-        const float rho = clip_factor(clip, n);
-        float st, istep;
-        int z;
-        range_params(lo[i] * rho, hi[i] * rho, st, istep, z);
-        if (lane < 16) {
-            step[n * KT + kt] = st;
-            zero[n * KT + kt] = (uint8_t)z;
-        }
-        const CodeRule rule = make_rule(istep, z);
-        uint32_t *tile = packed + ((int64_t)nt[i] * KT + kt) * (TILE_BYTES / 4) + row * 4 + kb;
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {   // word kb of lane (row, quarter c): 256 contiguous bytes per store
-            const uint2 q = codes8(x[i][c], rule);
-            tile[c * 64] = recode4(q.x, 0x01010101u) | (recode4(q.y, 0x01010101u) << 4);
+            for (int c = 0; c < 4; ++c) {   // word kb of lane (row, quarter c): 256 contiguous bytes per store
+                const uint2 q = codes8(x[i][c], rule);
+                tile[c * 64] = recode8(q.x, q.y, 0x01010101u);
+            }
         }
     }
 }
@@ -613,17 +645,21 @@ bool weight_quant_packs(const void *W, int w_dtype, int64_t N, int64_t K, int64_
 }
 
 int launch_weight_quant_packed(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s,
-                               int64_t G, uint8_t *packed, float *step, uint8_t *zero, Clipping clip,
-                               hipStream_t st)
+                               int64_t G, uint8_t *packed, float *step, uint8_t *zero, Clipping clip, hipStream_t st)
 {
-    if (!weight_quant_packs(W, w_dtype, N, K, ldw, G) || (uintptr_t)packed % 16 != 0) return W4A8_ERR_SHAPE;
+    const int count = clip.count;
+    if (!weight_quant_packs(W, w_dtype, N, K, ldw, G) || (uintptr_t)packed % 16 != 0 || count < 1 || clip.idx != nullptr)
+        return W4A8_ERR_SHAPE;
     const uint32_t NT = (uint32_t)(N / TILE_N), KT = (uint32_t)(K / TILE_K);
     const int64_t waves = (int64_t)((NT + WQT_TILES - 1) / WQT_TILES) * KT;
-    const dim3 grid((unsigned)((waves + WQ_THREADS / WAVE - 1) / (WQ_THREADS / WAVE)));
-    const int s_vec = (uintptr_t)s % 16 == 0;
+    const int64_t blocks = (waves + WQ_THREADS / WAVE - 1) / (WQ_THREADS / WAVE);
+    // all candidates in the block that has the weights, unless that leaves CUs without work
+    const int per_block = (int)std::max<int64_t>(1, std::min<int64_t>(count, blocks * count / 1024));
+    const dim3 grid((unsigned)blocks, (unsigned)((count + per_block - 1) / per_block));
+    const int s_vec = (uintptr_t)s % 16 == 0 && clip.s_stride % 4 == 0;
 #define W4A8_WQT_LAUNCH(T_)                                                                                    \
     hipLaunchKernelGGL((weight_quant_packed_kernel<T_>), grid, dim3(WQ_THREADS), 0, st, (const T_ *)W, NT, KT, \
-                       ldw, s, (uint32_t *)packed, step, zero, s_vec, clip)
+                       ldw, s, (uint32_t *)packed, step, zero, s_vec, clip, per_block)
     switch (w_dtype) {
         case W4A8_F32: W4A8_WQT_LAUNCH(float); break;
         case W4A8_F16: W4A8_WQT_LAUNCH(__half); break;

@@ -66,3 +66,42 @@ def test_equal_scales_give_equal_losses(lib, N):
         assert (host(s) == 1.0).all()
         assert (host(losses) == host(losses)[0]).all(), (N, seed)
         assert int(host(best)[0]) == 0
+
+
+# A workspace of the size that one candidate at a time needs is enough, whatever the search would like to have; candidates
+# side by side (several rounds of them on the last shape) see the same errors to fp16 rounding of single outputs.
+@pytest.mark.parametrize("M,K,N,G,dtype", [(17, 128, 16, 128, "f16"), (300, 384, 272, 128, "bf16"), (64, 8192, 64, 128, "f16"),
+                                           (129, 512, 80, 0, "f32"), (1100, 1024, 12288, 128, "f16")])
+def test_side_by_side_against_one_by_one(lib, M, K, N, G, dtype):
+    g = torch.Generator(device="cuda").manual_seed(M)
+    X = torch.randn((M, K), generator=g, device="cuda")
+    X[:, :: 37] *= 20.0
+    X, W = X.to(DTYPES[dtype]), (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(DTYPES[dtype])
+    c, i32, f64 = lib.load_library(), torch.int32, torch.float64
+    code = {"f32": 0, "f16": 1, "bf16": 2}[dtype]
+    full = int(c.aqas_search_workspace_bytes(M, N, K, G))
+    # what one candidate at a time needs: everything but the side-by-side operands (a bound from its parts)
+    small = full
+    part = [3 * 4 * K, M * K, 4 * M, N * K, 5 * N * (K // (G or K)) + 256, N * K // 2, 6 * M * N, 16 * N,
+            int(c.w4a8_gemm_workspace_bytes(M, N, K, G, 1))]
+    small = min(full, sum(part) + 256 * 16)
+    out = {}
+    for need in (full, small):
+        ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
+        s, best, losses = (torch.empty(n, dtype=t, device="cuda") for n, t in ((K, torch.float32), (1, i32), (17, f64)))
+        stream = torch.cuda.current_stream().cuda_stream
+        assert c.aqas_search(X.data_ptr(), W.data_ptr(), code, M, N, K, K, K, G, s.data_ptr(), best.data_ptr(),
+                             losses.data_ptr(), ws.data_ptr(), need, stream) == 0
+        ng = K // (G or K)
+        idx, step, zero, table = (torch.empty(n, dtype=t, device="cuda") for n, t in
+                                  ((N, i32), (N * ng, torch.float32), (N * ng, torch.uint8), (11 * N, f64)))
+        s.fill_(1.25)
+        assert c.aqas_clip_search(X.data_ptr(), W.data_ptr(), code, M, N, K, K, K, s.data_ptr(), G, idx.data_ptr(),
+                                  step.data_ptr(), zero.data_ptr(), table.data_ptr(), ws.data_ptr(), need, stream) == 0
+        out[need] = (host(losses), host(table).reshape(11, N))
+    np.testing.assert_allclose(out[full][0], out[small][0], rtol=LOSS_TOL)
+    # single channels: a few outputs may round the other way, each by one fp16 step of its value (see the bound above)
+    ulp = 2.0 ** -10 * host((X.float() @ W.float().t()).abs().amax(0)).astype(np.float64) * 1.1
+    err = out[small][1]
+    bound = 6 * ulp * (6 * np.sqrt(err / M) + ulp)
+    assert np.all(np.abs(out[full][1] - err) <= 1e-5 * err + bound)
