@@ -134,6 +134,10 @@ int unpack_dint4(const uint8_t *packed, int64_t N, int64_t K, uint8_t *codes, in
  * faster (w4a8_gemm_workspace_bytes knows which path a shape takes).  Results are deterministic (fixed reduction order). */
 size_t w4a8_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t group_size,
                                  int layout);
+/* What w4a8_gemm would like: at least w4a8_gemm_workspace_bytes(...); more (N*K bytes and a thirtieth) for group-wise
+ * products of so many tokens that it pays to decode the weights to int8 once.  With less the call does without, with
+ * the same bits in Y. */
+size_t w4a8_gemm_workspace_preferred_bytes(int64_t M, int64_t N, int64_t K, int64_t group_size, int layout);
 int w4a8_gemm(const int8_t *Xq, const float *sx, int64_t M,
               const uint8_t *Wp, int layout, const float *step, const uint8_t *zero,
               int64_t N, int64_t K, int64_t group_size,

@@ -29,7 +29,7 @@ _DTYPES = {torch.float32: F32, torch.float16: F16, torch.bfloat16: BF16}
 
 EXPORTS = (
     "quantize_act_int8", "quantize_weight_dint4", "pack_dint4", "unpack_dint4",
-    "w4a8_gemm_workspace_bytes", "w4a8_gemm", "w4a8_status_string",
+    "w4a8_gemm_workspace_bytes", "w4a8_gemm_workspace_preferred_bytes", "w4a8_gemm", "w4a8_status_string",
     "w4a8_gemm_static", "w4a8_gemm_static_scratch_bytes", "w4a8_linear", "w4a8_linear_workspace_bytes",
     "quantize_act_int8_asym", "dint4_weight_sums", "w4a8_gemm_asym", "w4a8_gemm_batched",
     "quantize_value_dint4",
@@ -75,6 +75,8 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
     lib.unpack_dint4.restype = ci
     lib.w4a8_gemm_workspace_bytes.argtypes = [i64, i64, i64, i64, ci]
     lib.w4a8_gemm_workspace_bytes.restype = sz
+    lib.w4a8_gemm_workspace_preferred_bytes.argtypes = [i64, i64, i64, i64, ci]
+    lib.w4a8_gemm_workspace_preferred_bytes.restype = sz
     lib.w4a8_gemm.argtypes = [vp, vp, i64, vp, ci, vp, vp, i64, i64, i64, vp, ci, i64, vp, vp, sz, vp]
     lib.w4a8_gemm.restype = ci
     lib.w4a8_gemm_static.argtypes = [vp, vp, i64, vp, ci, vp, vp, i64, i64, i64, vp, ci, i64, vp, vp]
@@ -147,7 +149,7 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
     # (several threads may be here at once: each global is published complete)
     _addr = {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
              for name in ("quantize_act_int8", "quantize_act_int8_asym", "w4a8_gemm", "w4a8_gemm_asym", "w4a8_linear",
-                          "w4a8_gemm_workspace_bytes", "w4a8_linear_workspace_bytes")}
+                          "w4a8_gemm_workspace_bytes", "w4a8_gemm_workspace_preferred_bytes", "w4a8_linear_workspace_bytes")}
     _native = native
     _lib = lib
     return lib
@@ -272,7 +274,8 @@ def w4a8_gemm(Xq: torch.Tensor, sx: torch.Tensor, Wp: torch.Tensor, step: torch.
               out_dtype=torch.float16, Y=None, acc_out=None, workspace=None, want_acc=False):
     """Y [M,N] = dequant(Xq . dINT4(Wp)^T); optionally also the exact int32 accumulators."""
     if Y is None and acc_out is None and workspace is None and not want_acc:
-        out = _native_call("gemm", "w4a8_gemm", _address("w4a8_gemm"), _address("w4a8_gemm_workspace_bytes"), Xq, sx,
+        out = _native_call("gemm", "w4a8_gemm", _address("w4a8_gemm"),
+                           _address("w4a8_gemm_workspace_preferred_bytes"), Xq, sx,
                            Wp, step, zero, N, K, group_size or 0, layout, _DTYPES[out_dtype])
         if out is not NotImplemented:
             return out
@@ -282,7 +285,7 @@ def w4a8_gemm(Xq: torch.Tensor, sx: torch.Tensor, Wp: torch.Tensor, step: torch.
     G = K if group_size in (0, None) else int(group_size)
     if want_acc and acc_out is None:
         acc_out = torch.empty((M, N, K // G), dtype=torch.int32, device=Xq.device)
-    need = gemm_workspace_bytes(M, N, K, group_size, layout)
+    need = int(load_library().w4a8_gemm_workspace_preferred_bytes(M, N, K, int(group_size or 0), int(layout)))
     if workspace is None and need > 0:
         workspace = torch.empty((need,), dtype=torch.uint8, device=Xq.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()

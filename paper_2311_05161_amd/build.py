@@ -25,6 +25,7 @@ SOURCES = {
     "pack.hip": [],
     "gemm_decode.hip": [],
     "gemm_prefill.hip": [],
+    "gemm_i8.hip": [],
     "aqas_search.hip": ["-ffp-contract=off"],
     "ceilings.hip": [],
 }

@@ -39,12 +39,13 @@ struct WsPlan {
     size_t repack_off, repack_bytes;  // canonical -> tiled copy of the weights
     size_t rs_off, rs_bytes;          // per-token row-sums (M > 16, per-channel weights only)
     size_t part_off, part_bytes;      // fp32 partial sums [splits][M][N] of a launch that splits K
-    size_t total;
+    size_t total;                     // what a call has to have
+    size_t i8_off, wanted;            // int8 weights behind it where the product would use them: what it would like
 };
 
 WsPlan plan_workspace(int64_t M, int64_t N, int64_t K, int64_t G, int layout)
 {
-    WsPlan w{0, 0, 0, 0, 0, 0, 0};
+    WsPlan w{0, 0, 0, 0, 0, 0, 0, 0, 0};
     size_t off = 0;
     if (layout == W4A8_LAYOUT_CANONICAL) {
         w.repack_off = off;
@@ -68,6 +69,8 @@ WsPlan plan_workspace(int64_t M, int64_t N, int64_t K, int64_t G, int layout)
         off = align_up(off + w.part_bytes);
     }
     w.total = off;
+    w.i8_off = off;
+    w.wanted = off + (M > 16 ? gemm_i8_workspace(M, N, K, G) : 0);
     return w;
 }
 
@@ -125,7 +128,8 @@ int gemm_common(const int8_t *Xq, const float *sx, const int32_t *zx, int64_t M,
         if (rc != W4A8_OK) return rc;
     }
     const int rc = launch_gemm(Xq, sx, zp, (int32_t *)(wsb + ws.rs_off), M, Wt, step, zero, N,
-                               K, G, Y, y_dtype, ldy, acc_out, (float *)(wsb + ws.part_off), st, plain, rs_ready);
+                               K, G, Y, y_dtype, ldy, acc_out, (float *)(wsb + ws.part_off), st, plain, rs_ready,
+                               ws.wanted > ws.total && workspace_bytes >= ws.wanted ? wsb + ws.i8_off : nullptr);
     if (rc != W4A8_OK || !zx || !acc_out) return rc;
     return launch_acc_zero_point(acc_out, zx, wsum, M, N * (K / G), st);
 }
@@ -265,6 +269,14 @@ size_t w4a8_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t group_
     return plan_workspace(M, N, K, G, layout).total;
 }
 
+size_t w4a8_gemm_workspace_preferred_bytes(int64_t M, int64_t N, int64_t K, int64_t group_size, int layout)
+{
+    int64_t G = group_size;
+    if (!resolve_group(K, G) || !gemm_shape_ok(M, N, K, G) || !valid_layout(layout) || M == 0 || N == 0)
+        return 0;
+    return plan_workspace(M, N, K, G, layout).wanted;
+}
+
 int w4a8_gemm(const int8_t *Xq, const float *sx, int64_t M,
               const uint8_t *Wp, int layout, const float *step, const uint8_t *zero,
               int64_t N, int64_t K, int64_t group_size,
@@ -318,7 +330,7 @@ int w4a8_gemm_batched(const int8_t *Xq, const float *sx, const int32_t *zx, int6
 namespace {
 
 struct LinearWs {
-    size_t xq, sx, gemm, gemm_bytes, total;
+    size_t xq, sx, gemm, total, wanted;   // (the product's workspace lies last)
 };
 LinearWs plan_linear(int64_t M, int64_t N, int64_t K, int64_t G, int layout)
 {
@@ -329,8 +341,9 @@ LinearWs plan_linear(int64_t M, int64_t N, int64_t K, int64_t G, int layout)
     w.sx = off;
     off = align_up(off + (size_t)M * sizeof(float));
     w.gemm = off;
-    w.gemm_bytes = plan_workspace(M, N, K, G, layout).total;
-    w.total = off + w.gemm_bytes;
+    const WsPlan g = plan_workspace(M, N, K, G, layout);
+    w.total = off + g.total;
+    w.wanted = off + g.wanted;
     return w;
 }
 
@@ -343,7 +356,7 @@ size_t w4a8_linear_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t grou
     int64_t G = group_size;
     if (!resolve_group(K, G) || !gemm_shape_ok(M, N, K, G) || !valid_layout(layout) || M == 0 || N == 0)
         return 0;
-    return plan_linear(M, N, K, G, layout).total;
+    return plan_linear(M, N, K, G, layout).wanted;
 }
 
 int w4a8_linear(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, const float *s,
@@ -386,12 +399,12 @@ int w4a8_linear(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, c
     const LinearWs w = plan_linear(M, N, K, G, layout);
     if (!workspace || workspace_bytes < w.total || (uintptr_t)workspace % WS_ALIGN != 0) return W4A8_ERR_WORKSPACE;
     uint8_t *wsb = (uint8_t *)workspace;
+    const size_t gemm_bytes = workspace_bytes - w.gemm;
     int8_t *Xq = Xq_out ? Xq_out : (int8_t *)(wsb + w.xq);
     float *sx = sx_out ? sx_out : (float *)(wsb + w.sx);
     // (all of the GEMM's own checks before anything is launched)
     int rc = gemm_common(Xq, sx, nullptr, M, Wp, layout, step, zero, nullptr, nullptr, N, K, group_size, Y,
-                         y_dtype, ldy, acc_out, w.gemm_bytes ? wsb + w.gemm : nullptr, w.gemm_bytes, stream,
-                         W4A8_FMT_DINT4, true);
+                         y_dtype, ldy, acc_out, wsb + w.gemm, gemm_bytes, stream, W4A8_FMT_DINT4, true);
     if (rc != W4A8_OK) return rc;
     // the quantizer also leaves the row-sums that a per-channel product of many tokens would make in a pre-pass
     const bool sums = M > 16 && gemv_token_blocks(M, N, K, G) == 0 && gemm_reads_row_sums(M, N, K, G) &&
@@ -400,8 +413,7 @@ int w4a8_linear(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, c
     rc = launch_act_quant(X, x_dtype, M, K, ldx, s, Xq, sx, nullptr, st, rs);
     if (rc != W4A8_OK) return rc;
     return gemm_common(Xq, sx, nullptr, M, Wp, layout, step, zero, nullptr, nullptr, N, K, group_size, Y,
-                       y_dtype, ldy, acc_out, w.gemm_bytes ? wsb + w.gemm : nullptr, w.gemm_bytes, stream,
-                       W4A8_FMT_DINT4, false, sums);
+                       y_dtype, ldy, acc_out, wsb + w.gemm, gemm_bytes, stream, W4A8_FMT_DINT4, false, sums);
 }
 
 // ---- w4a8_gemm for callers that cannot allocate: the workspace is a static device array ----------
@@ -482,7 +494,9 @@ constexpr int AQ_GRID = 16, AQ_CLIP_STEPS = 11;
 
 struct AqasWs {
     int cand;   // candidates of a search that run side by side (1: one after the other)
-    size_t ax, aw, s, r, Xq, sx, codes, step, zero, Wp, Y, Yref, err, best_err, rs, gemm, gemm_bytes, total;
+    size_t ax, aw, s, r, Xq, sx, codes, step, zero, Wp, Y, Yref, err, best_err, rs, w8, gemm, gemm_bytes, total;
+    int64_t w_stride;   // bytes between the candidates' int8 weights
+    int parts;          // partial error sums per channel
 };
 
 // How many candidates run side by side: as many as keep their operands and outputs within 320 MiB (a good half of the
@@ -490,8 +504,8 @@ struct AqasWs {
 // itself then).
 int aqas_candidates(int64_t M, int64_t N, int64_t K, int64_t G)
 {
-    if (M <= 16 || !aqas_act_quant_applies(K) || !gemm_shape_ok(M, N, K, G)) return 1;
-    const double each = (double)M * K + (double)N * K * (G == TILE_K ? 0.5 : 1.5) + (double)N * (K / G) * 5 + (double)M * N * 2 + (double)M * 8;
+    if (M <= 16 || !aqas_act_quant_applies(K) || !gemm_shape_ok(M, N, K, G) || N * K > 0x7f000000LL) return 1;
+    const double each = (double)M * (K + 4) + (G == K ? 1.5 * N * K + 5.0 * N + (double)M * (2 * N + 4) : (double)gemm_i8_bytes(N, K));
     const double fit = 320.0 * (1 << 20) / each;
     return fit >= AQ_GRID + 1 ? AQ_GRID + 1 : fit >= 4.0 ? (int)fit : 1;
 }
@@ -505,24 +519,30 @@ AqasWs plan_aqas(int64_t M, int64_t N, int64_t K, int64_t G, int cand)
         off = align_up(off + bytes);
         return at;
     };
-    const size_t ng = (size_t)(K / G), c = (size_t)cand, points = cand > 1 ? AQ_GRID + 1 : 1;
+    const size_t ng = (size_t)(K / G), points = cand > 1 ? AQ_GRID + 1 : 1;
+    // side by side, group-wise weights are int8 and their outputs stay in the product: room for one candidate's codes on
+    // the way there, where the quantizer cannot write int8 itself
+    const size_t c = (size_t)cand, cw = cand > 1 && G == K ? c : 1;
     w.cand = cand;
+    w.parts = cand > 1 && G != K ? gemm_i8_token_tiles(M) : 1;
     w.ax = take((size_t)K * 4);
     w.aw = take((size_t)K * 4);
     w.s = take(points * K * 4);
     w.Xq = take(c * M * K);
     w.sx = take(c * M * 4);
-    w.codes = take((G == TILE_K ? 1 : c) * N * K);   // (groups of 128 go straight to the packed form)
-    w.step = take(c * N * ng * 4);
-    w.zero = take(c * N * ng);
-    w.Wp = take(c * N * K / 2);
-    w.Y = take(c * M * N * 2);
+    w.codes = take(cw * N * K);
+    w.step = take(cw * N * ng * 4);
+    w.zero = take(cw * N * ng);
+    w.Wp = take(cw * N * K / 2);
+    w.Y = take(cand > 1 && G != K ? 0 : cw * M * N * 2);
     w.Yref = take((size_t)M * N * 4);
-    w.err = take(points * N * 8);
+    w.err = take(points * w.parts * N * 8);
     w.best_err = take((size_t)N * 8);
     if (cand > 1) {
         w.r = take(points * K * 4);
         w.rs = take(c * M * 4);
+        w.w_stride = (int64_t)align_up(gemm_i8_bytes(N, K));
+        w.w8 = take(G != K ? c * w.w_stride : 0);
     } else {
         w.gemm_bytes = plan_workspace(M, N, K, G, W4A8_LAYOUT_TILED).total;
         w.gemm = take(w.gemm_bytes);
@@ -589,34 +609,38 @@ int aqas_evaluate(const void *W, int dtype, int64_t M, int64_t N, int64_t K, int
                                   err_table, st);
 }
 
-// `count` candidates side by side, errors to err [count][N]: candidate v has the scales s + v s_stride, the clipping
+// `count` candidates side by side, errors to err [count][parts][N]: candidate v has the scales s + v s_stride, the clipping
 // index clip0 + v clip_stride and, where `tokens` is M, activations of its own (0: the same for all).
 int aqas_evaluate_batch(const void *W, int dtype, int64_t M, int64_t N, int64_t K, int64_t ldw, int64_t G, const float *s,
                         int64_t s_stride, int clip0, int clip_stride, int64_t tokens, int count, uint8_t *ws,
                         const AqasWs &w, double *err, hipStream_t st)
 {
+    const int8_t *Xq = (const int8_t *)(ws + w.Xq);
+    const float *sx = (const float *)(ws + w.sx), *Yref = (const float *)(ws + w.Yref);
     float *step = (float *)(ws + w.step);
-    uint8_t *zero = ws + w.zero, *Wp = ws + w.Wp;
-    int rc;
+    uint8_t *codes = ws + w.codes, *zero = ws + w.zero, *Wp = ws + w.Wp, *w8 = ws + w.w8;
     const Clipping clip = {nullptr, clip0, count, clip_stride, s_stride};
+    const GemmBatch batch = {count, tokens};
+    int rc = W4A8_OK;
+    if (G == K) {
+        rc = launch_weight_quant(W, dtype, N, K, ldw, s, G, 0, codes, step, zero, W4A8_FMT_DINT4, st, clip);
+        if (rc == W4A8_OK) rc = launch_pack(codes, count * N, K, Wp, W4A8_LAYOUT_TILED, st);
+        if (rc == W4A8_OK)
+            rc = launch_gemm_batch(Xq, sx, (int32_t *)(ws + w.rs), M, Wp, step, zero, N, K, ws + w.Y, W4A8_F16, batch, st);
+        return rc == W4A8_OK ? launch_sq_error_many(ws + w.Y, Yref, M, N, err, count, st) : rc;
+    }
     if (weight_quant_packs(W, dtype, N, K, ldw, G)) {
-        rc = launch_weight_quant_packed(W, dtype, N, K, ldw, s, G, Wp, step, zero, clip, st);
-    } else if (G != TILE_K) {
-        rc = launch_weight_quant(W, dtype, N, K, ldw, s, G, 0, ws + w.codes, step, zero, W4A8_FMT_DINT4, st, clip);
-        if (rc == W4A8_OK) rc = launch_pack(ws + w.codes, count * N, K, Wp, W4A8_LAYOUT_TILED, st);
-    } else {   // (unaligned weights: room for the codes of one candidate)
-        rc = W4A8_OK;
+        rc = launch_weight_quant_i8(W, dtype, N, K, ldw, s, G, w8, w.w_stride, clip, st);
+    } else {   // (other groups, unaligned weights)
         for (int v = 0; v < count && rc == W4A8_OK; ++v) {
-            rc = launch_weight_quant(W, dtype, N, K, ldw, s ? s + v * s_stride : nullptr, G, 0, ws + w.codes, step + v * N * (K / G),
-                                     zero + v * N * (K / G), W4A8_FMT_DINT4, st, Clipping{nullptr, clip0 + v * clip_stride});
-            if (rc == W4A8_OK) rc = launch_pack(ws + w.codes, N, K, Wp + v * (N * K / 2), W4A8_LAYOUT_TILED, st);
+            rc = launch_weight_quant(W, dtype, N, K, ldw, s ? s + v * s_stride : nullptr, G, 0, codes, step, zero,
+                                     W4A8_FMT_DINT4, st, Clipping{nullptr, clip0 + v * clip_stride});
+            if (rc == W4A8_OK) rc = launch_pack(codes, N, K, Wp, W4A8_LAYOUT_TILED, st);
+            if (rc == W4A8_OK) rc = launch_decode_i8(Wp, step, zero, N, K, G, w8 + v * w.w_stride, 0, st);
         }
     }
     if (rc != W4A8_OK) return rc;
-    rc = launch_gemm_batch((const int8_t *)(ws + w.Xq), (const float *)(ws + w.sx), (int32_t *)(ws + w.rs), M, Wp, step,
-                           zero, N, K, G, ws + w.Y, W4A8_F16, GemmBatch{count, tokens}, st);
-    if (rc != W4A8_OK) return rc;
-    return launch_sq_error_many(ws + w.Y, (const float *)(ws + w.Yref), M, N, err, count, st);
+    return launch_gemm_i8_errors(Xq, sx, M, w8, w.w_stride, N, K, G, Yref, err, batch, st);
 }
 
 }  // namespace
@@ -673,10 +697,10 @@ int aqas_search(const void *X, const void *W, int dtype, int64_t M, int64_t N, i
             rc = launch_aqas_act_quant(X, dtype, M, K, ldx, r + j * K, (int8_t *)(ws + w.Xq), (float *)(ws + w.sx), count, st);
             if (rc != W4A8_OK) return rc;
             rc = aqas_evaluate_batch(W, dtype, M, N, K, ldw, G, s + j * K, K, 0, 0, M, count, ws, w,
-                                     (double *)(ws + w.err) + j * N, st);
+                                     (double *)(ws + w.err) + j * w.parts * N, st);
             if (rc != W4A8_OK) return rc;
         }
-        return launch_aqas_finish_all(ax, aw, K, s_out, err, N, losses, best_j, st);
+        return launch_aqas_finish_all(ax, aw, K, s_out, err, w.parts, N, losses, best_j, st);
     }
     for (int j = 0; j <= AQ_GRID; ++j) {
         if ((rc = launch_aqas_next_point(ax, aw, K, j, s, err, N, losses, st)) != W4A8_OK) return rc;
@@ -725,7 +749,7 @@ int aqas_clip_search(const void *X, const void *W, int dtype, int64_t M, int64_t
             double *err = (double *)(ws + w.err);
             rc = aqas_evaluate_batch(W, dtype, M, N, K, ldw, G, s, 0, i, 1, 0, count, ws, w, err, st);
             if (rc != W4A8_OK) return rc;
-            rc = launch_clip_pick(err, N, i, count, (double *)(ws + w.best_err), index_out, err_table, st);
+            rc = launch_clip_pick(err, w.parts, N, i, count, (double *)(ws + w.best_err), index_out, err_table, st);
             if (rc != W4A8_OK) return rc;
         }
         return launch_weight_quant(W, dtype, N, K, ldw, s, G, 0, nullptr, step_out, zero_out, W4A8_FMT_DINT4, st,

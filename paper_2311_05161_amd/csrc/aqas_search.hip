@@ -499,32 +499,54 @@ __global__ __launch_bounds__(256) void aqas_act_quant_kernel(const T *__restrict
 
 bool aqas_act_quant_applies(int64_t K) { return K % 4 == 0 && K <= 8 * 1024; }
 
-__global__ __launch_bounds__(256) void aqas_losses_kernel(const double *__restrict__ err, int64_t N,
-                                                          double *__restrict__ losses)
+// losses[j] = sum of err[j][0 .. n - 1], all through one order (1024 partial sums, four loads in flight, one tree)
+__global__ __launch_bounds__(1024) void aqas_losses_kernel(const double *__restrict__ err, int64_t n,
+                                                           double *__restrict__ losses)
 {
-    __shared__ double part[LOSS_LANES];
-    const double sum = loss_sum(err + blockIdx.x * N, N, part);
-    if (threadIdx.x == 0) losses[blockIdx.x] = sum;
+    __shared__ double part[1024];
+    const int tid = threadIdx.x;
+    const double *e = err + blockIdx.x * n;
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int64_t i = tid; i < n; i += 4096) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) s[c] += i + c * 1024 < n ? e[i + c * 1024] : 0.0;
+    }
+    part[tid] = (s[0] + s[1]) + (s[2] + s[3]);
+    __syncthreads();
+    for (int w = 512; w >= 1; w >>= 1) {
+        if (tid < w) part[tid] += part[tid + w];
+        __syncthreads();
+    }
+    if (tid == 0) losses[blockIdx.x] = part[0];
 }
 
-// a candidate replaces a channel's incumbent only if strictly better (ties keep the larger range)
-__global__ __launch_bounds__(256) void clip_pick_kernel(const double *__restrict__ err, int64_t N, int i0, int count,
-                                                        double *__restrict__ best_err, int32_t *__restrict__ best_idx,
-                                                        double *__restrict__ err_table)
+// a candidate replaces a channel's incumbent only if strictly better (ties keep the larger range); the candidates'
+// sums of a token tile are loaded together
+__global__ __launch_bounds__(64) void clip_pick_kernel(const double *__restrict__ err, int parts, int64_t N, int i0, int count,
+                                                       double *__restrict__ best_err, int32_t *__restrict__ best_idx,
+                                                       double *__restrict__ err_table)
 {
-    const int64_t n = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t n = (int64_t)blockIdx.x * 64 + threadIdx.x;
     if (n >= N) return;
+    double e[AQ_CLIP_STEPS];
+#pragma unroll
+    for (int c = 0; c < AQ_CLIP_STEPS; ++c) e[c] = 0.0;
+    for (int i = 0; i < parts; ++i)
+#pragma unroll
+        for (int c = 0; c < AQ_CLIP_STEPS; ++c)
+            if (c < count) e[c] += err[((int64_t)c * parts + i) * N + n];
     double best = 0.0;
     int32_t idx = 0;
     if (i0 > 0) {
         best = best_err[n];
         idx = best_idx[n];
     }
-    for (int c = 0; c < count; ++c) {
-        const double e = err[c * N + n];
-        if (err_table != nullptr) err_table[(i0 + c) * N + n] = e;
-        if (i0 + c == 0 || e < best) {
-            best = e;
+#pragma unroll
+    for (int c = 0; c < AQ_CLIP_STEPS; ++c) {
+        if (c >= count) break;
+        if (err_table != nullptr) err_table[(i0 + c) * N + n] = e[c];
+        if (i0 + c == 0 || e[c] < best) {
+            best = e[c];
             idx = i0 + c;
         }
     }
@@ -571,18 +593,18 @@ int launch_aqas_act_quant(const void *X, int dtype, int64_t M, int64_t K, int64_
     }
 }
 
-int launch_aqas_finish_all(const float *ax, const float *aw, int64_t K, float *s, const double *err, int64_t N,
-                           double *losses, int32_t *best, hipStream_t st)
+int launch_aqas_finish_all(const float *ax, const float *aw, int64_t K, float *s, const double *err, int parts,
+                           int64_t N, double *losses, int32_t *best, hipStream_t st)
 {
-    hipLaunchKernelGGL(aqas_losses_kernel, dim3(AQ_GRID + 1), dim3(256), 0, st, err, N, losses);
+    hipLaunchKernelGGL(aqas_losses_kernel, dim3(AQ_GRID + 1), dim3(1024), 0, st, err, parts * N, losses);
     hipLaunchKernelGGL(aqas_finish_kernel, dim3(1), dim3(1024), 0, st, ax, aw, K, s, (const double *)nullptr, N, losses, best);
     return hip_status(hipGetLastError());
 }
 
-int launch_clip_pick(const double *err, int64_t N, int i0, int count, double *best_err, int32_t *best_idx,
+int launch_clip_pick(const double *err, int parts, int64_t N, int i0, int count, double *best_err, int32_t *best_idx,
                      double *err_table, hipStream_t st)
 {
-    hipLaunchKernelGGL(clip_pick_kernel, dim3((unsigned)((N + 255) / 256)), dim3(256), 0, st, err, N, i0, count, best_err,
+    hipLaunchKernelGGL(clip_pick_kernel, dim3((unsigned)((N + 63) / 64)), dim3(64), 0, st, err, parts, N, i0, count, best_err,
                        best_idx, err_table);
     return hip_status(hipGetLastError());
 }

@@ -129,11 +129,11 @@ __global__ __launch_bounds__(WM * WN * 64, TWO ? 4 : (BN < GM_BN ? 2 : 1)) void 
 {
     // (acc_ld: channels per token row of acc_out -- N, or the whole layer's when this launch covers a
     // range of its channels)
-    if (gridDim.y > 1) {   // blockIdx.y: independent problems of one shape
+    if (TWO && gridDim.y > 1) {   // blockIdx.y: independent problems of one shape (in the instance that launch_gemm_batch takes)
         const int64_t b = blockIdx.y;
         Xq += b * batch.tokens * K;
         sx += b * batch.tokens;
-        if (!GROUPED) rs += b * batch.tokens;
+        rs += b * batch.tokens;
         Wt += b * N * K / 2;
         step += b * N * ng;
         zero += b * N * ng;
@@ -753,17 +753,8 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     const int32_t *__restrict__ wsum, int M, const uint8_t *__restrict__ Wt,
     const float *__restrict__ step, const uint8_t *__restrict__ zero, int N, int K,
     uint16_t *__restrict__ Y, int y_dtype, int64_t ldy, int vec_store, int32_t *__restrict__ acc_out,
-    int grid_m, int plain, GemmBatch batch)
+    int grid_m, int plain)
 {
-    if (gridDim.y > 1) {   // blockIdx.y: independent problems of one shape
-        const int64_t b = blockIdx.y;
-        Xq += b * batch.tokens * K;
-        sx += b * batch.tokens;
-        Wt += b * N * K / 2;
-        step += b * N * (K / TILE_K);
-        zero += b * N * (K / TILE_K);
-        Y += b * M * ldy;
-    }
     constexpr int MS = MD_BM / 32;
     constexpr int WN = 8 / KQ;       // channel parts
     constexpr int BN = 32 * WN;      // channels of the workgroup (KQ * BN = 256)
@@ -1359,8 +1350,7 @@ int gemm_mid_phases(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
 template <int KQ, bool ASYM>
 static int launch_gemm_mid_t(const int8_t *Xq, const float *sx, ZeroPoint zp, int64_t M, const uint8_t *Wt,
                              const float *step, const uint8_t *zero, int64_t N, int64_t K, void *Y, int y_dtype,
-                             int64_t ldy, int32_t *acc_out, hipStream_t st, int plain,
-                             GemmBatch batch = GemmBatch{1, 0})
+                             int64_t ldy, int32_t *acc_out, hipStream_t st, int plain)
 {
     constexpr int BN = 256 / KQ;
     const int grid_m = (int)((M + MD_BM - 1) / MD_BM);
@@ -1372,9 +1362,9 @@ static int launch_gemm_mid_t(const int8_t *Xq, const float *sx, ZeroPoint zp, in
         static std::atomic<uint64_t> lds_opted{0};                                                             \
         if (opt_in_dynamic_lds((const void *)gemm_mid_kernel<AO_, KQ, ASYM>, lds_bytes, lds_opted) != W4A8_OK) \
             return W4A8_ERR_HIP;                                                                               \
-        hipLaunchKernelGGL((gemm_mid_kernel<AO_, KQ, ASYM>), dim3((unsigned)(grid_m * grid_n), (unsigned)batch.count), \
+        hipLaunchKernelGGL((gemm_mid_kernel<AO_, KQ, ASYM>), dim3((unsigned)(grid_m * grid_n)),                \
                            dim3(MD_THREADS), lds_bytes, st, Xq, sx, zp.zx, zp.wsum, (int)M, Wt, step, zero,    \
-                           (int)N, (int)K, (uint16_t *)Y, y_dtype, ldy, vec_store, acc_out, grid_m, plain, batch); \
+                           (int)N, (int)K, (uint16_t *)Y, y_dtype, ldy, vec_store, acc_out, grid_m, plain);    \
     } while (0)
     if (acc_out) W4A8_MD(true);
     else W4A8_MD(false);
@@ -1511,10 +1501,25 @@ bool gemm_reads_row_sums(int64_t M, int64_t N, int64_t K, int64_t G)
     return G == K && (gemm_mid_pc_applies(M, N, K, G, false) || plan_gemm(M, N, K, G).splits == 1);
 }
 
+// Whether the product decodes its weights beforehand (gemm_i8.hip).  A round of 512 tiles takes 0.35 us less per k-tile on int8
+// weights (1.35 against 1.7 us, however full it is); decoding moves 1.5 bytes per weight and is a launch more.  Without /
+// with, us, groups of 128 (tokens x K x N): 2048 x 13824 x 5120 219 / 198, 4096 x 4096 x 4096 101 / 89, 2500 x 13824 x 2048 163 / 119,
+// 1300 x 8192 x 3072 102 / 76, 1536 x 5120 x 5120 65.5 / 66.5; left out: 1024 x 8192 x 8192 96 / 101, 2048 x 4096 x 4096 50.6 / 53,
+// 2048 x 2048 x 4096 28 / 34.
+size_t gemm_i8_workspace(int64_t M, int64_t N, int64_t K, int64_t G)
+{
+    if (G == K || M <= 256 || M * K > 0x7fffffffLL || N * K > 0x7f000000LL || gemm_mid_phases(M, N, K, G, false)) return 0;
+    const GemmPlan pl = plan_gemm(M, N, K, G);
+    if (pl.bm != 128 || pl.splits != 1) return 0;
+    const int64_t rounds = ((M + 127) / 128 * ((N + 127) / 128) + 511) / 512;
+    const double saved = 0.35 * (double)(K / TILE_K * rounds), spent = 6.0 + 3.2e-7 * (double)N * (double)K;
+    return saved > spent ? gemm_i8_bytes(N, K) : 0;
+}
+
 int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, int64_t M,
                 const uint8_t *Wt, const float *step, const uint8_t *zero, int64_t N, int64_t K,
                 int64_t G, void *Y, int y_dtype, int64_t ldy, int32_t *acc_out, float *partial,
-                hipStream_t st, int plain, bool rs_ready)
+                hipStream_t st, int plain, bool rs_ready, uint8_t *w8)
 {
     const bool grouped = G != K;
     if ((M + 63) / 64 * ((N + 255) / 256) * 64 > 0x7fffffLL || M * K > 0x7fffffffLL)
@@ -1546,6 +1551,19 @@ int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, in
         // 128-token group-wise tiles are 128 channels wide, four waves of 128 x 32, two workgroups per CU:
         // the same two waves per SIMD as one 256-channel workgroup, but from workgroups that do not share
         // a barrier, so that one's rescale (vector ALU only) drifts under the other's MFMAs
+        if (w8 != nullptr && zp.zx == nullptr && acc_out == nullptr && gemm_i8_workspace(M, N, K, G) > 0) {
+            // the weights decoded once (gemm_i8.hip), the same launches
+            const int64_t n1 = N - pl.rem_n;
+            rc = launch_decode_i8(Wt, step, zero, N, K, G, w8, plain, st);
+            if (rc != W4A8_OK) return rc;
+            rc = launch_gemm_i8(Xq, sx, M, w8, N, 0, n1, K, G, Y, y_dtype, ldy, 1, (int)(K / TILE_K), nullptr, st);
+            if (rc != W4A8_OK || pl.rem_n == 0) return rc;
+            rc = launch_gemm_i8(Xq, sx, M, w8, N, n1, pl.rem_n, K, G, Y, y_dtype, ldy, pl.rem_splits, pl.rem_kt_per_split,
+                                partial, st);
+            if (rc != W4A8_OK) return rc;
+            return launch_gemv_combine(partial, sx, nullptr, ZeroPoint{nullptr, nullptr, nullptr}, M, pl.rem_n, pl.rem_splits,
+                                       (uint16_t *)Y + n1, y_dtype, ldy, st);
+        }
         if (pl.bm == 64) {
             W4A8_GM(64, 1, 4, true, false);
         } else if (pl.rem_n == 0) {
@@ -1598,29 +1616,20 @@ int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, in
 }
 
 int launch_gemm_batch(const int8_t *Xq, const float *sx, int32_t *rs, int64_t M, const uint8_t *Wt, const float *step,
-                      const uint8_t *zero, int64_t N, int64_t K, int64_t G, void *Y, int y_dtype, GemmBatch batch,
-                      hipStream_t st)
+                      const uint8_t *zero, int64_t N, int64_t K, void *Y, int y_dtype, GemmBatch batch, hipStream_t st)
 {
-    const bool grouped = G != K;
     if (batch.count < 1 || batch.count > 65535 || M < 1 || M * K > 0x7fffffffLL || N * K / 2 > 0x7fffffffLL ||
         (M + 63) / 64 * ((N + 127) / 128) > 0x7fffffLL)
         return W4A8_ERR_SHAPE;
-    const ZeroPoint none = {nullptr, nullptr, nullptr};
-    GemmPlan pl{};
-    pl.splits = 1;
-    pl.kt_per_split = (int)(K / TILE_K);
-#define W4A8_GB(...) \
-    return launch_gemm_t<__VA_ARGS__>(pl, Xq, sx, none, rs, M, Wt, step, zero, N, K, G, Y, y_dtype, N, nullptr, nullptr, st, 0, 0, batch)
-    if (grouped) {
-        if (M <= 64) W4A8_GB(64, 1, 4, true);
-        W4A8_GB(128, 1, 4, true, false, 128);
-    }
     // the tokens' row-sums, of every problem that has tokens of its own
     const int64_t rows = batch.tokens ? M * batch.count : M;
     hipLaunchKernelGGL(rowsum_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, Xq, rows, (int)K, 1, (int)K, rs);
     if (hipGetLastError() != hipSuccess) return W4A8_ERR_HIP;
-    W4A8_GB(128, 1, 8, false, true);
-#undef W4A8_GB
+    GemmPlan pl{};
+    pl.splits = 1;
+    pl.kt_per_split = (int)(K / TILE_K);
+    return launch_gemm_t<128, 1, 8, false, true>(pl, Xq, sx, ZeroPoint{nullptr, nullptr, nullptr}, rs, M, Wt, step, zero, N, K,
+                                                 K, Y, y_dtype, N, nullptr, nullptr, st, 0, 0, batch);
 }
 
 }  // namespace w4a8

@@ -223,11 +223,14 @@ int launch_weight_quant(const void *W, int w_dtype, int64_t N, int64_t K, int64_
                         const float *s, int64_t G, int use_given, uint8_t *codes, float *step,
                         uint8_t *zero, int format, hipStream_t st, Clipping clip = Clipping{nullptr, 0});
 // dINT4 straight to the tiled packed form (step and zero as launch_weight_quant makes them), where
-// weight_quant_packs() says that the group size and alignment allow it; no clipping per row
+// weight_quant_packs() says that the group size and alignment allow it; no clipping per row.  launch_weight_quant_i8: to
+// int8 weights with their scales, candidates w_stride bytes apart.
 bool weight_quant_packs(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, int64_t G);
 int launch_weight_quant_packed(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s,
                                int64_t G, uint8_t *packed, float *step, uint8_t *zero, Clipping clip,
                                hipStream_t st);
+int launch_weight_quant_i8(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s, int64_t G,
+                           uint8_t *W8, int64_t w_stride, Clipping clip, hipStream_t st);
 // AQAS scale search helpers (aqas_search.hip)
 int launch_channel_absmax(const void *A, int dtype, int64_t R, int64_t K, int64_t lda, float *out,
                           hipStream_t st);
@@ -246,9 +249,10 @@ bool aqas_act_quant_applies(int64_t K);
 int launch_aqas_all_scales(const float *ax, const float *aw, int64_t K, float *s, float *r, hipStream_t st);
 int launch_aqas_act_quant(const void *X, int dtype, int64_t M, int64_t K, int64_t ldx, const float *r, int8_t *Xq,
                           float *sx, int count, hipStream_t st);
-int launch_aqas_finish_all(const float *ax, const float *aw, int64_t K, float *s, const double *err, int64_t N,
+// (parts: err has that many partial sums per channel, [17 or count][parts][N])
+int launch_aqas_finish_all(const float *ax, const float *aw, int64_t K, float *s, const double *err, int parts, int64_t N,
                            double *losses, int32_t *best, hipStream_t st);
-int launch_clip_pick(const double *err, int64_t N, int i0, int count, double *best_err, int32_t *best_idx,
+int launch_clip_pick(const double *err, int parts, int64_t N, int i0, int count, double *best_err, int32_t *best_idx,
                      double *err_table, hipStream_t st);
 int launch_ref_gemm(const void *X, const void *W, int dtype, int64_t M, int64_t N, int64_t K,
                     int64_t ldx, int64_t ldw, float *Y, hipStream_t st);
@@ -354,21 +358,45 @@ struct GemmPlan {
     int pc_rem_n;
 };
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t G);
+// w8 != null (16-byte aligned, gemm_i8_workspace bytes): room for the weights as int8, for the products that pay
+// for decoding them beforehand
 int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, int64_t M,
                 const uint8_t *Wt, const float *step, const uint8_t *zero, int64_t N, int64_t K,
                 int64_t G, void *Y, int y_dtype, int64_t ldy, int32_t *acc_out, float *partial,
-                hipStream_t st, int plain = 0, bool rs_ready = false);
+                hipStream_t st, int plain = 0, bool rs_ready = false, uint8_t *w8 = nullptr);
 // Independent problems of one shape in one launch, densely stacked: weights, step, zero and Y always, the tokens (Xq,
 // sx, their row-sums) `tokens` rows apart (0: the same tokens for all).
 struct GemmBatch {
     int count;
     int64_t tokens;
 };
-// Y [count][M][N], whole rows of K per workgroup (no workspace but the row-sums rs of per-channel weights, one per
-// token); dINT4, symmetric activations.
+// Bytes that launch_gemm would like for int8 weights (0: it would not use them).
+size_t gemm_i8_workspace(int64_t M, int64_t N, int64_t K, int64_t G);
+// int8 weights of group-wise layers: blocks of 32 channels x 128 columns, block (n / 32, kt) at ((n / 32) (K / 128) + kt) * 4096; in
+// it, k-step s = 2 sp + h (1 KB) holds for lane r32 + 32 kh the 16 bytes of channel r32, columns 64 sp + 32 kh + 16 h ..: the
+// columns of the k-tile that the activation fragments of that step have.  Values: four times the weight in half steps.
+// Behind the blocks step / 8 as [group][channel], rows of i8_es_ld(N).  Channels past N are never written, and what
+// they give is not stored.
+constexpr int I8_BLOCK = 4096;
+__host__ __device__ inline int i8_es_ld(int N) { return (N + 255) / 256 * 256; }
+__host__ __device__ inline int64_t i8_scales_offset(int64_t N, int64_t K) { return (N + 31) / 32 * 32 * K; }
+// Group-wise product on weights decoded to int8 (gemm_i8.hip): whole rows of K per workgroup, symmetric activations.
+size_t gemm_i8_bytes(int64_t N, int64_t K);
+int launch_decode_i8(const uint8_t *Wt, const float *step, const uint8_t *zero, int64_t N, int64_t K, int64_t G, uint8_t *W8, int plain,
+                     hipStream_t st);
+// channels n0 (a multiple of 128) .. n0 + n - 1 of N; splits > 1: K in ranges of kt_per_split k-tiles, their fp32 sums to
+// partial [splits][M][n] (launch_gemv_combine finishes)
+int launch_gemm_i8(const int8_t *Xq, const float *sx, int64_t M, const uint8_t *W8, int64_t N, int64_t n0, int64_t n, int64_t K,
+                   int64_t G, void *Y, int y_dtype, int64_t ldy, int splits, int kt_per_split, float *partial, hipStream_t st);
+// Calibration: candidates side by side, weights w_stride bytes apart, tokens as in GemmBatch; err
+// [count][gemm_i8_token_tiles(M)][N] = per token tile, sum of squared differences between fp16 outputs and Yref [M][N]
+int gemm_i8_token_tiles(int64_t M);
+int launch_gemm_i8_errors(const int8_t *Xq, const float *sx, int64_t M, const uint8_t *W8, int64_t w_stride, int64_t N,
+                          int64_t K, int64_t G, const float *Yref, double *err, GemmBatch batch, hipStream_t st);
+// Y [count][M][N] of per-channel layers, whole rows of K per workgroup (rs: room for the tokens' row-sums); dINT4,
+// symmetric activations.
 int launch_gemm_batch(const int8_t *Xq, const float *sx, int32_t *rs, int64_t M, const uint8_t *Wt, const float *step,
-                      const uint8_t *zero, int64_t N, int64_t K, int64_t G, void *Y, int y_dtype, GemmBatch batch,
-                      hipStream_t st);
+                      const uint8_t *zero, int64_t N, int64_t K, void *Y, int y_dtype, GemmBatch batch, hipStream_t st);
 // Whether launch_gemm reads the tokens' row-sums over all of K from rs (per-channel weights, K in one range):
 // a caller that has them already passes rs_ready and saves the pre-pass.
 bool gemm_reads_row_sums(int64_t M, int64_t N, int64_t K, int64_t G);

@@ -290,7 +290,6 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_small_groups_kernel(
 {
     static_assert(ROWS == 1 || ROWS == 4, "the lanes of a quad share the work on four rows");
     constexpr int G = LANES * 8;
-    take_candidate(clip, N, K, K / G, s, codes, step, zero);
     const int lane = threadIdx.x & 63;
     const int64_t chunks = (K + 511) / 512;
     const int64_t seg = (int64_t)blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);   // (ROWS rows, chunk)
@@ -481,13 +480,13 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
 #define W4A8_WQ_LAUNCH(V_)                                                                        \
     hipLaunchKernelGGL((weight_quant_kernel<T, V_>), dim3((unsigned)blocks, 1, cands), dim3(WQ_THREADS), 0, \
                        st, W, N, K, ldw, s, G, use_given, codes, step, zero, fmt, s_vec, clip)
-    if ((G == 128 || G == 256) && aligned(8)) {
-        const int rows = N * K * cands <= (1 << 21) ? 1 : SG_ROWS;
+    if ((G == 128 || G == 256) && aligned(8) && cands == 1) {   // (candidates: per-channel layers of 128 or 256 columns only)
+        const int rows = N * K <= (1 << 21) ? 1 : SG_ROWS;
         const int64_t wsegs = (N + rows - 1) / rows * ((K + 511) / 512);
         const int64_t wblocks = (wsegs + (WQ_THREADS / WAVE) - 1) / (WQ_THREADS / WAVE);
         if (wblocks > 0x7fffffffLL) return W4A8_ERR_SHAPE;
 #define W4A8_WQ_SMALL(LANES_, ROWS_)                                                                              \
-    hipLaunchKernelGGL((weight_quant_small_groups_kernel<T, LANES_, ROWS_>), dim3((unsigned)wblocks, 1, cands), dim3(WQ_THREADS), \
+    hipLaunchKernelGGL((weight_quant_small_groups_kernel<T, LANES_, ROWS_>), dim3((unsigned)wblocks), dim3(WQ_THREADS), \
                        0, st, W, N, K, ldw, s, use_given, codes, step, zero, fmt, s_vec, clip)
         if (G == 128) {
             if (rows == 1) W4A8_WQ_SMALL(16, 1);
@@ -564,11 +563,30 @@ int launch_weight_quant(const void *W, int w_dtype, int64_t N, int64_t K, int64_
 // one after the other).  4096 x 4096 fp16: 14.7 + 5.5 -> 13.4 us.
 constexpr int WQT_TILES = 2;
 
-template <typename T>
+// Eight weights -> four times their value in half steps, as bytes: 8 (code - z), or +-4 for the special codes (the rule of
+// code_byte without the zero-point).
+__device__ __forceinline__ uint32_t level_byte(float x, const CodeRule &r)   // twice the level's quarter, in the low byte
+{
+    const float u = x * r.istep;
+    const uint32_t c = __float_as_uint(__builtin_amdgcn_fmed3f(u, r.lo, r.hi) + 12582912.0f) << 1;
+    const uint32_t bits = __float_as_uint(u);
+    const uint32_t sp = (uint32_t)((int)bits >> 31) | 1u;   // +-1
+    return (bits << 1) - r.band_lo < r.band_span ? sp : c;
+}
+__device__ __forceinline__ uint2 levels8(const float (&x)[8], const CodeRule &r)
+{
+    uint32_t b[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) b[j] = level_byte(x[j], r);
+    return make_uint2((pack_low_bytes(b[0], b[1], b[2], b[3]) << 2) & 0xfcfcfcfcu,
+                      (pack_low_bytes(b[4], b[5], b[6], b[7]) << 2) & 0xfcfcfcfcu);
+}
+
+template <typename T, bool I8>
 __global__ __launch_bounds__(WQ_THREADS) void weight_quant_packed_kernel(
     const T *__restrict__ W, uint32_t NT, uint32_t KT, int64_t ldw, const float *__restrict__ s,
     uint32_t *__restrict__ packed, float *__restrict__ step, uint8_t *__restrict__ zero, int s_vec, Clipping clip,
-    int per_block)
+    int per_block, int64_t w_stride, int64_t scales_offset, int es_ld)
 {
     const int lane = threadIdx.x & 63;
     const uint32_t wave = blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);
@@ -622,16 +640,27 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_packed_kernel(
             float st, istep;
             int z;
             range_params(lo[i] * rho, hi[i] * rho, st, istep, z);
-            if (lane < 16) {
-                step[tiles * TILE_N + n * KT + kt] = st;
-                zero[tiles * TILE_N + n * KT + kt] = (uint8_t)z;
-            }
             const CodeRule rule = make_rule(istep, z);
-            uint32_t *tile = packed + (tiles + (int64_t)nt[i] * KT + kt) * (TILE_BYTES / 4) + row * 4 + kb;
+            if constexpr (I8) {
+                uint8_t *w8 = reinterpret_cast<uint8_t *>(packed) + v * w_stride;
+                if (lane < 16) reinterpret_cast<float *>(w8 + scales_offset)[(int64_t)kt * es_ld + n] = st * 0.125f;
+                // columns 32 c + 8 kb ..: k-step 2 (c / 2) + kb / 2, lanes of half c % 2, upper or lower eight bytes
+                uint8_t *block = w8 + ((int64_t)(nt[i] >> 1) * KT + kt) * I8_BLOCK + (kb >> 1) * 1024 +
+                                 ((nt[i] & 1) * 16 + row) * 16 + (kb & 1) * 8;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) {   // word kb of lane (row, quarter c): 256 contiguous bytes per store
-                const uint2 q = codes8(x[i][c], rule);
-                tile[c * 64] = recode8(q.x, q.y, 0x01010101u);
+                for (int c = 0; c < 4; ++c)
+                    *reinterpret_cast<uint2 *>(block + (c >> 1) * 2048 + (c & 1) * 512) = levels8(x[i][c], rule);
+            } else {
+                if (lane < 16) {
+                    step[tiles * TILE_N + n * KT + kt] = st;
+                    zero[tiles * TILE_N + n * KT + kt] = (uint8_t)z;
+                }
+                uint32_t *tile = packed + (tiles + (int64_t)nt[i] * KT + kt) * (TILE_BYTES / 4) + row * 4 + kb;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {   // word kb of lane (row, quarter c): 256 contiguous bytes per store
+                    const uint2 q = codes8(x[i][c], rule);
+                    tile[c * 64] = recode8(q.x, q.y, 0x01010101u);
+                }
             }
         }
     }
@@ -644,11 +673,14 @@ bool weight_quant_packs(const void *W, int w_dtype, int64_t N, int64_t K, int64_
            (N / TILE_N) * (K / TILE_K) <= 0x7fffffffLL;
 }
 
-int launch_weight_quant_packed(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s,
-                               int64_t G, uint8_t *packed, float *step, uint8_t *zero, Clipping clip, hipStream_t st)
+template <bool I8>
+static int launch_weight_quant_tiles(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s,
+                                     int64_t G, uint8_t *out, float *step, uint8_t *zero, Clipping clip, int64_t w_stride,
+                                     hipStream_t st)
 {
     const int count = clip.count;
-    if (!weight_quant_packs(W, w_dtype, N, K, ldw, G) || (uintptr_t)packed % 16 != 0 || count < 1 || clip.idx != nullptr)
+    if (!weight_quant_packs(W, w_dtype, N, K, ldw, G) || (uintptr_t)out % 16 != 0 || w_stride % 16 != 0 || count < 1 ||
+        clip.idx != nullptr)
         return W4A8_ERR_SHAPE;
     const uint32_t NT = (uint32_t)(N / TILE_N), KT = (uint32_t)(K / TILE_K);
     const int64_t waves = (int64_t)((NT + WQT_TILES - 1) / WQT_TILES) * KT;
@@ -658,8 +690,9 @@ int launch_weight_quant_packed(const void *W, int w_dtype, int64_t N, int64_t K,
     const dim3 grid((unsigned)blocks, (unsigned)((count + per_block - 1) / per_block));
     const int s_vec = (uintptr_t)s % 16 == 0 && clip.s_stride % 4 == 0;
 #define W4A8_WQT_LAUNCH(T_)                                                                                    \
-    hipLaunchKernelGGL((weight_quant_packed_kernel<T_>), grid, dim3(WQ_THREADS), 0, st, (const T_ *)W, NT, KT, \
-                       ldw, s, (uint32_t *)packed, step, zero, s_vec, clip, per_block)
+    hipLaunchKernelGGL((weight_quant_packed_kernel<T_, I8>), grid, dim3(WQ_THREADS), 0, st, (const T_ *)W, NT, KT, \
+                       ldw, s, (uint32_t *)out, step, zero, s_vec, clip, per_block, w_stride, i8_scales_offset(N, K), \
+                       i8_es_ld((int)N))
     switch (w_dtype) {
         case W4A8_F32: W4A8_WQT_LAUNCH(float); break;
         case W4A8_F16: W4A8_WQT_LAUNCH(__half); break;
@@ -668,6 +701,18 @@ int launch_weight_quant_packed(const void *W, int w_dtype, int64_t N, int64_t K,
     }
 #undef W4A8_WQT_LAUNCH
     return hip_status(hipGetLastError());
+}
+
+int launch_weight_quant_packed(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s,
+                               int64_t G, uint8_t *packed, float *step, uint8_t *zero, Clipping clip, hipStream_t st)
+{
+    return launch_weight_quant_tiles<false>(W, w_dtype, N, K, ldw, s, G, packed, step, zero, clip, 0, st);
+}
+
+int launch_weight_quant_i8(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s, int64_t G,
+                           uint8_t *W8, int64_t w_stride, Clipping clip, hipStream_t st)
+{
+    return launch_weight_quant_tiles<true>(W, w_dtype, N, K, ldw, s, G, W8, nullptr, nullptr, clip, w_stride, st);
 }
 
 // ---- 4-bit Value cache (Sec. 5.1; App. A.1: channel-wise along the dimension the product with the
