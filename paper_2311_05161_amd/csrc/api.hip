@@ -113,7 +113,8 @@ int gemm_common(const int8_t *Xq, const float *sx, const int32_t *zx, int64_t M,
         if (rc != W4A8_OK) return rc;
         Wt = tiled;
     }
-    if (M <= 16 || gemv_token_blocks(M, N, K, G) > 0) {   // the streaming kernel, also for a few 16-token blocks
+    // the streaming kernel, also for a few 16-token blocks
+    if (M <= 16 || (gemv_token_blocks(M, N, K, G) > 0 && gemm_mid_form(M, N, K, G, zx != nullptr).phases == 0)) {
         if (acc_out) {  // the split-K waves add exact partial sums into it
             const int rc = launch_fill_i32(acc_out, M * N * (K / G), 0, st);
             if (rc != W4A8_OK) return rc;

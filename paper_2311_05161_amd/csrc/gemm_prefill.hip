@@ -744,10 +744,10 @@ static int launch_gemm_t(const GemmPlan &pl, const int8_t *Xq, const float *sx, 
 // (q0 + q1, or (q0 + q1) + (q2 + q3)), and the phase-0 waves apply the token scale and store.  No workspace, no second
 // launch.  KQ = 4: 64 channels per workgroup; KQ = 2: 128, for twice the tiles on the same CUs.
 // ASYM: token zero-points, one 24-bit multiply-add per accumulator and group as in gemm_kernel.
-constexpr int MD_BM = 128, MD_BN = 64, MD_KQ = 4, MD_THREADS = 512;
-constexpr int MD_TILE = MD_BM * TILE_K;   // bytes of one activation k-tile in LDS
+// MS: 32-token blocks of the workgroup, two to four (see gemm_mid_form).
+constexpr int MD_BN = 64, MD_KQ = 4, MD_THREADS = 512;
 
-template <bool ACC_OUT, int KQ, bool ASYM>
+template <bool ACC_OUT, int KQ, bool ASYM, int MS>
 __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     const int8_t *__restrict__ Xq, const float *__restrict__ sx, const int32_t *__restrict__ zx,
     const int32_t *__restrict__ wsum, int M, const uint8_t *__restrict__ Wt,
@@ -755,7 +755,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     uint16_t *__restrict__ Y, int y_dtype, int64_t ldy, int vec_store, int32_t *__restrict__ acc_out,
     int grid_m, int plain)
 {
-    constexpr int MS = MD_BM / 32;
+    constexpr int MD_BM = 32 * MS, MD_TILE = MD_BM * TILE_K;   // tokens; bytes of one activation k-tile in LDS
     constexpr int WN = 8 / KQ;       // channel parts
     constexpr int BN = 32 * WN;      // channels of the workgroup (KQ * BN = 256)
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];   // [2 * KQ][MD_TILE]
@@ -799,30 +799,32 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         dst[1] = __builtin_amdgcn_raw_buffer_load_b128(rw, wvoff + 512, wsoff + ktc * TILE_BYTES, 0);
     };
 
-    // activation k-tile -> LDS slot: 16 blocks of 8 rows, two per wave (swizzle as in gemm_kernel)
-    int avoff[2];
+    // activation k-tiles of a super-step -> LDS slots: KQ k-tiles of 4 MS blocks of 8 rows (1 KB each, swizzle as in
+    // gemm_kernel), CPW of them per wave: block q = 8 c + wave is rows 8 (q % (4 MS)) .. of k-tile q / (4 MS)
+    constexpr int TB = 4 * MS, CPW = KQ * TB / 8;
+    constexpr int OFFS = MS == 4 ? 2 : MS == 3 ? 3 : 1;   // (the row offsets repeat after so many of a wave's copies: 8 OFFS % TB == 0)
+    int avoff[OFFS];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int row = (i * 8 + wave) * 8 + (lane >> 3);
-        avoff[i] = (m0 + row) * K + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
+    for (int c = 0; c < OFFS; ++c) {
+        const int row = (c * 8 + wave) % TB * 8 + (lane >> 3);
+        avoff[c] = (m0 + row) * K + (((lane & 7) ^ ((row >> 1) & 7)) << 4);
     }
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)lds_raw;
-    // this wave's share of the KQ k-tiles of super-step ss (into the slots of its parity): 2 KQ copies
-    // of 1 KB, c = 2 j + i for block i of k-tile j
+    // copy c of this wave for super-step ss (into the slots of its parity)
     auto dma_one = [&](int ss, int c) {
-        const int j = c >> 1, i = c & 1;
+        const int q = c * 8 + wave, j = q / TB;
         const int kt = min(ss * KQ + j, KT - 1);
         const int slot = (ss & 1) * KQ + j;
-        dma_b128(rx, avoff[i], kt * TILE_K, lds_base + (uint32_t)(slot * MD_TILE + (i * 8 + wave) * 1024));
+        dma_b128(rx, avoff[c % OFFS], kt * TILE_K, lds_base + (uint32_t)(slot * MD_TILE + (q - j * TB) * 1024));
     };
     auto dma_super_step = [&](int ss) {
 #pragma unroll
-        for (int c = 0; c < 2 * KQ; ++c) dma_one(ss, c);
+        for (int c = 0; c < CPW; ++c) dma_one(ss, c);
     };
     // group parameters of a super-step: thread (j = tid / BN, ch = tid % BN), tid < 256
     float gp_es = 0.f;
     int gp_z = 0, gp_w = 0;
-    auto fetch_params = [&](int ss) {
+    auto fetch_params = [&](int ss, float &gp_es, int &gp_z, int &gp_w) {
         if (tid < KQ * BN) {
             const int kt = min(ss * KQ + tid / BN, KT - 1);
             const int nn = nb0 + tid % BN < N ? nb0 + tid % BN : 0;
@@ -831,7 +833,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
             if (ASYM) gp_w = wsum[(int64_t)nn * KT + kt];
         }
     };
-    auto publish_params = [&](int ss) {
+    auto publish_params = [&](int ss, float gp_es, int gp_z, int gp_w) {
         if (tid < KQ * BN) {
             s_ges[(ss & 3) * KQ + tid / BN][tid % BN] = gp_es * 0.125f;
             s_gz[(ss & 3) * KQ + tid / BN][tid % BN] = gp_z;
@@ -891,11 +893,16 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     dma_super_step(0);
 #pragma unroll
     for (int i = 0; i < 4; ++i) load_b(i * KQ + kq, pw[i]);
-    fetch_params(0);
-    publish_params(0);
-    fetch_params(min(1, SS - 1));
-    publish_params(1);
-    fetch_params(min(2, SS - 1));
+    {   // (all three super-steps' on their way before the first is waited for)
+        float es0 = 0.f, es1 = 0.f;
+        int z0 = 0, z1 = 0, w0 = 0, w1 = 0;
+        fetch_params(0, es0, z0, w0);
+        fetch_params(min(1, SS - 1), es1, z1, w1);
+        fetch_params(min(2, SS - 1), gp_es, gp_z, gp_w);
+        gm_order_fence();
+        publish_params(0, es0, z0, w0);
+        publish_params(1, es1, z1, w1);
+    }
     asm volatile("" : "+v"(pw[0][0]), "+v"(pw[0][1]), "+v"(pw[1][0]), "+v"(pw[1][1]));
     wait_copies<0>();
     __syncthreads();
@@ -904,7 +911,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     slut = make_signed_lut(s_gz[kq][wn * 32 + r32], plain != 0);
 #pragma unroll
     for (int k = 0; k < 4; ++k) decode_step(pw[0], k, w[k]);
-    bool pending = false;   // (uniform) accumulators of token block 3 of the previous k-tile wait for their rescale
+    bool pending = false;   // (uniform) accumulators of the last token block of the previous k-tile wait for their rescale
 
     // One super-step of this wave: k-tile kt = 4 ss + q (= one group) from LDS slot (ss parity, q).
     // The MFMAs run token block by token block (four k-steps each), so that the rescale of block ms - 1
@@ -935,7 +942,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         }
         if (pending) {
 #pragma unroll
-            for (int b = 0; b < 4; ++b) flush_quarter(3, b, kt - KQ);
+            for (int b = 0; b < 4; ++b) flush_quarter(MS - 1, b, kt - KQ);
             pending = false;
         }
         if (live) {
@@ -967,7 +974,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
                     // by all eight waves they fill the address queue of the CU and hold every wave up
                     if (ms == 0) {
 #pragma unroll
-                        for (int c = 0; c < KQ / 2; ++c) dma_one(ss + 1, k * (KQ / 2) + c);
+                        for (int c = CPW * k / 4; c < CPW * (k + 1) / 4; ++c) dma_one(ss + 1, c);
                     }
                     if (ms > 0) flush_quarter(ms - 1, k, kt);
                     if (ms + 1 == MS) {
@@ -991,9 +998,9 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         // (a use in every lane, outside any branch: all waits for the parameter loads and for PNN happen
         // here, none behind the copies issued below)
         asm volatile("" : "+v"(PNN[0]), "+v"(PNN[1]), "+v"(gp_es), "+v"(gp_z), "+v"(gp_w));
-        publish_params(ss + 2);   // (fetched behind the last barrier)
+        publish_params(ss + 2, gp_es, gp_z, gp_w);   // (fetched behind the last barrier)
         __syncthreads();
-        fetch_params(min(ss + 3, SS - 1));
+        fetch_params(min(ss + 3, SS - 1), gp_es, gp_z, gp_w);
         gm_order_fence();
     };
 
@@ -1011,48 +1018,65 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         if (pending) {   // the last live k-tile of this wave: KQ (SS - 1) + q, or the one before
             const int kt_last = (SS - 1) * KQ + kq;
 #pragma unroll
-            for (int b = 0; b < 4; ++b) flush_quarter(3, b, kt_last < KT ? kt_last : kt_last - KQ);
+            for (int b = 0; b < 4; ++b) flush_quarter(MS - 1, b, kt_last < KT ? kt_last : kt_last - KQ);
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
-    // ---- the phases' sums meet in LDS: q0 + q1, or (q0 + q1) + (q2 + q3)
-    float *red = reinterpret_cast<float *>(lds_raw);   // [..][64 lanes][64 floats], 16 KB per wave
-    auto red_ptr = [&](int slot) { return red + ((size_t)slot * 64 + lane) * 64; };
-    auto put = [&](int slot) {
+    // ---- the phases' sums meet in LDS: q0 + q1, or (q0 + q1) + (q2 + q3).  The two waves of a pair exchange halves:
+    // each hands over the token blocks that the other one finishes, LO of them the even phase's; likewise the pairs, so
+    // that all eight waves add and store (with the parameters of the first three super-steps on their way together instead of one
+    // after the other 512 x 4096 x 4096 22.9 -> 20.2 us).
+    v4f *red = reinterpret_cast<v4f *>(lds_raw);   // [wave][quarter][64 lanes]
+    constexpr int LO = (MS + 1) / 2;
+    auto put = [&](int ms, int at) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+            red[((wave * MS + at) * 4 + r) * 64 + lane] = v4f{y[ms][4 * r], y[ms][4 * r + 1], y[ms][4 * r + 2], y[ms][4 * r + 3]};
+    };
+    auto add = [&](int ms, int from, int at) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const v4f t = red[((from * MS + at) * 4 + r) * 64 + lane];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y[ms][4 * r + i] += t[i];
+        }
+    };
+    int first = 0, last = MS;   // this wave's token blocks
+    {
+        const bool odd = kq & 1;
 #pragma unroll
         for (int ms = 0; ms < MS; ++ms)
-#pragma unroll
-            for (int r = 0; r < 16; r += 4)
-                *reinterpret_cast<v4f *>(red_ptr(slot) + ((ms * 16 + r) ^ ((lane & 15) << 2))) =
-                    v4f{y[ms][r], y[ms][r + 1], y[ms][r + 2], y[ms][r + 3]};
-    };
-    auto add = [&](int slot) {
+            if ((ms < LO) == odd) put(ms, ms);
+        __syncthreads();
+        const int peer = wave + (odd ? -WN : WN);
 #pragma unroll
         for (int ms = 0; ms < MS; ++ms)
-#pragma unroll
-            for (int r = 0; r < 16; r += 4) {
-                const v4f t = *reinterpret_cast<const v4f *>(red_ptr(slot) + ((ms * 16 + r) ^ ((lane & 15) << 2)));
-                y[ms][r] += t.x; y[ms][r + 1] += t.y; y[ms][r + 2] += t.z; y[ms][r + 3] += t.w;
-            }
-    };
-    if (kq & 1) put((kq >> 1) * WN + wn);         // q1 -> the first WN slots, q3 -> the next
-    __syncthreads();
-    if (!(kq & 1)) add((kq >> 1) * WN + wn);      // q0 += q1, q2 += q3
-    if constexpr (KQ == 4) {
-        __syncthreads();
-        if (kq == 2) put(wn);
-        __syncthreads();
-        if (kq == 0) add(wn);
+            if ((ms < LO) != odd) add(ms, peer, ms);
+        if (odd) first = LO;
+        else last = LO;
     }
-    if (kq != 0) return;
+    if constexpr (KQ == 4) {   // q0 and q2 have the lower blocks of their pairs' sums, q1 and q3 the upper ones
+        __syncthreads();
+        const bool upper = kq >= 2;
+        const int mid = (first + last + 1) / 2, peer = wave + (upper ? -2 * WN : 2 * WN);
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+            if (ms >= first && ms < last && (ms < mid) == upper) put(ms, ms);
+        __syncthreads();
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+            if (ms >= first && ms < last && (ms < mid) != upper) add(ms, peer, ms);
+        if (upper) first = mid;
+        else last = mid;
+    }
 
-    // ---- epilogue (phase-0 waves): Y[m, n .. n+3] = cast(sx[m] * y)
+    // ---- epilogue: Y[m, n .. n+3] = cast(sx[m] * y)
 #pragma unroll
     for (int ms = 0; ms < MS; ++ms) {
         const int m = m0 + ms * 32 + r32;
-        if (m >= M) continue;
+        if (ms < first || ms >= last || m >= M) continue;
         const float sxm = sx[m];
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
@@ -1312,7 +1336,8 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_pc_kernel(
     }
 }
 
-// K phases with which a shape takes gemm_mid_kernel (0: it does not): 128-wide groups, more than 64 tokens, and a
+// K phases with which a shape takes gemm_mid_kernel on tiles of four token blocks where fewer do not pay (gemm_mid_form;
+// 0: it stays on the tile kernel): 128-wide groups, more than 64 tokens, and a
 // grid of at most one workgroup per CU -- with four phases (64 channels per workgroup) if that fits, else with two.
 // The line between it and the tile kernel with K in ranges: a workgroup here takes a time proportional to
 // its share of K whatever the grid (0.4 us per k-tile with four phases, 0.73 with two, some 5 us besides), the tile
@@ -1334,7 +1359,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_pc_kernel(
 // workgroups) 64.8 / 64.5, 512 x 13824 x 5120 (160) 78.0 / 82.8, 1024 x 1024 x 4096 (8 k-tiles) 14.0 / 16.5.
 int gemm_mid_phases(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
 {
-    const int64_t KT = K / TILE_K, gm = (M + MD_BM - 1) / MD_BM;
+    const int64_t KT = K / TILE_K, gm = (M + 127) / 128;
     if (G != TILE_K || G == K || M <= 64 || KT < 8) return 0;
     if (gm * ((N + MD_BN - 1) / MD_BN) <= 256) {
         if (gm == 2 && (N + 127) / 128 == 16 && KT >= 10) return 0;
@@ -1347,22 +1372,23 @@ int gemm_mid_phases(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
     return w2 <= 256 && KT >= 12 && KT * (216 - w2) <= (asym ? 3400 : 4800) ? 2 : 0;
 }
 
-template <int KQ, bool ASYM>
+template <int KQ, bool ASYM, int MS>
 static int launch_gemm_mid_t(const int8_t *Xq, const float *sx, ZeroPoint zp, int64_t M, const uint8_t *Wt,
                              const float *step, const uint8_t *zero, int64_t N, int64_t K, void *Y, int y_dtype,
                              int64_t ldy, int32_t *acc_out, hipStream_t st, int plain)
 {
-    constexpr int BN = 256 / KQ;
+    constexpr int BN = 256 / KQ, MD_BM = 32 * MS;
     const int grid_m = (int)((M + MD_BM - 1) / MD_BM);
     const int grid_n = (int)((N + BN - 1) / BN);
     const int vec_store = (((uintptr_t)Y % 8 == 0) && (ldy % 4 == 0)) ? 1 : 0;
-    constexpr int lds_bytes = 2 * KQ * MD_TILE;   // 128 or 64 KB
+    // two super-steps of activations (48 to 128 KB); then the sums that the waves exchange, 4 KB per wave and block
+    constexpr int lds_bytes = 2 * KQ * MD_BM * TILE_K > 8 * MS * 4096 ? 2 * KQ * MD_BM * TILE_K : 8 * MS * 4096;
 #define W4A8_MD(AO_)                                                                                           \
     do {                                                                                                       \
         static std::atomic<uint64_t> lds_opted{0};                                                             \
-        if (opt_in_dynamic_lds((const void *)gemm_mid_kernel<AO_, KQ, ASYM>, lds_bytes, lds_opted) != W4A8_OK) \
+        if (opt_in_dynamic_lds((const void *)gemm_mid_kernel<AO_, KQ, ASYM, MS>, lds_bytes, lds_opted) != W4A8_OK) \
             return W4A8_ERR_HIP;                                                                               \
-        hipLaunchKernelGGL((gemm_mid_kernel<AO_, KQ, ASYM>), dim3((unsigned)(grid_m * grid_n)),                \
+        hipLaunchKernelGGL((gemm_mid_kernel<AO_, KQ, ASYM, MS>), dim3((unsigned)(grid_m * grid_n)),                \
                            dim3(MD_THREADS), lds_bytes, st, Xq, sx, zp.zx, zp.wsum, (int)M, Wt, step, zero,    \
                            (int)N, (int)K, (uint16_t *)Y, y_dtype, ldy, vec_store, acc_out, grid_m, plain);    \
     } while (0)
@@ -1501,6 +1527,59 @@ bool gemm_reads_row_sums(int64_t M, int64_t N, int64_t K, int64_t G)
     return G == K && (gemm_mid_pc_applies(M, N, K, G, false) || plan_gemm(M, N, K, G).splits == 1);
 }
 
+// The form of gemm_mid_kernel that a shape takes, if any.  Tiles of fewer token blocks leave fewer rows without a token, and take
+// 0.8 (three blocks) and 0.65 (two) of the time of four wherever they still fit one workgroup per CU.  What a launch takes,
+// us, with KT k-tiles and w workgroups: a + b KT + d KT w / 256; the tile kernel with K in ranges: a time that goes with the
+// k-tiles of a range, its share of the chip and the partial sums; 16-token blocks of the streaming kernel: one that goes with
+// the generations of workgroups, the k-tiles of a wave and the weights that all blocks read.  Constants fitted to 620
+// shapes of 17 to 1600 tokens with every kernel timed on each; the choice is 0.2 % slower on average than the best of them
+// (without the forms of two and three blocks 9 % from 65 tokens on, 12 to 17 % from 33 to 64).
+// Before / now, us (tokens x K x N): 607 x 4096 x 4096 31.3 / 27.3, with zero-points 36.9 / 31.8, 700 x 8192 x 3072 49.6 / 44.0; instead of
+// the tile kernel 524 x 7936 x 1024 29.5 / 20.5, 59 x 9856 x 15712 51.6 / 26.2, 119 x 12672 x 3008 28.8 / 30.0; instead of token
+// blocks 113 x 4224 x 6496 21.8 / 13.9; those keep 57 x 1920 x 7296 8.9 (9.3 here), 62 x 7296 x 2960 14.1 (17.2), 32 x 2048 x 5344
+// 6.0 (8.7).
+MidForm gemm_mid_form(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
+{
+    const int64_t KT = K / TILE_K;
+    if (G != TILE_K || G == K || M <= 16 || KT < 6) return MidForm{0, 0};
+    static const double cost[2][2][3][3] = {   // [zero-points][phases 2, 4][blocks 2, 3, 4]: a, b, d
+        {{{5.1, 0.368, 0.119}, {6.8, 0.446, 0.152}, {6.8, 0.549, 0.165}}, {{5.4, 0.194, 0.063}, {6.1, 0.248, 0.069}, {6.4, 0.300, 0.102}}},
+        {{{5.3, 0.447, 0.149}, {7.1, 0.542, 0.191}, {7.3, 0.685, 0.221}}, {{5.8, 0.228, 0.077}, {6.7, 0.281, 0.110}, {7.5, 0.349, 0.137}}}};
+    const auto time_of = [&](int phases, int blocks) {
+        const int64_t w = (M + 32 * blocks - 1) / (32 * blocks) * ((N + 256 / phases - 1) / (256 / phases));
+        const double *c = cost[asym][phases == 4][blocks - 2];
+        return w <= 256 ? c[0] + (double)KT * (c[1] + c[2] * (double)w / 256.0) : 1e30;
+    };
+    MidForm best = {0, 4};
+    double t;
+    if (const int nb = gemv_token_blocks(M, N, K, G)) {
+        const GemvPlan pl = plan_gemv(16, N, K, G, nb, true);
+        const int gens = (pl.blocks_per_split * pl.splits * nb + 255) / 256;
+        t = 1.65 + gens * (2.0 + 0.18 * pl.q * pl.at) + (pl.splits > 1 ? 2.9 : 0.0) + 4.5e-8 * nb * (double)N * (double)K;
+        t *= 0.94;   // (the estimate is good to 6 %)
+    } else if (M <= 64) {
+        t = 1e29;    // (the tile kernel at 64 rows, on layers that token blocks leave it: twice the time of any form)
+    } else if ((best.phases = gemm_mid_phases(M, N, K, G, asym)) != 0) {
+        t = time_of(best.phases, 4);
+    } else if (KT < 8) {
+        return best;
+    } else {
+        const GemmPlan pl = plan_gemm(M, N, K, G);
+        const double wgs = (double)((M + 127) / 128 * ((N + 127) / 128) * pl.splits) / 512.0;
+        t = (double)pl.kt_per_split * (0.98 + (asym ? 0.73 : 0.48) * wgs) +
+            (pl.splits > 1 ? (asym ? 9.2 : 8.5) + (asym ? 1.8e-6 : 1.6e-6) * (double)(pl.splits * M * N) : 5.0);
+    }
+    for (int phases = 4; phases >= 2; phases -= 2)
+        for (int blocks = 2; blocks <= (M <= 128 ? 4 : 3); ++blocks) {
+            const double tf = time_of(phases, blocks);
+            if (tf < t) {
+                best = {phases, blocks};
+                t = tf;
+            }
+        }
+    return best;
+}
+
 // Whether the product decodes its weights beforehand (gemm_i8.hip).  A round of 512 tiles takes 0.35 us less per k-tile on int8
 // weights (1.35 against 1.7 us, however full it is); decoding moves 1.5 bytes per weight and is a launch more.  Without /
 // with, us, groups of 128 (tokens x K x N): 2048 x 13824 x 5120 219 / 198, 4096 x 4096 x 4096 101 / 89, 2500 x 13824 x 2048 163 / 119,
@@ -1508,7 +1587,9 @@ bool gemm_reads_row_sums(int64_t M, int64_t N, int64_t K, int64_t G)
 // 2048 x 2048 x 4096 28 / 34.
 size_t gemm_i8_workspace(int64_t M, int64_t N, int64_t K, int64_t G)
 {
-    if (G == K || M <= 256 || M * K > 0x7fffffffLL || N * K > 0x7f000000LL || gemm_mid_phases(M, N, K, G, false)) return 0;
+    if (G == K || M <= 256 || M * K > 0x7fffffffLL || N * K > 0x7f000000LL ||
+        gemm_mid_form(M, N, K, G, false).phases != 0)
+        return 0;
     const GemmPlan pl = plan_gemm(M, N, K, G);
     if (pl.bm != 128 || pl.splits != 1) return 0;
     const int64_t rounds = ((M + 127) / 128 * ((N + 127) / 128) + 511) / 512;
@@ -1524,11 +1605,24 @@ int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, in
     const bool grouped = G != K;
     if ((M + 63) / 64 * ((N + 255) / 256) * 64 > 0x7fffffLL || M * K > 0x7fffffffLL)
         return W4A8_ERR_SHAPE;
-    if (const int phases = gemm_mid_phases(M, N, K, G, zp.zx != nullptr)) {
-#define W4A8_MD_T(KQ_, AS_) \
-    launch_gemm_mid_t<KQ_, AS_>(Xq, sx, zp, M, Wt, step, zero, N, K, Y, y_dtype, ldy, acc_out, st, plain)
-        if (zp.zx != nullptr) return phases == 4 ? W4A8_MD_T(4, true) : W4A8_MD_T(2, true);
-        return phases == 4 ? W4A8_MD_T(4, false) : W4A8_MD_T(2, false);
+    const MidForm form = gemm_mid_form(M, N, K, G, zp.zx != nullptr);
+    if (form.phases != 0) {
+#define W4A8_MD_T(KQ_, AS_, MS_) \
+    return launch_gemm_mid_t<KQ_, AS_, MS_>(Xq, sx, zp, M, Wt, step, zero, N, K, Y, y_dtype, ldy, acc_out, st, plain)
+#define W4A8_MD_M(AS_, MS_)                           \
+    do {                                              \
+        if (form.phases == 4) W4A8_MD_T(4, AS_, MS_); \
+        W4A8_MD_T(2, AS_, MS_);                       \
+    } while (0)
+        if (zp.zx != nullptr) {
+            if (form.blocks == 2) W4A8_MD_M(true, 2);
+            if (form.blocks == 3) W4A8_MD_M(true, 3);
+            W4A8_MD_M(true, 4);
+        }
+        if (form.blocks == 2) W4A8_MD_M(false, 2);
+        if (form.blocks == 3) W4A8_MD_M(false, 3);
+        W4A8_MD_M(false, 4);
+#undef W4A8_MD_M
 #undef W4A8_MD_T
     }
     if (gemm_mid_pc_applies(M, N, K, G, zp.zx != nullptr))

@@ -358,6 +358,11 @@ struct GemmPlan {
     int pc_rem_n;
 };
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t G);
+// Group-128 products with K in phases inside the workgroup: how many, and 32-token blocks per workgroup (phases 0: another kernel)
+struct MidForm {
+    int phases, blocks;
+};
+MidForm gemm_mid_form(int64_t M, int64_t N, int64_t K, int64_t G, bool asym);
 // w8 != null (16-byte aligned, gemm_i8_workspace bytes): room for the weights as int8, for the products that pay
 // for decoding them beforehand
 int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, int64_t M,
