@@ -750,10 +750,10 @@ constexpr int MD_BN = 64, MD_KQ = 4, MD_THREADS = 512;
 template <bool ACC_OUT, int KQ, bool ASYM, int MS>
 __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     const int8_t *__restrict__ Xq, const float *__restrict__ sx, const int32_t *__restrict__ zx,
-    const int32_t *__restrict__ wsum, int M, const uint8_t *__restrict__ Wt,
+    const int32_t *__restrict__ tsum, int M, const uint8_t *__restrict__ Wt,
     const float *__restrict__ step, const uint8_t *__restrict__ zero, int N, int K,
     uint16_t *__restrict__ Y, int y_dtype, int64_t ldy, int vec_store, int32_t *__restrict__ acc_out,
-    int grid_m, int plain)
+    int grid_m, int plain, int ng, uint32_t inv_tpg)
 {
     constexpr int MD_BM = 32 * MS, MD_TILE = MD_BM * TILE_K;   // tokens; bytes of one activation k-tile in LDS
     constexpr int WN = 8 / KQ;       // channel parts
@@ -770,7 +770,10 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     const int kq = wave / WN;     // K phase
     const int r32 = lane & 31;
     const int kh = lane >> 5;
-    const int KT = K / TILE_K;    // = number of groups
+    const int KT = K / TILE_K;
+    // group of a k-tile, by a reciprocal (2^16 / k-tiles per group, rounded up: exact for 512 k-tiles and 64 of them per group)
+    // (groups of one k-tile only where another register would spill)
+    auto group_of = [&](int kt) { return ASYM && MS == 4 ? kt : (int)((uint32_t)__umul24((uint32_t)kt, inv_tpg) >> 16); };
     const int SS = (KT + KQ - 1) / KQ;
     // (workgroups are handed to the 8 XCDs round-robin: renumbered so that the token tiles that share weights
     // share an L2)
@@ -828,9 +831,10 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         if (tid < KQ * BN) {
             const int kt = min(ss * KQ + tid / BN, KT - 1);
             const int nn = nb0 + tid % BN < N ? nb0 + tid % BN : 0;
-            gp_es = step[(int64_t)nn * KT + kt];   // (used only in publish_params: nothing here waits for the load)
-            gp_z = zero[(int64_t)nn * KT + kt];
-            if (ASYM) gp_w = wsum[(int64_t)nn * KT + kt];
+            const int g = group_of(kt);
+            gp_es = step[(int64_t)nn * ng + g];   // (used only in publish_params: nothing here waits for the load)
+            gp_z = zero[(int64_t)nn * ng + g];
+            if (ASYM) gp_w = tsum[(int64_t)nn * KT + kt];
         }
     };
     auto publish_params = [&](int ss, float gp_es, int gp_z, int gp_w) {
@@ -882,7 +886,11 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
             y[ms][4 * b + r] = __builtin_fmaf(es4[b][r], (float)vz, y[ms][4 * b + r]);
             if (ACC_OUT && m < M) {
                 const int nn = nb0 + wn * 32 + 8 * b + 4 * kh + r;
-                if (nn < N) acc_out[((int64_t)m * N + nn) * KT + kt] = v >> 2;
+                if (nn < N) {
+                    int32_t *a = &acc_out[((int64_t)m * N + nn) * ng + group_of(kt)];
+                    if (ng == KT) *a = v >> 2;
+                    else atomicAdd(a, v >> 2);   // (the phases share a group; exact)
+                }
             }
         }
     };
@@ -1374,7 +1382,7 @@ int gemm_mid_phases(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
 
 template <int KQ, bool ASYM, int MS>
 static int launch_gemm_mid_t(const int8_t *Xq, const float *sx, ZeroPoint zp, int64_t M, const uint8_t *Wt,
-                             const float *step, const uint8_t *zero, int64_t N, int64_t K, void *Y, int y_dtype,
+                             const float *step, const uint8_t *zero, int64_t N, int64_t K, int64_t G, void *Y, int y_dtype,
                              int64_t ldy, int32_t *acc_out, hipStream_t st, int plain)
 {
     constexpr int BN = 256 / KQ, MD_BM = 32 * MS;
@@ -1389,8 +1397,9 @@ static int launch_gemm_mid_t(const int8_t *Xq, const float *sx, ZeroPoint zp, in
         if (opt_in_dynamic_lds((const void *)gemm_mid_kernel<AO_, KQ, ASYM, MS>, lds_bytes, lds_opted) != W4A8_OK) \
             return W4A8_ERR_HIP;                                                                               \
         hipLaunchKernelGGL((gemm_mid_kernel<AO_, KQ, ASYM, MS>), dim3((unsigned)(grid_m * grid_n)),                \
-                           dim3(MD_THREADS), lds_bytes, st, Xq, sx, zp.zx, zp.wsum, (int)M, Wt, step, zero,    \
-                           (int)N, (int)K, (uint16_t *)Y, y_dtype, ldy, vec_store, acc_out, grid_m, plain);    \
+                           dim3(MD_THREADS), lds_bytes, st, Xq, sx, zp.zx, zp.tsum, (int)M, Wt, step, zero,    \
+                           (int)N, (int)K, (uint16_t *)Y, y_dtype, ldy, vec_store, acc_out, grid_m, plain,     \
+                           (int)(K / G), (uint32_t)((65536 + G / TILE_K - 1) / (G / TILE_K)));                 \
     } while (0)
     if (acc_out) W4A8_MD(true);
     else W4A8_MD(false);
@@ -1531,7 +1540,8 @@ bool gemm_reads_row_sums(int64_t M, int64_t N, int64_t K, int64_t G)
 // 0.8 (three blocks) and 0.65 (two) of the time of four wherever they still fit one workgroup per CU.  What a launch takes,
 // us, with KT k-tiles and w workgroups: a + b KT + d KT w / 256; the tile kernel with K in ranges: a time that goes with the
 // k-tiles of a range, its share of the chip and the partial sums; 16-token blocks of the streaming kernel: one that goes with
-// the generations of workgroups, the k-tiles of a wave and the weights that all blocks read.  Constants fitted to 620
+// the generations of workgroups, the k-tiles of a wave and the weights that all blocks read.  Larger groups go the same way, a
+// k-tile at a time (groups of 256 209 x 2048 x 4320 21.1 / 11.1, 645 x 2048 x 2016 22.3 / 11.1).  Constants fitted to 620
 // shapes of 17 to 1600 tokens with every kernel timed on each; the choice is 0.2 % slower on average than the best of them
 // (without the forms of two and three blocks 9 % from 65 tokens on, 12 to 17 % from 33 to 64).
 // Before / now, us (tokens x K x N): 607 x 4096 x 4096 31.3 / 27.3, with zero-points 36.9 / 31.8, 700 x 8192 x 3072 49.6 / 44.0; instead of
@@ -1541,7 +1551,7 @@ bool gemm_reads_row_sums(int64_t M, int64_t N, int64_t K, int64_t G)
 MidForm gemm_mid_form(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
 {
     const int64_t KT = K / TILE_K;
-    if (G != TILE_K || G == K || M <= 16 || KT < 6) return MidForm{0, 0};
+    if (G % TILE_K != 0 || G > 64 * TILE_K || G == K || M <= 16 || KT < 6 || KT > 512) return MidForm{0, 0};
     static const double cost[2][2][3][3] = {   // [zero-points][phases 2, 4][blocks 2, 3, 4]: a, b, d
         {{{5.1, 0.368, 0.119}, {6.8, 0.446, 0.152}, {6.8, 0.549, 0.165}}, {{5.4, 0.194, 0.063}, {6.1, 0.248, 0.069}, {6.4, 0.300, 0.102}}},
         {{{5.3, 0.447, 0.149}, {7.1, 0.542, 0.191}, {7.3, 0.685, 0.221}}, {{5.8, 0.228, 0.077}, {6.7, 0.281, 0.110}, {7.5, 0.349, 0.137}}}};
@@ -1559,7 +1569,7 @@ MidForm gemm_mid_form(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
         t *= 0.94;   // (the estimate is good to 6 %)
     } else if (M <= 64) {
         t = 1e29;    // (the tile kernel at 64 rows, on layers that token blocks leave it: twice the time of any form)
-    } else if ((best.phases = gemm_mid_phases(M, N, K, G, asym)) != 0) {
+    } else if (G == TILE_K && (best.phases = gemm_mid_phases(M, N, K, G, asym)) != 0) {
         t = time_of(best.phases, 4);
     } else if (KT < 8) {
         return best;
@@ -1568,9 +1578,10 @@ MidForm gemm_mid_form(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
         const double wgs = (double)((M + 127) / 128 * ((N + 127) / 128) * pl.splits) / 512.0;
         t = (double)pl.kt_per_split * (0.98 + (asym ? 0.73 : 0.48) * wgs) +
             (pl.splits > 1 ? (asym ? 9.2 : 8.5) + (asym ? 1.8e-6 : 1.6e-6) * (double)(pl.splits * M * N) : 5.0);
+        if (G != TILE_K) t *= 0.85;   // (the tile kernel rescales once per group, this one once per k-tile)
     }
     for (int phases = 4; phases >= 2; phases -= 2)
-        for (int blocks = 2; blocks <= (M <= 128 ? 4 : 3); ++blocks) {
+        for (int blocks = 2; blocks <= (G != TILE_K ? (asym ? 3 : 4) : M <= 128 ? 4 : 3); ++blocks) {
             const double tf = time_of(phases, blocks);
             if (tf < t) {
                 best = {phases, blocks};
@@ -1584,7 +1595,8 @@ MidForm gemm_mid_form(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
 // weights (1.35 against 1.7 us, however full it is); decoding moves 1.5 bytes per weight and is a launch more.  Without /
 // with, us, groups of 128 (tokens x K x N): 2048 x 13824 x 5120 219 / 198, 4096 x 4096 x 4096 101 / 89, 2500 x 13824 x 2048 163 / 119,
 // 1300 x 8192 x 3072 102 / 76, 1536 x 5120 x 5120 65.5 / 66.5; left out: 1024 x 8192 x 8192 96 / 101, 2048 x 4096 x 4096 50.6 / 53,
-// 2048 x 2048 x 4096 28 / 34.
+// 2048 x 2048 x 4096 28 / 34.  Larger groups rescale less often and gain less: in groups of 256 2048 x 13824 x 5120 195 / 186,
+// 1024 x 13824 x 5120 127 / 120, but 1324 x 2304 x 26112 124 / 130.
 size_t gemm_i8_workspace(int64_t M, int64_t N, int64_t K, int64_t G)
 {
     if (G == K || M <= 256 || M * K > 0x7fffffffLL || N * K > 0x7f000000LL ||
@@ -1593,7 +1605,7 @@ size_t gemm_i8_workspace(int64_t M, int64_t N, int64_t K, int64_t G)
     const GemmPlan pl = plan_gemm(M, N, K, G);
     if (pl.bm != 128 || pl.splits != 1) return 0;
     const int64_t rounds = ((M + 127) / 128 * ((N + 127) / 128) + 511) / 512;
-    const double saved = 0.35 * (double)(K / TILE_K * rounds), spent = 6.0 + 3.2e-7 * (double)N * (double)K;
+    const double saved = (G == TILE_K ? 0.35 : 0.2) * (double)(K / TILE_K * rounds), spent = 6.0 + 3.2e-7 * (double)N * (double)K;
     return saved > spent ? gemm_i8_bytes(N, K) : 0;
 }
 
@@ -1607,8 +1619,12 @@ int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, in
         return W4A8_ERR_SHAPE;
     const MidForm form = gemm_mid_form(M, N, K, G, zp.zx != nullptr);
     if (form.phases != 0) {
+        if (acc_out && G != TILE_K) {   // the k-tiles of a group add their exact sums
+            const int rc = launch_fill_i32(acc_out, M * N * (K / G), 0, st);
+            if (rc != W4A8_OK) return rc;
+        }
 #define W4A8_MD_T(KQ_, AS_, MS_) \
-    return launch_gemm_mid_t<KQ_, AS_, MS_>(Xq, sx, zp, M, Wt, step, zero, N, K, Y, y_dtype, ldy, acc_out, st, plain)
+    return launch_gemm_mid_t<KQ_, AS_, MS_>(Xq, sx, zp, M, Wt, step, zero, N, K, G, Y, y_dtype, ldy, acc_out, st, plain)
 #define W4A8_MD_M(AS_, MS_)                           \
     do {                                              \
         if (form.phases == 4) W4A8_MD_T(4, AS_, MS_); \
@@ -1625,6 +1641,8 @@ int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, in
 #undef W4A8_MD_M
 #undef W4A8_MD_T
     }
+    // (the workspace of a shape with token blocks is sized for the streaming kernel: it does not come here)
+    if (gemv_token_blocks(M, N, K, G) > 0) return W4A8_ERR_SHAPE;
     if (gemm_mid_pc_applies(M, N, K, G, zp.zx != nullptr))
         return launch_gemm_mid_pc(Xq, sx, rs, M, Wt, step, zero, N, K, Y, y_dtype, ldy, acc_out, st, plain,
                                   rs_ready);

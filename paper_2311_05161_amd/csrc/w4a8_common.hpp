@@ -358,7 +358,8 @@ struct GemmPlan {
     int pc_rem_n;
 };
 GemmPlan plan_gemm(int64_t M, int64_t N, int64_t K, int64_t G);
-// Group-128 products with K in phases inside the workgroup: how many, and 32-token blocks per workgroup (phases 0: another kernel)
+// Group-wise products with K in phases inside the workgroup: how many, and 32-token blocks per workgroup (phases 0: another kernel).  They need no workspace, and come before the
+// streaming kernel's token blocks.
 struct MidForm {
     int phases, blocks;
 };

@@ -10,7 +10,7 @@ pytestmark = pytest.mark.gpu
 # ragged last tiles of tokens and channels (N % 32 = 16), groups of several k-tiles, an odd number of k-tiles, the last round of tiles
 # with K in ranges, outputs that allow 16-byte, 8-byte and 2-byte stores, all levels of plain INT4
 @pytest.mark.parametrize("M,K,N,G,fmt,y,pad", [
-    (4200, 3072, 1008, 128, 0, "f16", 0), (4224, 3200, 1024, 128, 0, "bf16", 4), (4200, 3072, 1008, 384, 0, "f16", 1),
+    (4200, 3072, 1008, 128, 0, "f16", 0), (4224, 3200, 1024, 128, 0, "bf16", 4), (4200, 6144, 1008, 384, 0, "f16", 1),
     (4104, 5120, 2032, 128, 0, "f16", 0), (4104, 5120, 2032, 256, 1, "bf16", 2), (8200, 2816, 528, 128, 1, "f16", 8)])
 def test_same_bits_as_packed(M, K, N, G, fmt, y, pad):
     import paper_2311_05161_amd as w

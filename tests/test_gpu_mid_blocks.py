@@ -47,6 +47,19 @@ def test_products(M, K, N, want, asym):
     _check(M, K, N, 128, asym, ydtype="bf16" if M % 2 else "f16", ypad=M % 3)
 
 
+# groups of several k-tiles: the phases share a group (the last shape would otherwise be token blocks, whose
+# workspace holds no partial sums)
+@pytest.mark.gpu
+@pytest.mark.parametrize("asym", [False, True])
+@pytest.mark.parametrize("M,K,N,G", [(129, 1536, 1040, 256), (300, 1152, 6160, 384), (513, 2560, 4112, 512), (50, 1280, 21520, 640)])
+def test_larger_groups(M, K, N, G, asym):
+    r = _rule("13gemm_mid_formEllllb", MidForm, I64, I64, I64, I64, ctypes.c_bool)(M, N, K, G, asym)
+    assert r.phases > 0
+    _check(M, K, N, G, asym)
+    if M < 200:
+        _check(M, K, N, G, asym, hook=True)
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("M,K,N", [(129, 1408, 1040), (300, 1152, 1360), (385, 1024, 1552)])
 def test_accumulators(M, K, N):
