@@ -114,7 +114,8 @@ int gemm_common(const int8_t *Xq, const float *sx, const int32_t *zx, int64_t M,
         Wt = tiled;
     }
     // the streaming kernel, also for a few 16-token blocks
-    if (M <= 16 || (gemv_token_blocks(M, N, K, G) > 0 && gemm_mid_form(M, N, K, G, zx != nullptr).phases == 0)) {
+    if (M <= 16 ||
+        (gemv_token_blocks(M, N, K, G) > 0 && gemm_mid_form(M, N, K, G, zx != nullptr).phases == 0)) {
         if (acc_out) {  // the split-K waves add exact partial sums into it
             const int rc = launch_fill_i32(acc_out, M * N * (K / G), 0, st);
             if (rc != W4A8_OK) return rc;
@@ -379,12 +380,15 @@ int w4a8_linear(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, c
     hipStream_t st = (hipStream_t)stream;
 
     // At most 16 tokens of fp16 activations on tiled weights whose K the streaming kernel takes in one
-    // range: ONE launch, the activations are quantized inside it.
-    // One launch / two, both under a graph, us: 4 x 4096 x 4096 6.3 / 7.9, 4 x 7168 x 2048 8.1 / 9.1, 16 x 768 x 768 4.6 / 5.2, 16 x 2048 x 1024
-    // 5.9 / 5.85; but beyond four tokens, where each workgroup quantizes sixteen rows, 5 x 4096 x 4096 8.9 / 7.9, 16 x 5120 x 13824 16.2 / 15.7,
-    // 16 x 7168 x 2048 12.4 / 9.7: there the line is from before the separate quantizer took 1024 lanes per row, and has not been moved.
-    const bool one_launch = M <= 16 && x_dtype == W4A8_F16 && layout == W4A8_LAYOUT_TILED &&
-                            (uintptr_t)X % 16 == 0 && ldx % 8 == 0 && ldx <= (1LL << 24) &&
+    // range: ONE launch, the activations are quantized inside it.  Beyond four tokens each workgroup quantizes sixteen rows, which
+    // grows with K: from K = 5120 the two steps one after the other are faster, also called eagerly, where two launches take the
+    // host 9.3 us (below that they would wait for it).  One launch / two, us, eagerly and as a graph: 16 x 768 x 768 4.6 / 9.4, 4.6 / 5.3;
+    // 8 x 4096 x 4096 8.4 / 9.3, 8.5 / 7.0; 16 x 5120 x 5120 11.6 / 11.1, 11.8 / 10.9; 5 x 5120 x 13824 14.6 / 14.2, 14.9 / 13.8; 8 x 7168 x 2048
+    // 11.6 / 9.3, 11.8 / 8.5.  (A caller without a workspace gets the one launch, which needs none.)
+    const LinearWs w = plan_linear(M, N, K, G, layout);
+    const bool room = workspace && workspace_bytes >= w.total && (uintptr_t)workspace % WS_ALIGN == 0;
+    const bool one_launch = M <= 16 && !(M > 4 && K >= 5120 && room) && x_dtype == W4A8_F16 &&
+                            layout == W4A8_LAYOUT_TILED && (uintptr_t)X % 16 == 0 && ldx % 8 == 0 && ldx <= (1LL << 24) &&
                             gemv_can_fuse(M, N, K, G);
     if (one_launch) {
         if (acc_out) {  // the compute waves add exact partial sums into it
@@ -397,8 +401,7 @@ int w4a8_linear(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, c
     }
     // Otherwise the two steps one after the other, the int8 activations and token scales in the workspace
     // (or where the caller wants to see them).
-    const LinearWs w = plan_linear(M, N, K, G, layout);
-    if (!workspace || workspace_bytes < w.total || (uintptr_t)workspace % WS_ALIGN != 0) return W4A8_ERR_WORKSPACE;
+    if (!room) return W4A8_ERR_WORKSPACE;
     uint8_t *wsb = (uint8_t *)workspace;
     const size_t gemm_bytes = workspace_bytes - w.gemm;
     int8_t *Xq = Xq_out ? Xq_out : (int8_t *)(wsb + w.xq);

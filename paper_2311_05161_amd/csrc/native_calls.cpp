@@ -231,8 +231,8 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
         Py_END_ALLOW_THREADS
     };
     // The one-launch decode step needs no workspace: try without (a call that needs one is turned down
-    // before anything is launched).
-    if (r.M <= 16 && r.dtype == W4A8_F16 && layout == LAYOUT_TILED) call(nullptr, 0);
+    // before anything is launched).  Beyond four tokens and from K = 5120 the call is faster with one.
+    if (r.M <= 16 && !(r.M > 4 && r.K >= 5120) && r.dtype == W4A8_F16 && layout == LAYOUT_TILED) call(nullptr, 0);
     if (rc == W4A8_ERR_WORKSPACE) {
         const size_t bytes = need(r.M, N, r.K, G, (int)layout);
         at::Tensor ws;
