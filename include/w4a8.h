@@ -131,7 +131,8 @@ int unpack_dint4(const uint8_t *packed, int64_t N, int64_t K, uint8_t *codes, in
  * The M <= 16 path streams the packed weights once (memory-bound "decode" GEMV); larger M
  * uses the MFMA tile kernel ("prefill"), except that 17 .. 64 tokens (.. 128 on layers of at most
  * 48 Mi weights) run as 16-token blocks of the streaming kernel in one launch where that is
- * faster (w4a8_gemm_workspace_bytes knows which path a shape takes).  Results are deterministic (fixed reduction order). */
+ * faster, and group-wise products of 17 tokens and more whose tiles would leave the chip idle cut K inside the
+ * workgroup (w4a8_gemm_workspace_bytes knows which path a shape takes).  Results are deterministic (fixed reduction order). */
 size_t w4a8_gemm_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t group_size,
                                  int layout);
 /* What w4a8_gemm would like: at least w4a8_gemm_workspace_bytes(...); more (N*K bytes and a thirtieth) for group-wise
