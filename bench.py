@@ -14,7 +14,7 @@ EXACTLY K steps between synchronizations (at least five, and more than 0.2 s of 
 kernel, from HIP events recorded around every w4a8_gemm call of those same timed steps.
 
 Second object (`decode`): the memory-bound half of the metric on the LLaMA-13B up-projection at 16
-tokens (M=16 K=5120 N=13824 group-128; one step = one w4a8_linear call), weights streamed
+tokens (M=16 K=5120 N=13824 group-128; one step = one w4a8_linear call = one launch), weights streamed
 from a ring of distinct quantized copies larger than the 256 MB Infinity Cache, with its own HBM roofline.  Prints ONE JSON line.
 """
 from __future__ import annotations
@@ -275,7 +275,7 @@ def main():
         gm_d = [(P(Xqd), P(sxd), Md, P(wp), w.LAYOUT_TILED, P(sp), P(zp), Nd, Kd, Gd, P(Yd), w.F16, Nd,
                  None, P(wsd), wsd_bytes, st) for (wp, sp, zp) in ring]
 
-        # the step as ONE call: w4a8_linear quantizes the 16 tokens and multiplies (two launches at this size)
+        # the step as ONE call: w4a8_linear quantizes the 16 tokens inside the streaming kernel's launch
         lin_ws_bytes = int(lib.w4a8_linear_workspace_bytes(Md, Nd, Kd, Gd, w.LAYOUT_TILED))
         lin_ws = torch.empty((max(1, lin_ws_bytes),), dtype=torch.uint8, device=dev)
         lin_d = [(P(Xdd), w.F16, Md, Kd, Kd, P(sdd), P(wp), w.LAYOUT_TILED, P(sp), P(zp), Nd, Gd, P(Yd), w.F16, Nd,
@@ -378,7 +378,7 @@ def main():
                        "sample": f"{n_cpu} whole steps (act-quant + int GEMM + dequant) in {cpu_s:.1f} s"}
         decode = {
             "workload": f"C4 LLaMA-13B up-projection decode: M={Md} K={Kd} N={Nd} group-{Gd} dINT4; step = "
-                        f"w4a8_linear (activation quantization + GEMM in one call, bit-identical to "
+                        f"w4a8_linear (activation quantization + GEMM in one launch, bit-identical to "
                         f"quantize_act_int8 + w4a8_gemm); ring of {R} weight copies ({R * per_copy / 2 ** 20:.0f} MiB)",
             "launch": "hip-graph" if use_graph else "eager",
             "value": round(Nd * Kd / 2 / d_step_s / 1e9, 1), "unit": "GB/s (packed weight bytes per step time)",

@@ -300,11 +300,12 @@ def w4a8_gemm(Xq: torch.Tensor, sx: torch.Tensor, Wp: torch.Tensor, step: torch.
 def w4a8_linear(X: torch.Tensor, s, Wp: torch.Tensor, step: torch.Tensor, zero: torch.Tensor, N: int,
                 group_size: int = 0, layout: int = LAYOUT_TILED, out_dtype=torch.float16, Y=None,
                 want_quantized=False, want_acc=False, workspace=None):
-    """The whole layer in one call (one launch for up to 16 tokens of fp16 activations).
+    """The whole layer in one call.  Up to 16 tokens of fp16 activations: one launch that leaves ``workspace`` alone (the header
+    says for which K), or, from five tokens and K = 5120 on where nothing but a fresh Y is asked for, two faster ones.
     Returns Y, or (Y, Xq, sx[, acc]) with want_quantized / want_acc."""
     if Y is None and workspace is None and not want_quantized and not want_acc:
         out = _native_call("linear", "w4a8_linear", _address("w4a8_linear"), _address("w4a8_linear_workspace_bytes"),
-                           X, s, Wp, step, zero, N, group_size or 0, layout, _DTYPES[out_dtype])
+                           _address("quantize_act_int8"), _address("w4a8_gemm"), _address("w4a8_gemm_workspace_bytes"), X, s, Wp, step, zero, N, group_size or 0, layout, _DTYPES[out_dtype])
         if out is not NotImplemented:
             return out
     M, K, ldx = _rows(X, "X")

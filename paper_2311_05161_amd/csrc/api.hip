@@ -380,15 +380,14 @@ int w4a8_linear(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, c
     hipStream_t st = (hipStream_t)stream;
 
     // At most 16 tokens of fp16 activations on tiled weights whose K the streaming kernel takes in one
-    // range: ONE launch, the activations are quantized inside it.  Beyond four tokens each workgroup quantizes sixteen rows, which
-    // grows with K: from K = 5120 the two steps one after the other are faster, also called eagerly, where two launches take the
-    // host 9.3 us (below that they would wait for it).  One launch / two, us, eagerly and as a graph: 16 x 768 x 768 4.6 / 9.4, 4.6 / 5.3;
+    // range: ONE launch, the activations are quantized inside it, and the workspace is left alone (the interface says so: calls
+    // on several streams may have handed in the same one).  Beyond four tokens each workgroup quantizes sixteen rows, which
+    // grows with K: from K = 5120 quantize_act_int8 and w4a8_gemm one after the other are faster, and a caller who has room for
+    // the int8 activations calls those (the binding does).  One launch / two, us, eagerly and as a graph: 16 x 768 x 768 4.6 / 9.4, 4.6 / 5.3;
     // 8 x 4096 x 4096 8.4 / 9.3, 8.5 / 7.0; 16 x 5120 x 5120 11.6 / 11.1, 11.8 / 10.9; 5 x 5120 x 13824 14.6 / 14.2, 14.9 / 13.8; 8 x 7168 x 2048
-    // 11.6 / 9.3, 11.8 / 8.5.  (A caller without a workspace gets the one launch, which needs none.)
-    const LinearWs w = plan_linear(M, N, K, G, layout);
-    const bool room = workspace && workspace_bytes >= w.total && (uintptr_t)workspace % WS_ALIGN == 0;
-    const bool one_launch = M <= 16 && !(M > 4 && K >= 5120 && room) && x_dtype == W4A8_F16 &&
-                            layout == W4A8_LAYOUT_TILED && (uintptr_t)X % 16 == 0 && ldx % 8 == 0 && ldx <= (1LL << 24) &&
+    // 11.6 / 9.3, 11.8 / 8.5.
+    const bool one_launch = M <= 16 && x_dtype == W4A8_F16 && layout == W4A8_LAYOUT_TILED &&
+                            (uintptr_t)X % 16 == 0 && ldx % 8 == 0 && ldx <= (1LL << 24) &&
                             gemv_can_fuse(M, N, K, G);
     if (one_launch) {
         if (acc_out) {  // the compute waves add exact partial sums into it
@@ -401,7 +400,8 @@ int w4a8_linear(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, c
     }
     // Otherwise the two steps one after the other, the int8 activations and token scales in the workspace
     // (or where the caller wants to see them).
-    if (!room) return W4A8_ERR_WORKSPACE;
+    const LinearWs w = plan_linear(M, N, K, G, layout);
+    if (!workspace || workspace_bytes < w.total || (uintptr_t)workspace % WS_ALIGN != 0) return W4A8_ERR_WORKSPACE;
     uint8_t *wsb = (uint8_t *)workspace;
     const size_t gemm_bytes = workspace_bytes - w.gemm;
     int8_t *Xq = Xq_out ? Xq_out : (int8_t *)(wsb + w.xq);

@@ -47,8 +47,10 @@ def _case(lib, oracle, seed, M, K, N, G, x_dtype="f16", use_s=True, pad=0, layou
     assert np.array_equal(host(Xq), r["Xq"]), "int8 activations differ"
     assert np.array_equal(host(acc), r["acc"]), "int32 accumulators differ"
     assert_y_close(host(Y), r["Y64"])
-    # the production form (no check outputs, no hook) and the two-call path: the same Y, bit for bit
+    # the production forms (no check outputs, no hook; with Y given the entry point itself, which is one launch wherever it can
+    # be) and the two-call path: the same Y, bit for bit
     Y1 = lib.w4a8_linear(Xd, sd, Wp, step, zero, N, G, layout=layout)
+    assert torch.equal(lib.w4a8_linear(Xd, sd, Wp, step, zero, N, G, layout=layout, Y=torch.empty_like(Y)), Y)
     Xq2, sx2 = lib.quantize_act_int8(Xd, sd)
     Y2 = lib.w4a8_gemm(Xq2, sx2, Wp, step, zero, N, K, G, layout=layout)
     assert torch.equal(Y1, Y) and torch.equal(Y2, Y)
@@ -117,6 +119,7 @@ def test_linear_full_size_c4_up_projection(lib, oracle):
     assert np.array_equal(host(acc), r["acc"])
     assert_y_close(host(Y), r["Y64"])
     assert torch.equal(lib.w4a8_linear(dev(X), dev(s), Wp, step, zero, N, G), Y)
+    assert torch.equal(lib.w4a8_linear(dev(X), dev(s), Wp, step, zero, N, G, Y=torch.empty_like(Y)), Y)
 
 
 def test_linear_exact_output_of_the_plain_one_launch_instances(lib, oracle):
@@ -133,7 +136,8 @@ def test_linear_exact_output_of_the_plain_one_launch_instances(lib, oracle):
         ref_q, ref_sx = oracle.quantize_act_int8(Xq.astype(np.float32), None)
         assert np.array_equal(ref_q, Xq) and np.array_equal(ref_sx, sx)      # premise: the quantizer is the identity here
         Wp = lib.pack_dint4(dev(codes), lib.LAYOUT_TILED)
-        Y = lib.w4a8_linear(dev(Xq.astype(np.float16)), None, Wp, dev(step), dev(zero), N, G)
+        Y = lib.w4a8_linear(dev(Xq.astype(np.float16)), None, Wp, dev(step), dev(zero), N, G,
+                            Y=torch.empty((M, N), dtype=torch.float16, device="cuda"))
         got = host(Y).astype(np.float32)
         assert np.array_equal(got, y32), f"{(got != y32).sum()} outputs differ from the exact result"
 
