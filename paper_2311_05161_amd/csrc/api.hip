@@ -129,9 +129,11 @@ int gemm_common(const int8_t *Xq, const float *sx, const int32_t *zx, int64_t M,
         const int rc = launch_fill_i32(acc_out, M * N, 0, st);
         if (rc != W4A8_OK) return rc;
     }
+    // (a workspace that the call does not have to have may lie anywhere: off the alignment it is not used)
+    const bool i8_room = ws.wanted > ws.total && workspace_bytes >= ws.wanted && (uintptr_t)workspace % WS_ALIGN == 0;
     const int rc = launch_gemm(Xq, sx, zp, (int32_t *)(wsb + ws.rs_off), M, Wt, step, zero, N,
                                K, G, Y, y_dtype, ldy, acc_out, (float *)(wsb + ws.part_off), st, plain, rs_ready,
-                               ws.wanted > ws.total && workspace_bytes >= ws.wanted ? wsb + ws.i8_off : nullptr);
+                               i8_room ? wsb + ws.i8_off : nullptr);
     if (rc != W4A8_OK || !zx || !acc_out) return rc;
     return launch_acc_zero_point(acc_out, zx, wsum, M, N * (K / G), st);
 }

@@ -35,3 +35,26 @@ def test_same_bits_as_packed(M, K, N, G, fmt, y, pad):
     assert torch.equal(out[0], out[1])
     if pad:
         assert (out[0][:, N:] == torch.full((), 7.0, dtype=Y.dtype).view(torch.int16).item()).all()
+
+
+# a product that needs no workspace takes one that lies anywhere, also where it would decode the weights into an aligned one
+@pytest.mark.parametrize("offset", [0, 8, 64])
+def test_workspace_off_the_alignment(offset):
+    import paper_2311_05161_amd as w
+    lib = w.load_library()
+    M, K, N, G = 4096, 3072, 2048, 128
+    g = torch.Generator(device="cuda").manual_seed(3)
+    Xq = torch.randint(-127, 128, (M, K), generator=g, device="cuda", dtype=torch.int8)
+    sx, step = torch.rand((M,), generator=g, device="cuda"), torch.rand((N, K // G), generator=g, device="cuda")
+    zero = torch.randint(0, 14, (N, K // G), generator=g, device="cuda", dtype=torch.uint8)
+    Wp = torch.randint(0, 256, (N * K // 2,), generator=g, device="cuda", dtype=torch.uint8)
+    need = int(lib.w4a8_gemm_workspace_preferred_bytes(M, N, K, G, 1))
+    assert need > 0 and int(lib.w4a8_gemm_workspace_bytes(M, N, K, G, 1)) == 0
+    ws = torch.empty((need + 256,), dtype=torch.uint8, device="cuda")
+    out = []
+    for p, size in ((ws.data_ptr() + offset, need), (None, 0)):
+        Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+        assert lib.w4a8_gemm(Xq.data_ptr(), sx.data_ptr(), M, Wp.data_ptr(), 1, step.data_ptr(), zero.data_ptr(), N, K, G,
+                             Y.data_ptr(), 1, N, None, p, size, torch.cuda.current_stream().cuda_stream) == 0
+        out.append(Y)
+    assert torch.equal(out[0], out[1])
