@@ -160,9 +160,11 @@ int w4a8_gemm(const int8_t *Xq, const float *sx, int64_t M,
  *   sx_out  NULL, or float [M] that receives the token scales        (both: checks, not needed for Y)
  *   workspace / workspace_bytes: at least w4a8_linear_workspace_bytes(...) bytes, 256-byte aligned: the int8
  *               activations, the token scales and w4a8_gemm's own workspace (untouched by the one-launch
- *               path, which needs none and accepts NULL).
+ *               path, which needs none and accepts NULL).  w4a8_linear_workspace_preferred_bytes: what the call would like,
+ *               as for w4a8_gemm (with less it does without, with the same bits in Y).
  * Shape limits and errors as for quantize_act_int8 and w4a8_gemm; M == 0 or N == 0 is a no-op. */
 size_t w4a8_linear_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t group_size, int layout);
+size_t w4a8_linear_workspace_preferred_bytes(int64_t M, int64_t N, int64_t K, int64_t group_size, int layout);
 int w4a8_linear(const void *X, int x_dtype, int64_t M, int64_t K, int64_t ldx, const float *s,
                 const uint8_t *Wp, int layout, const float *step, const uint8_t *zero,
                 int64_t N, int64_t group_size, void *Y, int y_dtype, int64_t ldy,

@@ -31,6 +31,7 @@ EXPORTS = (
     "quantize_act_int8", "quantize_weight_dint4", "pack_dint4", "unpack_dint4",
     "w4a8_gemm_workspace_bytes", "w4a8_gemm_workspace_preferred_bytes", "w4a8_gemm", "w4a8_status_string",
     "w4a8_gemm_static", "w4a8_gemm_static_scratch_bytes", "w4a8_linear", "w4a8_linear_workspace_bytes",
+    "w4a8_linear_workspace_preferred_bytes",
     "quantize_act_int8_asym", "dint4_weight_sums", "w4a8_gemm_asym", "w4a8_gemm_batched",
     "quantize_value_dint4",
     "aqas_search_workspace_bytes", "aqas_channel_absmax", "aqas_scale", "aqas_search",
@@ -83,6 +84,8 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
     lib.w4a8_gemm_static.restype = ci
     lib.w4a8_linear_workspace_bytes.argtypes = [i64, i64, i64, i64, ci]
     lib.w4a8_linear_workspace_bytes.restype = sz
+    lib.w4a8_linear_workspace_preferred_bytes.argtypes = [i64, i64, i64, i64, ci]
+    lib.w4a8_linear_workspace_preferred_bytes.restype = sz
     lib.w4a8_linear.argtypes = [vp, ci, i64, i64, i64, vp, vp, ci, vp, vp, i64, i64, vp, ci, i64, vp, vp, vp,
                                 vp, sz, vp]
     lib.w4a8_linear.restype = ci
@@ -149,7 +152,7 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
     # (several threads may be here at once: each global is published complete)
     _addr = {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
              for name in ("quantize_act_int8", "quantize_act_int8_asym", "w4a8_gemm", "w4a8_gemm_asym", "w4a8_linear",
-                          "w4a8_gemm_workspace_bytes", "w4a8_gemm_workspace_preferred_bytes", "w4a8_linear_workspace_bytes")}
+                          "w4a8_gemm_workspace_bytes", "w4a8_gemm_workspace_preferred_bytes", "w4a8_linear_workspace_preferred_bytes")}
     _native = native
     _lib = lib
     return lib
@@ -304,8 +307,9 @@ def w4a8_linear(X: torch.Tensor, s, Wp: torch.Tensor, step: torch.Tensor, zero: 
     says for which K), or, from five tokens and K = 5120 on where nothing but a fresh Y is asked for, two faster ones.
     Returns Y, or (Y, Xq, sx[, acc]) with want_quantized / want_acc."""
     if Y is None and workspace is None and not want_quantized and not want_acc:
-        out = _native_call("linear", "w4a8_linear", _address("w4a8_linear"), _address("w4a8_linear_workspace_bytes"),
-                           _address("quantize_act_int8"), _address("w4a8_gemm"), _address("w4a8_gemm_workspace_bytes"), X, s, Wp, step, zero, N, group_size or 0, layout, _DTYPES[out_dtype])
+        out = _native_call("linear", "w4a8_linear", _address("w4a8_linear"),
+                           _address("w4a8_linear_workspace_preferred_bytes"), _address("quantize_act_int8"), _address("w4a8_gemm"),
+                           _address("w4a8_gemm_workspace_bytes"), X, s, Wp, step, zero, N, group_size or 0, layout, _DTYPES[out_dtype])
         if out is not NotImplemented:
             return out
     M, K, ldx = _rows(X, "X")
@@ -315,7 +319,7 @@ def w4a8_linear(X: torch.Tensor, s, Wp: torch.Tensor, step: torch.Tensor, zero: 
     Xq = torch.empty((M, K), dtype=torch.int8, device=X.device) if want_quantized else None
     sx = torch.empty((M,), dtype=torch.float32, device=X.device) if want_quantized else None
     acc = torch.empty((M, N, K // G), dtype=torch.int32, device=X.device) if want_acc else None
-    need = int(load_library().w4a8_linear_workspace_bytes(M, N, K, int(group_size or 0), int(layout)))
+    need = int(load_library().w4a8_linear_workspace_preferred_bytes(M, N, K, int(group_size or 0), int(layout)))
     if workspace is None and need > 0:
         workspace = torch.empty((need,), dtype=torch.uint8, device=X.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()

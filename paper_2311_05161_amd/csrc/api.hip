@@ -360,6 +360,14 @@ size_t w4a8_linear_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t grou
     int64_t G = group_size;
     if (!resolve_group(K, G) || !gemm_shape_ok(M, N, K, G) || !valid_layout(layout) || M == 0 || N == 0)
         return 0;
+    return plan_linear(M, N, K, G, layout).total;
+}
+
+size_t w4a8_linear_workspace_preferred_bytes(int64_t M, int64_t N, int64_t K, int64_t group_size, int layout)
+{
+    int64_t G = group_size;
+    if (!resolve_group(K, G) || !gemm_shape_ok(M, N, K, G) || !valid_layout(layout) || M == 0 || N == 0)
+        return 0;
     return plan_linear(M, N, K, G, layout).wanted;
 }
 

@@ -78,6 +78,18 @@ def test_workspace_sizes(lib):
     # last 8 channel tiles (1024 channels) run with K in four ranges: their fp32 partial sums
     assert lib.gemm_workspace_bytes(2048, 5120, 5120, 128, lib.LAYOUT_TILED) == 4 * 2048 * 1024 * 4
     assert lib.gemm_workspace_bytes(2048, 4096, 4096, 128, lib.LAYOUT_TILED) == 0   # exactly one round
+    # the whole layer: int8 activations, token scales and the product's workspace; decoded weights (N K bytes and a thirtieth) are
+    # only what the call would like
+    L = lib.load_library()
+    for (M, N, K, G, wants) in ((16, 5120, 5120, 128, False), (200, 13824, 5120, 128, False), (2048, 5120, 13824, 128, True),
+                                (4096, 36864, 9216, 128, True), (4096, 36864, 9216, 0, False)):
+        up = lambda v: (v + 255) // 256 * 256   # noqa: E731
+        least = up(M * K) + up(4 * M) + lib.gemm_workspace_bytes(M, N, K, G, lib.LAYOUT_TILED)
+        assert L.w4a8_linear_workspace_bytes(M, N, K, G, lib.LAYOUT_TILED) == least
+        decoded = (N + 31) // 32 * 32 * K + K // 128 * ((N + 255) // 256 * 256) * 4 if wants else 0
+        assert L.w4a8_linear_workspace_preferred_bytes(M, N, K, G, lib.LAYOUT_TILED) == least + decoded
+    assert L.w4a8_linear_workspace_preferred_bytes(2048, 0, 1024, 128, 1) == 0
+    assert L.w4a8_linear_workspace_preferred_bytes(32, 16, 64, 0, 1) == 0
     # empty or invalid shapes size to nothing (and divide by nothing): an empty dimension, a K or a
     # group that is no multiple of 128, a channel count that is no multiple of 16
     L = lib.load_library()
