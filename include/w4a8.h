@@ -285,9 +285,12 @@ int w4a8_gemm_batched(const int8_t *Xq, const float *sx, const int32_t *zx, int6
  *                 F16: 16-byte aligned rows (pointer % 16 == 0, ld % 8 == 0)
  *   s_out    out  [K] float: s at the chosen grid point      best_j  out  int32 (device)
  *   losses   out  [17] double (device): loss of every grid point
- *   workspace     device scratch of aqas_search_workspace_bytes(M, N, K, group_size) bytes, 256-byte aligned
+ *   workspace     device scratch of at least aqas_search_workspace_bytes(M, N, K, group_size) bytes, 256-byte aligned;
+ *                 with aqas_search_workspace_preferred_bytes (up to some 350 MB more) a search of more than 16 tokens tries its
+ *                 candidates side by side, in up to half the time
  * Shape limits as for w4a8_gemm (N % 16 == 0, K % 128 == 0, groups multiples of 128). */
 size_t aqas_search_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t group_size);
+size_t aqas_search_workspace_preferred_bytes(int64_t M, int64_t N, int64_t K, int64_t group_size);
 int aqas_channel_absmax(const void *A, int dtype, int64_t R, int64_t K, int64_t lda, float *out,
                         void *stream);                         /* out[k] = max_r |A[r,k]|, exact */
 int aqas_scale(const float *ax, const float *aw, int64_t K, int j, float *s, void *stream);

@@ -34,7 +34,7 @@ EXPORTS = (
     "w4a8_linear_workspace_preferred_bytes",
     "quantize_act_int8_asym", "dint4_weight_sums", "w4a8_gemm_asym", "w4a8_gemm_batched",
     "quantize_value_dint4",
-    "aqas_search_workspace_bytes", "aqas_channel_absmax", "aqas_scale", "aqas_search",
+    "aqas_search_workspace_bytes", "aqas_search_workspace_preferred_bytes", "aqas_channel_absmax", "aqas_scale", "aqas_search",
     "dint4_clipped_params", "aqas_clip_search",
     "quantize_weight_format", "w4a8_gemm_format", "pack_dint3", "unpack_dint3", "pack_format",
     "unpack_format",
@@ -105,6 +105,8 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
     lib.quantize_value_dint4.restype = ci
     lib.aqas_search_workspace_bytes.argtypes = [i64, i64, i64, i64]
     lib.aqas_search_workspace_bytes.restype = sz
+    lib.aqas_search_workspace_preferred_bytes.argtypes = [i64, i64, i64, i64]
+    lib.aqas_search_workspace_preferred_bytes.restype = sz
     lib.aqas_channel_absmax.argtypes = [vp, ci, i64, i64, i64, vp, vp]
     lib.aqas_channel_absmax.restype = ci
     lib.aqas_scale.argtypes = [vp, vp, i64, ci, vp, vp]
@@ -463,7 +465,7 @@ def aqas_scale(ax: torch.Tensor, aw: torch.Tensor, j: int) -> torch.Tensor:
 
 
 def _aqas_ws(M, N, K, group_size, device):
-    need = int(load_library().aqas_search_workspace_bytes(M, N, K, int(group_size or 0)))
+    need = int(load_library().aqas_search_workspace_preferred_bytes(M, N, K, int(group_size or 0)))
     return torch.empty((max(need, 1),), dtype=torch.uint8, device=device), need
 
 

@@ -565,7 +565,7 @@ AqasWs plan_aqas(int64_t M, int64_t N, int64_t K, int64_t G, int cand)
     return w;
 }
 
-// the side-by-side plan where the workspace holds it (a caller may have kept a size from when there was none)
+// the side-by-side plan where the workspace holds it
 AqasWs plan_aqas_for(int64_t M, int64_t N, int64_t K, int64_t G, size_t workspace_bytes)
 {
     const int cand = aqas_candidates(M, N, K, G);
@@ -662,6 +662,14 @@ int aqas_evaluate_batch(const void *W, int dtype, int64_t M, int64_t N, int64_t 
 extern "C" {
 
 size_t aqas_search_workspace_bytes(int64_t M, int64_t N, int64_t K, int64_t group_size)
+{
+    int64_t G = group_size;
+    if (M < 1 || N < 1 || !resolve_group(K, G) || K % TILE_K != 0 || G % TILE_K != 0 || N % TILE_N != 0)
+        return 0;
+    return plan_aqas(M, N, K, G, 1).total;
+}
+
+size_t aqas_search_workspace_preferred_bytes(int64_t M, int64_t N, int64_t K, int64_t group_size)
 {
     int64_t G = group_size;
     if (M < 1 || N < 1 || !resolve_group(K, G) || K % TILE_K != 0 || G % TILE_K != 0 || N % TILE_N != 0)

@@ -221,6 +221,14 @@ def test_argument_errors_are_reported_before_any_launch(lib):
     need = lib.load_library().aqas_search_workspace_bytes(32, 64, 256, 0)
     assert need > 32 * 256 + 64 * 256 + 64 * 128 + 32 * 64 * 6
     assert lib.load_library().aqas_search_workspace_bytes(32, 60, 256, 0) == 0   # N % 16
+    # the size that is enough holds one candidate; many side by side are only what a search would like
+    M, N, K, G = 512, 4096, 4096, 128
+    least = lib.load_library().aqas_search_workspace_bytes(M, N, K, G)
+    parts = 3 * 4 * K + M * K + 4 * M + 3 * N * K // 2 + 5 * N * (K // G) + 6 * M * N + 16 * N + lib.gemm_workspace_bytes(M, N, K, G)
+    assert parts <= least <= parts + 16 * 256
+    assert lib.load_library().aqas_search_workspace_preferred_bytes(M, N, K, G) > 4 * least
+    assert lib.load_library().aqas_search_workspace_preferred_bytes(32, 60, 256, 0) == 0
+    assert lib.load_library().aqas_search_workspace_preferred_bytes(16, N, K, G) == lib.load_library().aqas_search_workspace_bytes(16, N, K, G)
 
     def search(dt=b.F16, M=32, N=64, K=256, ldx=256, G=0, X=P, ws=ctypes.c_void_p(0x10000), wsb=1 << 30,
                s_out=P):

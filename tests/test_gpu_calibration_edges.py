@@ -79,12 +79,12 @@ def test_side_by_side_against_one_by_one(lib, M, K, N, G, dtype):
     X, W = X.to(DTYPES[dtype]), (torch.randn((N, K), generator=g, device="cuda") * 0.02).to(DTYPES[dtype])
     c, i32, f64 = lib.load_library(), torch.int32, torch.float64
     code = {"f32": 0, "f16": 1, "bf16": 2}[dtype]
-    full = int(c.aqas_search_workspace_bytes(M, N, K, G))
-    # what one candidate at a time needs: everything but the side-by-side operands (a bound from its parts)
-    small = full
-    part = [3 * 4 * K, M * K, 4 * M, N * K, 5 * N * (K // (G or K)) + 256, N * K // 2, 6 * M * N, 16 * N,
+    full, small = int(c.aqas_search_workspace_preferred_bytes(M, N, K, G)), int(c.aqas_search_workspace_bytes(M, N, K, G))
+    # what one candidate at a time needs, from its parts; side by side needs more (the operands of 17 candidates, or of fewer in
+    # several rounds), so that the two sizes are two paths
+    part = [3 * 4 * K, M * K, 4 * M, N * K, 5 * N * (K // (G or K)), N * K // 2, 6 * M * N, 16 * N,
             int(c.w4a8_gemm_workspace_bytes(M, N, K, G, 1))]
-    small = min(full, sum(part) + 256 * 16)
+    assert sum(part) <= small <= sum(part) + 256 * 16 and small + 3 * M * K < full
     out = {}
     for need in (full, small):
         ws = torch.full((need,), 255, dtype=torch.uint8, device="cuda")
