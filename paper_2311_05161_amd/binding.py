@@ -154,7 +154,8 @@ def load_library(path: str | None = None) -> ctypes.CDLL:
     # (several threads may be here at once: each global is published complete)
     _addr = {name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
              for name in ("quantize_act_int8", "quantize_act_int8_asym", "w4a8_gemm", "w4a8_gemm_asym", "w4a8_linear",
-                          "w4a8_gemm_workspace_bytes", "w4a8_gemm_workspace_preferred_bytes", "w4a8_linear_workspace_preferred_bytes")}
+                          "w4a8_gemm_workspace_bytes", "w4a8_gemm_workspace_preferred_bytes", "w4a8_linear_workspace_bytes",
+                          "w4a8_linear_workspace_preferred_bytes")}
     _native = native
     _lib = lib
     return lib
@@ -274,14 +275,39 @@ def gemm_workspace_bytes(M: int, N: int, K: int, group_size: int = 0,
     return int(load_library().w4a8_gemm_workspace_bytes(M, N, K, int(group_size or 0), int(layout)))
 
 
+def gemm_workspace_preferred_bytes(M: int, N: int, K: int, group_size: int = 0,
+                                   layout: int = LAYOUT_TILED) -> int:
+    """What w4a8_gemm would like; gemm_workspace_bytes is what it has to have."""
+    return int(load_library().w4a8_gemm_workspace_preferred_bytes(M, N, K, int(group_size or 0), int(layout)))
+
+
+def linear_workspace_bytes(M: int, N: int, K: int, group_size: int = 0, layout: int = LAYOUT_TILED) -> int:
+    return int(load_library().w4a8_linear_workspace_bytes(M, N, K, int(group_size or 0), int(layout)))
+
+
+def linear_workspace_preferred_bytes(M: int, N: int, K: int, group_size: int = 0,
+                                     layout: int = LAYOUT_TILED) -> int:
+    return int(load_library().w4a8_linear_workspace_preferred_bytes(M, N, K, int(group_size or 0), int(layout)))
+
+
+def _scratch(preferred: int, least: int, device):
+    """Scratch of the size that a call would like, or of the size that it has to have where the allocator does not give so
+    much (None for none)."""
+    if preferred > least:
+        try:
+            return torch.empty((preferred,), dtype=torch.uint8, device=device)
+        except torch.OutOfMemoryError:
+            pass
+    return torch.empty((least,), dtype=torch.uint8, device=device) if least > 0 else None
+
+
 def w4a8_gemm(Xq: torch.Tensor, sx: torch.Tensor, Wp: torch.Tensor, step: torch.Tensor,
               zero: torch.Tensor, N: int, K: int, group_size: int = 0, layout: int = LAYOUT_TILED,
               out_dtype=torch.float16, Y=None, acc_out=None, workspace=None, want_acc=False):
     """Y [M,N] = dequant(Xq . dINT4(Wp)^T); optionally also the exact int32 accumulators."""
     if Y is None and acc_out is None and workspace is None and not want_acc:
-        out = _native_call("gemm", "w4a8_gemm", _address("w4a8_gemm"),
-                           _address("w4a8_gemm_workspace_preferred_bytes"), Xq, sx,
-                           Wp, step, zero, N, K, group_size or 0, layout, _DTYPES[out_dtype])
+        out = _native_call("gemm", "w4a8_gemm", _address("w4a8_gemm"), _address("w4a8_gemm_workspace_preferred_bytes"),
+                           _address("w4a8_gemm_workspace_bytes"), Xq, sx, Wp, step, zero, N, K, group_size or 0, layout, _DTYPES[out_dtype])
         if out is not NotImplemented:
             return out
     M = Xq.shape[0]
@@ -290,9 +316,9 @@ def w4a8_gemm(Xq: torch.Tensor, sx: torch.Tensor, Wp: torch.Tensor, step: torch.
     G = K if group_size in (0, None) else int(group_size)
     if want_acc and acc_out is None:
         acc_out = torch.empty((M, N, K // G), dtype=torch.int32, device=Xq.device)
-    need = int(load_library().w4a8_gemm_workspace_preferred_bytes(M, N, K, int(group_size or 0), int(layout)))
-    if workspace is None and need > 0:
-        workspace = torch.empty((need,), dtype=torch.uint8, device=Xq.device)
+    if workspace is None:
+        workspace = _scratch(gemm_workspace_preferred_bytes(M, N, K, group_size, layout),
+                             gemm_workspace_bytes(M, N, K, group_size, layout), Xq.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     ldy = Y.stride(0) if M > 1 else max(Y.stride(0), N)
     _check(load_library().w4a8_gemm(_ptr(Xq), _ptr(sx), M, _ptr(Wp), int(layout), _ptr(step),
@@ -310,8 +336,8 @@ def w4a8_linear(X: torch.Tensor, s, Wp: torch.Tensor, step: torch.Tensor, zero: 
     Returns Y, or (Y, Xq, sx[, acc]) with want_quantized / want_acc."""
     if Y is None and workspace is None and not want_quantized and not want_acc:
         out = _native_call("linear", "w4a8_linear", _address("w4a8_linear"),
-                           _address("w4a8_linear_workspace_preferred_bytes"), _address("quantize_act_int8"), _address("w4a8_gemm"),
-                           _address("w4a8_gemm_workspace_bytes"), X, s, Wp, step, zero, N, group_size or 0, layout, _DTYPES[out_dtype])
+                           _address("w4a8_linear_workspace_preferred_bytes"), _address("w4a8_linear_workspace_bytes"),
+                           _address("quantize_act_int8"), _address("w4a8_gemm"), _address("w4a8_gemm_workspace_bytes"), X, s, Wp, step, zero, N, group_size or 0, layout, _DTYPES[out_dtype])
         if out is not NotImplemented:
             return out
     M, K, ldx = _rows(X, "X")
@@ -321,9 +347,9 @@ def w4a8_linear(X: torch.Tensor, s, Wp: torch.Tensor, step: torch.Tensor, zero: 
     Xq = torch.empty((M, K), dtype=torch.int8, device=X.device) if want_quantized else None
     sx = torch.empty((M,), dtype=torch.float32, device=X.device) if want_quantized else None
     acc = torch.empty((M, N, K // G), dtype=torch.int32, device=X.device) if want_acc else None
-    need = int(load_library().w4a8_linear_workspace_preferred_bytes(M, N, K, int(group_size or 0), int(layout)))
-    if workspace is None and need > 0:
-        workspace = torch.empty((need,), dtype=torch.uint8, device=X.device)
+    if workspace is None:
+        workspace = _scratch(linear_workspace_preferred_bytes(M, N, K, group_size, layout),
+                             linear_workspace_bytes(M, N, K, group_size, layout), X.device)
     ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
     ldy = Y.stride(0) if M > 1 else max(Y.stride(0), N)
     _check(load_library().w4a8_linear(_ptr(X), _DTYPES[X.dtype], M, K, ldx, _ptr(s), _ptr(Wp), int(layout),
@@ -465,8 +491,10 @@ def aqas_scale(ax: torch.Tensor, aw: torch.Tensor, j: int) -> torch.Tensor:
 
 
 def _aqas_ws(M, N, K, group_size, device):
-    need = int(load_library().aqas_search_workspace_preferred_bytes(M, N, K, int(group_size or 0)))
-    return torch.empty((max(need, 1),), dtype=torch.uint8, device=device), need
+    lib, G = load_library(), int(group_size or 0)
+    least = int(lib.aqas_search_workspace_bytes(M, N, K, G))
+    ws = _scratch(int(lib.aqas_search_workspace_preferred_bytes(M, N, K, G)), max(least, 1), device)
+    return ws, ws.numel() if least > 0 else 0
 
 
 def aqas_search(X: torch.Tensor, W: torch.Tensor, group_size: int = 0):

@@ -74,6 +74,21 @@ at::Tensor make(const at::Tensor &like, at::IntArrayRef size, at::ScalarType t)
     return at::empty(size, like.options().dtype(t));
 }
 
+// Scratch of the size that a call would like, or of the size that it has to have where the allocator does not give so much
+// (undefined for none).
+at::Tensor scratch(const at::Tensor &like, size_t preferred, size_t least)
+{
+    if (preferred > least) {
+        try {
+            return make(like, {(int64_t)preferred}, at::kByte);
+        } catch (const c10::OutOfMemoryError &) {
+        }
+    }
+    return least > 0 ? make(like, {(int64_t)least}, at::kByte) : at::Tensor();
+}
+void *data(const at::Tensor &t) { return t.defined() ? t.data_ptr() : nullptr; }
+size_t size(const at::Tensor &t) { return t.defined() ? (size_t)t.numel() : 0; }
+
 PyObject *not_implemented() { Py_RETURN_NOTIMPLEMENTED; }
 PyObject *status(int rc) { return PyLong_FromLong(rc); }
 
@@ -133,31 +148,30 @@ PyObject *act_quant_asym(PyObject *, PyObject *const *a, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
-// gemm(entry, workspace_entry, Xq, sx, Wp, step, zero, N, K, group_size, layout, y_dtype, stream) -> Y
+// gemm(entry, preferred_workspace_entry, workspace_entry, Xq, sx, Wp, step, zero, N, K, group_size, layout, y_dtype, stream) -> Y
 PyObject *gemm(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
-    if (n != 13) return not_implemented();
-    for (int i = 2; i < 7; ++i)
+    if (n != 14) return not_implemented();
+    for (int i = 3; i < 8; ++i)
         if (!plain(a[i])) return not_implemented();
     decltype(&w4a8_gemm) entry;
-    decltype(&w4a8_gemm_workspace_bytes) need;
+    decltype(&w4a8_gemm_workspace_bytes) wish, need;
     int64_t N, K, G, layout, yd, stream;
-    if (!to_fn(a[0], entry) || !to_fn(a[1], need)) return nullptr;
-    if (!to_i64(a[7], N) || !to_i64(a[8], K) || !to_i64(a[9], G) ||
-        !to_i64(a[10], layout) || !to_i64(a[11], yd) || !to_i64(a[12], stream))
+    if (!to_fn(a[0], entry) || !to_fn(a[1], wish) || !to_fn(a[2], need)) return nullptr;
+    if (!to_i64(a[8], N) || !to_i64(a[9], K) || !to_i64(a[10], G) ||
+        !to_i64(a[11], layout) || !to_i64(a[12], yd) || !to_i64(a[13], stream))
         return not_implemented();
-    const at::Tensor &Xq = THPVariable_Unpack(a[2]);
+    const at::Tensor &Xq = THPVariable_Unpack(a[3]);
     if (Xq.dim() < 1 || N < 0) return not_implemented();
     const int64_t M = Xq.size(0);
     at::Tensor Y = make(Xq, {M, N}, y_type(yd));
-    const size_t bytes = need(M, N, K, G, (int)layout);
-    at::Tensor ws;
-    if (bytes > 0) ws = make(Xq, {(int64_t)bytes}, at::kByte);
-    const int8_t *q = (const int8_t *)ptr(a[2]);
-    const float *sx = (const float *)ptr(a[3]), *step = (const float *)ptr(a[5]);
-    const uint8_t *Wp = (const uint8_t *)ptr(a[4]), *zero = (const uint8_t *)ptr(a[6]);
-    void *y = Y.data_ptr(), *w = bytes > 0 ? ws.data_ptr() : nullptr;
+    const at::Tensor ws = scratch(Xq, wish(M, N, K, G, (int)layout), need(M, N, K, G, (int)layout));
+    const size_t bytes = size(ws);
+    const int8_t *q = (const int8_t *)ptr(a[3]);
+    const float *sx = (const float *)ptr(a[4]), *step = (const float *)ptr(a[6]);
+    const uint8_t *Wp = (const uint8_t *)ptr(a[5]), *zero = (const uint8_t *)ptr(a[7]);
+    void *y = Y.data_ptr(), *w = data(ws);
     int rc;
     Py_BEGIN_ALLOW_THREADS
     rc = entry(q, sx, M, Wp, (int)layout, step, zero, N, K, G, y, (int)yd, N, nullptr, w, bytes, (void *)stream);
@@ -202,42 +216,42 @@ PyObject *gemm_asym(PyObject *, PyObject *const *a, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
-// linear(entry, workspace_entry, act_quant_entry, gemm_entry, gemm_workspace_entry, X, s, Wp, step, zero, N, group_size,
-//        layout, y_dtype, stream) -> Y
+// linear(entry, preferred_workspace_entry, workspace_entry, act_quant_entry, gemm_entry, gemm_workspace_entry, X, s, Wp, step,
+//        zero, N, group_size, layout, y_dtype, stream) -> Y
 PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
-    if (n != 15 || !plain(a[5]) || !plain_or_none(a[6]) || !plain(a[7]) || !plain(a[8]) || !plain(a[9]))
+    if (n != 16 || !plain(a[6]) || !plain_or_none(a[7]) || !plain(a[8]) || !plain(a[9]) || !plain(a[10]))
         return not_implemented();
     decltype(&w4a8_linear) entry;
-    decltype(&w4a8_linear_workspace_bytes) need;
+    decltype(&w4a8_linear_workspace_bytes) wish, need;
     decltype(&quantize_act_int8) quantize;
     decltype(&w4a8_gemm) product;
     decltype(&w4a8_gemm_workspace_bytes) product_need;
     int64_t N, G, layout, yd, stream;
-    if (!to_fn(a[0], entry) || !to_fn(a[1], need) || !to_fn(a[2], quantize) || !to_fn(a[3], product) ||
-        !to_fn(a[4], product_need))
+    if (!to_fn(a[0], entry) || !to_fn(a[1], wish) || !to_fn(a[2], need) || !to_fn(a[3], quantize) ||
+        !to_fn(a[4], product) || !to_fn(a[5], product_need))
         return nullptr;
-    if (!to_i64(a[10], N) || !to_i64(a[11], G) ||
-        !to_i64(a[12], layout) || !to_i64(a[13], yd) || !to_i64(a[14], stream))
+    if (!to_i64(a[11], N) || !to_i64(a[12], G) ||
+        !to_i64(a[13], layout) || !to_i64(a[14], yd) || !to_i64(a[15], stream))
         return not_implemented();
-    const at::Tensor &X = THPVariable_Unpack(a[5]);
+    const at::Tensor &X = THPVariable_Unpack(a[6]);
     const Rows r = rows_of(X);
     if (!r.ok || N < 0) return not_implemented();
     at::Tensor Y = make(X, {r.M, N}, y_type(yd));
     const void *x = X.data_ptr();
-    const float *s = (const float *)ptr(a[6]), *step = (const float *)ptr(a[8]);
-    const uint8_t *Wp = (const uint8_t *)ptr(a[7]), *zero = (const uint8_t *)ptr(a[9]);
+    const float *s = (const float *)ptr(a[7]), *step = (const float *)ptr(a[9]);
+    const uint8_t *Wp = (const uint8_t *)ptr(a[8]), *zero = (const uint8_t *)ptr(a[10]);
     void *y = Y.data_ptr();
     int rc = W4A8_ERR_WORKSPACE;
     if (r.M > 4 && r.M <= 16 && r.K >= 5120 && r.dtype == W4A8_F16 && layout == LAYOUT_TILED) {
         // the two steps by themselves, faster here than in one launch (the times stand beside w4a8_linear's rule)
-        const size_t bytes = product_need(r.M, N, r.K, G, (int)layout);
-        at::Tensor Xq = make(X, {r.M, r.K}, at::kChar), sx = make(X, {r.M}, at::kFloat), ws;
-        if (bytes > 0) ws = make(X, {(int64_t)bytes}, at::kByte);
+        const at::Tensor Xq = make(X, {r.M, r.K}, at::kChar), sx = make(X, {r.M}, at::kFloat);
+        const at::Tensor ws = scratch(X, 0, product_need(r.M, N, r.K, G, (int)layout));
+        const size_t bytes = size(ws);
         int8_t *q = (int8_t *)Xq.data_ptr();
         float *sxp = (float *)sx.data_ptr();
-        void *w = bytes > 0 ? ws.data_ptr() : nullptr;
+        void *w = data(ws);
         Py_BEGIN_ALLOW_THREADS
         rc = quantize(x, r.dtype, r.M, r.K, r.ld, s, q, sxp, (void *)stream);
         if (rc == W4A8_OK)
@@ -255,10 +269,8 @@ PyObject *linear(PyObject *, PyObject *const *a, Py_ssize_t n)
     // before anything is launched).
     if (r.M <= 16 && r.dtype == W4A8_F16 && layout == LAYOUT_TILED) call(nullptr, 0);
     if (rc == W4A8_ERR_WORKSPACE) {
-        const size_t bytes = need(r.M, N, r.K, G, (int)layout);
-        at::Tensor ws;
-        if (bytes > 0) ws = make(X, {(int64_t)bytes}, at::kByte);
-        call(bytes > 0 ? ws.data_ptr() : nullptr, bytes);
+        const at::Tensor ws = scratch(X, wish(r.M, N, r.K, G, (int)layout), need(r.M, N, r.K, G, (int)layout));
+        call(data(ws), size(ws));
     }
     return rc != W4A8_OK ? status(rc) : THPVariable_Wrap(Y);
     END_HANDLE_TH_ERRORS
