@@ -730,30 +730,37 @@ static int launch_gemm_t(const GemmPlan &pl, const int8_t *Xq, const float *sx, 
 #undef W4A8_GM2
 }
 
-// ---- group-128 weights whose tiles do not fill the chip twice --------------------------------------
+// ---- group-wise weights whose tiles do not fill the chip twice -------------------------------------
 // Between the streaming kernel (<= 16 tokens per pass over the weights) and the tile kernel at full
 // occupancy (512 resident 128 x 128 tiles) lie a few hundred tokens, or more on narrow layers: the tile kernel has
 // too few tiles there, and cutting K into ranges over more workgroups moves more fp32 partial sums through
 // memory than the layer has weights.  This kernel cuts K inside the workgroup instead.  A workgroup
-// owns 128 tokens x 256 / KQ channels; its 8 waves are 8 / KQ channel parts of 32 x KQ K phases: phase q takes
-// the k-tiles kt = KQ i + q -- with 128-wide groups each k-tile is one whole group, so a wave decodes,
-// multiplies and rescales complete groups exactly like the tile kernel does, and no group is shared.
+// owns 32 MS tokens x 256 / KQ channels; its 8 waves are 8 / KQ channel parts of 32 x KQ K phases: phase q takes
+// the groups KQ i + q, so a wave decodes, multiplies and rescales complete groups exactly like the tile kernel does (one rounding
+// of a group's exact integer sum), and no group is shared.
 // The KQ k-tiles of a super-step are consumed concurrently from KQ LDS slots while the next KQ
 // land in the other KQ (global -> LDS copies, issued under the first MFMAs behind the barrier that frees the slots):
 // one barrier per KQ k-tiles.  At the end the phases' fp32 sums meet through LDS in a fixed order
-// (q0 + q1, or (q0 + q1) + (q2 + q3)), and the phase-0 waves apply the token scale and store.  No workspace, no second
-// launch.  KQ = 4: 64 channels per workgroup; KQ = 2: 128, for twice the tiles on the same CUs.
+// (q0 + q1, or (q0 + q1) + (q2 + q3)), and every wave applies the token scale to its share of the tile and stores it.  No
+// workspace, no second launch.  KQ = 4: 64 channels per workgroup; KQ = 2: 128, for twice the tiles on the same CUs.
 // ASYM: token zero-points, one 24-bit multiply-add per accumulator and group as in gemm_kernel.
 // MS: 32-token blocks of the workgroup, two to four (see gemm_mid_form).
+// MULTI: groups of tpg k-tiles.  A round of KQ groups takes tpg super-steps; the integer sums run on from k-tile to k-tile and are
+// rescaled behind the last one of a group (between the matrix instructions, as with one k-tile per group, would take the
+// loop's body twice, which spills).  Phases without a group in the last round wait.  (Phases that share the k-tiles of a group,
+// each rounding its own, were 3 % faster on 77 shapes and 10 % on the shortest, and rounded tpg times as often: rms error of the fp32
+// sums of K = 8192 in groups of 1024 1.06e-7 with two phases and 0.84e-7 with four, 0.49e-7 and 0.50e-7 here, 0.54e-7 in a chain of all
+// groups as in the tile kernel.)  Before / now, us: groups of 256 209 x 2048 x 4320 20.8 / 11.7, 510 x 1280 x 1280 15.0 /
+// 8.9, 636 x 10240 x 1024 27.0 / 25.8, of 512 513 x 3072 x 4112 30.1 / 19.1, of 1024 502 x 12288 x 3120 41.5 / 37.9.
 constexpr int MD_BN = 64, MD_KQ = 4, MD_THREADS = 512;
 
-template <bool ACC_OUT, int KQ, bool ASYM, int MS>
+template <bool ACC_OUT, int KQ, bool ASYM, int MS, bool MULTI>
 __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     const int8_t *__restrict__ Xq, const float *__restrict__ sx, const int32_t *__restrict__ zx,
-    const int32_t *__restrict__ tsum, int M, const uint8_t *__restrict__ Wt,
+    const int32_t *__restrict__ wsum, int M, const uint8_t *__restrict__ Wt,
     const float *__restrict__ step, const uint8_t *__restrict__ zero, int N, int K,
     uint16_t *__restrict__ Y, int y_dtype, int64_t ldy, int vec_store, int32_t *__restrict__ acc_out,
-    int grid_m, int plain, int ng, uint32_t inv_tpg)
+    int grid_m, int plain, int ng, int tpg, uint32_t inv_tpg)
 {
     constexpr int MD_BM = 32 * MS, MD_TILE = MD_BM * TILE_K;   // tokens; bytes of one activation k-tile in LDS
     constexpr int WN = 8 / KQ;       // channel parts
@@ -771,10 +778,12 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     const int r32 = lane & 31;
     const int kh = lane >> 5;
     const int KT = K / TILE_K;
-    // group of a k-tile, by a reciprocal (2^16 / k-tiles per group, rounded up: exact for 512 k-tiles and 64 of them per group)
-    // (groups of one k-tile only where another register would spill)
-    auto group_of = [&](int kt) { return ASYM && MS == 4 ? kt : (int)((uint32_t)__umul24((uint32_t)kt, inv_tpg) >> 16); };
-    const int SS = (KT + KQ - 1) / KQ;
+    const int SS = MULTI ? (ng + KQ - 1) / KQ * tpg : (KT + KQ - 1) / KQ;
+    // the round of groups that super-step ss belongs to, by a reciprocal (2^16 / tpg, rounded up: exact while ss tpg < 2^16), the
+    // k-tile and the group of phase j in it (past the end where there is none)
+    auto round_of = [&](int ss) { return MULTI ? (int)(((uint32_t)ss * inv_tpg) >> 16) : ss; };
+    auto kt_of = [&](int ss, int j) { return MULTI ? ss + (round_of(ss) * (KQ - 1) + j) * tpg : ss * KQ + j; };
+    auto group_of = [&](int ss, int j) { return round_of(ss) * KQ + j; };
     // (workgroups are handed to the 8 XCDs round-robin: renumbered so that the token tiles that share weights
     // share an L2)
     int bid = blockIdx.x;
@@ -816,7 +825,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     // copy c of this wave for super-step ss (into the slots of its parity)
     auto dma_one = [&](int ss, int c) {
         const int q = c * 8 + wave, j = q / TB;
-        const int kt = min(ss * KQ + j, KT - 1);
+        const int kt = min(kt_of(ss, j), KT - 1);
         const int slot = (ss & 1) * KQ + j;
         dma_b128(rx, avoff[c % OFFS], kt * TILE_K, lds_base + (uint32_t)(slot * MD_TILE + (q - j * TB) * 1024));
     };
@@ -829,12 +838,11 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     int gp_z = 0, gp_w = 0;
     auto fetch_params = [&](int ss, float &gp_es, int &gp_z, int &gp_w) {
         if (tid < KQ * BN) {
-            const int kt = min(ss * KQ + tid / BN, KT - 1);
+            const int g = min(group_of(ss, tid / BN), ng - 1);
             const int nn = nb0 + tid % BN < N ? nb0 + tid % BN : 0;
-            const int g = group_of(kt);
             gp_es = step[(int64_t)nn * ng + g];   // (used only in publish_params: nothing here waits for the load)
             gp_z = zero[(int64_t)nn * ng + g];
-            if (ASYM) gp_w = tsum[(int64_t)nn * KT + kt];
+            if (ASYM) gp_w = wsum[(int64_t)nn * ng + g];
         }
     };
     auto publish_params = [&](int ss, float gp_es, int gp_z, int gp_w) {
@@ -871,26 +879,23 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         decode_word_signed(q1, slut, c, d);
         dst = v4i{a, b, c, d};
     };
-    // y += (step / 8) * acc for accumulator registers 4 b .. 4 b + 3 of token block ms (group kt)
+    // y += (step / 8) * acc for accumulator registers 4 b .. 4 b + 3 of token block ms (group g)
     v4f es4[4];   // step / 8 of this lane's 16 channels for the group in the accumulators
     v4i gw4[ASYM ? 4 : 1];   // and 4 * (sum of the group's weights)
     int nzx[MS];  // minus the zero-point of this lane's token of each block
 #pragma unroll
     for (int ms = 0; ms < MS; ++ms) nzx[ms] = (ASYM && m0 + ms * 32 + r32 < M) ? -zx[m0 + ms * 32 + r32] : 0;
-    auto flush_quarter = [&](int ms, int b, int kt) {
+    auto flush_quarter = [&](int ms, int b, int g) {
         const int m = m0 + ms * 32 + r32;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int v = acc[ms][4 * b + r];
+            if (MULTI) acc[ms][4 * b + r] = 0;   // (the next group adds on)
             const int vz = ASYM ? v + __mul24(nzx[ms], gw4[ASYM ? b : 0][r]) : v;   // (|4 wsum| < 2^23)
             y[ms][4 * b + r] = __builtin_fmaf(es4[b][r], (float)vz, y[ms][4 * b + r]);
             if (ACC_OUT && m < M) {
                 const int nn = nb0 + wn * 32 + 8 * b + 4 * kh + r;
-                if (nn < N) {
-                    int32_t *a = &acc_out[((int64_t)m * N + nn) * ng + group_of(kt)];
-                    if (ng == KT) *a = v >> 2;
-                    else atomicAdd(a, v >> 2);   // (the phases share a group; exact)
-                }
+                if (nn < N) acc_out[((int64_t)m * N + nn) * ng + g] = v >> 2;
             }
         }
     };
@@ -900,7 +905,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     v4u pw[4][2];   // packed weights of this wave's next four k-tiles (the weights come from HBM, read once)
     dma_super_step(0);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) load_b(i * KQ + kq, pw[i]);
+    for (int i = 0; i < 4; ++i) load_b(kt_of(i, kq), pw[i]);
     {   // (all three super-steps' on their way before the first is waited for)
         float es0 = 0.f, es1 = 0.f;
         int z0 = 0, z1 = 0, w0 = 0, w1 = 0;
@@ -920,8 +925,14 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
 #pragma unroll
     for (int k = 0; k < 4; ++k) decode_step(pw[0], k, w[k]);
     bool pending = false;   // (uniform) accumulators of the last token block of the previous k-tile wait for their rescale
+    if (MULTI) {
+#pragma unroll
+        for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[ms][r] = 0;
+    }
 
-    // One super-step of this wave: k-tile kt = 4 ss + q (= one group) from LDS slot (ss parity, q).
+    // One super-step of this wave: its k-tile kt_of(ss, q) from LDS slot (ss parity, q).
     // The MFMAs run token block by token block (four k-steps each), so that the rescale of block ms - 1
     // -- whose group sum is complete -- and, under the last block, the decode of the NEXT k-tile (each
     // w[k] is free once the last MFMA that reads it has issued) sit between the MFMAs of block ms:
@@ -939,7 +950,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     // of ss for ss + 2.  Group parameters: ring of four super-steps, published two ahead (the decode of
     // the next k-tile needs its zero-points before the next barrier).
     auto super_step = [&](v4u(&P)[2], v4u(&PN)[2], v4u(&PNN)[2], int ss) __attribute__((always_inline)) {
-        const int kt = ss * KQ + kq;
+        const int kt = kt_of(ss, kq), g = group_of(ss, kq);
         const int slot = (ss & 1) * KQ + kq;
         const int pslot = (ss & 3) * KQ + kq;
         const int pslot_next = ((ss + 1) & 3) * KQ + kq;
@@ -948,9 +959,9 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
 #pragma unroll
             for (int k = 0; k < 4; ++k) af[k] = read_a(slot, 0, k);
         }
-        if (pending) {
+        if (!MULTI && pending) {   // (of the group before)
 #pragma unroll
-            for (int b = 0; b < 4; ++b) flush_quarter(MS - 1, b, kt - KQ);
+            for (int b = 0; b < 4; ++b) flush_quarter(MS - 1, b, g - KQ);
             pending = false;
         }
         if (live) {
@@ -975,7 +986,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
                 }
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
-                    if (k == 0) acc[ms] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[0], af[0], z16, 0, 0, 0);
+                    if (k == 0 && !MULTI) acc[ms] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[0], af[0], z16, 0, 0, 0);
                     else acc[ms] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[k], af[k], acc[ms], 0, 0, 0);
                     if (ms + 1 < MS) af[k] = read_a(slot, ms + 1, k);
                     // the copies of the next super-step, spread over the MFMAs of the first block: issued in one burst
@@ -984,7 +995,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
 #pragma unroll
                         for (int c = CPW * k / 4; c < CPW * (k + 1) / 4; ++c) dma_one(ss + 1, c);
                     }
-                    if (ms > 0) flush_quarter(ms - 1, k, kt);
+                    if (!MULTI && ms > 0) flush_quarter(ms - 1, k, g);
                     if (ms + 1 == MS) {
                         if (k == 0) slut = make_signed_lut(z_next, plain != 0);
                         decode_step(PN, k, w[k]);
@@ -992,15 +1003,21 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
                     __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                     if (ms + 1 < MS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
                     if (ms + 1 == MS) __builtin_amdgcn_sched_group_barrier(0x002, 32, 0);
-                    else if (ms > 0) __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
+                    else if (!MULTI && ms > 0) __builtin_amdgcn_sched_group_barrier(0x002, 8, 0);
                 }
             }
-            pending = true;
+            if (!MULTI) pending = true;
+            else if (ss + 1 == (round_of(ss) + 1) * tpg) {   // (uniform) the last k-tile of its group
+#pragma unroll
+                for (int ms = 0; ms < MS; ++ms)
+#pragma unroll
+                    for (int b = 0; b < 4; ++b) flush_quarter(ms, b, g);
+            }
         } else {
             dma_super_step(ss + 1);
         }
         gm_order_fence();
-        load_b((ss + 4) * KQ + kq, P);
+        load_b(kt_of(ss + 4, kq), P);
         gm_order_fence();
         wait_copies<2>();
         // (a use in every lane, outside any branch: all waits for the parameter loads and for PNN happen
@@ -1023,10 +1040,10 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         if (ss < SS) super_step(pw[0], pw[1], pw[2], ss);
         if (ss + 1 < SS) super_step(pw[1], pw[2], pw[3], ss + 1);
         if (ss + 2 < SS) super_step(pw[2], pw[3], pw[0], ss + 2);
-        if (pending) {   // the last live k-tile of this wave: KQ (SS - 1) + q, or the one before
-            const int kt_last = (SS - 1) * KQ + kq;
+        if (!MULTI && pending) {   // the last live k-tile of this wave: KQ (SS - 1) + q, or the one before
+            const int g_last = group_of(SS - 1, kq);
 #pragma unroll
-            for (int b = 0; b < 4; ++b) flush_quarter(MS - 1, b, kt_last < KT ? kt_last : kt_last - KQ);
+            for (int b = 0; b < 4; ++b) flush_quarter(MS - 1, b, g_last < ng ? g_last : g_last - KQ);
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1380,7 +1397,7 @@ int gemm_mid_phases(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
     return w2 <= 256 && KT >= 12 && KT * (216 - w2) <= (asym ? 3400 : 4800) ? 2 : 0;
 }
 
-template <int KQ, bool ASYM, int MS>
+template <int KQ, bool ASYM, int MS, bool MULTI>
 static int launch_gemm_mid_t(const int8_t *Xq, const float *sx, ZeroPoint zp, int64_t M, const uint8_t *Wt,
                              const float *step, const uint8_t *zero, int64_t N, int64_t K, int64_t G, void *Y, int y_dtype,
                              int64_t ldy, int32_t *acc_out, hipStream_t st, int plain)
@@ -1394,12 +1411,12 @@ static int launch_gemm_mid_t(const int8_t *Xq, const float *sx, ZeroPoint zp, in
 #define W4A8_MD(AO_)                                                                                           \
     do {                                                                                                       \
         static std::atomic<uint64_t> lds_opted{0};                                                             \
-        if (opt_in_dynamic_lds((const void *)gemm_mid_kernel<AO_, KQ, ASYM, MS>, lds_bytes, lds_opted) != W4A8_OK) \
+        if (opt_in_dynamic_lds((const void *)gemm_mid_kernel<AO_, KQ, ASYM, MS, MULTI>, lds_bytes, lds_opted) != W4A8_OK) \
             return W4A8_ERR_HIP;                                                                               \
-        hipLaunchKernelGGL((gemm_mid_kernel<AO_, KQ, ASYM, MS>), dim3((unsigned)(grid_m * grid_n)),                \
-                           dim3(MD_THREADS), lds_bytes, st, Xq, sx, zp.zx, zp.tsum, (int)M, Wt, step, zero,    \
+        hipLaunchKernelGGL((gemm_mid_kernel<AO_, KQ, ASYM, MS, MULTI>), dim3((unsigned)(grid_m * grid_n)),                \
+                           dim3(MD_THREADS), lds_bytes, st, Xq, sx, zp.zx, zp.wsum, (int)M, Wt, step, zero,    \
                            (int)N, (int)K, (uint16_t *)Y, y_dtype, ldy, vec_store, acc_out, grid_m, plain,     \
-                           (int)(K / G), (uint32_t)((65536 + G / TILE_K - 1) / (G / TILE_K)));                 \
+                           (int)(K / G), (int)(G / TILE_K), (uint32_t)((65536 + G / TILE_K - 1) / (G / TILE_K)));                 \
     } while (0)
     if (acc_out) W4A8_MD(true);
     else W4A8_MD(false);
@@ -1540,8 +1557,9 @@ bool gemm_reads_row_sums(int64_t M, int64_t N, int64_t K, int64_t G)
 // 0.8 (three blocks) and 0.65 (two) of the time of four wherever they still fit one workgroup per CU.  What a launch takes,
 // us, with KT k-tiles and w workgroups: a + b KT + d KT w / 256; the tile kernel with K in ranges: a time that goes with the
 // k-tiles of a range, its share of the chip and the partial sums; 16-token blocks of the streaming kernel: one that goes with
-// the generations of workgroups, the k-tiles of a wave and the weights that all blocks read.  Larger groups go the same way, a
-// k-tile at a time (groups of 256 209 x 2048 x 4320 21.1 / 11.1, 645 x 2048 x 2016 22.3 / 11.1).  Constants fitted to 620
+// the generations of workgroups, the k-tiles of a wave and the weights that all blocks read.  Larger groups go by the same constants
+// with KT counting the k-tiles of whole rounds of groups (measured times of groups of 256 over them 0.92 to 1.09, mean 1.00, of 512
+// and more 0.82 to 0.99).  Constants fitted to 620
 // shapes of 17 to 1600 tokens with every kernel timed on each; the choice is 0.2 % slower on average than the best of them
 // (without the forms of two and three blocks 9 % from 65 tokens on, 12 to 17 % from 33 to 64).
 // Before / now, us (tokens x K x N): 607 x 4096 x 4096 31.3 / 27.3, with zero-points 36.9 / 31.8, 700 x 8192 x 3072 49.6 / 44.0; instead of
@@ -1558,8 +1576,30 @@ MidForm gemm_mid_form(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
     const auto time_of = [&](int phases, int blocks) {
         const int64_t w = (M + 32 * blocks - 1) / (32 * blocks) * ((N + 256 / phases - 1) / (256 / phases));
         const double *c = cost[asym][phases == 4][blocks - 2];
-        return w <= 256 ? c[0] + (double)KT * (c[1] + c[2] * (double)w / 256.0) : 1e30;
+        // (larger groups: whole ones per phase, so that some of the last round's phases may have none)
+        const int64_t kts = G == TILE_K ? KT : (K / G + phases - 1) / phases * phases * (G / TILE_K);
+        return w <= 256 ? c[0] + (double)kts * (c[1] + c[2] * (double)w / 256.0) : 1e30;
     };
+    // Mean square of the roundings of an output's fp32 sum, in units of one rounding of the whole (a partial sum of n of ng groups
+    // counts n / ng): with few large groups the phases' sums can be rounded more often than the tile kernel's, in one chain of all
+    // groups or in the ranges that it would cut here, and then the shape stays there.  (Token blocks round every k-tile.)
+    const int64_t ng = K / G;
+    const auto chain = [&](int64_t n) { return 0.5 * (double)(n * (n + 1)) / (double)ng; };
+    const auto roundings = [&](int phases) {
+        const int64_t n = ng / phases, longer = ng % phases;
+        return (double)longer * chain(n + 1) + (double)(phases - longer) * chain(n) + (phases == 4 ? 2.0 : 1.0);
+    };
+    double allowed = 1e30;
+    if (G != TILE_K && gemv_token_blocks(M, N, K, G) == 0) {
+        const GemmPlan pl = plan_gemm(M, N, K, G);
+        const int64_t n = std::max<int64_t>(1, pl.kt_per_split / (G / TILE_K));
+        allowed = chain(std::min(n, ng));
+        for (int64_t at = n; at < ng; at += n) {   // a range's own sum, and its addition to those before it
+            const int64_t to = std::min(at + n, ng);
+            allowed += chain(to - at) + (double)to / (double)ng;
+        }
+        allowed = std::max(allowed, chain(ng));
+    }
     MidForm best = {0, 4};
     double t;
     if (const int nb = gemv_token_blocks(M, N, K, G)) {
@@ -1578,9 +1618,10 @@ MidForm gemm_mid_form(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
         const double wgs = (double)((M + 127) / 128 * ((N + 127) / 128) * pl.splits) / 512.0;
         t = (double)pl.kt_per_split * (0.98 + (asym ? 0.73 : 0.48) * wgs) +
             (pl.splits > 1 ? (asym ? 9.2 : 8.5) + (asym ? 1.8e-6 : 1.6e-6) * (double)(pl.splits * M * N) : 5.0);
-        if (G != TILE_K) t *= 0.85;   // (the tile kernel rescales once per group, this one once per k-tile)
+        if (G != TILE_K) t *= 0.85;   // (the tile kernel rescales less often in larger groups)
     }
-    for (int phases = 4; phases >= 2; phases -= 2)
+    for (int phases = 4; phases >= 2; phases -= 2) {
+        if (G != TILE_K && roundings(phases) > allowed) continue;
         for (int blocks = 2; blocks <= (G != TILE_K ? (asym ? 3 : 4) : M <= 128 ? 4 : 3); ++blocks) {
             const double tf = time_of(phases, blocks);
             if (tf < t) {
@@ -1588,6 +1629,7 @@ MidForm gemm_mid_form(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)
                 t = tf;
             }
         }
+    }
     return best;
 }
 
@@ -1619,12 +1661,14 @@ int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, in
         return W4A8_ERR_SHAPE;
     const MidForm form = gemm_mid_form(M, N, K, G, zp.zx != nullptr);
     if (form.phases != 0) {
-        if (acc_out && G != TILE_K) {   // the k-tiles of a group add their exact sums
-            const int rc = launch_fill_i32(acc_out, M * N * (K / G), 0, st);
-            if (rc != W4A8_OK) return rc;
-        }
-#define W4A8_MD_T(KQ_, AS_, MS_) \
-    return launch_gemm_mid_t<KQ_, AS_, MS_>(Xq, sx, zp, M, Wt, step, zero, N, K, G, Y, y_dtype, ldy, acc_out, st, plain)
+#define W4A8_MD_L(KQ_, AS_, MS_, MULTI_) \
+    return launch_gemm_mid_t<KQ_, AS_, MS_, MULTI_>(Xq, sx, zp, M, Wt, step, zero, N, K, G, Y, y_dtype, ldy, acc_out, st, plain)
+#define W4A8_MD_T(KQ_, AS_, MS_)                              \
+    do {                                                      \
+        if (G == TILE_K) W4A8_MD_L(KQ_, AS_, MS_, false);     \
+        if (MS_ == 4 && AS_) return W4A8_ERR_SHAPE;   /* (the rule has no such form; it would spill) */ \
+        W4A8_MD_L(KQ_, AS_, MS_, (MS_ < 4 || !AS_));          \
+    } while (0)
 #define W4A8_MD_M(AS_, MS_)                           \
     do {                                              \
         if (form.phases == 4) W4A8_MD_T(4, AS_, MS_); \
@@ -1640,6 +1684,7 @@ int launch_gemm(const int8_t *Xq, const float *sx, ZeroPoint zp, int32_t *rs, in
         W4A8_MD_M(false, 4);
 #undef W4A8_MD_M
 #undef W4A8_MD_T
+#undef W4A8_MD_L
     }
     // (the workspace of a shape with token blocks is sized for the streaming kernel: it does not come here)
     if (gemv_token_blocks(M, N, K, G) > 0) return W4A8_ERR_SHAPE;

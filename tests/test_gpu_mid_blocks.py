@@ -47,7 +47,7 @@ def test_products(M, K, N, want, asym):
     _check(M, K, N, 128, asym, ydtype="bf16" if M % 2 else "f16", ypad=M % 3)
 
 
-# groups of several k-tiles: the phases share a group (the last shape would otherwise be token blocks, whose
+# groups of several k-tiles: a phase has whole ones (the last shape would otherwise be token blocks, whose
 # workspace holds no partial sums)
 @pytest.mark.gpu
 @pytest.mark.parametrize("asym", [False, True])
