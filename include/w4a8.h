@@ -273,7 +273,9 @@ int w4a8_gemm_batched(const int8_t *Xq, const float *sx, const int32_t *zx, int6
  * X [M, K] and the layer's weights W [N, K] it looks for the per-input-channel scale s that minimizes
  *     loss(s) = sum_{m,n} ( Yq[m,n] - sum_k X[m,k] W[n,k] )^2,    Yq = the fp16 output of the quantized
  * layer computed by this library's own kernels (quantize_act_int8, quantize_weight_dint4, pack_dint4,
- * w4a8_gemm) with that s.  Representatives are the maximum magnitudes per input channel (App. A.4):
+ * w4a8_gemm) with that s; of more than 16 tokens, with a workspace of the preferred size, by kernels that take several
+ * candidates at once, whose outputs are w4a8_gemm's up to the order of its fp32 sums (an fp16 output near a tie may round the
+ * other way: losses differ by some 1e-6, and candidates that are that close may change places).  Representatives are the maximum magnitudes per input channel (App. A.4):
  *     ax[k] = max_m |X[m,k]|,   aw[k] = max_n |W[n,k]|,
  * and the candidates are the 17 grid points j = 0..16 of
  *     s_k(j) = ax[k]^(j/16) / aw[k]^(1 - j/16)        (1 where ax[k] or aw[k] is 0; clamped to [1e-4, 1e4]),
@@ -304,7 +306,7 @@ int aqas_search(const void *X, const void *W, int dtype, int64_t M, int64_t N, i
  * that function with use_given_params (values beyond the range saturate).
  *   dint4_clipped_params: index [N] int32 (device) gives i per output channel, or NULL: uniform_index for all.
  *   aqas_clip_search: tries every i for all channels, measures each output channel's own error
- *     sum_m (Yq[m,n] - Y[m,n])^2 with the layer's kernels as in aqas_search, and keeps per channel the
+ *     sum_m (Yq[m,n] - Y[m,n])^2 as aqas_search does (one candidate at a time or several at once), and keeps per channel the
  *     first i with the smallest error.  index_out [N] int32, step_out / zero_out [N, K/G] the chosen
  *     parameters, err_table NULL or [11, N] double (every candidate's errors).  Workspace as aqas_search. */
 int dint4_clipped_params(const void *W, int w_dtype, int64_t N, int64_t K, int64_t ldw, const float *s,

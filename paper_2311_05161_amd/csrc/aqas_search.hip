@@ -1,8 +1,9 @@
 // AQAS scale search (Sec. 3.2, Eq. 1: the scale vector s minimizes the squared error of the quantized
 // layer's output against the unquantized product on calibration activations; App. A.4: maximum
 // magnitude per input channel as the representative of activations and weights, a grid search, then
-// weight clipping).  Offline work whose inner loop is the layer itself: every candidate runs the layer's
-// activation and weight quantizers, packing and w4a8_gemm, the kernels below supply the
+// weight clipping).  One candidate at a time, the inner loop is the layer itself: the layer's activation and weight
+// quantizers, packing and w4a8_gemm; several at a time, the same definitions in kernels with a candidate index (below and in
+// weight_quant.hip, gemm_i8.hip, gemm_prefill.hip), whose fp32 sums may run in another order.  The kernels below supply the
 // representatives, the scale family, the unquantized product and the error sums.  Everything stays on
 // the stream: the best grid point is picked on the device and the final scale is computed from it there.
 //

@@ -68,6 +68,24 @@ def test_equal_scales_give_equal_losses(lib, N):
         assert int(host(best)[0]) == 0
 
 
+# the same for candidates side by side: group-wise with one and several token tiles, a last tile of one row, per channel, all in one
+# round and in several rounds of unequal size (the last two)
+@pytest.mark.parametrize("M,K,N,G", [(17, 256, 2064, 128), (300, 256, 4096, 128), (257, 384, 272, 128), (300, 128, 2064, 0), (129, 512, 80, 0),
+                                     (1024, 1024, 8192, 0), (1100, 1024, 12288, 128)])
+def test_equal_scales_give_equal_losses_side_by_side(lib, M, K, N, G):
+    c = lib.load_library()
+    assert c.aqas_search_workspace_preferred_bytes(M, N, K, G) > c.aqas_search_workspace_bytes(M, N, K, G) + 3 * M * K
+    for seed in range(4):
+        g = torch.Generator(device="cuda").manual_seed(seed)
+        X = (torch.rand((M, K), generator=g, device="cuda") * 2 - 1).half()
+        W = (torch.rand((N, K), generator=g, device="cuda") * 2 - 1).half()
+        X[0], W[0] = 1.0, -1.0
+        s, best, losses = lib.aqas_search(X, W, G)
+        assert (host(s) == 1.0).all()
+        assert (host(losses) == host(losses)[0]).all(), seed
+        assert int(host(best)[0]) == 0
+
+
 # A workspace of the size that one candidate at a time needs is enough, whatever the search would like to have; candidates
 # side by side (several rounds of them on the last shape) see the same errors to fp16 rounding of single outputs.
 @pytest.mark.parametrize("M,K,N,G,dtype", [(17, 128, 16, 128, "f16"), (300, 384, 272, 128, "bf16"), (64, 8192, 64, 128, "f16"),
@@ -95,13 +113,26 @@ def test_side_by_side_against_one_by_one(lib, M, K, N, G, dtype):
         ng = K // (G or K)
         idx, step, zero, table = (torch.empty(n, dtype=t, device="cuda") for n, t in
                                   ((N, i32), (N * ng, torch.float32), (N * ng, torch.uint8), (11 * N, f64)))
+        j = int(host(best)[0])
         s.fill_(1.25)
         assert c.aqas_clip_search(X.data_ptr(), W.data_ptr(), code, M, N, K, K, K, s.data_ptr(), G, idx.data_ptr(),
                                   step.data_ptr(), zero.data_ptr(), table.data_ptr(), ws.data_ptr(), need, stream) == 0
-        out[need] = (host(losses), host(table).reshape(11, N))
+        out[need] = (host(losses), host(table).reshape(11, N), j, host(idx), host(step), host(zero))
     np.testing.assert_allclose(out[full][0], out[small][0], rtol=LOSS_TOL)
     # single channels: a few outputs may round the other way, each by one fp16 step of its value (see the bound above)
     ulp = 2.0 ** -10 * host((X.float() @ W.float().t()).abs().amax(0)).astype(np.float64) * 1.1
     err = out[small][1]
     bound = 6 * ulp * (6 * np.sqrt(err / M) + ulp)
     assert np.all(np.abs(out[full][1] - err) <= 1e-5 * err + bound)
+    # the same winners, but for grid points and factors whose errors are equal to within that
+    j, k = out[full][2], out[small][2]
+    assert out[small][0][j] <= out[small][0][k] * (1 + 2 * LOSS_TOL)
+    a, b = out[full][3], out[small][3]
+    n = np.arange(N)
+    gap = err[a, n] - err[b, n]
+    assert np.all((gap >= 0) & (gap <= 2e-5 * err[a, n] + bound[a, n] + bound[b, n]))
+    same = a == b
+    print(f"grid point {j} / {k}, clipping factors the same in {same.mean():.4f} of {N} channels")
+    ng = K // (G or K)
+    for p in (4, 5):
+        np.testing.assert_array_equal(out[full][p].reshape(N, ng)[same], out[small][p].reshape(N, ng)[same])
