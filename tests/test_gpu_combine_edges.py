@@ -7,8 +7,21 @@ import pytest
 torch = pytest.importorskip("torch")
 
 from gpu_util import acc_by_float64_matmul, assert_y_close, decode_table_np, dev, host  # noqa: E402
+from test_launch_plans import route  # noqa: E402
 
 pytestmark = pytest.mark.gpu
+
+
+# tile kernel with K in ranges: one output per thread beyond 1024 blocks, the XCDs' eighths whole and ragged, row-major order whole
+# and ragged, each up to four ranges and beyond
+RANGES = [(1033, 5376, 48, 128), (385, 1024, 6944, 128), (361, 4608, 912, 512), (1298, 4608, 256, 512), (153, 1280, 5888, 0),
+          (149, 2304, 5760, 0), (779, 1024, 1280, 0), (586, 1024, 4752, 128), (1208, 4608, 272, 512), (1109, 1536, 48, 512)]
+
+
+@pytest.mark.parametrize("M,K,N,G", RANGES)
+def test_ranges_are_on_the_tile_kernel(M, K, N, G):
+    r = route(M, K, N, G)
+    assert r[0] == "tile" and r[2] >= 2
 
 
 @pytest.mark.parametrize("M,K,N,G", [(16, 13824, 1040, 128), (3, 11008, 48, 0), (130, 16384, 48, 128),
@@ -16,7 +29,7 @@ pytestmark = pytest.mark.gpu
                                      (64, 11008, 4096, 0), (70, 13824, 4112, 512),
                                      (1290, 5120, 48, 128), (1030, 16384, 304, 128),
                                      (390, 5120, 1024, 256), (173, 1280, 8128, 256), (150, 2048, 2064, 512),
-                                     (130, 5120, 4112, 0)])
+                                     (130, 5120, 4112, 0)] + RANGES)
 @pytest.mark.parametrize("ypad,ydtype", [(0, "f16"), (1, "bf16"), (6, "f16")])
 def test_combine_edges(M, K, N, G, ypad, ydtype):
     import paper_2311_05161_amd as lib

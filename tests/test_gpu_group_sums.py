@@ -1,14 +1,11 @@
 """Everywhere but on the streaming kernel, whose waves share the k-tiles of a group, the integer sum of a whole group is rounded once:
 activations whose k-tiles cancel inside every group (against weights that repeat from k-tile to k-tile) give exact zeros, where sums
 rounded k-tile by k-tile leave rests."""
-import ctypes
-
 import pytest
 
 torch = pytest.importorskip("torch")
 
-from test_gpu_mid_blocks import MidForm  # noqa: E402
-from test_launch_plans import I64, _rule  # noqa: E402
+from test_launch_plans import route  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
@@ -22,9 +19,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("asym", [False, True])
 def test_whole_groups_are_rounded_once(M, K, N, G, form, asym):
     import paper_2311_05161_amd as w
-    r = _rule("13gemm_mid_formEllllb", MidForm, I64, I64, I64, I64, ctypes.c_bool)(M, N, K, G, asym)
     if not asym:
-        assert ((r.phases, r.blocks) if r.phases else None) == form
+        r = route(M, K, N, G)
+        assert r[1:] == form if form else r[0] == "tile"
     g = torch.Generator(device="cuda").manual_seed(K + N)
     T = G // 128
     a, b = (torch.randint(-60, 61, (M, K // G, 128), generator=g, device="cuda") for _ in "ab")

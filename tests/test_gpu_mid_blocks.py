@@ -8,11 +8,7 @@ import pytest
 pytest.importorskip("torch")
 
 from test_gpu_mid_edges import _check  # noqa: E402
-from test_launch_plans import I64, _rule  # noqa: E402
-
-
-class MidForm(ctypes.Structure):   # csrc/w4a8_common.hpp
-    _fields_ = [("phases", ctypes.c_int), ("blocks", ctypes.c_int)]
+from test_launch_plans import I64, MidForm, _rule  # noqa: E402
 
 
 def form(M, K, N, asym=False):

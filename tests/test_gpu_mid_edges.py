@@ -41,12 +41,13 @@ def _check(M, K, N, G, asym, ydtype="f16", ypad=0, fmt=0, hook=False):
         assert np.array_equal(host(acc_gpu), acc.astype(np.int64))
 
 
-# four phases: 64 .. 256 workgroups of 64 channels; 9, 10, 11, 13 k-tiles leave phases without one in the last step
+# Where the four-block form has four phases: 64 .. 256 workgroups of 64 channels; 9, 10, 11, 13 k-tiles leave phases without one in the
+# last step (which form each shape gets: test_launch_plans.py; every form at its ragged edges: test_gpu_routes.py)
 FOUR = [(65, 1024, 4096), (257, 1152, 1360), (300, 1280, 1360), (385, 1408, 1040), (512, 1664, 4096), (1000, 1024, 1040)]
-# two phases: more than 256 of those, up to 256 of 128 channels; odd and even counts of k-tiles
+# where it has two: more than 256 of those, up to 256 of 128 channels; odd and even counts of k-tiles
 TWO = [(129, 1536, 13824), (513, 1664, 4112), (640, 2048, 4096), (1024, 1792, 4096), (2048, 1536, 2032)]
-# what the rule leaves to the tile kernel: too few workgroups, long K on few workgroups, few k-tiles, too many workgroups (and
-# four phases over 128 k-tiles, which it takes)
+# few workgroups and long K (two or three token blocks by now), four phases over 128 k-tiles, and what stays on the tile kernel: few
+# k-tiles, too many workgroups
 TILE = [(300, 2048, 512), (600, 16384, 1040), (600, 16384, 2560), (1024, 1024, 4096), (1100, 1536, 4096), (2048, 1536, 2064)]
 
 

@@ -429,11 +429,14 @@ def test_k_phase_kernel_per_channel_on_a_full_size_layer(lib, oracle, M):
 
 
 def test_64_token_tiles_on_a_layer_too_large_for_token_blocks(lib, oracle):
-    """64 tokens on 24832 x 5120 group-128 weights: four 16-token blocks would need more than two
-    generations of workgroups, so this runs on the tile kernel's 64-row instance."""
-    # (the workspace tells: two K-ranges of fp32 partial sums, which only the tile kernel asks for here)
-    assert lib.gemm_workspace_bytes(64, 24832, 5120, 128, lib.LAYOUT_TILED) == 2 * 64 * 24832 * 4
+    """64 tokens on 24832 x 5120 and 36928 x 5120 group-128 weights: four 16-token blocks would need more than two
+    generations of workgroups.  The former fits the K-phase kernel (two phases, 64-token tiles), the latter has more channels
+    than it takes and runs on the tile kernel's 64-row instance."""
+    from test_launch_plans import route
+    assert route(64, 5120, 24832, 128) == ("phases", 2, 2)
     _full_size_case(lib, oracle, "C4_5120x13824", M=64, N=24832, seed=64)
+    assert route(64, 5120, 36928, 128) == ("tile", 64, 1, 0)
+    _full_size_case(lib, oracle, "C4_5120x13824", M=64, N=36928, seed=64)
 
 
 def test_last_round_of_group_wise_tiles_runs_with_k_in_ranges(lib, oracle):

@@ -112,7 +112,9 @@ GEMM_CASES = [
     ("blocks_m20_k_ranges_per_channel", 20, 11008, 32, 0),
     ("blocks_m36_k_ranges_g128", 36, 9216, 48, 128),
     ("prefill_m64_g128", 64, 512, 256, 128),
-    ("prefill_m130_g128_ksplit", 130, 1024, 304, 128),
+    ("k_phases_m130_g128", 130, 1024, 304, 128),
+    ("tile_k_ranges_m132_g128", 132, 5504, 48, 128),
+    ("tile_k_ranges_m148_g512", 148, 2560, 64, 512),
     ("prefill_m300", 300, 768, 1040, 0),
     ("prefill_two_workgroups_per_cu_ragged", 1030, 256, 7440, 0),
     ("prefill_m300_g256", 300, 768, 512, 256),

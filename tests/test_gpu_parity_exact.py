@@ -109,13 +109,16 @@ EXACT_CASES = [
     ("tile_128_rows_per_channel_one_per_cu", 300, 768, 1040, 0),
     ("tile_128_rows_per_channel_two_per_cu", 2048, 256, 11008, 0),
     ("tile_128_rows_group128", 300, 768, 512, 128),
-    ("tile_128_rows_group256_ragged", 270, 1024, 400, 256),
+    ("tile_128_rows_group256_ragged", 270, 512, 400, 256),
     ("tile_128_rows_group128_many_tiles", 1100, 512, 4112, 128),
     ("tile_128_rows_group128_last_round_k_ranges", 1100, 5120, 7696, 128),
-    ("tile_k_ranges_group256", 130, 2048, 304, 256),
+    ("tile_k_ranges_group128", 132, 5632, 48, 128),
+    ("tile_k_ranges_group512", 148, 3072, 64, 512),
     ("tile_k_ranges_per_channel", 300, 2048, 304, 0),
     # K in four phases inside the workgroup (group-128, 129 .. 256 tokens, few output tiles)
     ("k_phases_group128", 130, 2048, 304, 128),
+    ("k_phases_group256", 130, 2048, 304, 256),
+    ("two_k_phases_group256", 270, 1024, 400, 256),
     ("k_phases_group128_ragged_last_super_step", 256, 2816, 1040, 128),
     ("k_phases_group128_40_ktiles", 130, 5120, 1040, 128),
     ("k_phases_per_channel", 130, 2048, 304, 0),

@@ -19,6 +19,10 @@ class GemmPlan(ctypes.Structure):
         (n, ctypes.c_int) for n in ("rem_n", "rem_splits", "rem_kt_per_split", "pc_rem_n")]
 
 
+class MidForm(ctypes.Structure):
+    _fields_ = [("phases", ctypes.c_int), ("blocks", ctypes.c_int)]
+
+
 def _rule(symbol, restype, *argtypes):
     f = w.load_library()["_ZN4w4a8" + symbol]
     f.restype, f.argtypes = restype, argtypes
@@ -28,6 +32,22 @@ def _rule(symbol, restype, *argtypes):
 def plan_gemv(M, N, K, G, batch=1, token_blocks=False):
     f = _rule("9plan_gemvElllllb", GemvPlan, I64, I64, I64, I64, I64, ctypes.c_bool)
     return f(M, N, K, G or K, batch, token_blocks)
+
+
+def route(M, K, N, G, asym=False):
+    """The kernel that a product of more than 16 tokens runs on: ("phases", phases, token blocks), ("stream", blocks),
+    ("phases per channel",) or ("tile", rows, K ranges, channels of the last round that run with K in ranges)."""
+    G = G or K
+    r = _rule("13gemm_mid_formEllllb", MidForm, I64, I64, I64, I64, ctypes.c_bool)(M, N, K, G, asym)
+    if r.phases:
+        return "phases", r.phases, r.blocks
+    blocks = _rule("17gemv_token_blocksEllll", ctypes.c_int, I64, I64, I64, I64)(M, N, K, G)
+    if blocks:
+        return "stream", blocks
+    if _rule("19gemm_mid_pc_appliesEllllb", ctypes.c_bool, I64, I64, I64, I64, ctypes.c_bool)(M, N, K, G, asym):
+        return ("phases per channel",)
+    p = _rule("9plan_gemmEllll", GemmPlan, I64, I64, I64, I64)(M, N, K, G)
+    return "tile", p.bm, p.splits, p.rem_n
 
 
 # problems with weights of their own: all the workgroups that fit 256 CUs; 16-token blocks of one problem: a multiple of
@@ -52,15 +72,16 @@ def mid_phases(M, N, K, asym):
     return _rule("15gemm_mid_phasesEllllb", ctypes.c_int, I64, I64, I64, I64, ctypes.c_bool)(M, N, K, 128, asym)
 
 
-# group-128 weights, one shape on either side of each line at which the K-phase and the tile kernel were timed against each
-# other (the times stand beside the rule)
+# group-128 weights, one shape on either side of each line at which the four-block form of the K-phase kernel and the tile kernel
+# were timed against each other (the times stand beside the rule).  Where these lines say yes, the cost rule (gemm_mid_form, which
+# decides) compares the other forms with this one and not with the tile kernel.
 @pytest.mark.parametrize("M,K,N,asym,phases", [
     (512, 5120, 2560, False, 4), (256, 8192, 5120, False, 4), (230, 6144, 3200, False, 4), (192, 12800, 5760, False, 4),
     (250, 9728, 4608, False, 4), (256, 13824, 5120, False, 4), (150, 1536, 1552, False, 4), (129, 1280, 1168, False, 4), (230, 3584, 1984, False, 0),
     (230, 11008, 3840, False, 0), (140, 8192, 3840, False, 0), (450, 7168, 1344, False, 0), (135, 2176, 1152, False, 0),
     (230, 6144, 3840, True, 4), (640, 5120, 1792, True, 4), (384, 8192, 2560, True, 0), (512, 4096, 768, True, 0),
     (256, 2048, 2048, True, 0), (1024, 4096, 4096, False, 2), (512, 13824, 5120, False, 0), (1024, 1024, 4096, False, 0)])
-def test_group_128_route(M, K, N, asym, phases):
+def test_four_block_lines(M, K, N, asym, phases):
     assert mid_phases(M, N, K, asym) == phases
 
 
@@ -74,10 +95,10 @@ def test_per_channel_remainder(M, K, N, rem_n):
     assert pl.pc_rem_n == rem_n and pl.splits == 1
 
 
-# the shapes of the kernels' own tests are on the kernels that they are meant for
+# what decides, at the shapes of the edge tests: every one but a token-block shape and the last three is on the K-phase kernel
 def test_edge_shapes_take_their_kernels():
     from test_gpu_mid_edges import FOUR, TILE, TWO
     for asym in (False, True):
-        assert [mid_phases(s[0], s[2], s[1], asym) for s in FOUR[1:]] == [4] * (len(FOUR) - 1)
-        assert [mid_phases(s[0], s[2], s[1], asym) for s in TWO] == [2] * len(TWO)
-        assert [mid_phases(s[0], s[2], s[1], asym) for s in TILE] == [0, 0, 4, 0, 0, 0]
+        got = [route(*s, 128, asym) for s in FOUR + TWO + TILE]
+        assert got[0] == ("stream", 5) and [r[0] for r in got[1:-3]] == ["phases"] * (len(got) - 4)
+        assert got[-3:] == [("tile", 128, 1, 0)] * 3
