@@ -513,8 +513,8 @@ struct AqasWs {
     int parts;          // partial error sums per channel
 };
 
-// How many candidates run side by side: as many as keep their operands and outputs within 320 MiB (a good half of the
-// last-level cache, through which the launches hand them on).  Fewer than four gain nothing (the layer fills the chip by
+// How many candidates run side by side: as many as keep their operands and outputs within 320 MiB (all 17 of a layer of 4096 x 4096
+// on 512 tokens, a little more than the last-level cache's 256 MB, through which the launches hand them on).  Fewer than four gain nothing (the layer fills the chip by
 // itself then).
 int aqas_candidates(int64_t M, int64_t N, int64_t K, int64_t G)
 {

@@ -54,14 +54,6 @@ __device__ __forceinline__ void lds_barrier()
     asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-// Pins the program order of memory instructions and of everything scheduled around them, at
-// every level of the compiler (emits no instruction).
-__device__ __forceinline__ void order_fence()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
-
 // Decode record of one (channel, k-tile): LUT halves, step / 8, and in the last word -4 beta as an
 // int8 in byte 0 with 4 * tsum in the upper 24 bits (tsum: sum of the tile's weights in half steps,
 // |4 tsum| <= 4 * 26 * 128; zero without a token zero-point).

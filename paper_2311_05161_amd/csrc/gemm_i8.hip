@@ -25,18 +25,6 @@ template <> struct I8Ring<true> { static constexpr int RING = 3; };   // (with 2
 constexpr int I8_CHUNK = 8;      // ERR: k-tiles per block of the running sums
 constexpr int I8_LDS_SUMS = 6;   // ERR: quarters of 4 x 4 block sums per lane that lie in LDS (the last ones), of 16
 
-__device__ __forceinline__ void i8_order_fence()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
-// (see gemm_prefill.hip: global -> LDS copy, lane l's 16 bytes to lds_addr + 16 l; the compiler does not count it)
-__device__ __forceinline__ void i8_dma_b128(v4i rsrc, int voff, int soff, uint32_t lds_addr)
-{
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                 :: "v"(voff), "s"(rsrc), "s"(soff), "s"(lds_addr) : "memory");
-}
-
 // Packed tiles -> int8 blocks, 4 d per weight (the signed decode of the tile kernel).  A wave per tile and turn: lane l
 // (row l % 16, 32-column quarter l / 16) decodes its 16 bytes to the two 16-byte pieces of steps 2 sp and 2 sp + 1.
 // Bound by memory: 1.5 bytes per weight (57 M weights 15.6 us, with the scales of 71 M 24).
@@ -76,10 +64,10 @@ __global__ __launch_bounds__(256) void decode_i8_kernel(const v4u *__restrict__ 
 // partial != null: K in ranges of kt_per_split k-tiles over blockIdx.x (see gemm_kernel), fp32 sums of a range out.
 // ERR (calibration): blockIdx.y is a candidate with weights, scales and (x_tokens = M) activations of its own, and what
 // comes out is, per channel and token tile, the sum of squared differences between the fp16 outputs and Yref: the outputs
-// themselves never leave the registers.  The running sums go in blocks of eight groups there: one rounding per group at
+// themselves never leave the registers.  The running sums go in blocks of eight k-tiles there: one rounding per group at
 // the size of a block's sum and one per block at the size of the whole (a chain of 32 groups rounds at the size of the
-// whole 32 times, and more outputs fall on the other side of an fp16 tie); half of the block sums are kept in
-// registers, half in LDS.
+// whole 32 times, and more outputs fall on the other side of an fp16 tie); of the sixteen quarters of block sums of a lane, ten
+// are kept in registers and six in LDS.
 template <bool ERR>
 __global__ __launch_bounds__(I8_THREADS, 2) void gemm_i8_kernel(
     const int8_t *__restrict__ Xq, const float *__restrict__ sx, int M, const uint8_t *__restrict__ W8,
@@ -141,7 +129,7 @@ __global__ __launch_bounds__(I8_THREADS, 2) void gemm_i8_kernel(
     auto dma = [&](int kt, int slot) {
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            i8_dma_b128(rx, avoff[i], (kt0 + kt) * TILE_K, lds_base + (uint32_t)(slot * I8_TILE + (i * 4 + wave) * 1024));
+            dma_b128(rx, avoff[i], (kt0 + kt) * TILE_K, lds_base + (uint32_t)(slot * I8_TILE + (i * 4 + wave) * 1024));
     };
     // scales of the workgroup's channels (threads 0 .. 127), fetched three groups ahead
     const int g0 = kt0 / tiles_per_group, g_end = g0 + KTl / tiles_per_group;
@@ -248,9 +236,9 @@ __global__ __launch_bounds__(I8_THREADS, 2) void gemm_i8_kernel(
             if (s < 3) __builtin_amdgcn_sched_group_barrier(0x100, I8_MS, 0);
             __builtin_amdgcn_sched_group_barrier(0x008, I8_MS, 0);
         }
-        i8_order_fence();
+        order_fence();
         load_b(min(kt + 2, ktl), P);
-        i8_order_fence();
+        order_fence();
         if (t == 0 && g + 2 < g_end) publish_group(g + 2);   // (read for group g - 2 last, a barrier ago)
         // everything but the loads into P has arrived: the next tile's weights, and the copies of tile kt + RING - 2 (the
         // uses of PN behind the wait keep the compiler from waiting again behind the copies that follow)
@@ -258,12 +246,12 @@ __global__ __launch_bounds__(I8_THREADS, 2) void gemm_i8_kernel(
         asm volatile("" : "+v"(PN[0]), "+v"(PN[1]), "+v"(PN[2]), "+v"(PN[3]));
         dma(min(kt + RING - 1, ktl), slot == 0 ? RING - 1 : slot - 1);
         if (t == 0 && g + 3 < g_end) fetch_group(g + 3);
-        i8_order_fence();
+        order_fence();
         __syncthreads();   // (waits for no copy: the compiler does not know of them)
         // the next tile's first fragments arrive under the rescale
 #pragma unroll
         for (int ms = 0; ms < I8_MS; ++ms) af[0][ms] = read_a(next, 0, ms);
-        i8_order_fence();
+        order_fence();
         if (t == tiles_per_group - 1) flush_group(g);
         if constexpr (ERR && decltype(second)::value) {
             if ((kt & (I8_CHUNK - 1)) == I8_CHUNK - 1) close_block();

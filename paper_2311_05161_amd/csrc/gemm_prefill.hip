@@ -38,24 +38,6 @@ constexpr int GM_OOB = 0x7fff0000;
 constexpr int GM_RING = 4;  // activation tiles in LDS
 constexpr int GM_PANEL = 4; // token tiles per panel of the tile numbering
 
-// Pins the program order of memory instructions and of everything scheduled around them, at every
-// level of the compiler (emits no instruction).
-__device__ __forceinline__ void gm_order_fence()
-{
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_sched_barrier(0);
-}
-
-// Global -> LDS copy that bypasses the registers: lane l of the wave writes its 16 bytes to
-// lds_addr + 16 l (lds_addr: byte address in LDS, wave-uniform); addresses beyond the buffer
-// write zeros.  Completion is counted by vmcnt like any buffer load, but the compiler does not
-// know that this one writes LDS: whoever reads the bytes waits for vmcnt and a barrier first.
-__device__ __forceinline__ void dma_b128(v4i rsrc, int voff, int soff, uint32_t lds_addr)
-{
-    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
-                 :: "v"(voff), "s"(rsrc), "s"(soff), "s"(lds_addr) : "memory");
-}
-
 // Copies issued by dma_b128 are invisible to the compiler's own wait insertion: wait_copies<Y>()
 // returns once at most Y accesses issued after the copies in question are outstanding (vmcnt
 // retires in issue order), and must be followed by a barrier before other waves read the tile.
@@ -423,9 +405,9 @@ __global__ __launch_bounds__(WM * WN * 64, TWO ? 4 : (BN < GM_BN ? 2 : 1)) void 
                 if (!ROLL) read_a(cur, s + 1, af[ROLL ? 0 : ((s + 1) & 1)]);
                 decode_step(P, s + 1, w[(s + 1) & 1]);
             } else {
-                gm_order_fence();
+                order_fence();
                 load_b(min(kt + 2, ktl), P);   // P: last read by the decode during the previous k-step
-                gm_order_fence();
+                order_fence();
                 if (GROUPED && t == tiles_in_group - 1 && g + 1 < g_end) load_luts(g + 1);
                 if (!ROLL) read_a(nxt, 0, af[0]);
                 use_all(PN);
@@ -475,7 +457,7 @@ __global__ __launch_bounds__(WM * WN * 64, TWO ? 4 : (BN < GM_BN ? 2 : 1)) void 
         }
 #pragma unroll
         for (int ns = 0; ns < GM_NS; ++ns) pin_value(w[0][ns]);
-        gm_order_fence();
+        order_fence();
         // group parameters: the values fetched an iteration (or more) ago go to LDS, the next
         // fetch joins this iteration's loads as the youngest
         // tile kt + 2 has landed, and so have the group parameters fetched a group ago (younger:
@@ -484,7 +466,7 @@ __global__ __launch_bounds__(WM * WN * 64, TWO ? 4 : (BN < GM_BN ? 2 : 1)) void 
         wait_copies<NB>();
         dma_a(min(kt + 3, ktl), (kt + 3) & (GM_RING - 1));
         if (GROUPED && t == 0 && g + 3 < g_end) fetch_group(g + 3);
-        gm_order_fence();
+        order_fence();
         __syncthreads();
         if (GROUPED && t == tiles_in_group - 1) flush_group(g);
     };
@@ -766,7 +748,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     constexpr int WN = 8 / KQ;       // channel parts
     constexpr int BN = 32 * WN;      // channels of the workgroup (KQ * BN = 256)
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];   // [2 * KQ][MD_TILE]
-    __shared__ __attribute__((aligned(16))) float s_ges[4 * KQ][BN];   // step / 8 per k-tile (= group) of four super-steps, and channel
+    __shared__ __attribute__((aligned(16))) float s_ges[4 * KQ][BN];   // step / 8 of the groups of four super-steps, per phase and channel
     __shared__ int s_gz[4 * KQ][BN];
     __shared__ __attribute__((aligned(16))) int s_gw[ASYM ? 4 * KQ : 1][ASYM ? BN : 4];   // 4 * (sum of the group's weights)
 
@@ -912,7 +894,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         fetch_params(0, es0, z0, w0);
         fetch_params(min(1, SS - 1), es1, z1, w1);
         fetch_params(min(2, SS - 1), gp_es, gp_z, gp_w);
-        gm_order_fence();
+        order_fence();
         publish_params(0, es0, z0, w0);
         publish_params(1, es1, z1, w1);
     }
@@ -934,7 +916,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
 
     // One super-step of this wave: its k-tile kt_of(ss, q) from LDS slot (ss parity, q).
     // The MFMAs run token block by token block (four k-steps each), so that the rescale of block ms - 1
-    // -- whose group sum is complete -- and, under the last block, the decode of the NEXT k-tile (each
+    // -- whose group sum is complete unless MULTI, see above -- and, under the last block, the decode of the NEXT k-tile (each
     // w[k] is free once the last MFMA that reads it has issued) sit between the MFMAs of block ms:
     // a wave overlaps its own vector and matrix work instead of relying on its SIMD neighbour.
     // The last block's rescale is deferred to the start of the next super-step, where it covers the
@@ -943,7 +925,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     // the next super-step (decoded here); PNN: those of the one after (completed here, see below).
     // Order of the memory accesses of a wave (vmcnt retires in this order):
     //   behind barrier(ss - 1): [2 (ASYM: 3) parameter loads of ss + 2]
-    //   in super-step ss:       2 KQ copies of super-step ss + 1 (their slots were freed by barrier(ss - 1))
+    //   in super-step ss:       CPW copies of super-step ss + 1 (their slots were freed by barrier(ss - 1))
     //   at the end of ss:       2 weight loads for ss + 4
     // so "at most 2 outstanding" at the end of super-step ss means the copies of ss + 1 have landed and
     // every older weight load is complete; the barrier then publishes the copies and frees the slots
@@ -1016,9 +998,9 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         } else {
             dma_super_step(ss + 1);
         }
-        gm_order_fence();
+        order_fence();
         load_b(kt_of(ss + 4, kq), P);
-        gm_order_fence();
+        order_fence();
         wait_copies<2>();
         // (a use in every lane, outside any branch: all waits for the parameter loads and for PNN happen
         // here, none behind the copies issued below)
@@ -1026,7 +1008,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         publish_params(ss + 2, gp_es, gp_z, gp_w);   // (fetched behind the last barrier)
         __syncthreads();
         fetch_params(min(ss + 3, SS - 1), gp_es, gp_z, gp_w);
-        gm_order_fence();
+        order_fence();
     };
 
     {
@@ -1406,7 +1388,7 @@ static int launch_gemm_mid_t(const int8_t *Xq, const float *sx, ZeroPoint zp, in
     const int grid_m = (int)((M + MD_BM - 1) / MD_BM);
     const int grid_n = (int)((N + BN - 1) / BN);
     const int vec_store = (((uintptr_t)Y % 8 == 0) && (ldy % 4 == 0)) ? 1 : 0;
-    // two super-steps of activations (48 to 128 KB); then the sums that the waves exchange, 4 KB per wave and block
+    // two super-steps of activations (32 to 128 KB); then the sums that the waves exchange, 4 KB per wave and block
     constexpr int lds_bytes = 2 * KQ * MD_BM * TILE_K > 8 * MS * 4096 ? 2 * KQ * MD_BM * TILE_K : 8 * MS * 4096;
 #define W4A8_MD(AO_)                                                                                           \
     do {                                                                                                       \
@@ -1563,7 +1545,7 @@ bool gemm_reads_row_sums(int64_t M, int64_t N, int64_t K, int64_t G)
 // shapes of 17 to 1600 tokens with every kernel timed on each; the choice is 0.2 % slower on average than the best of them
 // (without the forms of two and three blocks 9 % from 65 tokens on, 12 to 17 % from 33 to 64).
 // Before / now, us (tokens x K x N): 607 x 4096 x 4096 31.3 / 27.3, with zero-points 36.9 / 31.8, 700 x 8192 x 3072 49.6 / 44.0; instead of
-// the tile kernel 524 x 7936 x 1024 29.5 / 20.5, 59 x 9856 x 15712 51.6 / 26.2, 119 x 12672 x 3008 28.8 / 30.0; instead of token
+// the tile kernel 524 x 7936 x 1024 29.5 / 20.5, 59 x 9856 x 15712 51.6 / 26.2 (119 x 12672 x 3008 stays there: 28.8, here 30.0); instead of token
 // blocks 113 x 4224 x 6496 21.8 / 13.9; those keep 57 x 1920 x 7296 8.9 (9.3 here), 62 x 7296 x 2960 14.1 (17.2), 32 x 2048 x 5344
 // 6.0 (8.7).
 MidForm gemm_mid_form(int64_t M, int64_t N, int64_t K, int64_t G, bool asym)

@@ -114,6 +114,24 @@ __device__ __forceinline__ uint32_t recode8(uint32_t lo, uint32_t hi, uint32_t s
     return ((p >> 1) & 0x77777777u) | (((p & 0x11111111u) ^ m) << 3);
 }
 
+// Pins the program order of memory instructions and of everything scheduled around them, at every
+// level of the compiler (emits no instruction).
+__device__ __forceinline__ void order_fence()
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+// Global -> LDS copy that bypasses the registers: lane l of the wave writes its 16 bytes to
+// lds_addr + 16 l (lds_addr: byte address in LDS, wave-uniform); addresses beyond the buffer
+// write zeros.  Completion is counted by vmcnt like any buffer load, but the compiler does not
+// know that this one writes LDS: whoever reads the bytes waits for vmcnt and a barrier first.
+__device__ __forceinline__ void dma_b128(v4i rsrc, int voff, int soff, uint32_t lds_addr)
+{
+    asm volatile("s_mov_b32 m0, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %1, %2 offen lds"
+                 :: "v"(voff), "s"(rsrc), "s"(soff), "s"(lds_addr) : "memory");
+}
+
 // ---- dINT4 nibble decode for the int8 matrix cores -----------------------------------------
 //
 // A stored nibble is e = l | h << 3 (see the tiled layout in w4a8.h): l in 0..6 names the pair
@@ -386,7 +404,7 @@ size_t gemm_i8_workspace(int64_t M, int64_t N, int64_t K, int64_t G);
 constexpr int I8_BLOCK = 4096;
 __host__ __device__ inline int i8_es_ld(int N) { return (N + 255) / 256 * 256; }
 __host__ __device__ inline int64_t i8_scales_offset(int64_t N, int64_t K) { return (N + 31) / 32 * 32 * K; }
-// Group-wise product on weights decoded to int8 (gemm_i8.hip): whole rows of K per workgroup, symmetric activations.
+// Group-wise product on weights decoded to int8 (gemm_i8.hip), symmetric activations.
 size_t gemm_i8_bytes(int64_t N, int64_t K);
 int launch_decode_i8(const uint8_t *Wt, const float *step, const uint8_t *zero, int64_t N, int64_t K, int64_t G, uint8_t *W8, int plain,
                      hipStream_t st);
