@@ -54,15 +54,30 @@ struct CodeFormat {
 __host__ __device__ constexpr CodeFormat dint4_format() { return CodeFormat{DINT4_P, 1}; }
 
 // The code rule with everything that is constant over a (row, group).  The vector ALU is what bounds the
-// quantizer kernels before memory does, so the rule is written for few operations: eight per weight
-// and three quarters of one for packing.
+// quantizer kernels before memory does, and not all of its operations cost the same: two waves of a SIMD issue an addition,
+// multiplication, fused multiply-add, shift or AND every 2.35 clocks, but only one med3, minimum, conversion, comparison, select, byte
+// permute, left shift, three-operand integer operation (bitop3 apart), or any of the former with a scalar register, every 4.6
+// (measured, 16 independent chains).  So the rule keeps to the
+// former where it can: per weight three of the latter (med3, comparison, select) and five of the former, and four weights
+// share the rest.  (With the band as a shift-and-add and an unsigned comparison and the special code by a bit-align five
+// and three.)
 struct CodeRule {
     float istep;
     float lo, hi;        // -z, p - z: clamping u there is clamping rne(u) + z to 0 .. p (the bounds are integers)
     int z;
-    uint32_t band_lo;    // the special bands (lo_t, hi_t] of |u|, on the bits of |u| shifted left by one:
-    uint32_t band_span;  // a subtraction and one unsigned comparison (span 0: no special levels)
+    float magic;         // 1.5 * 2^23 + z rounded up to even: adding it rounds to nearest even and converts
+    uint32_t special;    // 14, and one more where the magic number holds one more than z
+    uint32_t odd;        // that one, in every byte
+    float band_scale, band_magic;   // see in_band: constants, in vector registers
+    float target;        // what in_band's sum is in the special bands (0: no special levels)
+    uint32_t band_lo;    // other special values (code_byte): the bands (lo_t, hi_t] of |u|, on the bits of |u| shifted
+    uint32_t band_span;  // left by one: a subtraction and one unsigned comparison (span 0: no special levels)
 };
+
+constexpr float ROUND_MAGIC = 12582912.0f;   // 1.5 * 2^23
+// 2 (1 - 2^-24).  fma(|u|, BAND_SCALE, ROUND_MAGIC), rounded once, is ROUND_MAGIC + 1 exactly where 0.25 < |u| <= 0.75: the factor
+// takes the ties 0.5 and 1.5 of 2 |u| downwards and nothing else across them (checked for every binary32 u).
+constexpr float BAND_SCALE = 1.99999988079071044921875f;
 
 __device__ __forceinline__ CodeRule make_rule(float istep, int z, CodeFormat f = dint4_format())
 {
@@ -75,20 +90,39 @@ __device__ __forceinline__ CodeRule make_rule(float istep, int z, CodeFormat f =
     r.lo = (float)-z;
     r.hi = (float)(f.p - z);
     r.z = z;
+    r.magic = ROUND_MAGIC + (float)(z + (z & 1));
+    r.special = 14u + (uint32_t)(z & 1);
+    r.odd = (uint32_t)(z & 1) * 0x01010101u;
+    r.band_scale = BAND_SCALE;
+    r.band_magic = ROUND_MAGIC;
+    asm("" : "+v"(r.band_scale), "+v"(r.band_magic));
+    r.target = f.special ? ROUND_MAGIC + 1.0f : 0.0f;
     r.band_lo = (__float_as_uint(lo_t) << 1) + 1u;
     r.band_span = f.special ? (__float_as_uint(hi_t) - __float_as_uint(lo_t)) << 1 : 0u;
     return r;
 }
 
-// The code of x in the low byte (the upper bits are whatever the arithmetic left there).
+// Whether u = x / step lies in the bands of +-step / 2.
+__device__ __forceinline__ bool in_band(float u, const CodeRule &r)
+{
+    return __builtin_fmaf(__builtin_fabsf(u), r.band_scale, r.band_magic) == r.target;
+}
+// The code of x, or that and one (r.odd), in the low byte; the upper bits are whatever the arithmetic left there.
+// Special values +-step / 2 or none.
+__device__ __forceinline__ uint32_t code_byte_odd(float u, const CodeRule &r)   // u = x / step
+{
+    const uint32_t c = __float_as_uint(__builtin_amdgcn_fmed3f(u, r.lo, r.hi) + r.magic);
+    const uint32_t sp = (__float_as_uint(u) >> 31) + r.special;
+    // (a select, not a branch: the lanes of a wave disagree all the time)
+    return in_band(u, r) ? sp : c;
+}
+// The code of x in the low byte, any special value.
 __device__ __forceinline__ uint32_t code_byte(float x, const CodeRule &r)
 {
     const float u = x * r.istep;
-    // rne and the conversion are one addition: y + 1.5 * 2^23 holds rne(y) in its low bits (|y| <= 255)
-    const uint32_t c = __float_as_uint(__builtin_amdgcn_fmed3f(u, r.lo, r.hi) + 12582912.0f) + (uint32_t)r.z;
+    const uint32_t c = __float_as_uint(__builtin_amdgcn_fmed3f(u, r.lo, r.hi) + ROUND_MAGIC) + (uint32_t)r.z;
     const uint32_t bits = __float_as_uint(u);
     const uint32_t sp = __builtin_amdgcn_alignbit(7u, bits, 31u);   // 14 + the sign bit
-    // (a select, not a branch: the lanes of a wave disagree all the time)
     return (bits << 1) - r.band_lo < r.band_span ? sp : c;
 }
 
@@ -98,8 +132,21 @@ __device__ __forceinline__ uint32_t pack_low_bytes(uint32_t a, uint32_t b, uint3
     return __builtin_amdgcn_perm(b, a, 0x0c0c0400u) | __builtin_amdgcn_perm(d, c, 0x04000c0cu);
 }
 
+// Four codes (special values +-step / 2 or none): no byte is below the one that r.odd takes off, so nothing borrows.
+__device__ __forceinline__ uint32_t codes4(float u0, float u1, float u2, float u3, const CodeRule &r)
+{
+    return pack_low_bytes(code_byte_odd(u0, r), code_byte_odd(u1, r), code_byte_odd(u2, r), code_byte_odd(u3, r)) - r.odd;
+}
 __device__ __forceinline__ uint2 codes8(const float (&x)[8], const CodeRule &r)
 {
+    const float i = r.istep;
+    return make_uint2(codes4(x[0] * i, x[1] * i, x[2] * i, x[3] * i, r), codes4(x[4] * i, x[5] * i, x[6] * i, x[7] * i, r));
+}
+// HALF: special values +-step / 2 or none; else any.
+template <bool HALF>
+__device__ __forceinline__ uint2 codes8_of(const float (&x)[8], const CodeRule &r)
+{
+    if (HALF) return codes8(x, r);
     uint32_t q[8];
 #pragma unroll
     for (int j = 0; j < 8; ++j) q[j] = code_byte(x[j], r);
@@ -223,7 +270,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_kernel(
 #pragma unroll
         for (int j = 0; j < V; ++j) x[j] = sg ? v[j] * sv[j] : v[j];
         if constexpr (V == 8)
-            *reinterpret_cast<uint2 *>(c + k) = codes8(x, rule);
+            *reinterpret_cast<uint2 *>(c + k) = fmt.shift == 1 ? codes8(x, rule) : codes8_of<false>(x, rule);
         else if constexpr (V == 2)
             *reinterpret_cast<uint16_t *>(c + k) =
                 (uint16_t)pack_low_bytes(code_byte(x[0], rule), code_byte(x[1], rule), 0u, 0u);
@@ -232,18 +279,12 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_kernel(
     }
 }
 
-// x[j] = v[j] * sv[j], the eight elements still in their storage type.  fp16: x * s + 0, the same single
-// rounding of the exact product (only the sign of a zero can differ, which neither the range nor the code
-// sees), because the widening folds into a mixed-precision multiply-add.
+// x[j] = v[j] * sv[j], the eight elements still in their storage type (no scale vector: times 1, exactly v[j]).
 template <typename T>
-__device__ __forceinline__ void scaled8(const T *e, const float (&sv)[8], bool has_s, float (&x)[8])
+__device__ __forceinline__ void scaled8(const T *e, const float (&sv)[8], float (&x)[8])
 {
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        if (!has_s) x[j] = to_f32(e[j]);
-        else if constexpr (__is_same(T, __half)) x[j] = __builtin_fmaf(to_f32(e[j]), sv[j], 0.0f);
-        else x[j] = to_f32(e[j]) * sv[j];
-    }
+    for (int j = 0; j < 8; ++j) x[j] = to_f32(e[j]) * sv[j];
 }
 
 template <typename T>
@@ -266,13 +307,25 @@ __device__ __forceinline__ void min_max8(const float (&x)[8], float &lo, float &
     }
 }
 
+// The larger of this lane's and another lane's value, and of ends of ranges as bits: hi >= 0 without its sign, lo <= 0 as it
+// is, whose bits grow with its magnitude (and of the zeros either will do).
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_max_u32(uint32_t keep, uint32_t send)
+{
+    return max(keep, (uint32_t)dpp_i32<CTRL>((int)send));
+}
+__device__ __forceinline__ uint32_t hi_bits(float hi) { return __float_as_uint(hi) & 0x7fffffffu; }
+
 // Groups of 128 or 256 columns: a wave takes 512 consecutive columns (8 per lane, one 16-byte load) of
 // ROWS rows, i.e. 4 or 2 whole groups of each row, each reduced over its own LANES = G / 8 lanes; the
 // elements stay in registers between the range and the codes, so W is read once.
-// Bound by the vector ALU and memory about equally; the rows share the lane's eight AQAS scales (twice the
-// bytes of fp16 weights) and the two IEEE divisions of a group (some 25 operations): lane l computes the
-// parameters of row l % 4 for its group and the four lanes of a quad exchange them.
-// 13824 x 5120, G = 128: 68 -> 47 us (4.5 TB/s).
+// Bound by the vector ALU until some 17 operations per lane and weight are left, so whatever is not per weight is kept off it:
+// the four waves of a block take four times ROWS rows of the same columns, which needs no division and leaves the row
+// addresses to the scalar unit; the rows share the lane's eight AQAS scales (twice the
+// bytes of fp16 weights) and the two IEEE divisions of a group (some 25 operations): the rows' ranges are reduced
+// together, on bits, and end with row l % 4 in lane l, which computes its parameters, and the four lanes of a quad exchange them.
+// 13824 x 5120, G = 128: 48 -> 41 us (5.1 TB/s; a plain pass of the same loads and stores takes 33), 8192 x 8192, G = 256: 46 -> 38.
+// (Non-temporal loads of W: the same, fp32 8 % slower.)
 // ROWS = 1: small matrices, for which four rows per wave leave most CUs idle (one / four rows, us: 768 x 768 3.5 / 4.3,
 // 1024 x 1024 3.6 / 4.3, 512 x 4096 4.5 / 4.5, 1024 x 4096 6.2 / 5.8).
 constexpr int SG_ROWS = 4;
@@ -280,80 +333,94 @@ constexpr int SG_ROWS = 4;
 template <int ROW>
 __device__ __forceinline__ float quad_lane_f32(float v) { return dpp_f32<ROW * 0x55>(v); }
 template <int ROW>
-__device__ __forceinline__ int quad_lane_i32(int v) { return dpp_i32<ROW * 0x55>(v); }
+__device__ __forceinline__ CodeRule quad_lane_rule(const CodeRule &m, CodeFormat fmt)
+{
+    CodeRule r = m;
+    r.istep = quad_lane_f32<ROW>(m.istep);
+    r.lo = quad_lane_f32<ROW>(m.lo);
+    r.hi = r.lo + (float)fmt.p;   // (whole numbers)
+    r.magic = quad_lane_f32<ROW>(m.magic);
+    r.odd = (uint32_t)dpp_i32<ROW * 0x55>((int)m.odd);
+    r.special = 14u + (r.odd & 1u);
+    r.z = (int)-r.lo;
+    return r;
+}
 
-template <typename T, int LANES, int ROWS>
+template <typename T, int LANES, int ROWS, bool HALF>
 __global__ __launch_bounds__(WQ_THREADS) void weight_quant_small_groups_kernel(
     const T *__restrict__ W, int64_t N, int64_t K, int64_t ldw, const float *__restrict__ s,
     int use_given, uint8_t *__restrict__ codes, float *__restrict__ step, uint8_t *__restrict__ zero,
     CodeFormat fmt, int s_vec, Clipping clip)
 {
     static_assert(ROWS == 1 || ROWS == 4, "the lanes of a quad share the work on four rows");
-    constexpr int G = LANES * 8;
+    constexpr int G = LANES * 8, WAVES = WQ_THREADS / WAVE;
     const int lane = threadIdx.x & 63;
-    const int64_t chunks = (K + 511) / 512;
-    const int64_t seg = (int64_t)blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);   // (ROWS rows, chunk)
-    if (seg >= (N + ROWS - 1) / ROWS * chunks) return;
-    const int64_t n0 = seg / chunks * ROWS, c = seg - n0 / ROWS * chunks;
-    const int64_t k = c * 512 + lane * 8;
-    if (k >= K) return;   // whole groups of LANES lanes leave together (K % G == 0)
-    Raw8<T> raw[ROWS];
-#pragma unroll
-    for (int r = 0; r < ROWS; ++r) raw[r].load(W + min(n0 + r, N - 1) * ldw + k);   // (rows past the end: not stored)
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t k0 = (int64_t)blockIdx.x * 512;
+    const int kl = lane * 8;
+    if (k0 + kl >= K) return;   // whole groups of LANES lanes leave together (K % G == 0)
     float sv[8];
-    load_scales<8>(s, k, s_vec, sv);
-    const int64_t ng = K / G, g = k / G;
+    load_scales<8>(s ? s + k0 : nullptr, kl, s_vec, sv);
+    const int64_t ng = K / G;
+    const int64_t g0 = k0 / G;
+    const int gl = lane / LANES;
     const int mine = ROWS == 4 ? lane & 3 : 0;   // the row whose parameters this lane computes
-    float x[ROWS][8];
-    float lo_m = 0.0f, hi_m = 0.0f;
+    for (int64_t n0 = ((int64_t)blockIdx.y * WAVES + wave) * ROWS; n0 < N; n0 += (int64_t)gridDim.y * WAVES * ROWS) {
+        Raw8<T> raw[ROWS];
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        T e[8];
-        raw[r].elements(e);
-        scaled8(e, sv, s != nullptr, x[r]);
-        if (!use_given) {
-            float lo = 0.0f, hi = 0.0f;
-            min_max8(x[r], lo, hi);
-            lo = fminf(lo, dpp_f32<DPP_QUAD_XOR1>(lo));
-            hi = fmaxf(hi, dpp_f32<DPP_QUAD_XOR1>(hi));
-            lo = fminf(lo, dpp_f32<DPP_QUAD_XOR2>(lo));
-            hi = fmaxf(hi, dpp_f32<DPP_QUAD_XOR2>(hi));
-            lo = fminf(lo, dpp_f32<DPP_ROW_HALF_MIRROR>(lo));
-            hi = fmaxf(hi, dpp_f32<DPP_ROW_HALF_MIRROR>(hi));
-            lo = fminf(lo, dpp_f32<DPP_ROW_MIRROR>(lo));
-            hi = fmaxf(hi, dpp_f32<DPP_ROW_MIRROR>(hi));
-            if (LANES == 32) {
-                lo = fminf(lo, __shfl_xor(lo, 16, WAVE));
-                hi = fmaxf(hi, __shfl_xor(hi, 16, WAVE));
+        for (int r = 0; r < ROWS; ++r) raw[r].load(W + min(n0 + r, N - 1) * ldw + k0 + kl);   // (rows past the end: not stored)
+        float x[ROWS][8];
+        uint32_t lo[ROWS], hi[ROWS];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            T e[8];
+            raw[r].elements(e);
+            scaled8(e, sv, x[r]);
+            float l = 0.0f, h = 0.0f;
+            min_max8(x[r], l, h);
+            lo[r] = __float_as_uint(l);
+            hi[r] = hi_bits(h);
+        }
+        float st, istep;
+        int z;
+        const int64_t pidx = min(n0 + mine, N - 1) * ng + g0 + gl;
+        if (use_given) {
+            st = step[pidx];
+            z = zero[pidx];
+            istep = 1.0f / st;
+        } else {
+            auto reduce = [&](uint32_t(&v)[ROWS]) {
+                uint32_t m;
+                if constexpr (ROWS == 4) {   // lanes that differ in bit 0, then bit 1, keep the rows with their bit
+                    const bool b0 = lane & 1, b1 = lane & 2;
+                    const uint32_t a = dpp_max_u32<DPP_QUAD_XOR1>(b0 ? v[1] : v[0], b0 ? v[0] : v[1]);
+                    const uint32_t c = dpp_max_u32<DPP_QUAD_XOR1>(b0 ? v[3] : v[2], b0 ? v[2] : v[3]);
+                    m = dpp_max_u32<DPP_QUAD_XOR2>(b1 ? c : a, b1 ? a : c);
+                } else {
+                    m = dpp_max_u32<DPP_QUAD_XOR1>(v[0], v[0]);
+                    m = dpp_max_u32<DPP_QUAD_XOR2>(m, m);
+                }
+                m = dpp_max_u32<DPP_ROW_ROR4>(m, m);
+                m = dpp_max_u32<DPP_ROW_ROR8>(m, m);
+                if (LANES == 32) m = max(m, (uint32_t)__shfl_xor((int)m, 16, WAVE));
+                return __uint_as_float(m);
+            };
+            const float rho = clip_factor(clip, min(n0 + mine, N - 1));
+            range_params(reduce(lo) * rho, reduce(hi) * rho, st, istep, z, fmt);
+            if ((lane & (LANES - 1)) < ROWS && n0 + mine < N) {
+                step[pidx] = st;
+                zero[pidx] = (uint8_t)z;
             }
-            lo_m = mine == r ? lo : lo_m;
-            hi_m = mine == r ? hi : hi_m;
         }
-    }
-    float st, istep;
-    int z;
-    const int64_t pidx = min(n0 + mine, N - 1) * ng + g;
-    if (use_given) {
-        st = step[pidx];
-        z = zero[pidx];
-        istep = 1.0f / st;
-    } else {
-        const float rho = clip_factor(clip, min(n0 + mine, N - 1));
-        range_params(lo_m * rho, hi_m * rho, st, istep, z, fmt);
-        if ((lane & (LANES - 1)) < ROWS && n0 + mine < N) {
-            step[pidx] = st;
-            zero[pidx] = (uint8_t)z;
-        }
-    }
-    if (codes == nullptr) return;
-    // (one row: every lane has its parameters)
-    const float is[4] = {ROWS == 4 ? quad_lane_f32<0>(istep) : istep, quad_lane_f32<1>(istep), quad_lane_f32<2>(istep),
-                         quad_lane_f32<3>(istep)};
-    const int zs[4] = {ROWS == 4 ? quad_lane_i32<0>(z) : z, quad_lane_i32<1>(z), quad_lane_i32<2>(z), quad_lane_i32<3>(z)};
+        if (codes == nullptr) continue;
+        const CodeRule own = make_rule(istep, z, fmt);
+        const CodeRule rule[4] = {ROWS == 4 ? quad_lane_rule<0>(own, fmt) : own, quad_lane_rule<1>(own, fmt),
+                                  quad_lane_rule<2>(own, fmt), quad_lane_rule<3>(own, fmt)};   // (one row: every lane has its own)
 #pragma unroll
-    for (int r = 0; r < ROWS; ++r) {
-        const uint2 q = codes8(x[r], make_rule(is[r], zs[r], fmt));
-        if (n0 + r < N) *reinterpret_cast<uint2 *>(codes + (n0 + r) * K + k) = q;
+        for (int r = 0; r < ROWS; ++r) {
+            const uint2 q = codes8_of<HALF>(x[r], rule[r]);
+            if (n0 + r < N) *reinterpret_cast<uint2 *>(codes + (n0 + r) * K + k0 + kl) = q;
+        }
     }
 }
 
@@ -362,11 +429,12 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_small_groups_kernel(
 // and the codes: W is read once, and the AQAS scales once for both rows.  One barrier.  Bound by
 // memory (3 bytes per fp16 weight) and the vector ALU.  The wave-per-segment kernel above sweeps W
 // twice, and the second time much of it comes from beyond the L2.
-// 36864 x 9216 per channel: 322 -> 217 us (4.7 TB/s).
+// 36864 x 9216 per channel: 322 -> 217 -> 199 us (5.1 TB/s), the last by the cheaper code rule.  (Keeping the 16-bit
+// elements instead of the scaled values, which are half the registers: 221.)
 constexpr int SEG_ROWS = 2;
 constexpr int SEG_MAX_CHUNKS = 8;
 
-template <typename T, int CH>
+template <typename T, int CH, bool HALF>
 __global__ __launch_bounds__(WQ_THREADS) void weight_quant_segment_kernel(
     const T *__restrict__ W, int64_t N, int64_t K, int64_t ldw, const float *__restrict__ s, int G,
     int use_given, uint8_t *__restrict__ codes, float *__restrict__ step, uint8_t *__restrict__ zero,
@@ -399,7 +467,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_segment_kernel(
         for (int r = 0; r < SEG_ROWS; ++r) {
             T e[8];
             raw[r][c].elements(e);
-            scaled8(e, sv, s != nullptr, x[r][c]);
+            scaled8(e, sv, x[r][c]);
             if (!use_given) min_max8(x[r][c], lo[r], hi[r]);
         }
     }
@@ -445,7 +513,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_segment_kernel(
 #pragma unroll
         for (int r = 0; r < SEG_ROWS; ++r)
             if (r == 0 || second)
-                *reinterpret_cast<uint2 *>(codes + (n0 + r) * K + col + (int64_t)at * 8) = codes8(x[r][c], rule[r]);
+                *reinterpret_cast<uint2 *>(codes + (n0 + r) * K + col + (int64_t)at * 8) = codes8_of<HALF>(x[r][c], rule[r]);
     }
 }
 
@@ -482,12 +550,17 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
                        st, W, N, K, ldw, s, G, use_given, codes, step, zero, fmt, s_vec, clip)
     if ((G == 128 || G == 256) && aligned(8) && cands == 1) {   // (candidates: per-channel layers of 128 or 256 columns only)
         const int rows = N * K <= (1 << 21) ? 1 : SG_ROWS;
-        const int64_t wsegs = (N + rows - 1) / rows * ((K + 511) / 512);
-        const int64_t wblocks = (wsegs + (WQ_THREADS / WAVE) - 1) / (WQ_THREADS / WAVE);
-        if (wblocks > 0x7fffffffLL) return W4A8_ERR_SHAPE;
-#define W4A8_WQ_SMALL(LANES_, ROWS_)                                                                              \
-    hipLaunchKernelGGL((weight_quant_small_groups_kernel<T, LANES_, ROWS_>), dim3((unsigned)wblocks), dim3(WQ_THREADS), \
-                       0, st, W, N, K, ldw, s, use_given, codes, step, zero, fmt, s_vec, clip)
+        const int64_t strips = (N + rows * (WQ_THREADS / WAVE) - 1) / (rows * (WQ_THREADS / WAVE)), chunks = (K + 511) / 512;
+        if (chunks > 0x7fffffffLL) return W4A8_ERR_SHAPE;
+        const dim3 grid((unsigned)chunks, (unsigned)(strips < 65535 ? strips : 65535));
+#define W4A8_WQ_SMALL_F(LANES_, ROWS_, HALF_)                                                                     \
+    hipLaunchKernelGGL((weight_quant_small_groups_kernel<T, LANES_, ROWS_, HALF_>), grid, dim3(WQ_THREADS), 0, st, \
+                       W, N, K, ldw, s, use_given, codes, step, zero, fmt, s_vec, clip)
+#define W4A8_WQ_SMALL(LANES_, ROWS_)                              \
+    do {                                                          \
+        if (fmt.shift == 1) W4A8_WQ_SMALL_F(LANES_, ROWS_, true); \
+        else W4A8_WQ_SMALL_F(LANES_, ROWS_, false);               \
+    } while (0)
         if (G == 128) {
             if (rows == 1) W4A8_WQ_SMALL(16, 1);
             else W4A8_WQ_SMALL(16, SG_ROWS);
@@ -496,13 +569,17 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
             else W4A8_WQ_SMALL(32, SG_ROWS);
         }
 #undef W4A8_WQ_SMALL
+#undef W4A8_WQ_SMALL_F
     } else if (G >= 1024 && G <= SEG_MAX_CHUNKS * 8 * WQ_THREADS && aligned(8) && K / G <= 65535 &&
                N <= 0x7fffffffLL && segment_pays()) {
         const dim3 grid((unsigned)((N + SEG_ROWS - 1) / SEG_ROWS), (unsigned)(K / G), cands);
+#define W4A8_WQ_SEGMENT_F(CH_, HALF_)                                                                            \
+    hipLaunchKernelGGL((weight_quant_segment_kernel<T, CH_, HALF_>), grid, dim3(WQ_THREADS), 0, st, W, N, K, ldw, \
+                       s, (int)G, use_given, codes, step, zero, fmt, s_vec, clip)
 #define W4A8_WQ_SEGMENT(CH_)                                                                              \
     case CH_:                                                                                             \
-        hipLaunchKernelGGL((weight_quant_segment_kernel<T, CH_>), grid, dim3(WQ_THREADS), 0, st, W, N, K, \
-                           ldw, s, (int)G, use_given, codes, step, zero, fmt, s_vec, clip);                     \
+        if (fmt.shift == 1) W4A8_WQ_SEGMENT_F(CH_, true);                                                  \
+        else W4A8_WQ_SEGMENT_F(CH_, false);                                                                \
         break
         switch ((int)((G / 8 + WQ_THREADS - 1) / WQ_THREADS)) {
             W4A8_WQ_SEGMENT(1);
@@ -515,6 +592,7 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
             W4A8_WQ_SEGMENT(8);
         }
 #undef W4A8_WQ_SEGMENT
+#undef W4A8_WQ_SEGMENT_F
     } else if (G >= 512 && aligned(8)) {
         W4A8_WQ_LAUNCH(8);
     } else if (aligned(2)) {
@@ -568,10 +646,10 @@ constexpr int WQT_TILES = 2;
 __device__ __forceinline__ uint32_t level_byte(float x, const CodeRule &r)   // twice the level's quarter, in the low byte
 {
     const float u = x * r.istep;
-    const uint32_t c = __float_as_uint(__builtin_amdgcn_fmed3f(u, r.lo, r.hi) + 12582912.0f) << 1;
-    const uint32_t bits = __float_as_uint(u);
-    const uint32_t sp = (uint32_t)((int)bits >> 31) | 1u;   // +-1
-    return (bits << 1) - r.band_lo < r.band_span ? sp : c;
+    uint32_t c = __float_as_uint(__builtin_amdgcn_fmed3f(u, r.lo, r.hi) + ROUND_MAGIC);
+    asm("v_add_u32 %0, %1, %1" : "=v"(c) : "v"(c));   // (twice it; the compiler would shift, at half the rate)
+    const uint32_t sp = __float_as_uint(__builtin_fmaf(u, r.band_scale, r.band_magic));   // +-1 in the bands
+    return in_band(u, r) ? sp : c;
 }
 __device__ __forceinline__ uint2 levels8(const float (&x)[8], const CodeRule &r)
 {
@@ -620,7 +698,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_packed_kernel(
                 for (int i = 0; i < WQT_TILES; ++i) {
                     T e[8];
                     raw[i][c].elements(e);
-                    scaled8(e, sv, s != nullptr, x[i][c]);
+                    scaled8(e, sv, x[i][c]);
                     min_max8(x[i][c], lo[i], hi[i]);
                 }
             }
@@ -799,6 +877,21 @@ __global__ __launch_bounds__(256) void value_quant_kernel(const T *__restrict__ 
     }
 }
 
+// A channel's rule as 16 bytes of LDS, and back.
+__device__ __forceinline__ float4 rule_entry(const CodeRule &r)
+{
+    return make_float4(r.istep, r.lo, r.magic, __uint_as_float(r.odd));
+}
+__device__ __forceinline__ CodeRule rule_of(const float4 &f)
+{
+    CodeRule r = make_rule(f.x, 0);
+    r.lo = f.y;
+    r.hi = f.y + (float)DINT4_P;
+    r.magic = f.z;
+    r.odd = __float_as_uint(f.w);
+    r.special = 14u + (r.odd & 1u);
+    return r;
+}
 // The same for 16-bit elements with everything 16-byte aligned (D % 8 == 0, G % 128 == 0): a thread
 // loads eight consecutive channels of a token at once, so a wave instruction moves eight 128-byte
 // row segments instead of one (the channel-per-lane kernel above moves 128 bytes per instruction).
@@ -814,7 +907,7 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
 {
     static_assert(sizeof(T) == 2, "16-bit elements");
     __shared__ float s_lo[4][64], s_hi[4][64];
-    __shared__ float4 s_rule[64];          // 1 / step, -z, p - z, z of each channel
+    __shared__ float4 s_rule[64];          // each channel's rule
     __shared__ uint32_t s_codes[64][33];   // [channel][32 words of 4 tokens], odd stride
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c8 = tid & 7, t4 = tid >> 3;
@@ -864,7 +957,7 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
         int z;
         range_params(l, h, st, istep, z);
         const CodeRule r = make_rule(istep, z);
-        s_rule[tid] = make_float4(r.istep, r.lo, r.hi, __int_as_float(r.z));
+        s_rule[tid] = rule_entry(r);
         if (d0 + tid < D) {
             step[(b * D + d0 + tid) * ng + g] = st;
             zero[(b * D + d0 + tid) * ng + g] = (uint8_t)z;
@@ -885,13 +978,9 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
         for (int j = 0; j < 8; ++j) {
             // (the channel's rule comes from LDS each time: eight of them in registers cost the kernel
             // a wave per SIMD and 6 % of its time)
-            const float4 f = s_rule[c8 * 8 + j];
-            CodeRule rule = make_rule(f.x, 0);
-            rule.lo = f.y;
-            rule.hi = f.z;
-            rule.z = __float_as_int(f.w);
-            s_codes[c8 * 8 + j][t4] = pack_low_bytes(code_byte(to_f32(e[0][j]), rule), code_byte(to_f32(e[1][j]), rule),
-                                                     code_byte(to_f32(e[2][j]), rule), code_byte(to_f32(e[3][j]), rule));
+            const CodeRule rule = rule_of(s_rule[c8 * 8 + j]);
+            s_codes[c8 * 8 + j][t4] = codes4(to_f32(e[0][j]) * rule.istep, to_f32(e[1][j]) * rule.istep,
+                                             to_f32(e[2][j]) * rule.istep, to_f32(e[3][j]) * rule.istep, rule);
         }
         __syncthreads();
         if (d0 + r < D) {
@@ -926,7 +1015,7 @@ __global__ __launch_bounds__(VR_THREADS) void value_quant_resident_kernel(const 
     static_assert(sizeof(T) == 2, "16-bit elements");
     constexpr int WAVES = VR_THREADS / WAVE;
     __shared__ float s_lo[WAVES][VR_CHANNELS], s_hi[WAVES][VR_CHANNELS];
-    __shared__ float4 s_rule[VR_CHANNELS];          // 1 / step, -z, p - z, z of each channel
+    __shared__ float4 s_rule[VR_CHANNELS];          // each channel's rule
     __shared__ __attribute__((aligned(16))) uint32_t s_codes[R > 1 ? 2 : 1][VR_CHANNELS * VR_STRIDE];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // block -> (head and group, channel part): the parts of one follow each other on one XCD (blocks go round-robin
@@ -950,8 +1039,8 @@ __global__ __launch_bounds__(VR_THREADS) void value_quant_resident_kernel(const 
     }
     auto element = [](const v4u &w, int j) {
         const uint32_t h = (j & 1) ? w[j >> 1] >> 16 : w[j >> 1] & 0xffffu;
-        if constexpr (__is_same(T, bf16_t)) return __uint_as_float(h << 16);
-        else return __half2float(__ushort_as_half((uint16_t)h));
+        if constexpr (__is_same(T, bf16_t)) return bf16_t{(uint16_t)h};
+        else return __ushort_as_half((uint16_t)h);
     };
     // ---- ranges: the thread's tokens, the 16 lanes of the wave with the same channels, the waves
 #pragma unroll
@@ -961,7 +1050,7 @@ __global__ __launch_bounds__(VR_THREADS) void value_quant_resident_kernel(const 
         for (int r = 0; r < R; ++r)
 #pragma unroll
             for (int i = 0; i < 4; i += 2) {
-                const float x0 = element(raw[r][i], j), x1 = element(raw[r][i + 1], j);
+                const float x0 = to_f32(element(raw[r][i], j)), x1 = to_f32(element(raw[r][i + 1], j));
                 lo = fminf(fminf(lo, x0), x1);
                 hi = fmaxf(fmaxf(hi, x0), x1);
             }
@@ -992,7 +1081,7 @@ __global__ __launch_bounds__(VR_THREADS) void value_quant_resident_kernel(const 
         int z;
         range_params(l, h, st, istep, z);
         const CodeRule rule = make_rule(istep, z);
-        s_rule[tid] = make_float4(rule.istep, rule.lo, rule.hi, __int_as_float(rule.z));
+        s_rule[tid] = rule_entry(rule);
         if (d0 + tid < D) {
             step[(b * D + d0 + tid) * ng + g] = st;
             zero[(b * D + d0 + tid) * ng + g] = (uint8_t)z;
@@ -1010,14 +1099,10 @@ __global__ __launch_bounds__(VR_THREADS) void value_quant_resident_kernel(const 
         uint32_t *buf = s_codes[R > 1 ? r & 1 : 0];
 #pragma unroll
         for (int j = 0; j < 8; ++j) {
-            const float4 f = s_rule[c4 * 8 + j];
-            CodeRule rule = make_rule(f.x, 0);
-            rule.lo = f.y;
-            rule.hi = f.z;
-            rule.z = __float_as_int(f.w);
+            const CodeRule rule = rule_of(s_rule[c4 * 8 + j]);
             buf[(c4 * 8 + j) * VR_STRIDE + t4] =
-                pack_low_bytes(code_byte(element(raw[r][0], j), rule), code_byte(element(raw[r][1], j), rule),
-                               code_byte(element(raw[r][2], j), rule), code_byte(element(raw[r][3], j), rule));
+                codes4(to_f32(element(raw[r][0], j)) * rule.istep, to_f32(element(raw[r][1], j)) * rule.istep,
+                       to_f32(element(raw[r][2], j)) * rule.istep, to_f32(element(raw[r][3], j)) * rule.istep, rule);
             __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();   // (a wave that is a round ahead writes the other buffer)

@@ -189,3 +189,37 @@ def test_value_quant_edges(lib, oracle, B, T, D, G, dtype, interleaved):
         assert np.array_equal(host(step)[rows].view(np.uint32), rs.view(np.uint32))
         assert np.array_equal(host(zero)[rows], rz)
         assert np.array_equal(host(codes)[rows], rc)
+
+
+# every edge of the code rule with its two binary32 neighbours, zero-points of either parity and beyond the code space (where
+# the clamp alone says what comes out), in every kernel: four rows and one row per wave, long segments, the general form
+@pytest.mark.parametrize("N,K,G", [(2050, 1024, 128), (2050, 1024, 256), (40, 256, 128), (6, 4096, 0), (3, 2304, 0), (9, 96, 48)])
+def test_code_rule_edges(lib, oracle, N, K, G):
+    edges = np.concatenate([[0.0, 0.25, 0.75], np.arange(0, 31) + 0.5, np.arange(1, 31), [300.0, 2.0 ** 22]]).astype(np.float32)
+    near = np.concatenate([edges, np.nextafter(edges, np.float32(np.inf)), np.nextafter(edges, np.float32(-np.inf))])
+    near = np.concatenate([near, -near])
+    rng = np.random.default_rng(N + K)
+    W = rng.choice(near, size=(N, K)).astype(np.float32)
+    ng = K // (G or K)
+    zero = rng.integers(0, 14, (N, ng), dtype=np.uint8)
+    zero[0], zero[1], zero[2] = 13, 200, 255
+    step = np.ones((N, ng), dtype=np.float32)
+    want = oracle.quantize_weight_dint4(W, None, G, step=step, zero=zero)[0]
+    got = lib.quantize_weight_dint4(dev(W), None, G, step=dev(step), zero=dev(zero))[0]
+    assert np.array_equal(host(got), want)
+
+
+# the same edges in the Value cache's kernels (short groups, groups that stay in registers): channel d runs from -(d % 14) to
+# 13 - d % 14, so that the step is 1 and the zero-point d % 14
+@pytest.mark.parametrize("B,T,D,G", [(2, 256, 64, 128), (1, 1024, 48, 0), (1, 4096, 40, 0)])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16])
+def test_value_code_rule_edges(lib, oracle, B, T, D, G, dtype):
+    rng = np.random.default_rng(T + D)
+    z = np.arange(D) % 14
+    V = rng.integers(-4 * z[None, None, :], 4 * (13 - z)[None, None, :] + 1, (B, T, D)).astype(np.float32) / 4
+    V[:, ::128], V[:, 1::128] = -z, 13 - z
+    Vd = dev(V).to(dtype)
+    codes, step, zero = oracle.quantize_value_dint4(host(Vd.float()), G)
+    got = lib.quantize_value_dint4(Vd, G)
+    assert np.array_equal(host(got[2]).reshape(zero.shape), zero) and np.array_equal(host(got[1]).reshape(step.shape), step)
+    assert np.array_equal(host(got[0]).reshape(codes.shape), codes)
