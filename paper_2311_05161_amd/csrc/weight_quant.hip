@@ -998,9 +998,12 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
 // it twice, and beyond the last-level cache's reach the second sweep comes from memory again.
 // Bound by memory: 3 bytes per value.  Thread (c4, t4) = (tid % 4, tid / 4) owns channels 8 c4 .. + 7 and the tokens
 // 1024 r + 4 t4 .. + 3, r < R: one word of codes per channel and r, which goes through LDS (two buffers, one barrier
-// per r) to the thread that stores 32 tokens of the channel's row.  A row of 32 channels is 64 bytes, half a cache line:
-// the channel parts of a head run on one XCD, so that its L2 serves the other half.
-// 256 heads x 4096 tokens x 128 channels: 126 -> 112 us (3.6 TB/s; 64 heads 60 -> 27).
+// per r) to the wave that stores 1024 tokens of the channel's row, a kilobyte per instruction.  A row of 32 channels is 64 bytes,
+// half a cache line: the channel parts of a head run on one XCD, so that its L2 serves the other half -- unless the codes have
+// pushed it out in the meantime, so they are stored with the streaming hint (the packing that reads them next takes 3 us more,
+// 256 heads).  256 heads x 4096 tokens x 128 channels: 126 (two sweeps) -> 116 -> 102 us (4.0 TB/s; without the vector work 93, the
+// loads alone 63); 256 x 2048 47 -> 40, 64 x 4096 25 -> 23.  (Blocks that go on to the next group and load it under the
+// codes of the one before: 102, and 2048 tokens 56, as two blocks of it no longer share a CU.)
 constexpr int VR_THREADS = 1024, VR_CHANNELS = 32, VR_TOKENS = 1024;
 constexpr int VR_STRIDE = VR_TOKENS / 4 + 4;   // words per channel row in LDS (16-byte aligned)
 
@@ -1093,7 +1096,6 @@ __global__ __launch_bounds__(VR_THREADS) void value_quant_resident_kernel(const 
 #pragma unroll
     for (int r = 0; r < R; ++r) asm volatile("" : "+v"(raw[r][0]), "+v"(raw[r][1]), "+v"(raw[r][2]), "+v"(raw[r][3]));
     // ---- codes, transposed through LDS to token-contiguous rows
-    const int row = tid >> 5, q = tid & 31;   // write side: channel row, 32-token piece
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         uint32_t *buf = s_codes[R > 1 ? r & 1 : 0];
@@ -1106,12 +1108,15 @@ __global__ __launch_bounds__(VR_THREADS) void value_quant_resident_kernel(const 
             __builtin_amdgcn_sched_barrier(0);
         }
         __syncthreads();   // (a wave that is a round ahead writes the other buffer)
-        const int t = r * VR_TOKENS + q * 32;
-        if (d0 + row < D && t < G) {   // G % 32 == 0
-            v4u *dst = reinterpret_cast<v4u *>(codes + (b * D + d0 + row) * Tn + g * G + t);
-            const v4u *w = reinterpret_cast<const v4u *>(buf + row * VR_STRIDE + q * 8);
-            dst[0] = w[0];
-            dst[1] = w[1];
+        const int t = r * VR_TOKENS + lane * 16;
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const int row = wave * 2 + i;
+            if (d0 + row < D && t < G) {   // G % 16 == 0
+                const v4u w = *reinterpret_cast<const v4u *>(buf + row * VR_STRIDE + lane * 4);
+                v4u *dst = reinterpret_cast<v4u *>(codes + (b * D + d0 + row) * Tn + g * G + t);
+                __builtin_nontemporal_store(w, dst);
+            }
         }
     }
 }
@@ -1128,8 +1133,8 @@ int launch_value_quant(const void *V, int v_dtype, int64_t batch, int64_t T, int
         const int64_t parts = (D + VR_CHANNELS - 1) / VR_CHANNELS, groups = batch * (T / G);
         const int64_t blocks = (groups + 7) / 8 * 8 * parts;
         const int64_t rounds = (G + VR_TOKENS - 1) / VR_TOKENS;
-        // Groups that fill at least three quarters of their rounds.  Measured, the two-sweep kernel / this, us (256 heads of
-        // 128 channels): 1024 tokens 30.8 / 27.1, 2048 62.8 / 45.7, 4096 146 / 122 (64 heads 60 / 27, 8 heads 47 / 18); but 512
+        // Groups that fill at least three quarters of their rounds.  Measured before the streaming stores, the two-sweep kernel / this, us
+        // (256 heads of 128 channels): 1024 tokens 30.8 / 27.1, 2048 62.8 / 45.7, 4096 146 / 122 (64 heads 60 / 27, 8 heads 47 / 18); but 512
         // tokens 19.2 / 23.7, 640 21.9 / 25.0 and 1152 33.4 / 36.4.
         if (G >= VR_TOKENS && rounds <= 5 && 4 * G >= 3 * rounds * VR_TOKENS && blocks <= 0x7fffffffLL) {
 #define W4A8_VR_LAUNCH(T_, R_)                                                                                     \
