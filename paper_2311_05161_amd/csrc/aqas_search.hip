@@ -119,60 +119,70 @@ int launch_aqas_scale(const float *ax, const float *aw, int64_t K, int j, float 
 
 // ---- the unquantized product Yref[m,n] = sum_k X[m,k] W[n,k] in fp32 on the matrix cores ----------
 // 16-bit inputs, rows 16-byte aligned and K % 64 == 0: products of 16-bit numbers are exact in fp32, so the 16-bit matrix
-// instructions (32 x 32 x 16) lose nothing against widened operands.  A block of four waves makes a 64 x 128 tile,
-// wave w the columns 32 w .. + 31 of all 64 rows; 64 columns of K at a time go through LDS (rows of 128 bytes in
-// 16-byte chunks, chunk index XORed with half the row so that the reads of 16 rows at one chunk cover all
-// banks), the next four steps are on their way to registers meanwhile.  Bound by the L2 reads of the tiles (24 KB
-// per step and block): at 512 x 4096 x 4096 the grid is one block per CU.  One wave per 32 x 32 tile straight from global memory, 16
-// bytes of 32 rows per load, took 127 us there, this 41 us.
-constexpr int RG_BM = 64, RG_BN = 128, RG_BK = 64, RG_AHEAD = 4;
+// instructions (32 x 32 x 16) lose nothing against widened operands.  A block makes a 64 x 128 tile with RG_PHASES x 4 waves:
+// wave (p, w) the columns 32 w .. + 31 of all 64 rows over every RG_PHASES-th step of 64 columns of K.  A round of RG_PHASES
+// steps lies in one of RG_RING LDS buffers (rows of 128 bytes in 16-byte chunks, chunk index XORed with half the row so that
+// the reads of 16 rows at one chunk cover all banks -- on the global side, as a copy lands in lane order), filled by direct
+// copies RG_RING - 1 rounds ahead; the phases' sums meet in LDS at the end, in their order.
+// At 512 x 4096 x 4096 the grid is one block per CU, and what bounds it is the way of the tiles through the CU's memory pipe
+// (48 KB per round: 768 clocks).  us there: one wave per 32 x 32 tile straight from global memory 127; four waves, through
+// registers to LDS, 38.6; two phases 32.7; copies straight to LDS 28.9
+// (97 x 3072 x 2000 26 / 19, 2048 x 4096 x 4096 106 / 103; rms error against 64 bits 8.1e-7 / 1.8e-7 with two shorter chains).
+constexpr int RG_BM = 64, RG_BN = 128, RG_BK = 64, RG_PHASES = 2, RG_RING = 3;
+constexpr int RG_THREADS = RG_PHASES * 256;
+constexpr int RG_ROWS = RG_BM + RG_BN;                    // rows of X, then rows of W
+constexpr int RG_STEP = RG_ROWS * RG_BK * 2;              // bytes of a step in LDS (24 KB)
 
 template <typename T>
-__global__ __launch_bounds__(256) void ref_gemm16_kernel(const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx,
-                                                         const T *__restrict__ W, int64_t N, int64_t ldw,
-                                                         float *__restrict__ Y, uint32_t grid_n)
+__global__ __launch_bounds__(RG_THREADS) void ref_gemm16_kernel(const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx,
+                                                                const T *__restrict__ W, int64_t N, int64_t ldw,
+                                                                float *__restrict__ Y, uint32_t grid_n)
 {
-    constexpr int ROWS = RG_BM + RG_BN;          // rows of X, then rows of W
-    constexpr int LOADS = ROWS * 8 / 256;        // 16-byte chunks per thread and step (6)
-    __shared__ __attribute__((aligned(16))) v4u tile[2][ROWS * 8];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    constexpr int COPIES = RG_ROWS / 8 / 4;               // of eight rows, per wave and round (6)
+    extern __shared__ __attribute__((aligned(16))) uint8_t rg_lds[];   // [RG_RING][RG_PHASES][RG_STEP]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3), phase = __builtin_amdgcn_readfirstlane(tid >> 8);
     const uint32_t bm = blockIdx.x / grid_n, bn = blockIdx.x - bm * grid_n;
     const int64_t m0 = (int64_t)bm * RG_BM, n0 = (int64_t)bn * RG_BN;
     const int r32 = lane & 31, kh = lane >> 5;
-    // thread: rows tid / 8 + 32 i, chunk tid % 8 (eight lanes read 128 contiguous bytes of a row)
-    const v4u *src[LOADS];
-    int dst[LOADS];
+    // Copy i of a wave: rows 8 (4 i + wave) .. + 7 of its phase's step, eight lanes a row.  (Rows past the end repeat the last one;
+    // they are not stored.  A descriptor starts at the first of the eight rows: seven row strides are below 2^31 bytes.)
+    v4i rsrc[COPIES];
+    int voff[COPIES];
 #pragma unroll
-    for (int i = 0; i < LOADS; ++i) {
-        const int row = tid / 8 + 32 * i, c = tid & 7;
-        // (rows past the end repeat the last one; they are not stored)
-        const T *p = row < RG_BM ? X + min(m0 + row, M - 1) * ldx : W + min(n0 + row - RG_BM, N - 1) * ldw;
-        src[i] = reinterpret_cast<const v4u *>(p) + c;
-        dst[i] = row * 8 + (c ^ ((row >> 1) & 7));
+    for (int i = 0; i < COPIES; ++i) {
+        const int row0 = 8 * (4 * i + wave), row = row0 + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
+        const bool is_x = row0 < RG_BM;   // (RG_BM % 8 == 0: uniform)
+        const int64_t last = is_x ? M - 1 : N - 1, at = is_x ? m0 : n0 - RG_BM, ld = is_x ? ldx : ldw;
+        const int64_t first = min(at + row0, last);
+        const uint64_t base = (uint64_t)((is_x ? X : W) + first * ld);
+        rsrc[i] = v4i{(int)(uint32_t)base, (int)((base >> 32) & 0xffffu), 0x7fffffff, 0x00020000};
+        voff[i] = (int)((min(at + row, last) - first) * ld * 2) + c * 16;
     }
     v16f acc[2];
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.0f;
-    // RG_AHEAD steps of loads are in flight against the memory latency (vector-typed registers: an array of the
-    // HIP struct type went to scratch memory, and the kernel took 128 to 168 us)
-    v4u ring[RG_AHEAD][LOADS];
-    const int64_t steps = K / RG_BK;
+    const int steps = (int)(K / RG_BK), rounds = (steps + RG_PHASES - 1) / RG_PHASES;
+    const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)rg_lds;
+    auto copy_round = [&](int round, int slot) {
+        const int step = min(round * RG_PHASES + phase, steps - 1);   // (past the end: the last step, unused)
 #pragma unroll
-    for (int p = 0; p < RG_AHEAD; ++p)
+        for (int i = 0; i < COPIES; ++i)
+            dma_b128(rsrc[i], voff[i], step * (RG_BK * 2),
+                     lds_base + (uint32_t)((slot * RG_PHASES + phase) * RG_STEP + (4 * i + wave) * 1024));
+    };
 #pragma unroll
-        for (int i = 0; i < LOADS; ++i) ring[p][i] = src[i][min((int64_t)p, steps - 1) * 8];
-    for (int64_t s0 = 0; s0 < steps; s0 += RG_AHEAD) {
-#pragma unroll
-        for (int p = 0; p < RG_AHEAD; ++p) {   // (RG_AHEAD is even: step s0 + p uses buffer p & 1)
-            if (s0 + p >= steps) break;        // uniform
-            v4u *t = tile[p & 1];
-#pragma unroll
-            for (int i = 0; i < LOADS; ++i) t[dst[i]] = ring[p][i];
-            const int64_t ahead = min(s0 + p + RG_AHEAD, steps - 1);   // (past the end: the last step again, unused)
-#pragma unroll
-            for (int i = 0; i < LOADS; ++i) ring[p][i] = src[i][ahead * 8];
-            // (one barrier per step: a wave that is a step ahead writes the other buffer; the loads above stay in flight)
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    for (int i = 0; i < RG_RING - 1; ++i) copy_round(i, i);
+    int slot = 0;
+    for (int round = 0; round < rounds; ++round) {
+        // this round's copies have landed, the next ones' are on their way; behind the barrier everyone's have, and the slot
+        // of the round before is free
+        static_assert(RG_RING == 3 && COPIES == 6, "the wait counts the copies of one round");
+        asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
+        __syncthreads();
+        copy_round(round + RG_RING - 1, slot == 0 ? RG_RING - 1 : slot - 1);
+        if (round * RG_PHASES + phase < steps) {   // (uniform over the wave: the last round may have no step for a phase)
+            const v4u *t = reinterpret_cast<const v4u *>(rg_lds + (slot * RG_PHASES + phase) * RG_STEP);
 #pragma unroll
             for (int q = 0; q < RG_BK / 16; ++q) {   // lane (r32, kh) holds 8 consecutive k of its row, as both operands agree on
                 const int c = (2 * q + kh) ^ ((r32 >> 1) & 7);
@@ -189,7 +199,32 @@ __global__ __launch_bounds__(256) void ref_gemm16_kernel(const T *__restrict__ X
                 }
             }
         }
+        slot = slot + 1 == RG_RING ? 0 : slot + 1;
     }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (copies past the end: the buffers are used again below)
+    // the phases' sums: phase 1 .. hand theirs over, phase 0 adds them in order and stores
+    __syncthreads();
+    v4f *red = reinterpret_cast<v4f *>(rg_lds);   // [phase - 1][wave][half][quarter][lane]
+    auto at = [&](int p, int h, int i) { return (((p - 1) * 4 + wave) * 8 + h * 4 + i) * 64 + lane; };
+    if (phase > 0) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                red[at(phase, h, i)] = v4f{acc[h][4 * i], acc[h][4 * i + 1], acc[h][4 * i + 2], acc[h][4 * i + 3]};
+    }
+    __syncthreads();
+    if (phase > 0) return;
+#pragma unroll
+    for (int p = 1; p < RG_PHASES; ++p)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const v4f o = red[at(p, h, i)];
+#pragma unroll
+                for (int r = 0; r < 4; ++r) acc[h][4 * i + r] += o[r];
+            }
     // D[i][j], A = tokens, B = channels: lane holds channel n0 + 32 wave + r32, tokens 8 (r / 4) + 4 kh + r % 4
     const int64_t n = n0 + wave * 32 + r32;
     if (n < N) {
@@ -203,7 +238,7 @@ __global__ __launch_bounds__(256) void ref_gemm16_kernel(const T *__restrict__ X
     }
 }
 
-// Binary32, and bfloat16 off the 16-byte alignment (fp16 rows have to have it): one wave per 32 x 32 output tile, operands
+// Binary32, bfloat16 off the 16-byte alignment (fp16 rows have to have it), and row strides beyond the tile kernel's descriptors: one wave per 32 x 32 output tile, operands
 // straight from global memory, widened exactly, v_mfma_f32_32x32x2_f32.
 template <typename T>
 __global__ __launch_bounds__(256) void ref_gemm_kernel(const T *__restrict__ X, int64_t M, int64_t K,
@@ -239,19 +274,27 @@ int launch_ref_gemm(const void *X, const void *W, int dtype, int64_t M, int64_t 
 {
     const int64_t gn16 = (N + RG_BN - 1) / RG_BN, blocks16 = (M + RG_BM - 1) / RG_BM * gn16;
     if (dtype != W4A8_F32 && K % RG_BK == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)W % 16 == 0 && ldx % 8 == 0 &&
-        ldw % 8 == 0 && blocks16 <= 0x7fffffffLL) {
+        ldw % 8 == 0 && blocks16 <= 0x7fffffffLL && ldx <= (1 << 26) && ldw <= (1 << 26) && K <= 0x3fffffffLL) {
         const dim3 grid16((unsigned)blocks16);
-        if (dtype == W4A8_F16)
-            hipLaunchKernelGGL((ref_gemm16_kernel<__half>), grid16, dim3(256), 0, st, (const __half *)X, M, K, ldx,
-                               (const __half *)W, N, ldw, Y, (uint32_t)gn16);
-        else
-            hipLaunchKernelGGL((ref_gemm16_kernel<bf16_t>), grid16, dim3(256), 0, st, (const bf16_t *)X, M, K, ldx,
-                               (const bf16_t *)W, N, ldw, Y, (uint32_t)gn16);
+        constexpr int lds_bytes = RG_RING * RG_PHASES * RG_STEP;   // 144 KB
+#define W4A8_RG(T_)                                                                                                        \
+    do {                                                                                                                   \
+        static std::atomic<uint64_t> lds_opted{0};                                                                         \
+        if (opt_in_dynamic_lds((const void *)ref_gemm16_kernel<T_>, lds_bytes, lds_opted) != W4A8_OK) return W4A8_ERR_HIP; \
+        hipLaunchKernelGGL((ref_gemm16_kernel<T_>), grid16, dim3(RG_THREADS), lds_bytes, st, (const T_ *)X, M, K, ldx,     \
+                           (const T_ *)W, N, ldw, Y, (uint32_t)gn16);                                                      \
+    } while (0)
+        if (dtype == W4A8_F16) W4A8_RG(__half);
+        else W4A8_RG(bf16_t);
+#undef W4A8_RG
         return hip_status(hipGetLastError());
     }
     const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
     switch (dtype) {
-        case W4A8_F16: return W4A8_ERR_SHAPE;   // (all that the callers accept went above)
+        case W4A8_F16:
+            hipLaunchKernelGGL((ref_gemm_kernel<__half>), grid, dim3(256), 0, st, (const __half *)X, M, K, ldx,
+                               (const __half *)W, N, ldw, Y);
+            break;
         case W4A8_BF16:
             hipLaunchKernelGGL((ref_gemm_kernel<bf16_t>), grid, dim3(256), 0, st, (const bf16_t *)X, M, K, ldx,
                                (const bf16_t *)W, N, ldw, Y);
@@ -374,7 +417,9 @@ __global__ __launch_bounds__(256) void aqas_next_point_kernel(const float *__res
     if (k < K) s[k] = scale_at(ax[k], aw[k], j);
 }
 
-// After the last grid point: its loss, the first minimum of all of them, the scale there.
+// After the last grid point: its loss, the first minimum of all of them, the scale there.  With err one block; without it
+// (all losses are there) every block looks for the minimum and takes its share of the scales (one block of 1024 threads
+// for 4096 channels: 8.0 us, sixteen of 256 4.9).
 __global__ __launch_bounds__(1024) void aqas_finish_kernel(const float *__restrict__ ax,
                                                            const float *__restrict__ aw, int64_t K,
                                                            float *__restrict__ s,
@@ -386,22 +431,26 @@ __global__ __launch_bounds__(1024) void aqas_finish_kernel(const float *__restri
     // (err null: all losses are there)
     const double last = err != nullptr ? loss_sum(err, N, part) : losses[AQ_GRID];
     if (threadIdx.x == 0) {
-        losses[AQ_GRID] = last;
+        if (err != nullptr) losses[AQ_GRID] = last;
+        double l[AQ_GRID + 1];   // (all on their way together)
+#pragma unroll
+        for (int i = 0; i <= AQ_GRID; ++i) l[i] = i == AQ_GRID ? last : losses[i];
         int b = 0;
-        double at_b = losses[0];
+        double at_b = l[0];
+#pragma unroll
         for (int i = 1; i <= AQ_GRID; ++i) {
-            const double l = i == AQ_GRID ? last : losses[i];
-            if (l < at_b) {
+            if (l[i] < at_b) {
                 b = i;
-                at_b = l;
+                at_b = l[i];
             }
         }
-        *best = b;
+        if (blockIdx.x == 0) *best = b;
         s_best = b;
     }
     __syncthreads();
     const int j = s_best;
-    for (int64_t k = threadIdx.x; k < K; k += 1024) s[k] = scale_at(ax[k], aw[k], j);
+    for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < K; k += (int64_t)gridDim.x * blockDim.x)
+        s[k] = scale_at(ax[k], aw[k], j);
 }
 
 // Y and Yref [M, N] dense, N % 16 == 0, both 16-byte aligned.  best_err null: err[n] is written; else the
@@ -532,10 +581,22 @@ __global__ __launch_bounds__(64) void clip_pick_kernel(const double *__restrict_
     double e[AQ_CLIP_STEPS];
 #pragma unroll
     for (int c = 0; c < AQ_CLIP_STEPS; ++c) e[c] = 0.0;
-    for (int i = 0; i < parts; ++i)
+    // (one thread per channel: what counts is the memory latency, so four token tiles' sums are on their way at a time;
+    // 4096 channels, 4 tiles: 15.9 -> 5.3 us)
+    constexpr int AHEAD = 4;
+    for (int i = 0; i < parts; i += AHEAD) {
+        double t[AHEAD][AQ_CLIP_STEPS];
 #pragma unroll
-        for (int c = 0; c < AQ_CLIP_STEPS; ++c)
-            if (c < count) e[c] += err[((int64_t)c * parts + i) * N + n];
+        for (int a = 0; a < AHEAD; ++a)
+#pragma unroll
+            for (int c = 0; c < AQ_CLIP_STEPS; ++c)
+                t[a][c] = err[((int64_t)min(c, count - 1) * parts + min(i + a, parts - 1)) * N + n];   // (past the end: not added)
+#pragma unroll
+        for (int a = 0; a < AHEAD; ++a)
+#pragma unroll
+            for (int c = 0; c < AQ_CLIP_STEPS; ++c)
+                if (i + a < parts && c < count) e[c] += t[a][c];
+    }
     double best = 0.0;
     int32_t idx = 0;
     if (i0 > 0) {
@@ -598,7 +659,8 @@ int launch_aqas_finish_all(const float *ax, const float *aw, int64_t K, float *s
                            int64_t N, double *losses, int32_t *best, hipStream_t st)
 {
     hipLaunchKernelGGL(aqas_losses_kernel, dim3(AQ_GRID + 1), dim3(1024), 0, st, err, parts * N, losses);
-    hipLaunchKernelGGL(aqas_finish_kernel, dim3(1), dim3(1024), 0, st, ax, aw, K, s, (const double *)nullptr, N, losses, best);
+    hipLaunchKernelGGL(aqas_finish_kernel, dim3((unsigned)((K + 255) / 256)), dim3(256), 0, st, ax, aw, K, s, (const double *)nullptr, N,
+                       losses, best);
     return hip_status(hipGetLastError());
 }
 
