@@ -632,14 +632,16 @@ int launch_weight_quant(const void *W, int w_dtype, int64_t N, int64_t K, int64_
 }
 
 // ---- quantized straight to the tiled packed form --------------------------------------------------
-// dINT4 with groups of 128: a 16 x 128 tile of the packed form is 16 whole groups.  A wave takes two tiles of
+// dINT4 with groups of 128: a 16 x 128 tile of the packed form is 16 whole groups.  A wave takes WQT_TILES tiles of
 // the same columns (they share the AQAS scales): lane l holds row l % 16, columns 32 c + 8 (l / 16) .. + 7,
 // c = 0..3, so that a load instruction reads 64 contiguous bytes of each row (32 consecutive columns per
 // lane, which would make one 16-byte store, read 16-byte pieces and measured the same), the four
 // lanes of a group meet in two shuffles, and codes 8 c' .. of quarter c are one word of the tile.
-// Bound by the read of W (2.5 bytes per fp16 weight move instead of the 4 of quantizing and packing
-// one after the other).  4096 x 4096 fp16: 14.7 + 5.5 -> 13.4 us.
-constexpr int WQT_TILES = 2;
+// Bound by the vector ALU (a candidate's weights: two multiplications, the range, the code rule) and the stores; more waves
+// on a SIMD serve both better than shared scales: one tile per wave (111 registers) instead of two (163), with streaming
+// stores, 4096 x 4096 straight to int8, us: 17 scales 113 -> 101, 11 clipping factors 56 -> 50 (without the code
+// rule's arithmetic 68 and 33), 2048 x 3072 46 -> 39 and 28 -> 22.
+constexpr int WQT_TILES = 1;
 
 // Eight weights -> four times their value in half steps, as bytes: 8 (code - z), or +-4 for the special codes (the rule of
 // code_byte without the zero-point).
@@ -727,7 +729,10 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_packed_kernel(
                                  ((nt[i] & 1) * 16 + row) * 16 + (kb & 1) * 8;
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
-                    *reinterpret_cast<uint2 *>(block + (c >> 1) * 2048 + (c & 1) * 512) = levels8(x[i][c], rule);
+                {   // (streaming: the candidates' weights together are more than the last-level cache holds)
+                    const uint2 q = levels8(x[i][c], rule);
+                    __builtin_nontemporal_store(v2u{q.x, q.y}, reinterpret_cast<v2u *>(block + (c >> 1) * 2048 + (c & 1) * 512));
+                }
             } else {
                 if (lane < 16) {
                     step[tiles * TILE_N + n * KT + kt] = st;
