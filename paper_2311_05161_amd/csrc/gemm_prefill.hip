@@ -725,7 +725,7 @@ static int launch_gemm_t(const GemmPlan &pl, const int8_t *Xq, const float *sx, 
 // one barrier per KQ k-tiles.  At the end the phases' fp32 sums meet through LDS in a fixed order
 // (q0 + q1, or (q0 + q1) + (q2 + q3)), and every wave applies the token scale to its share of the tile and stores it.  No
 // workspace, no second launch.  KQ = 4: 64 channels per workgroup; KQ = 2: 128, for twice the tiles on the same CUs.
-// ASYM: token zero-points, one 24-bit multiply-add per accumulator and group as in gemm_kernel.
+// ASYM: token zero-points, one multiply-add per accumulator and group (607 x 4096 x 4096 31.1 -> 30.0 us with it in binary32).
 // MS: 32-token blocks of the workgroup, two to four (see gemm_mid_form).
 // MULTI: groups of tpg k-tiles.  A round of KQ groups takes tpg super-steps; the integer sums run on from k-tile to k-tile and are
 // rescaled behind the last one of a group (between the matrix instructions, as with one k-tile per group, would take the
@@ -750,7 +750,11 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     extern __shared__ __attribute__((aligned(16))) uint8_t lds_raw[];   // [2 * KQ][MD_TILE]
     __shared__ __attribute__((aligned(16))) float s_ges[4 * KQ][BN];   // step / 8 of the groups of four super-steps, per phase and channel
     __shared__ int s_gz[4 * KQ][BN];
-    __shared__ __attribute__((aligned(16))) int s_gw[ASYM ? 4 * KQ : 1][ASYM ? BN : 4];   // 4 * (sum of the group's weights)
+    // Token zero-points: in groups of 128 the products with the weight sums, and the sums without them, are whole numbers below
+    // 2^24, so they leave in binary32, exactly -- a fused multiply-add issues at twice the rate of a 24-bit integer one.
+    using Wsum = std::conditional_t<MULTI, int, float>;
+    typedef Wsum v4w __attribute__((ext_vector_type(4)));
+    __shared__ __attribute__((aligned(16))) Wsum s_gw[ASYM ? 4 * KQ : 1][ASYM ? BN : 4];   // 4 * (sum of the group's weights)
 
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -831,7 +835,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
         if (tid < KQ * BN) {
             s_ges[(ss & 3) * KQ + tid / BN][tid % BN] = gp_es * 0.125f;
             s_gz[(ss & 3) * KQ + tid / BN][tid % BN] = gp_z;
-            if (ASYM) s_gw[(ss & 3) * KQ + tid / BN][tid % BN] = 4 * gp_w;
+            if (ASYM) s_gw[(ss & 3) * KQ + tid / BN][tid % BN] = (Wsum)(4 * gp_w);
         }
     };
 
@@ -863,18 +867,21 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     };
     // y += (step / 8) * acc for accumulator registers 4 b .. 4 b + 3 of token block ms (group g)
     v4f es4[4];   // step / 8 of this lane's 16 channels for the group in the accumulators
-    v4i gw4[ASYM ? 4 : 1];   // and 4 * (sum of the group's weights)
-    int nzx[MS];  // minus the zero-point of this lane's token of each block
+    v4w gw4[ASYM ? 4 : 1];   // and 4 * (sum of the group's weights)
+    Wsum nzx[MS];  // minus the zero-point of this lane's token of each block
 #pragma unroll
-    for (int ms = 0; ms < MS; ++ms) nzx[ms] = (ASYM && m0 + ms * 32 + r32 < M) ? -zx[m0 + ms * 32 + r32] : 0;
+    for (int ms = 0; ms < MS; ++ms) nzx[ms] = (ASYM && m0 + ms * 32 + r32 < M) ? (Wsum)-zx[m0 + ms * 32 + r32] : 0;
     auto flush_quarter = [&](int ms, int b, int g) {
         const int m = m0 + ms * 32 + r32;
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int v = acc[ms][4 * b + r];
             if (MULTI) acc[ms][4 * b + r] = 0;   // (the next group adds on)
-            const int vz = ASYM ? v + __mul24(nzx[ms], gw4[ASYM ? b : 0][r]) : v;   // (|4 wsum| < 2^23)
-            y[ms][4 * b + r] = __builtin_fmaf(es4[b][r], (float)vz, y[ms][4 * b + r]);
+            float vz;
+            if constexpr (!ASYM) vz = (float)v;
+            else if constexpr (MULTI) vz = (float)(v + __mul24(nzx[ms], gw4[b][r]));   // (|4 wsum| < 2^23)
+            else vz = __builtin_fmaf(nzx[ms], gw4[b][r], (float)v);
+            y[ms][4 * b + r] = __builtin_fmaf(es4[b][r], vz, y[ms][4 * b + r]);
             if (ACC_OUT && m < M) {
                 const int nn = nb0 + wn * 32 + 8 * b + 4 * kh + r;
                 if (nn < N) acc_out[((int64_t)m * N + nn) * ng + g] = v >> 2;
@@ -953,7 +960,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
             if constexpr (ASYM) {
 #pragma unroll
                 for (int b = 0; b < 4; ++b)
-                    gw4[b] = *reinterpret_cast<const v4i *>(&s_gw[pslot][wn * 32 + 8 * b + 4 * kh]);
+                    gw4[b] = *reinterpret_cast<const v4w *>(&s_gw[pslot][wn * 32 + 8 * b + 4 * kh]);
             }
             int z_next = s_gz[pslot_next][wn * 32 + r32];
             const v16i z16 = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
@@ -1031,6 +1038,9 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
+    float sxv[MS];   // (on their way under the exchange: fetched block by block behind it, 2000 clocks of a launch)
+#pragma unroll
+    for (int ms = 0; ms < MS; ++ms) sxv[ms] = sx[min(m0 + ms * 32 + r32, M - 1)];
     // ---- the phases' sums meet in LDS: q0 + q1, or (q0 + q1) + (q2 + q3).  The two waves of a pair exchange halves:
     // each hands over the token blocks that the other one finishes, LO of them the even phase's; likewise the pairs, so
     // that all eight waves add and store (with the parameters of the first three super-steps on their way together instead of one
@@ -1084,7 +1094,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     for (int ms = 0; ms < MS; ++ms) {
         const int m = m0 + ms * 32 + r32;
         if (ms < first || ms >= last || m >= M) continue;
-        const float sxm = sx[m];
+        const float sxm = sxv[ms];
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             const int nn = nb0 + wn * 32 + 8 * b + 4 * kh;

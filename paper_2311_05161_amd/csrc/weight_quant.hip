@@ -728,8 +728,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_packed_kernel(
                 uint8_t *block = w8 + ((int64_t)(nt[i] >> 1) * KT + kt) * I8_BLOCK + (kb >> 1) * 1024 +
                                  ((nt[i] & 1) * 16 + row) * 16 + (kb & 1) * 8;
 #pragma unroll
-                for (int c = 0; c < 4; ++c)
-                {   // (streaming: the candidates' weights together are more than the last-level cache holds)
+                for (int c = 0; c < 4; ++c) {   // (streaming: all candidates' weights are more than the last-level cache holds)
                     const uint2 q = levels8(x[i][c], rule);
                     __builtin_nontemporal_store(v2u{q.x, q.y}, reinterpret_cast<v2u *>(block + (c >> 1) * 2048 + (c & 1) * 512));
                 }

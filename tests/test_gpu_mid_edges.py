@@ -90,3 +90,26 @@ def test_per_channel_remainder(M, K, N):
     Wp = lib.pack_dint4(codes)
     Y, _ = lib.w4a8_gemm(Xq, sx, Wp, step, zero, N, K, 0, want_acc=True)
     assert torch.equal(Y, lib.w4a8_gemm(Xq, sx, Wp, step, zero, N, K, 0))
+
+
+# token zero-points at the ends of their range against the largest weight sums of a group, where the products and sums that leave
+# the accumulators in binary32 are largest (below 2^21)
+@pytest.mark.parametrize("M,K,N", [FOUR[0], TWO[0], (607, 1024, 4096), (97, 2048, 4112)])
+@pytest.mark.parametrize("code,z", [(13, 0), (0, 13), (12, 0)])
+def test_zero_points_at_the_ends(M, K, N, code, z):
+    import paper_2311_05161_amd as lib
+    Xq = np.full((M, K), 127, np.int8)
+    Xq[::2] = -128
+    Xq[::3, ::7] = -127
+    zx = np.where(np.arange(M) % 4 < 2, -128, 127).astype(np.int32)
+    sx = np.full(M, 0.01, np.float32)
+    codes = np.full((N, K), code, np.uint8)
+    codes[::5, ::9] = 14
+    zero = np.full((N, K // 128), z, np.uint8)
+    step = np.full((N, K // 128), 1e-5, np.float32)
+    cd, zd = dev(codes), dev(zero)
+    ws, ts = lib.dint4_weight_sums(cd, zd, 128)
+    Y = torch.empty((M, N), dtype=torch.float16, device="cuda")
+    lib.w4a8_gemm_asym(dev(Xq), dev(sx), dev(zx), lib.pack_dint4(cd), dev(step), zd, ws, ts, N, K, 128, Y=Y)
+    acc = acc_by_float64_matmul(Xq.astype(np.int32) - zx[:, None], decode_table_np(codes, zero, 128), 128)
+    assert_y_close(host(Y), sx.astype(np.float64)[:, None] * (acc * (step.astype(np.float64) / 2)).sum(2), "f16")
