@@ -194,7 +194,7 @@ def test_value_quant_edges(lib, oracle, B, T, D, G, dtype, interleaved):
 # every edge of the code rule with its two binary32 neighbours, zero-points of either parity and beyond the code space (where
 # the clamp alone says what comes out), in every kernel: four rows and one row per wave, long segments, the general form
 @pytest.mark.parametrize("N,K,G", [(2050, 1024, 128), (2050, 1024, 256), (40, 256, 128), (6, 4096, 0), (3, 2304, 0), (9, 96, 48)])
-def test_code_rule_edges(lib, oracle, N, K, G):
+def test_code_rule_edges_of_kernels(lib, oracle, N, K, G):
     edges = np.concatenate([[0.0, 0.25, 0.75], np.arange(0, 31) + 0.5, np.arange(1, 31), [300.0, 2.0 ** 22]]).astype(np.float32)
     near = np.concatenate([edges, np.nextafter(edges, np.float32(np.inf)), np.nextafter(edges, np.float32(-np.inf))])
     near = np.concatenate([near, -near])
