@@ -881,12 +881,13 @@ __global__ __launch_bounds__(256) void value_quant_kernel(const T *__restrict__ 
     }
 }
 
-// A channel's rule as 16 bytes of LDS, and back.
-__device__ __forceinline__ float4 rule_entry(const CodeRule &r)
+// A channel's rule as 16 bytes of LDS, and back.  (Vectors and not float4: the compiler takes that struct apart, and its four
+// reads of four bytes, eight channels a stride of 128 bytes apart, cost value_quant_vec_kernel 13 % of its time.)
+__device__ __forceinline__ v4f rule_entry(const CodeRule &r)
 {
-    return make_float4(r.istep, r.lo, r.magic, __uint_as_float(r.odd));
+    return v4f{r.istep, r.lo, r.magic, __uint_as_float(r.odd)};
 }
-__device__ __forceinline__ CodeRule rule_of(const float4 &f)
+__device__ __forceinline__ CodeRule rule_of(const v4f f)
 {
     CodeRule r = make_rule(f.x, 0);
     r.lo = f.y;
@@ -902,6 +903,9 @@ __device__ __forceinline__ CodeRule rule_of(const float4 &f)
 // Thread (c8, t4) = (tid % 8, tid / 8) owns channels 8 c8 .. + 7 and, per block of 128 tokens, the
 // four tokens 4 t4 .. + 3: exactly one 32-bit word of codes per channel, which goes through LDS to
 // the thread that stores the channel's row segment.
+// Four codes per channel and round are too few for the rule with the folded zero-point: what it takes off and makes up per
+// channel is as much as it saves, and with few workgroups more (32 heads x 5248 tokens x 128 channels 82.9 us with
+// code_byte, 84.5 with codes4; 256 x 4096 in groups of 128 the same, 96.0 and 96.4).
 template <typename T>
 __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restrict__ V, int64_t Tn,
                                                               int64_t D, int64_t ld_t, int64_t ld_b,
@@ -911,7 +915,7 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
 {
     static_assert(sizeof(T) == 2, "16-bit elements");
     __shared__ float s_lo[4][64], s_hi[4][64];
-    __shared__ float4 s_rule[64];          // each channel's rule
+    __shared__ v4f s_rule[64];             // 1 / step, -z, p - z, z of each channel
     __shared__ uint32_t s_codes[64][33];   // [channel][32 words of 4 tokens], odd stride
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c8 = tid & 7, t4 = tid >> 3;
@@ -961,7 +965,7 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
         int z;
         range_params(l, h, st, istep, z);
         const CodeRule r = make_rule(istep, z);
-        s_rule[tid] = rule_entry(r);
+        s_rule[tid] = v4f{r.istep, r.lo, r.hi, __int_as_float(r.z)};
         if (d0 + tid < D) {
             step[(b * D + d0 + tid) * ng + g] = st;
             zero[(b * D + d0 + tid) * ng + g] = (uint8_t)z;
@@ -982,9 +986,13 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
         for (int j = 0; j < 8; ++j) {
             // (the channel's rule comes from LDS each time: eight of them in registers cost the kernel
             // a wave per SIMD and 6 % of its time)
-            const CodeRule rule = rule_of(s_rule[c8 * 8 + j]);
-            s_codes[c8 * 8 + j][t4] = codes4(to_f32(e[0][j]) * rule.istep, to_f32(e[1][j]) * rule.istep,
-                                             to_f32(e[2][j]) * rule.istep, to_f32(e[3][j]) * rule.istep, rule);
+            const v4f f = s_rule[c8 * 8 + j];
+            CodeRule rule = make_rule(f.x, 0);
+            rule.lo = f.y;
+            rule.hi = f.z;
+            rule.z = __float_as_int(f.w);
+            s_codes[c8 * 8 + j][t4] = pack_low_bytes(code_byte(to_f32(e[0][j]), rule), code_byte(to_f32(e[1][j]), rule),
+                                                     code_byte(to_f32(e[2][j]), rule), code_byte(to_f32(e[3][j]), rule));
         }
         __syncthreads();
         if (d0 + r < D) {
@@ -1022,7 +1030,7 @@ __global__ __launch_bounds__(VR_THREADS) void value_quant_resident_kernel(const 
     static_assert(sizeof(T) == 2, "16-bit elements");
     constexpr int WAVES = VR_THREADS / WAVE;
     __shared__ float s_lo[WAVES][VR_CHANNELS], s_hi[WAVES][VR_CHANNELS];
-    __shared__ float4 s_rule[VR_CHANNELS];          // each channel's rule
+    __shared__ v4f s_rule[VR_CHANNELS];             // each channel's rule
     __shared__ __attribute__((aligned(16))) uint32_t s_codes[R > 1 ? 2 : 1][VR_CHANNELS * VR_STRIDE];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // block -> (head and group, channel part): the parts of one follow each other on one XCD (blocks go round-robin
