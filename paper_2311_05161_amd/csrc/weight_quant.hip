@@ -215,7 +215,11 @@ __device__ __forceinline__ void load_scales(const float *sg, int64_t k, int s_ve
     }
 }
 
-template <typename T, int V>
+// A wave per (row, group), two sweeps; V columns per lane and load, times 1 where there is no scale vector.
+// HALF (V = 8): special values +-step / 2 or none -- an instance of its own, as the choice between the two rules in the loop cost
+// a long row 3 to 7 % (300 x 16392 fp16, us: one rule for all 26.0, the choice 28.0, instances 25.4; 768 x 768 3.90 / 4.02 / 3.89;
+// 4096 x 4096 in groups of 512 21.4 / 20.9 / 20.6).
+template <typename T, int V, bool HALF>
 __global__ __launch_bounds__(WQ_THREADS) void weight_quant_kernel(
     const T *__restrict__ W, int64_t N, int64_t K, int64_t ldw, const float *__restrict__ s,
     int64_t G, int use_given, uint8_t *__restrict__ codes, float *__restrict__ step,
@@ -244,7 +248,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_kernel(
             load_scales<V>(sg, k, s_vec, sv);
 #pragma unroll
             for (int j = 0; j < V; ++j) {
-                const float x = sg ? v[j] * sv[j] : v[j];
+                const float x = v[j] * sv[j];
                 lo = fminf(lo, x);
                 hi = fmaxf(hi, x);
             }
@@ -268,9 +272,9 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_kernel(
         load_scales<V>(sg, k, s_vec, sv);
         float x[V];
 #pragma unroll
-        for (int j = 0; j < V; ++j) x[j] = sg ? v[j] * sv[j] : v[j];
+        for (int j = 0; j < V; ++j) x[j] = v[j] * sv[j];
         if constexpr (V == 8)
-            *reinterpret_cast<uint2 *>(c + k) = fmt.shift == 1 ? codes8(x, rule) : codes8_of<false>(x, rule);
+            *reinterpret_cast<uint2 *>(c + k) = codes8_of<HALF>(x, rule);
         else if constexpr (V == 2)
             *reinterpret_cast<uint16_t *>(c + k) =
                 (uint16_t)pack_low_bytes(code_byte(x[0], rule), code_byte(x[1], rule), 0u, 0u);
@@ -545,8 +549,8 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
         return segs * cands <= (rounds >= 3 ? 1536 : 1024) || rounds == 4 || rounds >= 6 ||
                (sizeof(T) == 4 && (rounds == 5 || (rounds == 3 && N * K * 4 > (70 << 20))));
     };
-#define W4A8_WQ_LAUNCH(V_)                                                                        \
-    hipLaunchKernelGGL((weight_quant_kernel<T, V_>), dim3((unsigned)blocks, 1, cands), dim3(WQ_THREADS), 0, \
+#define W4A8_WQ_LAUNCH(V_, HALF_)                                                                 \
+    hipLaunchKernelGGL((weight_quant_kernel<T, V_, HALF_>), dim3((unsigned)blocks, 1, cands), dim3(WQ_THREADS), 0, \
                        st, W, N, K, ldw, s, G, use_given, codes, step, zero, fmt, s_vec, clip)
     if ((G == 128 || G == 256) && aligned(8) && cands == 1) {   // (candidates: per-channel layers of 128 or 256 columns only)
         const int rows = N * K <= (1 << 21) ? 1 : SG_ROWS;
@@ -594,11 +598,12 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
 #undef W4A8_WQ_SEGMENT
 #undef W4A8_WQ_SEGMENT_F
     } else if (G >= 512 && aligned(8)) {
-        W4A8_WQ_LAUNCH(8);
+        if (fmt.shift == 1) W4A8_WQ_LAUNCH(8, true);
+        else W4A8_WQ_LAUNCH(8, false);
     } else if (aligned(2)) {
-        W4A8_WQ_LAUNCH(2);
+        W4A8_WQ_LAUNCH(2, false);
     } else {
-        W4A8_WQ_LAUNCH(1);
+        W4A8_WQ_LAUNCH(1, false);
     }
 #undef W4A8_WQ_LAUNCH
     return hip_status(hipGetLastError());

@@ -192,8 +192,9 @@ def test_value_quant_edges(lib, oracle, B, T, D, G, dtype, interleaved):
 
 
 # every edge of the code rule with its two binary32 neighbours, zero-points of either parity and beyond the code space (where
-# the clamp alone says what comes out), in every kernel: four rows and one row per wave, long segments, the general form
-@pytest.mark.parametrize("N,K,G", [(2050, 1024, 128), (2050, 1024, 256), (40, 256, 128), (6, 4096, 0), (3, 2304, 0), (9, 96, 48)])
+# the clamp alone says what comes out): four rows and one row per wave, long segments, the wave-per-segment kernel with two and with eight columns per lane
+@pytest.mark.parametrize("N,K,G", [(2050, 1024, 128), (2050, 1024, 256), (40, 256, 128), (6, 4096, 0), (3, 2304, 0), (9, 96, 48),
+                                   (5, 1024, 512), (3, 768, 0)])
 def test_code_rule_edges_of_kernels(lib, oracle, N, K, G):
     edges = np.concatenate([[0.0, 0.25, 0.75], np.arange(0, 31) + 0.5, np.arange(1, 31), [300.0, 2.0 ** 22]]).astype(np.float32)
     near = np.concatenate([edges, np.nextafter(edges, np.float32(np.inf)), np.nextafter(edges, np.float32(-np.inf))])
@@ -223,3 +224,20 @@ def test_value_code_rule_edges(lib, oracle, B, T, D, G, dtype):
     got = lib.quantize_value_dint4(Vd, G)
     assert np.array_equal(host(got[2]).reshape(zero.shape), zero) and np.array_equal(host(got[1]).reshape(step.shape), step)
     assert np.array_equal(host(got[0]).reshape(codes.shape), codes)
+
+
+# every code space in the wave-per-segment kernel, whose instances differ in the special values they know: eight columns per lane
+# (groups of 512, a row of 768) and two (rows off the alignment), a last round that is partly empty, with and without scales
+@pytest.mark.parametrize("fmt,name,shift", [(0, "dint4", 1), (1, "int4", 1), (2, "dint3", 1), (3, "dint4", 2), (4, "dint4", 3)])
+@pytest.mark.parametrize("N,K,G,pad", [(9, 1024, 512, 0), (6, 768, 0, 8), (6, 768, 0, 2)])
+def test_formats_in_the_wave_per_segment_kernel(lib, oracle, fmt, name, shift, N, K, G, pad):
+    rng = np.random.default_rng(N + K + fmt)
+    W = (rng.standard_normal((N, K)) * 0.02).astype(np.float32).astype(np.float16)
+    W[1] = np.abs(W[1])
+    s = rng.uniform(0.5, 2.0, K).astype(np.float32)
+    Wd = torch.zeros((N, K + pad), dtype=torch.float16, device="cuda")[:, :K]
+    Wd.copy_(torch.from_numpy(W))
+    for scale in (s, None):
+        got = lib.quantize_weight_format(Wd, None if scale is None else dev(scale), G, fmt)
+        for a, b in zip(got, oracle.formats.quantize_weight(W.astype(np.float32), scale, G, name, shift)):
+            assert np.array_equal(host(a), b)
