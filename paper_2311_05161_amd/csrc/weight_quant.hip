@@ -553,7 +553,9 @@ static int launch_weight_quant_t(const T *W, int64_t N, int64_t K, int64_t ldw, 
     hipLaunchKernelGGL((weight_quant_kernel<T, V_, HALF_>), dim3((unsigned)blocks, 1, cands), dim3(WQ_THREADS), 0, \
                        st, W, N, K, ldw, s, G, use_given, codes, step, zero, fmt, s_vec, clip)
     if ((G == 128 || G == 256) && aligned(8) && cands == 1) {   // (candidates: per-channel layers of 128 or 256 columns only)
-        const int rows = N * K <= (1 << 21) ? 1 : SG_ROWS;
+        // (fewer rows than a block of four per wave has room for leave waves of it idle: one per wave up to 1.5 * 2^23 weights,
+        // and of one or two rows always.  One / four, us: 4 x 2^20 5.4 / 6.5, 9 x 2^20 9.0 / 9.9, 1 x 2^24 22.6 / 30.3; 15 x 1118208 15.5 / 15.0, 12 x 5592064 49 / 44)
+        const int rows = N * K <= (N < SG_ROWS * (WQ_THREADS / WAVE) ? 3 << 22 : 1 << 21) || N <= 2 ? 1 : SG_ROWS;
         const int64_t strips = (N + rows * (WQ_THREADS / WAVE) - 1) / (rows * (WQ_THREADS / WAVE)), chunks = (K + 511) / 512;
         if (chunks > 0x7fffffffLL) return W4A8_ERR_SHAPE;
         const dim3 grid((unsigned)chunks, (unsigned)(strips < 65535 ? strips : 65535));

@@ -78,10 +78,11 @@ def test_pack_tiles_edges(lib, N, K, plain, shift):
 
 # rows that do not fill the last set of rows of a block, a last round of columns that is partly empty, the shortest
 # and longest segments of the register-resident kernel and the lengths just outside it, more than 2^21 weights in small
-# groups (four rows per wave; below, one), more than 1024 and 1536 segments on both sides of the rule's lengths, every input type, rows off the vector alignment; ranges made and given
+# groups (four rows per wave; below, and of a few rows, one), more than 1024 and 1536 segments on both sides of the rule's lengths, every input type, rows off the vector alignment; ranges made and given
 @pytest.mark.parametrize("N,K,G", [(1, 128, 128), (5, 640, 128), (6, 768, 256), (7, 1792, 256), (3, 1016, 0),
                                    (3, 1024, 0), (2, 2056, 0), (5, 9216, 0), (1, 16384, 0), (2, 16392, 0),
-                                   (4, 4096, 1024), (7, 300160, 128), (5, 420608, 256),
+                                   (4, 4096, 1024), (7, 300160, 128), (5, 420608, 256), (18, 116736, 128), (21, 100096, 256),
+                                   (2, 6291584, 128), (3, 4194432, 128),
                                    (1025, 1024, 0), (1537, 1536, 0), (1537, 1544, 0), (1539, 2056, 0), (513, 6144, 2048),
                                    (385, 10240, 2560)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
@@ -108,6 +109,23 @@ def test_weight_quant_edges(lib, oracle, N, K, G, dtype):
     assert np.array_equal(host(codes), rc)
 
 
+# more rows than a grid of four per wave covers at once: the waves go on to further rows, the last of them not full
+def test_weight_quant_many_rows(lib, oracle):
+    N, K = 16 * 65535 + 19, 128
+    g = torch.Generator(device="cuda").manual_seed(N)
+    W = (torch.randn((N, K), generator=g, device="cuda", dtype=torch.float32) * 0.02).half()
+    s = torch.rand((K,), generator=g, device="cuda") + 0.5
+    got = lib.quantize_weight_dint4(W, s, 128)
+    rows = np.r_[0:33, 16 * 65535 - 33:N]
+    at = torch.from_numpy(rows).cuda()
+    for a, b in zip(got, oracle.quantize_weight_dint4(host(W[at].float()), host(s), 128)):
+        assert np.array_equal(host(a[at]), b)
+    # the rows between, against the same rows in parts that one turn covers
+    for r in range(0, N, 1 << 19):
+        for a, b in zip(got, lib.quantize_weight_dint4(W[r:r + (1 << 19)], s, 128)):
+            assert torch.equal(a[r:r + (1 << 19)], b)
+
+
 # every tie and band edge of the rule, one binary32 step to either side of it, and values far beyond the range (within int32, where the oracle rounds): the
 # steps are given, powers of two, so that u is exact
 @pytest.mark.parametrize("G,K", [(128, 1024), (0, 1024), (0, 320)])
@@ -127,7 +145,7 @@ def test_code_rule_edges(lib, oracle, G, K):
 # Infinities and NaN: with given parameters an infinity takes the end level and NaN code 0; with ranges from the weights every
 # kernel gives what the element-per-lane kernel gives on the same weights (rows off the alignment).  One and four rows per
 # wave, the segment kernel, the wave-per-segment kernel.
-@pytest.mark.parametrize("N,K,G", [(6, 1024, 128), (5, 420608, 256), (6, 2048, 0), (6, 1000, 0), (5, 512, 512)])
+@pytest.mark.parametrize("N,K,G", [(6, 1024, 128), (5, 420608, 256), (17, 123648, 256), (6, 2048, 0), (6, 1000, 0), (5, 512, 512)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
 def test_weight_quant_nonfinite(lib, N, K, G, dtype):
     td = {"f16": torch.float16, "bf16": torch.bfloat16, "f32": torch.float32}[dtype]
