@@ -360,7 +360,11 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_small_groups_kernel(
     constexpr int G = LANES * 8, WAVES = WQ_THREADS / WAVE;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t k0 = (int64_t)blockIdx.x * 512;
+    // One row per wave, four chunks (1544 to 2048 columns): every four rows start one chunk on.  In their order each chunk lies on
+    // the same two XCDs in all rows, which is the slower way there: 1024 x 2048 fp16 4.1 -> 3.65 us (with given parameters 3.7 -> 3.3;
+    // blocks along a row 4.1 and 3.6), 900 x 1664 3.75 -> 3.6.  With two or eight chunks it is the faster one (512 x 4096 3.6, turned 3.75).
+    const uint32_t chunk = ROWS == 1 && gridDim.x == 4 ? (blockIdx.x + blockIdx.y) & 3u : blockIdx.x;
+    const int64_t k0 = (int64_t)chunk * 512;
     const int kl = lane * 8;
     if (k0 + kl >= K) return;   // whole groups of LANES lanes leave together (K % G == 0)
     float sv[8];

@@ -78,11 +78,11 @@ def test_pack_tiles_edges(lib, N, K, plain, shift):
 
 # rows that do not fill the last set of rows of a block, a last round of columns that is partly empty, the shortest
 # and longest segments of the register-resident kernel and the lengths just outside it, more than 2^21 weights in small
-# groups (four rows per wave; below, and of a few rows, one), more than 1024 and 1536 segments on both sides of the rule's lengths, every input type, rows off the vector alignment; ranges made and given
+# groups (four rows per wave; below, and of a few rows, one; four chunks, which every four rows start elsewhere), more than 1024 and 1536 segments on both sides of the rule's lengths, every input type, rows off the vector alignment; ranges made and given
 @pytest.mark.parametrize("N,K,G", [(1, 128, 128), (5, 640, 128), (6, 768, 256), (7, 1792, 256), (3, 1016, 0),
                                    (3, 1024, 0), (2, 2056, 0), (5, 9216, 0), (1, 16384, 0), (2, 16392, 0),
                                    (4, 4096, 1024), (7, 300160, 128), (5, 420608, 256), (18, 116736, 128), (21, 100096, 256),
-                                   (2, 6291584, 128), (3, 4194432, 128),
+                                   (2, 6291584, 128), (3, 4194432, 128), (21, 2048, 128), (18, 1664, 128),
                                    (1025, 1024, 0), (1537, 1536, 0), (1537, 1544, 0), (1539, 2056, 0), (513, 6144, 2048),
                                    (385, 10240, 2560)])
 @pytest.mark.parametrize("dtype", ["f16", "bf16", "f32"])
