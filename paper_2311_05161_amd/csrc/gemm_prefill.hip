@@ -1038,11 +1038,14 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
 
-    // Token zero-points: the token scales are on their way under the exchange (fetched block by block behind it they take 2000
-    // clocks of a launch).  Without zero-points that is the slower way: 200 x 5120 x 13824
-    // 35.3 us with the loads behind the exchange, 35.6 with them here.
-    float sxv[ASYM ? MS : 1];
-    if constexpr (ASYM) {
+    // Token zero-points: the token scales are on their way under the exchange.  us, fetched here / block by block behind it: 607 x
+    // 4096 x 4096 (two phases of three blocks, groups of 256) 27.2 / 27.8, 367 x 1152 x 5392 (four of four, groups of 128) 11.36 / 11.63.
+    // With four phases of three blocks they come behind it in groups of several k-tiles (513 x 2048 x 2064 in groups of 512 11.39 / 11.22, 300 x
+    // 2048 x 4096 11.30 / 11.13; in groups of 128 12.21 / 12.12, but 69 x 1152 x 9584 9.11 / 9.24), and without zero-points in every form
+    // (200 x 5120 x 13824 35.6 / 35.3).
+    constexpr bool EARLY = ASYM && !(MULTI && KQ == 4 && MS == 3);
+    float sxv[EARLY ? MS : 1];
+    if constexpr (EARLY) {
 #pragma unroll
         for (int ms = 0; ms < MS; ++ms) sxv[ms] = sx[min(m0 + ms * 32 + r32, M - 1)];
     }
@@ -1099,7 +1102,7 @@ __global__ __launch_bounds__(MD_THREADS, 2) void gemm_mid_kernel(
     for (int ms = 0; ms < MS; ++ms) {
         const int m = m0 + ms * 32 + r32;
         if (ms < first || ms >= last || m >= M) continue;
-        const float sxm = ASYM ? sxv[ASYM ? ms : 0] : sx[m];
+        const float sxm = EARLY ? sxv[EARLY ? ms : 0] : sx[m];
 #pragma unroll
         for (int b = 0; b < 4; ++b) {
             const int nn = nb0 + wn * 32 + 8 * b + 4 * kh;
