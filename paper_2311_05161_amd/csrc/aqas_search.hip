@@ -133,7 +133,9 @@ constexpr int RG_THREADS = RG_PHASES * 256;
 constexpr int RG_ROWS = RG_BM + RG_BN;                    // rows of X, then rows of W
 constexpr int RG_STEP = RG_ROWS * RG_BK * 2;              // bytes of a step in LDS (24 KB)
 
-template <typename T>
+// FAR: rows too far apart for the 32-bit offsets of a buffer descriptor (eight of its rows below 2^31 bytes): the same copies
+// by 64-bit addresses.  (64 x 4096 x 128, rows 2^26 + 8 elements apart: clipping choice 95 us; with the kernel below 1760.)
+template <typename T, bool FAR>
 __global__ __launch_bounds__(RG_THREADS) void ref_gemm16_kernel(const T *__restrict__ X, int64_t M, int64_t K, int64_t ldx,
                                                                 const T *__restrict__ W, int64_t N, int64_t ldw,
                                                                 float *__restrict__ Y, uint32_t grid_n)
@@ -146,18 +148,23 @@ __global__ __launch_bounds__(RG_THREADS) void ref_gemm16_kernel(const T *__restr
     const int64_t m0 = (int64_t)bm * RG_BM, n0 = (int64_t)bn * RG_BN;
     const int r32 = lane & 31, kh = lane >> 5;
     // Copy i of a wave: rows 8 (4 i + wave) .. + 7 of its phase's step, eight lanes a row.  (Rows past the end repeat the last one;
-    // they are not stored.  A descriptor starts at the first of the eight rows: seven row strides are below 2^31 bytes.)
-    v4i rsrc[COPIES];
-    int voff[COPIES];
+    // they are not stored.  A descriptor starts at the first of the eight rows.)
+    v4i rsrc[FAR ? 1 : COPIES];
+    int voff[FAR ? 1 : COPIES];
+    const T *far[FAR ? COPIES : 1];
 #pragma unroll
     for (int i = 0; i < COPIES; ++i) {
         const int row0 = 8 * (4 * i + wave), row = row0 + (lane >> 3), c = (lane & 7) ^ ((row >> 1) & 7);
         const bool is_x = row0 < RG_BM;   // (RG_BM % 8 == 0: uniform)
         const int64_t last = is_x ? M - 1 : N - 1, at = is_x ? m0 : n0 - RG_BM, ld = is_x ? ldx : ldw;
-        const int64_t first = min(at + row0, last);
-        const uint64_t base = (uint64_t)((is_x ? X : W) + first * ld);
-        rsrc[i] = v4i{(int)(uint32_t)base, (int)((base >> 32) & 0xffffu), 0x7fffffff, 0x00020000};
-        voff[i] = (int)((min(at + row, last) - first) * ld * 2) + c * 16;
+        if constexpr (FAR) {
+            far[i] = (is_x ? X : W) + min(at + row, last) * ld + c * 8;
+        } else {
+            const int64_t first = min(at + row0, last);
+            const uint64_t base = (uint64_t)((is_x ? X : W) + first * ld);
+            rsrc[i] = v4i{(int)(uint32_t)base, (int)((base >> 32) & 0xffffu), 0x7fffffff, 0x00020000};
+            voff[i] = (int)((min(at + row, last) - first) * ld * 2) + c * 16;
+        }
     }
     v16f acc[2];
 #pragma unroll
@@ -167,9 +174,14 @@ __global__ __launch_bounds__(RG_THREADS) void ref_gemm16_kernel(const T *__restr
     auto copy_round = [&](int round, int slot) {
         const int step = min(round * RG_PHASES + phase, steps - 1);   // (past the end: the last step, unused)
 #pragma unroll
-        for (int i = 0; i < COPIES; ++i)
-            dma_b128(rsrc[i], voff[i], step * (RG_BK * 2),
-                     lds_base + (uint32_t)((slot * RG_PHASES + phase) * RG_STEP + (4 * i + wave) * 1024));
+        for (int i = 0; i < COPIES; ++i) {
+            const int at = (slot * RG_PHASES + phase) * RG_STEP + (4 * i + wave) * 1024;
+            if constexpr (FAR)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(uintptr_t)(far[i] + (int64_t)step * RG_BK),
+                                                 (__attribute__((address_space(3))) void *)(rg_lds + at), 16, 0, 0);
+            else
+                dma_b128(rsrc[i], voff[i], step * (RG_BK * 2), lds_base + (uint32_t)at);
+        }
     };
 #pragma unroll
     for (int i = 0; i < RG_RING - 1; ++i) copy_round(i, i);
@@ -238,7 +250,7 @@ __global__ __launch_bounds__(RG_THREADS) void ref_gemm16_kernel(const T *__restr
     }
 }
 
-// Binary32, bfloat16 off the 16-byte alignment (fp16 rows have to have it), and row strides beyond the tile kernel's descriptors: one wave per 32 x 32 output tile, operands
+// Binary32, and bfloat16 off the 16-byte alignment (fp16 rows have to have it): one wave per 32 x 32 output tile, operands
 // straight from global memory, widened exactly, v_mfma_f32_32x32x2_f32.
 template <typename T>
 __global__ __launch_bounds__(256) void ref_gemm_kernel(const T *__restrict__ X, int64_t M, int64_t K,
@@ -274,27 +286,31 @@ int launch_ref_gemm(const void *X, const void *W, int dtype, int64_t M, int64_t 
 {
     const int64_t gn16 = (N + RG_BN - 1) / RG_BN, blocks16 = (M + RG_BM - 1) / RG_BM * gn16;
     if (dtype != W4A8_F32 && K % RG_BK == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)W % 16 == 0 && ldx % 8 == 0 &&
-        ldw % 8 == 0 && blocks16 <= 0x7fffffffLL && ldx <= (1 << 26) && ldw <= (1 << 26) && K <= 0x3fffffffLL) {
+        ldw % 8 == 0 && blocks16 <= 0x7fffffffLL) {
+        const bool far = ldx > (1 << 26) || ldw > (1 << 26);
         const dim3 grid16((unsigned)blocks16);
         constexpr int lds_bytes = RG_RING * RG_PHASES * RG_STEP;   // 144 KB
-#define W4A8_RG(T_)                                                                                                        \
-    do {                                                                                                                   \
-        static std::atomic<uint64_t> lds_opted{0};                                                                         \
-        if (opt_in_dynamic_lds((const void *)ref_gemm16_kernel<T_>, lds_bytes, lds_opted) != W4A8_OK) return W4A8_ERR_HIP; \
-        hipLaunchKernelGGL((ref_gemm16_kernel<T_>), grid16, dim3(RG_THREADS), lds_bytes, st, (const T_ *)X, M, K, ldx,     \
-                           (const T_ *)W, N, ldw, Y, (uint32_t)gn16);                                                      \
+#define W4A8_RG(T_, FAR_)                                                                                                   \
+    do {                                                                                                                    \
+        static std::atomic<uint64_t> lds_opted{0};                                                                          \
+        if (opt_in_dynamic_lds((const void *)ref_gemm16_kernel<T_, FAR_>, lds_bytes, lds_opted) != W4A8_OK)                 \
+            return W4A8_ERR_HIP;                                                                                            \
+        hipLaunchKernelGGL((ref_gemm16_kernel<T_, FAR_>), grid16, dim3(RG_THREADS), lds_bytes, st, (const T_ *)X, M, K, ldx, \
+                           (const T_ *)W, N, ldw, Y, (uint32_t)gn16);                                                       \
     } while (0)
-        if (dtype == W4A8_F16) W4A8_RG(__half);
-        else W4A8_RG(bf16_t);
+        if (dtype == W4A8_F16) {
+            if (far) W4A8_RG(__half, true);
+            else W4A8_RG(__half, false);
+        } else {
+            if (far) W4A8_RG(bf16_t, true);
+            else W4A8_RG(bf16_t, false);
+        }
 #undef W4A8_RG
         return hip_status(hipGetLastError());
     }
     const dim3 grid((unsigned)((N + 63) / 64), (unsigned)((M + 63) / 64));
     switch (dtype) {
-        case W4A8_F16:
-            hipLaunchKernelGGL((ref_gemm_kernel<__half>), grid, dim3(256), 0, st, (const __half *)X, M, K, ldx,
-                               (const __half *)W, N, ldw, Y);
-            break;
+        case W4A8_F16: return W4A8_ERR_SHAPE;   // (all that the callers accept went above)
         case W4A8_BF16:
             hipLaunchKernelGGL((ref_gemm_kernel<bf16_t>), grid, dim3(256), 0, st, (const bf16_t *)X, M, K, ldx,
                                (const bf16_t *)W, N, ldw, Y);

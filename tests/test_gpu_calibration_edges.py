@@ -136,3 +136,24 @@ def test_side_by_side_against_one_by_one(lib, M, K, N, G, dtype):
     ng = K // (G or K)
     for p in (4, 5):
         np.testing.assert_array_equal(out[full][p].reshape(N, ng)[same], out[small][p].reshape(N, ng)[same])
+
+
+# rows further apart than a buffer descriptor reaches (2^26 elements), in X, in W and in both: the same bits as dense rows
+@pytest.mark.parametrize("far_x,far_w", [(True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_rows_far_apart(lib, far_x, far_w, dtype):
+    M, K, N, stride = 70, 384, 48, (1 << 26) + 8
+    g = torch.Generator(device="cuda").manual_seed(7)
+    dense = [(torch.randn((rows, K), generator=g, device="cuda") * scale).to(DTYPES[dtype]) for rows, scale in ((M, 1.0), (N, 0.02))]
+    spread = []
+    for t, far in zip(dense, (far_x, far_w)):
+        if far:
+            wide = torch.empty((t.shape[0], stride), dtype=t.dtype, device="cuda")[:, :K]
+            wide.copy_(t)
+            t = wide
+        spread.append(t)
+    assert spread[0].stride(0) == (stride if far_x else K) and spread[1].stride(0) == (stride if far_w else K)
+    want, got = (lib.aqas_search(X, W, 128) for X, W in (dense, spread))
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
+    want, got = (lib.aqas_clip_search(X, W, want[0], 128, want_table=True) for X, W in (dense, spread))
+    assert all(torch.equal(a, b) for a, b in zip(want, got))
