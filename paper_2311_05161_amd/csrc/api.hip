@@ -585,7 +585,7 @@ int aqas_check(const void *X, const void *W, int dtype, int64_t M, int64_t N, in
         M > 0x7fffffffLL || N * K / 2 > 0x7fffffffLL || M * K > 0x7fffffffLL)
         return W4A8_ERR_SHAPE;
     if (!X || !W) return W4A8_ERR_NULL;
-    // (part of the interface: the fp16 product has only the form with 16-byte loads; bfloat16 has another one besides)
+    // (part of the interface: the fp16 product has only the form that copies 16 bytes at a time; bfloat16 has another one besides)
     if (dtype == W4A8_F16 && ((uintptr_t)X % 16 != 0 || (uintptr_t)W % 16 != 0 || ldx % 8 != 0 || ldw % 8 != 0))
         return W4A8_ERR_SHAPE;
     if (!workspace || (uintptr_t)workspace % WS_ALIGN != 0 || workspace_bytes < plan_aqas(M, N, K, G, 1).total)

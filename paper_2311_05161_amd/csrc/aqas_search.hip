@@ -118,7 +118,7 @@ int launch_aqas_scale(const float *ax, const float *aw, int64_t K, int j, float 
 }
 
 // ---- the unquantized product Yref[m,n] = sum_k X[m,k] W[n,k] in fp32 on the matrix cores ----------
-// 16-bit inputs, rows 16-byte aligned and K % 64 == 0: products of 16-bit numbers are exact in fp32, so the 16-bit matrix
+// 16-bit inputs, rows 16-byte aligned and K % 128 == 0: products of 16-bit numbers are exact in fp32, so the 16-bit matrix
 // instructions (32 x 32 x 16) lose nothing against widened operands.  A block makes a 64 x 128 tile with RG_PHASES x 4 waves:
 // wave (p, w) the columns 32 w .. + 31 of all 64 rows over every RG_PHASES-th step of 64 columns of K.  A round of RG_PHASES
 // steps lies in one of RG_RING LDS buffers (rows of 128 bytes in 16-byte chunks, chunk index XORed with half the row so that
@@ -169,7 +169,7 @@ __global__ __launch_bounds__(RG_THREADS) void ref_gemm16_kernel(const T *__restr
     v16f acc[2];
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.0f;
-    const int steps = (int)(K / RG_BK), rounds = (steps + RG_PHASES - 1) / RG_PHASES;
+    const int steps = (int)(K / RG_BK), rounds = steps / RG_PHASES;   // (K is a multiple of the columns of a round)
     const uint32_t lds_base = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)rg_lds;
     auto copy_round = [&](int round, int slot) {
         const int step = min(round * RG_PHASES + phase, steps - 1);   // (past the end: the last step, unused)
@@ -193,22 +193,20 @@ __global__ __launch_bounds__(RG_THREADS) void ref_gemm16_kernel(const T *__restr
         asm volatile("s_waitcnt vmcnt(6)" ::: "memory");
         __syncthreads();
         copy_round(round + RG_RING - 1, slot == 0 ? RG_RING - 1 : slot - 1);
-        if (round * RG_PHASES + phase < steps) {   // (uniform over the wave: the last round may have no step for a phase)
-            const v4u *t = reinterpret_cast<const v4u *>(rg_lds + (slot * RG_PHASES + phase) * RG_STEP);
+        const v4u *t = reinterpret_cast<const v4u *>(rg_lds + (slot * RG_PHASES + phase) * RG_STEP);
 #pragma unroll
-            for (int q = 0; q < RG_BK / 16; ++q) {   // lane (r32, kh) holds 8 consecutive k of its row, as both operands agree on
-                const int c = (2 * q + kh) ^ ((r32 >> 1) & 7);
-                const v4u wv = t[(RG_BM + wave * 32 + r32) * 8 + c];
+        for (int q = 0; q < RG_BK / 16; ++q) {   // lane (r32, kh) holds 8 consecutive k of its row, as both operands agree on
+            const int c = (2 * q + kh) ^ ((r32 >> 1) & 7);
+            const v4u wv = t[(RG_BM + wave * 32 + r32) * 8 + c];
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const v4u xv = t[(h * 32 + r32) * 8 + c];
-                    if constexpr (__is_same(T, bf16_t))
-                        acc[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, xv),
-                                                                         __builtin_bit_cast(v8bf, wv), acc[h], 0, 0, 0);
-                    else
-                        acc[h] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, xv),
-                                                                        __builtin_bit_cast(v8h, wv), acc[h], 0, 0, 0);
-                }
+            for (int h = 0; h < 2; ++h) {
+                const v4u xv = t[(h * 32 + r32) * 8 + c];
+                if constexpr (__is_same(T, bf16_t))
+                    acc[h] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(v8bf, xv),
+                                                                     __builtin_bit_cast(v8bf, wv), acc[h], 0, 0, 0);
+                else
+                    acc[h] = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(v8h, xv),
+                                                                    __builtin_bit_cast(v8h, wv), acc[h], 0, 0, 0);
             }
         }
         slot = slot + 1 == RG_RING ? 0 : slot + 1;
@@ -285,7 +283,7 @@ int launch_ref_gemm(const void *X, const void *W, int dtype, int64_t M, int64_t 
                     int64_t ldx, int64_t ldw, float *Y, hipStream_t st)
 {
     const int64_t gn16 = (N + RG_BN - 1) / RG_BN, blocks16 = (M + RG_BM - 1) / RG_BM * gn16;
-    if (dtype != W4A8_F32 && K % RG_BK == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)W % 16 == 0 && ldx % 8 == 0 &&
+    if (dtype != W4A8_F32 && K % (RG_BK * RG_PHASES) == 0 && (uintptr_t)X % 16 == 0 && (uintptr_t)W % 16 == 0 && ldx % 8 == 0 &&
         ldw % 8 == 0 && blocks16 <= 0x7fffffffLL) {
         const bool far = ldx > (1 << 26) || ldw > (1 << 26);
         const dim3 grid16((unsigned)blocks16);
