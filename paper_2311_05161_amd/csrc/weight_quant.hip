@@ -1023,14 +1023,16 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
 // 1024 r + 4 t4 .. + 3, r < R: one word of codes per channel and r, which goes through LDS (two buffers, one barrier
 // per r) to the wave that stores 1024 tokens of the channel's row, a kilobyte per instruction.  A row of 32 channels is 64 bytes,
 // half a cache line: the channel parts of a head run on one XCD, so that its L2 serves the other half -- unless the codes have
-// pushed it out in the meantime, so they are stored with the streaming hint (the packing that reads them next takes 3 us more,
-// 256 heads).  256 heads x 4096 tokens x 128 channels: 126 (two sweeps) -> 116 -> 102 us (4.0 TB/s; without the vector work 93, the
-// loads alone 63); 256 x 2048 47 -> 40, 64 x 4096 25 -> 23.  (Blocks that go on to the next group and load it under the
-// codes of the one before: 102, and 2048 tokens 56, as two blocks of it no longer share a CU.)
+// pushed it out in the meantime, so many of them are stored with the streaming hint.
+// 256 heads x 4096 tokens x 128 channels: 126 (two sweeps) -> 115 -> 100 us (4.0 TB/s; without the vector work 93, the
+// loads alone 63); 256 x 2048 48 -> 44, 64 x 4096 31 -> 26.  (Blocks that go on to the next group and load it under the
+// codes of the one before were no faster, and with 2048 tokens slower, as two blocks of it no longer share a CU.)
 constexpr int VR_THREADS = 1024, VR_CHANNELS = 32, VR_TOKENS = 1024;
 constexpr int VR_STRIDE = VR_TOKENS / 4 + 4;   // words per channel row in LDS (16-byte aligned)
 
-template <typename T, int R>
+// STREAM: the codes are stored with the streaming hint (launch_value_quant).  (Of both stores behind a uniform branch the compiler
+// makes one without it.)
+template <typename T, int R, bool STREAM>
 __global__ __launch_bounds__(VR_THREADS) void value_quant_resident_kernel(const T *__restrict__ V, uint32_t groups,
                                                                           uint32_t parts, uint32_t ng, int64_t Tn,
                                                                           int64_t D, int64_t ld_t, int64_t ld_b,
@@ -1138,7 +1140,8 @@ __global__ __launch_bounds__(VR_THREADS) void value_quant_resident_kernel(const 
             if (d0 + row < D && t < G) {   // G % 16 == 0
                 const v4u w = *reinterpret_cast<const v4u *>(buf + row * VR_STRIDE + lane * 4);
                 v4u *dst = reinterpret_cast<v4u *>(codes + (b * D + d0 + row) * Tn + g * G + t);
-                __builtin_nontemporal_store(w, dst);
+                if constexpr (STREAM) __builtin_nontemporal_store(w, dst);
+                else *dst = w;
             }
         }
     }
@@ -1160,14 +1163,20 @@ int launch_value_quant(const void *V, int v_dtype, int64_t batch, int64_t T, int
         // (256 heads of 128 channels): 1024 tokens 30.8 / 27.1, 2048 62.8 / 45.7, 4096 146 / 122 (64 heads 60 / 27, 8 heads 47 / 18); but 512
         // tokens 19.2 / 23.7, 640 21.9 / 25.0 and 1152 33.4 / 36.4.
         if (G >= VR_TOKENS && rounds <= 5 && 4 * G >= 3 * rounds * VR_TOKENS && blocks <= 0x7fffffffLL) {
-#define W4A8_VR_LAUNCH(T_, R_)                                                                                     \
-    hipLaunchKernelGGL((value_quant_resident_kernel<T_, R_>), dim3((unsigned)blocks), dim3(VR_THREADS), 0, st,     \
+            // Codes of more than 6 MB are stored with the streaming hint.  Quantizer, packing and product, us, without / with it: 8
+            // heads x 1024 tokens 14.87 / 15.08, 16 x 3072 25.6 / 26.0, 48 x 1024 (6 MB) 19.15 / 19.12, 32 x 2048 (8 MB) 23.2 / 22.4,
+            // 32 x 4096 40.0 / 38.2, 256 x 4096 162 / 151.
+            const bool stream = batch * D * T > (6 << 20);
+#define W4A8_VR_LAUNCH(T_, R_, S_)                                                                                 \
+    hipLaunchKernelGGL((value_quant_resident_kernel<T_, R_, S_>), dim3((unsigned)blocks), dim3(VR_THREADS), 0, st, \
                        (const T_ *)V, (uint32_t)groups, (uint32_t)parts, (uint32_t)(T / G), T, D, ld_t, ld_b, (int)G, \
                        codes, step, zero)
-#define W4A8_VR_CASE(R_)                                     \
-    case R_:                                                 \
-        if (v_dtype == W4A8_F16) W4A8_VR_LAUNCH(__half, R_); \
-        else W4A8_VR_LAUNCH(bf16_t, R_);                     \
+#define W4A8_VR_CASE(R_)                                                         \
+    case R_:                                                                     \
+        if (v_dtype == W4A8_F16 && stream) W4A8_VR_LAUNCH(__half, R_, true);     \
+        else if (v_dtype == W4A8_F16) W4A8_VR_LAUNCH(__half, R_, false);         \
+        else if (stream) W4A8_VR_LAUNCH(bf16_t, R_, true);                       \
+        else W4A8_VR_LAUNCH(bf16_t, R_, false);                                  \
         break
             switch ((int)rounds) {
                 W4A8_VR_CASE(1);

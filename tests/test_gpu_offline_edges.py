@@ -188,7 +188,10 @@ def test_value_quant_nonfinite(lib, T, dtype):
 # eight XCDs, interleaved heads, rows off the alignment (general kernel)
 @pytest.mark.parametrize("B,T,D,G", [(1, 896, 32, 0), (3, 384, 40, 0), (9, 1024, 64, 0), (2, 1024, 128, 0), (1, 1152, 80, 0),
                                      (5, 2048, 64, 1024), (2, 3072, 128, 1536), (1, 3072, 32, 0), (1, 4096, 128, 0), (2, 5120, 72, 0),
-                                     (1, 5248, 40, 0), (2, 1040, 64, 0)])
+                                     (1, 5248, 40, 0), (2, 1040, 64, 0),
+                                     # more than 6 MB of codes: one round of the group to five
+                                     (49, 1024, 128, 0), (26, 2048, 128, 0), (17, 3072, 128, 1536), (18, 3072, 128, 0), (13, 4096, 128, 0),
+                                     (11, 5120, 120, 0)])
 @pytest.mark.parametrize("dtype,interleaved", [("f16", False), ("bf16", True), ("f16", True)])
 def test_value_quant_edges(lib, oracle, B, T, D, G, dtype, interleaved):
     _, V = syn.attention_value(B + T + D, B, 1, T, D, v_dtype="f32")
