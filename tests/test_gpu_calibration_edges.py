@@ -157,3 +157,40 @@ def test_rows_far_apart(lib, far_x, far_w, dtype):
     assert all(torch.equal(a, b) for a, b in zip(want, got))
     want, got = (lib.aqas_clip_search(X, W, want[0], 128, want_table=True) for X, W in (dense, spread))
     assert all(torch.equal(a, b) for a, b in zip(want, got))
+
+
+# The quantizers that write packed weights (one candidate at a time) and int8 weights (side by side), at the edges of the code rule with
+# both neighbours: every group runs from -z to 13 - z, so that its step is 1, and token m excites channel m and one whose weight
+# lies 0.3 off its level, so that the two sides of a tie differ in the squared error -- by 0.3 * 127^2 for one code, 1e-3 of a
+# row's sum, against 4e-5 for the rounding of the binary32 product (1e-4 of 6 in a difference, squared).
+@pytest.mark.parametrize("dtype", ["f32", "f16", "bf16"])
+@pytest.mark.parametrize("side_by_side", [False, True])
+def test_clipping_errors_at_the_rule_edges(lib, oracle, dtype, side_by_side):
+    M, K, N, G = 256, 256, 32, 128
+    rng = np.random.default_rng(3)
+    W = np.empty((N, K), np.float32)
+    for n in range(N):
+        z = n % 14
+        half = np.concatenate([np.arange(-z, 13 - z) + 0.5, [-0.75, -0.25, 0.25, 0.75]])
+        half = torch.from_numpy(half[(half > -z) & (half < 13 - z)]).to(DTYPES[dtype])
+        inf = torch.tensor(float("inf"), dtype=half.dtype)
+        edges = torch.cat([half, torch.nextafter(half, inf), torch.nextafter(half, -inf)]).float().numpy()
+        W[n] = np.concatenate([rng.permutation(np.resize(rng.permutation(edges), G)) for _ in range(K // G)])
+        W[n, 0::G], W[n, 1::G], W[n, 2::G] = -z, 13 - z, 1.296875 if z < 11 else -1.296875   # (exact in every type)
+    X = np.zeros((M, K), np.float32)
+    X[np.arange(M), np.arange(M)] = X[np.arange(M), np.arange(M) // G * G + 2] = 127.0
+    s = np.ones(K, np.float32)
+    want = oracle.aqas_search.clip_search(X, W, s, G)["err"][0]
+    Xd, Wd, sd = (torch.from_numpy(a).cuda() for a in (X, W, s))
+    Xd, Wd = Xd.to(DTYPES[dtype]), Wd.to(DTYPES[dtype])
+    c = lib.load_library()
+    full, small = int(c.aqas_search_workspace_preferred_bytes(M, N, K, G)), int(c.aqas_search_workspace_bytes(M, N, K, G))
+    assert full > small + 10 * N * K
+    need = full if side_by_side else small
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    idx, step, zero, table = (torch.empty(n, dtype=t, device="cuda") for n, t in
+                              ((N, torch.int32), (N * K // G, torch.float32), (N * K // G, torch.uint8), (11 * N, torch.float64)))
+    assert c.aqas_clip_search(Xd.data_ptr(), Wd.data_ptr(), {"f32": 0, "f16": 1, "bf16": 2}[dtype], M, N, K, K, K, sd.data_ptr(), G,
+                              idx.data_ptr(), step.data_ptr(), zero.data_ptr(), table.data_ptr(), ws.data_ptr(), need,
+                              torch.cuda.current_stream().cuda_stream) == 0
+    np.testing.assert_allclose(host(table).reshape(11, N)[0], want, rtol=1e-4)

@@ -92,8 +92,8 @@ def test_per_channel_remainder(M, K, N):
     assert torch.equal(Y, lib.w4a8_gemm(Xq, sx, Wp, step, zero, N, K, 0))
 
 
-# token zero-points at the ends of their range against the largest weight sums of a group, where the products and sums that leave
-# the accumulators in binary32 are largest (below 2^21)
+# token zero-points at the ends of their range against the largest weight sums of a group, where what leaves the accumulators in
+# binary32 is largest: products up to 128 * 104 * 128 (below 2^21), sums with them up to 255 * 104 * 128 (below 2^22), both exact
 @pytest.mark.parametrize("M,K,N", [FOUR[0], TWO[0], (607, 1024, 4096), (97, 2048, 4112)])
 @pytest.mark.parametrize("code,z", [(13, 0), (0, 13), (12, 0)])
 def test_zero_points_at_the_ends(M, K, N, code, z):
