@@ -643,15 +643,18 @@ int launch_weight_quant(const void *W, int w_dtype, int64_t N, int64_t K, int64_
 }
 
 // ---- quantized straight to the tiled packed form --------------------------------------------------
-// dINT4 with groups of 128: a 16 x 128 tile of the packed form is 16 whole groups.  A wave takes WQT_TILES tiles of
-// the same columns (they share the AQAS scales): lane l holds row l % 16, columns 32 c + 8 (l / 16) .. + 7,
+// dINT4 with groups of 128: a 16 x 128 tile of the packed form is 16 whole groups.  A wave takes WQT_TILES row tiles of
+// the same columns (one): lane l holds row l % 16, columns 32 c + 8 (l / 16) .. + 7,
 // c = 0..3, so that a load instruction reads 64 contiguous bytes of each row (32 consecutive columns per
 // lane, which would make one 16-byte store, read 16-byte pieces and measured the same), the four
 // lanes of a group meet in two shuffles, and codes 8 c' .. of quarter c are one word of the tile.
 // Bound by the vector ALU (a candidate's weights: two multiplications, the range, the code rule) and the stores; more waves
-// on a SIMD serve both better than shared scales: one tile per wave (111 registers) instead of two (163), with streaming
-// stores, 4096 x 4096 straight to int8, us: 17 scales 113 -> 101, 11 clipping factors 56 -> 50 (without the code
-// rule's arithmetic 68 and 33), 2048 x 3072 46 -> 39 and 28 -> 22.
+// on a SIMD serve both better than scales that two tiles share: one tile per wave (int8 111 registers, packed 97) instead of two (163, 173).
+// us, two tiles / one, 4096 x 4096 fp16: int8 (one also with streaming stores) of 17 scales 113 / 101, of 11 clipping factors 56 / 50 (without
+// the code rule's arithmetic 68 and 33), packed 15.1 / 12.6; 2048 x 3072: 46 / 39, 28 / 22 and 8.2 / 6.5.
+// The streaming hint of the int8 stores takes from the quantizer what it costs the product that reads them next: ten layers of 64 to 2048 calibration
+// tokens, whole searches, 5 % faster to 4 % slower with it in no order of size, 0.8 % faster on average (512 x 4096 x 4096 401 with, 416
+// without; 97 x 1920 x 3072 112 and 108).
 constexpr int WQT_TILES = 1;
 
 // Eight weights -> four times their value in half steps, as bytes: 8 (code - z), or +-4 for the special codes (the rule of
@@ -681,7 +684,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_packed_kernel(
 {
     const int lane = threadIdx.x & 63;
     const uint32_t wave = blockIdx.x * (WQ_THREADS / WAVE) + (threadIdx.x >> 6);
-    const uint32_t ntp = wave / KT, kt = wave - ntp * KT;   // (pair of row tiles, k-tile)
+    const uint32_t ntp = wave / KT, kt = wave - ntp * KT;   // (WQT_TILES row tiles, k-tile)
     if (ntp * WQT_TILES >= NT) return;                      // whole wave
     const int row = lane & 15;
     const int kb = lane >> 4;
@@ -739,7 +742,7 @@ __global__ __launch_bounds__(WQ_THREADS) void weight_quant_packed_kernel(
                 uint8_t *block = w8 + ((int64_t)(nt[i] >> 1) * KT + kt) * I8_BLOCK + (kb >> 1) * 1024 +
                                  ((nt[i] & 1) * 16 + row) * 16 + (kb & 1) * 8;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) {   // (streaming: all candidates' weights are more than the last-level cache holds)
+                for (int c = 0; c < 4; ++c) {
                     const uint2 q = levels8(x[i][c], rule);
                     __builtin_nontemporal_store(v2u{q.x, q.y}, reinterpret_cast<v2u *>(block + (c >> 1) * 2048 + (c & 1) * 512));
                 }
