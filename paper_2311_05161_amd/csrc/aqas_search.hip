@@ -126,8 +126,9 @@ int launch_aqas_scale(const float *ax, const float *aw, int64_t K, int j, float 
 // copies RG_RING - 1 rounds ahead; the phases' sums meet in LDS at the end, in their order.
 // At 512 x 4096 x 4096 the grid is one block per CU, and what bounds it is the way of the tiles through the CU's memory pipe
 // (48 KB per round: 768 clocks).  us there: one wave per 32 x 32 tile straight from global memory 127; four waves, through
-// registers to LDS, 38.6; two phases 32.7; copies straight to LDS 28.9
-// (97 x 3072 x 2000 26 / 19, 2048 x 4096 x 4096 106 / 103; rms error against 64 bits 8.1e-7 / 1.8e-7 with two shorter chains).
+// registers to LDS, 39.5; two phases and copies straight to LDS 28.9 (medians of a trace of searches one candidate at a time; side by side,
+// where the weights come from further away, 33) (97 x 3072 x 2000 26 / 19, 2048 x 4096 x 4096 106 / 103; rms error against
+// 64 bits 8.1e-7 / 1.8e-7 with two shorter chains).
 constexpr int RG_BM = 64, RG_BN = 128, RG_BK = 64, RG_PHASES = 2, RG_RING = 3;
 constexpr int RG_THREADS = RG_PHASES * 256;
 constexpr int RG_ROWS = RG_BM + RG_BN;                    // rows of X, then rows of W

@@ -1027,8 +1027,8 @@ __global__ __launch_bounds__(256) void value_quant_vec_kernel(const T *__restric
 // per r) to the wave that stores 1024 tokens of the channel's row, a kilobyte per instruction.  A row of 32 channels is 64 bytes,
 // half a cache line: the channel parts of a head run on one XCD, so that its L2 serves the other half -- unless the codes have
 // pushed it out in the meantime, so many of them are stored with the streaming hint.
-// 256 heads x 4096 tokens x 128 channels: 126 (two sweeps) -> 115 -> 100 us (4.0 TB/s; without the vector work 93, the
-// loads alone 63); 256 x 2048 48 -> 44, 64 x 4096 31 -> 26.  (Blocks that go on to the next group and load it under the
+// 256 heads x 4096 tokens x 128 channels, kernel trace: 126 (two sweeps) -> 112 -> 102 us (3.9 TB/s; without the vector work 93, the
+// loads alone 63); calls in a graph: 115 -> 100, 256 x 2048 48 -> 44, 64 x 4096 31 -> 26.  (Blocks that go on to the next group and load it under the
 // codes of the one before were no faster, and with 2048 tokens slower, as two blocks of it no longer share a CU.)
 constexpr int VR_THREADS = 1024, VR_CHANNELS = 32, VR_TOKENS = 1024;
 constexpr int VR_STRIDE = VR_TOKENS / 4 + 4;   // words per channel row in LDS (16-byte aligned)
